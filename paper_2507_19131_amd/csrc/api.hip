@@ -608,7 +608,9 @@ static int block_create(const mixaq_block_desc* desc, const mixaq_shared_params*
                             token_src(b, wr, wc, j, &rj, &cj);
                             if (!(std::abs(ri - rj) < WS && std::abs(ci - cj) < WS)) v = v + MASK_VALUE;
                         }
-                        tab[(((size_t)type * heads + h) * TOK + j) * 64 + i] = v * LOG2E_F;
+                        // a bias that shuts a pair out altogether (-infinity, or not a number) becomes a finite one: see exp2_pinned
+                        v = v * LOG2E_F;
+                        tab[(((size_t)type * heads + h) * TOK + j) * 64 + i] = v > -1e30f ? v : -1e30f;
                     }
         }
         if ((rc = upload(b->owned, tab, &b->bias2))) return bail(rc);

@@ -19,11 +19,7 @@ namespace mixaq {
 template <int W>
 __device__ __forceinline__ double group_sum(double v, int first = 0)
 {
-    if ((W & (W - 1)) == 0) {
-#pragma unroll
-        for (int o = W / 2; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
-        return v;
-    }
+    if ((W & (W - 1)) == 0) return lanes_sum<W>(v);
     double tot = __shfl(v, first, 64);
 #pragma unroll
     for (int k = 1; k < W; ++k) tot += __shfl(v, first + k, 64);
@@ -32,25 +28,24 @@ __device__ __forceinline__ double group_sum(double v, int first = 0)
 
 // LayerNorm of one token spread over LPT lanes (NV float4 per lane; channel of
 // element e of vector k on lane i: (k*LPT + i)*4 + e).  Mean and variance in
-// binary64, rounded once.
+// binary64, rounded once (see Moments).
 template <int LPT, int NV>
 __device__ __forceinline__ void token_ln_stats(const float4 (&v)[NV], int C, float eps, float& mean, float& rstd, int first = 0)
 {
-    double s = 0.0;
+    Moments m;
 #pragma unroll
-    for (int k = 0; k < NV; ++k) s += ((double)v[k].x + (double)v[k].y) + ((double)v[k].z + (double)v[k].w);
-    s = group_sum<LPT>(s, first);
-    mean = (float)(s / (double)C);
-    double q = 0.0;
+    for (int k = 0; k < NV; ++k) moments_add(m, v[k].x, v[k].y, v[k].z, v[k].w);
+    const double s = group_sum<LPT>(m.s, first), q = group_sum<LPT>(m.q, first);
+    mean = moments_mean(s, C);
+    bool shaky;
+    double var = moments_centred(s, q, mean, C, shaky);
+    if (shaky) {                                                 // the same in every lane of the token
+        var = 0.0;
 #pragma unroll
-    for (int k = 0; k < NV; ++k) {
-        double a = (double)v[k].x - (double)mean, b = (double)v[k].y - (double)mean;
-        double c = (double)v[k].z - (double)mean, d = (double)v[k].w - (double)mean;
-        q += (a * a + b * b) + (c * c + d * d);
+        for (int k = 0; k < NV; ++k) var += centred_squares(v[k].x, v[k].y, v[k].z, v[k].w, mean);
+        var = group_sum<LPT>(var, first);
     }
-    q = group_sum<LPT>(q, first);
-    const float var = (float)(q / (double)C);
-    rstd = 1.0f / sqrtf(var + eps);
+    rstd = moments_rstd(var, C, eps);
 }
 
 template <int LPT, int NV>
@@ -378,15 +373,19 @@ __global__ __launch_bounds__(256) void gemm_tile_kernel(Geom G, GemmArgs A)
 // so the softmax reduces in registers; the packed P codes are then directly the B operand
 // of O^T = V^T P^T.  qf/kf: lane = token tb*32+j, 16 bytes = the lane half's 16 dims (any
 // mapping, the same for q and k).  vt: lane = dim j, byte r of slab kb = V[kb*32 +
-// mfma_row(r,g)][j], zero for keys >= 49.  Returns the raw P.V sums (lane = query, register
-// r = dim mfma_row(r,g)).  The wave runs NIB query blocks starting at block ib0 (both, or one of the
+// mfma_row(r,g)][j], zero for keys >= 49.  Returns the zero-point corrected P.V sums (lane = query, register
+// r = dim mfma_row(r,g)), zero-point corrected.  The wave runs NIB query blocks starting at block ib0 (both, or one of the
 // two when a pair of waves shares the head).
+// The P.V sums start at nzcsum[d] = -zp * sum of the V codes of dim d over the keys, formed once per dim by the caller
+// (an integer multiply is a quarter-rate instruction; and starting the accumulators there costs no instruction, where
+// subtracting afterwards took one per output element).
 struct AttnCore {
     const PolyCoef* poly;
     const float* bq;          // (bias + mask) * log2e of query j of query block ib0 at key g*4, in the [49 keys][64 queries]
                               // table of this head and mask type: key k + g*4, query block ib0 + ib is bq[k * 64 + ib * 32]
     float m2;
     QDev qp;
+    const int* nzcsum;        // [HD], LDS
     int32_t* tap_s;           // already offset to this (slot, head): [49][49]
     int8_t* tap_p;
 };
@@ -418,7 +417,7 @@ __device__ __forceinline__ void attention_core(const v4i (&qf)[NIB], const v4i (
                 }
                 lg[kb][r] = v;
             }
-        mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+        mx = half_max(mx);
         double den = 0.0;
 #pragma unroll
         for (int kb = 0; kb < 2; ++kb)
@@ -432,7 +431,7 @@ __device__ __forceinline__ void attention_core(const v4i (&qf)[NIB], const v4i (
                     den += (double)e;
                 }
             }
-        den += __shfl_xor(den, 32, 64);
+        den = half_sum(den);
         const float rden = 1.0f / (float)den;
         v4i pk[2];
 #pragma unroll
@@ -457,17 +456,20 @@ __device__ __forceinline__ void attention_core(const v4i (&qf)[NIB], const v4i (
             }
             pk[kb] = (v4i){wd[0], wd[1], wd[2], wd[3]};
         }
-        o[ib] = mfma32(vt[0], pk[0], zero16);
+#pragma unroll
+        for (int qd = 0; qd < 4; ++qd) {
+            const int4 cz = *(const int4*)(A.nzcsum + qd * 8 + g * 4);
+            o[ib][qd * 4 + 0] = cz.x; o[ib][qd * 4 + 1] = cz.y; o[ib][qd * 4 + 2] = cz.z; o[ib][qd * 4 + 3] = cz.w;
+        }
+        o[ib] = mfma32(vt[0], pk[0], o[ib]);
         o[ib] = mfma32(vt[1], pk[1], o[ib]);
     }
 }
 
-// zero-point correction, dequantization and requantization of the P.V sums; writes the codes
-// of head `head` for the window's tokens to out[row0 + token][C] (and the taps).  zcsum[d] = zp * sum of
-// the V codes of dim d over the keys, formed once per dim by the caller (an integer multiply is a
-// quarter-rate instruction; inside the loop it would be one per output element).
+// dequantization and requantization of the P.V sums; writes the codes of head `head` for the window's tokens to
+// out[row0 + token][C] (and the taps)
 template <bool TAPS, int NIB>
-__device__ __forceinline__ void attention_store(const v16i (&o)[NIB], const int* zcsum, const QDev& qo, float m_o,
+__device__ __forceinline__ void attention_store(const v16i (&o)[NIB], const QDev& qo, float m_o,
                                                 int j, int g, int ib0, int head, int C, int8_t* out, int row0, int32_t* tap_o,
                                                 int8_t* tap_code, size_t canon_row0, int pack = 0)
 {
@@ -479,9 +481,7 @@ __device__ __forceinline__ void attention_store(const v16i (&o)[NIB], const int*
 #pragma unroll
             for (int qd = 0; qd < 4; ++qd) {
                 const int d0 = qd * 8 + g * 4;
-                const int4 cz = *(const int4*)(zcsum + d0);
-                int a0 = o[ib][qd * 4 + 0] - cz.x, a1 = o[ib][qd * 4 + 1] - cz.y;
-                int a2 = o[ib][qd * 4 + 2] - cz.z, a3 = o[ib][qd * 4 + 3] - cz.w;
+                const int a0 = o[ib][qd * 4 + 0], a1 = o[ib][qd * 4 + 1], a2 = o[ib][qd * 4 + 2], a3 = o[ib][qd * 4 + 3];
                 code[qd] = pack4(quant_code((float)a0 * m_o, qo), quant_code((float)a1 * m_o, qo),
                                  quant_code((float)a2 * m_o, qo), quant_code((float)a3 * m_o, qo));
                 const int ch = head * HD + d0;
@@ -565,9 +565,12 @@ __global__ __launch_bounds__(256) void attn_kernel(Geom G, AttnArgs A)
         }
         vt[kb] = (v4i){wd[0], wd[1], wd[2], wd[3]};
     }
-    cs += __shfl_xor(cs, 32, 64);
-    if (g == 0) csum[wave][j] = A.qp[branch].zp * cs;
+    cs = half_sum(cs);
+    if (g == 0) csum[wave][j] = -(A.qp[branch].zp * cs);
+    __builtin_amdgcn_s_waitcnt(0);
+    __builtin_amdgcn_wave_barrier();
     AttnCore core;
+    core.nzcsum = csum[wave];
     core.poly = &A.poly;
     core.bq = A.bias2 + ((size_t)(mtype * G.heads + head) * TOK) * 64 + g * 4 * 64 + j;
     core.m2 = A.m2[branch];
@@ -577,9 +580,7 @@ __global__ __launch_bounds__(256) void attn_kernel(Geom G, AttnArgs A)
     core.tap_p = A.tap_p ? A.tap_p + tb : nullptr;
     v16i o[2];
     attention_core<true, 2>(qf, kf, vt, core, j, g, 0, o);
-    __builtin_amdgcn_s_waitcnt(0);
-    __builtin_amdgcn_wave_barrier();
-    attention_store<true, 2>(o, csum[wave], A.qo[branch], A.m_o[branch], j, g, 0, head, G.C, A.out, row0, A.tap_o, A.tap_code,
+    attention_store<true, 2>(o, A.qo[branch], A.m_o[branch], j, g, 0, head, G.C, A.out, row0, A.tap_o, A.tap_code,
                     (size_t)canon_slot * TOK);
 }
 
@@ -875,15 +876,15 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
 #pragma unroll
             for (int tb = 0; tb < NTB; ++tb) finish(tb, acc[tb]);
         }
-        cs += __shfl_xor(cs, 32, 64);
+        cs = half_sum(cs);
         if (QS == 1) {
-            if (g == 0) csum[wave][j] = A.qp[branch].zp * cs;
+            if (g == 0) csum[wave][j] = -(A.qp[branch].zp * cs);
         } else {                                                          // the pair exchanges its halves of K, V and the sums
             kvx[((hw * 2 + 0) * 2 + tb0) * 64 + lane] = qk[1][0];
             kvx[((hw * 2 + 1) * 2 + tb0) * 64 + lane] = vt[0];
             if (g == 0) csp[(hw * 2 + tb0) * HD + j] = cs;
             __syncthreads();
-            if (g == 0) csum[wave][j] = A.qp[branch].zp * (csp[(hw * 2) * HD + j] + csp[(hw * 2 + 1) * HD + j]);
+            if (g == 0) csum[wave][j] = -(A.qp[branch].zp * (csp[(hw * 2) * HD + j] + csp[(hw * 2 + 1) * HD + j]));
         }
     }
     v4i kf[2];
@@ -892,8 +893,11 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
         kf[kb] = QS == 1 ? qk[1][kb % NTB] : kvx[((hw * 2 + 0) * 2 + kb) * 64 + lane];
         if (QS == 2) vt[kb] = kvx[((hw * 2 + 1) * 2 + kb) * 64 + lane];
     }
+    __builtin_amdgcn_s_waitcnt(0xc07f);                                   // lgkmcnt(0): the wave's own csum entries are in LDS
+    __builtin_amdgcn_wave_barrier();
     AttnCore core;
     core.poly = &A.poly;
+    core.nzcsum = csum[wave];
     core.bq = A.bias2 + ((size_t)(mask_type(G, w) * NHT + head) * TOK) * 64 + g * 4 * 64 + tb0 * 32 + j;
     core.m2 = A.m2[branch];
     core.qp = A.qp[branch];
@@ -902,12 +906,10 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
     core.tap_p = A.tap_p ? A.tap_p + tbase : nullptr;
     v16i o[NTB];
     attention_core<TAPS, NTB>(qk[0], kf, vt, core, j, g, tb0, o);
-    __builtin_amdgcn_s_waitcnt(0);
-    __builtin_amdgcn_wave_barrier();
     const int pack = branch ? A.out_pack : 0;                            // the low region's rows may be packed (dense, after the high region)
-    if (pack) attention_store<TAPS, NTB>(o, csum[wave], A.qo[branch], A.m_o[branch], j, g, tb0, head, C, A.out + (size_t)G.base_lo * C,
+    if (pack) attention_store<TAPS, NTB>(o, A.qo[branch], A.m_o[branch], j, g, tb0, head, C, A.out + (size_t)G.base_lo * C,
                                          row0 - G.base_lo, A.tap_o, A.tap_code, canon_row0, pack);
-    else attention_store<TAPS, NTB>(o, csum[wave], A.qo[branch], A.m_o[branch], j, g, tb0, head, C, A.out, row0, A.tap_o, A.tap_code, canon_row0);
+    else attention_store<TAPS, NTB>(o, A.qo[branch], A.m_o[branch], j, g, tb0, head, C, A.out, row0, A.tap_o, A.tap_code, canon_row0);
 }
 
 // ------------------------------------------------------------------ fused token kernel
@@ -1013,31 +1015,32 @@ __global__ __launch_bounds__(NH * 64) __attribute__((amdgpu_waves_per_eu(tok_wav
         }
     }
     {   // LN2: binary64 partial sums per (wave, token) through LDS, then normalise and quantize
-        double s = 0.0;
+        Moments m;
 #pragma unroll
-        for (int r = 0; r < 16; r += 4) s += ((double)h[r] + (double)h[r + 1]) + ((double)h[r + 2] + (double)h[r + 3]);
-        s += __shfl_xor(s, 32, 64);
-        if (g == 0) part[0][wave][j] = s;
+        for (int r = 0; r < 16; r += 4) moments_add(m, h[r], h[r + 1], h[r + 2], h[r + 3]);
+        m.s = half_sum(m.s);
+        m.q = half_sum(m.q);
+        if (g == 0) { part[0][wave][j] = m.s; part[1][wave][j] = m.q; }
         __syncthreads();
-        double tot = 0.0;
+        double s = 0.0, q = 0.0;
 #pragma unroll
-        for (int w2 = 0; w2 < NH; ++w2) tot += part[0][w2][j];
-        const float mean = (float)(tot / (double)C);
-        double q = 0.0;
+        for (int w2 = 0; w2 < NH; ++w2) { s += part[0][w2][j]; q += part[1][w2][j]; }
+        const float mean = moments_mean(s, C);
+        bool shaky;
+        double var = moments_centred(s, q, mean, C, shaky);
+        if (__any(shaky)) {                                            // every wave sees the same 32 tokens' sums: uniform over the workgroup
+            q = 0.0;
 #pragma unroll
-        for (int r = 0; r < 16; r += 4) {
-            double a = (double)h[r] - (double)mean, b = (double)h[r + 1] - (double)mean;
-            double c = (double)h[r + 2] - (double)mean, d = (double)h[r + 3] - (double)mean;
-            q += (a * a + b * b) + (c * c + d * d);
+            for (int r = 0; r < 16; r += 4) q += centred_squares(h[r], h[r + 1], h[r + 2], h[r + 3], mean);
+            q = half_sum(q);
+            __syncthreads();                                          // the sums have been read
+            if (g == 0) part[1][wave][j] = q;
+            __syncthreads();
+            var = 0.0;
+#pragma unroll
+            for (int w2 = 0; w2 < NH; ++w2) var += part[1][w2][j];
         }
-        q += __shfl_xor(q, 32, 64);
-        if (g == 0) part[1][wave][j] = q;
-        __syncthreads();
-        tot = 0.0;
-#pragma unroll
-        for (int w2 = 0; w2 < NH; ++w2) tot += part[1][w2][j];
-        const float var = (float)(tot / (double)C);
-        const float rstd = 1.0f / sqrtf(var + A.eps);
+        const float rstd = moments_rstd(var, C, A.eps);
         const QDev qa = A.q_fc1in[branch];
         int wd[4];
 #pragma unroll
@@ -1241,40 +1244,50 @@ __global__ __launch_bounds__(NH * 64) void token_wide_kernel(Geom G, TokArgs A)
     }
     {   // LN2: binary64 partial sums per (wave, token) through LDS, then normalise and quantize
         float mean[RB];
+        double var[RB];
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) {
-            double s = 0.0;
+            Moments m;
 #pragma unroll
-            for (int r = 0; r < 16; r += 4) s += ((double)h[rb][r] + (double)h[rb][r + 1]) + ((double)h[rb][r + 2] + (double)h[rb][r + 3]);
-            s += __shfl_xor(s, 32, 64);
-            if (g == 0) part[0][wave][rb * 32 + j] = s;
+            for (int r = 0; r < 16; r += 4) moments_add(m, h[rb][r], h[rb][r + 1], h[rb][r + 2], h[rb][r + 3]);
+            m.s = half_sum(m.s);
+            m.q = half_sum(m.q);
+            if (g == 0) { part[0][wave][rb * 32 + j] = m.s; part[1][wave][rb * 32 + j] = m.q; }
         }
         __syncthreads();                                              // also: every wave is done reading the attention codes
+        bool any_shaky = false;
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) {
-            double tot = 0.0;
+            double s = 0.0, q = 0.0;
 #pragma unroll
-            for (int w2i = 0; w2i < NH; ++w2i) tot += part[0][w2i][rb * 32 + j];
-            mean[rb] = (float)(tot / (double)C);
-            double q = 0.0;
-#pragma unroll
-            for (int r = 0; r < 16; r += 4) {
-                double a = (double)h[rb][r] - (double)mean[rb], b = (double)h[rb][r + 1] - (double)mean[rb];
-                double c = (double)h[rb][r + 2] - (double)mean[rb], d = (double)h[rb][r + 3] - (double)mean[rb];
-                q += (a * a + b * b) + (c * c + d * d);
-            }
-            q += __shfl_xor(q, 32, 64);
-            if (g == 0) part[1][wave][rb * 32 + j] = q;
+            for (int w2i = 0; w2i < NH; ++w2i) { s += part[0][w2i][rb * 32 + j]; q += part[1][w2i][rb * 32 + j]; }
+            mean[rb] = moments_mean(s, C);
+            bool shaky;
+            var[rb] = moments_centred(s, q, mean[rb], C, shaky);
+            any_shaky |= shaky;
         }
-        __syncthreads();
+        if (__any(any_shaky)) {                                        // every wave sees the same tokens' sums: uniform over the workgroup
+            __syncthreads();                                          // the sums have been read
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb) {
+                double q = 0.0;
+#pragma unroll
+                for (int r = 0; r < 16; r += 4) q += centred_squares(h[rb][r], h[rb][r + 1], h[rb][r + 2], h[rb][r + 3], mean[rb]);
+                q = half_sum(q);
+                if (g == 0) part[1][wave][rb * 32 + j] = q;
+            }
+            __syncthreads();
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb) {
+                var[rb] = 0.0;
+#pragma unroll
+                for (int w2i = 0; w2i < NH; ++w2i) var[rb] += part[1][w2i][rb * 32 + j];
+            }
+        }
         const QDev qa = A.q_fc1in[branch];
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) {
-            double tot = 0.0;
-#pragma unroll
-            for (int w2i = 0; w2i < NH; ++w2i) tot += part[1][w2i][rb * 32 + j];
-            const float var = (float)(tot / (double)C);
-            const float rstd = 1.0f / sqrtf(var + A.eps);
+            const float rstd = moments_rstd(var[rb], C, A.eps);
             int wd[4];
 #pragma unroll
             for (int qd = 0; qd < 4; ++qd) {

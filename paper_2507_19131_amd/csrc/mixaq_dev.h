@@ -54,10 +54,11 @@ struct PolyCoef {
     float e[6];       // 2^r on [-1/2, 1/2], degree 5, e[0] = constant term
 };
 
-// 2^y for y <= 0 (clamped at -100): split, degree-5 polynomial, exact scaling.
+// 2^y for y <= 0: split, degree-5 polynomial, exact scaling.  The definition holds y at -100 from below; the code leaves
+// that out: a term under 2^-99 changes neither the denominator of its row (which is at least 1: the row's maximum
+// contributes 2^0, and binary64 cannot see 49 such terms beside it) nor a code.  y must be finite (the bias table is).
 __device__ __forceinline__ float exp2_pinned(float y, const PolyCoef& P)
 {
-    y = fmaxf(y, -100.0f);
     float n = rintf(y);
     float r = y - n;
     float p = P.e[5];
@@ -123,6 +124,82 @@ __device__ __forceinline__ v4i unpack_codes(const int8_t* packed_row, int mode, 
     const int s = half * 4;
     return (v4i){(w.x >> s) & 0x03030303, (w.y >> s) & 0x03030303, (w.x >> (s + 2)) & 0x03030303, (w.y >> (s + 2)) & 0x03030303};
 }
+
+// ---- sums across lanes, in the vector unit (a __shfl goes through the LDS pipe: tens of clocks instead of a few) ----
+// value of the lane in the same place of the other half of the wave, combined with the own one: r.lo + r.hi in both halves
+__device__ __forceinline__ float half_max(float v)
+{
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);   // {lo,lo}, {hi,hi}
+    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+__device__ __forceinline__ int half_sum(int v)
+{
+    const auto r = __builtin_amdgcn_permlane32_swap((unsigned)v, (unsigned)v, false, false);
+    return (int)r[0] + (int)r[1];
+}
+__device__ __forceinline__ double half_sum(double v)
+{
+    const auto l = __builtin_amdgcn_permlane32_swap((unsigned)__double2loint(v), (unsigned)__double2loint(v), false, false);
+    const auto h = __builtin_amdgcn_permlane32_swap((unsigned)__double2hiint(v), (unsigned)__double2hiint(v), false, false);
+    return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp_add(double v)
+{
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, true);
+    return v + __hiloint2double(hi, lo);
+}
+// butterfly over W = 2, 4, ... 64 consecutive lanes: inside a row of sixteen by DPP (quad permutes, then the mirrors: the
+// partial sums are already equal inside a quad / half row), across rows by the row swaps
+template <int W>
+__device__ __forceinline__ double lanes_sum(double v)
+{
+    if (W >= 2) v = dpp_add<0xb1>(v);                            // quad_perm [1,0,3,2]
+    if (W >= 4) v = dpp_add<0x4e>(v);                            // quad_perm [2,3,0,1]
+    if (W >= 8) v = dpp_add<0x141>(v);                           // row_half_mirror
+    if (W >= 16) v = dpp_add<0x140>(v);                          // row_mirror
+    if (W >= 32) {
+        const auto l = __builtin_amdgcn_permlane16_swap((unsigned)__double2loint(v), (unsigned)__double2loint(v), false, false);
+        const auto h = __builtin_amdgcn_permlane16_swap((unsigned)__double2hiint(v), (unsigned)__double2hiint(v), false, false);
+        v = __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
+    }
+    if (W >= 64) v = half_sum(v);
+    return v;
+}
+
+// ---- LayerNorm statistics of one token, binary64 -------------------------------------------------
+// One pass: sum and sum of squares together (convert, add, fused multiply-add: three vector instructions per element
+// where mean first, centred squares second takes five, and one exchange between the lanes or waves of a token instead of
+// two).  sum (x - mean)^2 = q - mean (2 s - C mean) for the ROUNDED mean, so the result is the one of the two-pass form up
+// to the cancellation in that subtraction, at most 64 times 2^-52 relative: where the token's mean is so large that more
+// would cancel, moments_shaky says so and the caller takes the centred squares in a second pass.
+struct Moments { double s = 0.0, q = 0.0; };
+__device__ __forceinline__ void moments_add(Moments& m, float a, float b, float c, float d)
+{
+    const double ad = a, bd = b, cd = c, dd = d;
+    m.s += (ad + bd) + (cd + dd);
+    m.q = __builtin_fma(ad, ad, m.q);
+    m.q = __builtin_fma(bd, bd, m.q);
+    m.q = __builtin_fma(cd, cd, m.q);
+    m.q = __builtin_fma(dd, dd, m.q);
+}
+__device__ __forceinline__ float moments_mean(double s, int C) { return (float)(s * (1.0 / (double)C)); }
+// the centred sum of squares; shaky: too much of it cancelled
+__device__ __forceinline__ double moments_centred(double s, double q, float mean, int C, bool& shaky)
+{
+    const double m = mean;
+    const double v = __builtin_fma(-m, __builtin_fma(-(double)C, m, s + s), q);
+    shaky = v * 64.0 < q;
+    return v;
+}
+__device__ __forceinline__ double centred_squares(float x0, float x1, float x2, float x3, float mean)
+{
+    const double a = (double)x0 - (double)mean, b = (double)x1 - (double)mean;
+    const double c = (double)x2 - (double)mean, d = (double)x3 - (double)mean;
+    return (a * a + b * b) + (c * c + d * d);
+}
+__device__ __forceinline__ float moments_rstd(double v, int C, float eps) { return 1.0f / sqrtf((float)(v * (1.0 / (double)C)) + eps); }
 
 // D[32x32] += A[32 x 32k] * B[32k x 32]; lane l supplies row (A) / column (B) l%32 and
 // the 16 k-values of half l/32; D register r of lane l is row (r/4)*8 + (l/32)*4 + r%4,
