@@ -381,8 +381,8 @@ __global__ __launch_bounds__(256) void gemm_tile_kernel(Geom G, GemmArgs A)
 // subtracting afterwards took one per output element).
 struct AttnCore {
     const PolyCoef* poly;
-    const float* bq;          // (bias + mask) * log2e of query j of query block ib0 at key g*4, in the [49 keys][64 queries]
-                              // table of this head and mask type: key k + g*4, query block ib0 + ib is bq[k * 64 + ib * 32]
+    const float* bq;          // (bias + mask) * log2e of query j of query block 0 at key g*4, in the [49 keys][64 queries]
+                              // table of this head and mask type: key k + g*4, query block ib is bq[k * 64 + ib * 32]
     float m2;
     QDev qp;
     const int* nzcsum;        // [HD], LDS
@@ -390,17 +390,17 @@ struct AttnCore {
     int8_t* tap_p;
 };
 
-template <bool TAPS, int NIB>
-__device__ __forceinline__ void attention_core(const v4i (&qf)[NIB], const v4i (&kf)[2], const v4i (&vt)[2],
-                                               const AttnCore& A, int j, int g, int ib0, v16i (&o)[NIB])
+template <bool TAPS>
+__device__ __forceinline__ v16i attention_core(const v4i& qf, const v4i (&kf)[2], const v4i (&vt)[2],
+                                               const AttnCore& A, int j, int g, int ib)
 {
     const v16i zero16 = {0};
-#pragma unroll
-    for (int ib = 0; ib < NIB; ++ib) {
-        const int qi = (ib0 + ib) * 32 + j;                               // this lane's query
+    v16i o;
+    {
+        const int qi = ib * 32 + j;                               // this lane's query
         v16i s[2];                                                        // S^T tiles of this query block, per key block
-        s[0] = mfma32(kf[0], qf[ib], zero16);
-        s[1] = mfma32(kf[1], qf[ib], zero16);
+        s[0] = mfma32(kf[0], qf, zero16);
+        s[1] = mfma32(kf[1], qf, zero16);
         float lg[2][16];
         float mx = -INFINITY;
 #pragma unroll
@@ -459,29 +459,29 @@ __device__ __forceinline__ void attention_core(const v4i (&qf)[NIB], const v4i (
 #pragma unroll
         for (int qd = 0; qd < 4; ++qd) {
             const int4 cz = *(const int4*)(A.nzcsum + qd * 8 + g * 4);
-            o[ib][qd * 4 + 0] = cz.x; o[ib][qd * 4 + 1] = cz.y; o[ib][qd * 4 + 2] = cz.z; o[ib][qd * 4 + 3] = cz.w;
+            o[qd * 4 + 0] = cz.x; o[qd * 4 + 1] = cz.y; o[qd * 4 + 2] = cz.z; o[qd * 4 + 3] = cz.w;
         }
-        o[ib] = mfma32(vt[0], pk[0], o[ib]);
-        o[ib] = mfma32(vt[1], pk[1], o[ib]);
+        o = mfma32(vt[0], pk[0], o);
+        o = mfma32(vt[1], pk[1], o);
     }
+    return o;
 }
 
 // dequantization and requantization of the P.V sums; writes the codes of head `head` for the window's tokens to
 // out[row0 + token][C] (and the taps)
-template <bool TAPS, int NIB>
-__device__ __forceinline__ void attention_store(const v16i (&o)[NIB], const QDev& qo, float m_o,
-                                                int j, int g, int ib0, int head, int C, int8_t* out, int row0, int32_t* tap_o,
+template <bool TAPS>
+__device__ __forceinline__ void attention_store(const v16i& o, const QDev& qo, float m_o,
+                                                int j, int g, int ib, int head, int C, int8_t* out, int row0, int32_t* tap_o,
                                                 int8_t* tap_code, size_t canon_row0, int pack = 0)
 {
-#pragma unroll
-    for (int ib = 0; ib < NIB; ++ib) {
-        const int qi = (ib0 + ib) * 32 + j;
+    {
+        const int qi = ib * 32 + j;
         if (qi < TOK) {
             int code[4];
 #pragma unroll
             for (int qd = 0; qd < 4; ++qd) {
                 const int d0 = qd * 8 + g * 4;
-                const int a0 = o[ib][qd * 4 + 0], a1 = o[ib][qd * 4 + 1], a2 = o[ib][qd * 4 + 2], a3 = o[ib][qd * 4 + 3];
+                const int a0 = o[qd * 4 + 0], a1 = o[qd * 4 + 1], a2 = o[qd * 4 + 2], a3 = o[qd * 4 + 3];
                 code[qd] = pack4(quant_code((float)a0 * m_o, qo), quant_code((float)a1 * m_o, qo),
                                  quant_code((float)a2 * m_o, qo), quant_code((float)a3 * m_o, qo));
                 const int ch = head * HD + d0;
@@ -578,10 +578,11 @@ __global__ __launch_bounds__(256) void attn_kernel(Geom G, AttnArgs A)
     const size_t tb = ((size_t)canon_slot * G.heads + head) * TOK * TOK;
     core.tap_s = A.tap_s ? A.tap_s + tb : nullptr;
     core.tap_p = A.tap_p ? A.tap_p + tb : nullptr;
-    v16i o[2];
-    attention_core<true, 2>(qf, kf, vt, core, j, g, 0, o);
-    attention_store<true, 2>(o, A.qo[branch], A.m_o[branch], j, g, 0, head, G.C, A.out, row0, A.tap_o, A.tap_code,
-                    (size_t)canon_slot * TOK);
+#pragma unroll 1
+    for (int ib = 0; ib < 2; ++ib) {
+        const v16i o = attention_core<true>(ib ? qf[1] : qf[0], kf, vt, core, j, g, ib);
+        attention_store<true>(o, A.qo[branch], A.m_o[branch], j, g, ib, head, G.C, A.out, row0, A.tap_o, A.tap_code, (size_t)canon_slot * TOK);
+    }
 }
 
 // ------------------------------------------------------------------ fused window kernel
@@ -592,7 +593,6 @@ __global__ __launch_bounds__(256) void attn_kernel(Geom G, AttnArgs A)
 //   gather (shift folded into the index map) + LN1 + quantize, shared through LDS as MFMA
 //   fragments -> per head: q, k (transposed product, lane = token) and v (plain product, lane =
 //   dim) straight into operand registers -> attention core -> codes of the attention output.
-constexpr int WIN_WAVES_PER_EU = 3;
 template <int NH, int HG, int QS>
 struct WinCfg {
     // lanes per token in the LN phase: one per wave (3 ... 16), so that the 49 tokens fit one pass
@@ -601,7 +601,12 @@ struct WinCfg {
     static constexpr int GPW = 64 / LPT;                             // groups (tokens) per wave
     static constexpr int NV = NH * HG * 32 / (4 * LPT);              // float4 per lane = 8 * HG / QS
 };
-constexpr int win_waves_per_eu(int NH, int HG, int QS) { return QS == 2 ? (NH * HG > 8 ? 3 : 4) : (HG == 2 && NH <= 8) ? 2 : WIN_WAVES_PER_EU; }
+// Waves per SIMD the kernel is compiled for.  The loops over q / k and over the query blocks are real loops (unrolled, the
+// scheduler spreads their loads over the whole kernel and wants 160 registers): with them a wave that owns a head needs 96
+// to 128 registers instead of 160, one of a pair 80 instead of 100.  A workgroup of six or twelve waves only gets a second
+// place on a CU when its share per SIMD, rounded up, fits twice: 360 windows at C = 192 ran in two rounds of one workgroup
+// per CU (24.6 us), now in one round (20.8 us); C = 256, 1444 windows: 83 -> 72 us.
+constexpr int win_waves_per_eu(int NH, int HG, int QS) { return QS == 2 ? (NH * HG > 8 ? 4 : 6) : NH * HG > 8 ? 3 : NH == 3 ? 5 : 4; }
 
 // word offsets inside the window kernel's parameter block of one branch (see WinArgs::params)
 template <int C> struct WinPrm {
@@ -627,8 +632,7 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, j = lane & 31, g = lane >> 5;
     const int hw = QS == 1 ? wave : wave >> 1, tb0 = QS == 1 ? 0 : wave & 1;   // head inside the workgroup, first token block
     const int head = hg * NH + hw;
-    constexpr bool HOIST = KS <= 8;
-    constexpr int RING = 6;
+    constexpr int RING = KS < 6 ? KS : 6;                                // weight fragments in flight
     auto weights_of = [&](int which) { return A.Wqkv + (size_t)(which * NHT + head) * KS * 64 + lane; };
     // SCORED: the workgroup is given a window and finds its own place in the selection (its rank
     // under the total order of the scores); otherwise it is given a slot and looks the window up.
@@ -746,17 +750,9 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
         }
     }
     __syncthreads();
-    // Operand handling.  Up to eight heads the LN1 fragments of both token blocks and the weight
-    // fragments of one output block sit in registers; beyond that the B operand is read from LDS
-    // inside the chain and the weight fragments stream through a short ring.
-    v4i bf[NTB][HOIST ? KS : 1];
-    if (HOIST) {
-#pragma unroll
-        for (int tb = 0; tb < NTB; ++tb)
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks) bf[tb][ks] = a1s[((tb0 + tb) * KS + ks) * 64 + lane];
-    }
-    // streaming form: acc[tb] += (weights as A operand ? W * act^T : act * W^T) over the whole K
+    // The B operand (LN1 fragments) is read from LDS inside the chain and the weight fragments come through a short ring of
+    // loads: held in registers instead (24 to 64 of them) they cost the kernel its fourth and fifth wave per SIMD.
+    // acc[tb] += (weights as A operand ? W * act^T : act * W^T) over the whole K
     auto chain = [&](const v4i* wp, v16i* acc, bool weights_first) {
         v4i ring[RING];
 #pragma unroll
@@ -774,8 +770,9 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
     };
     const size_t canon_row0 = (size_t)canon_slot * TOK;
     v4i qk[2][NTB];                                                      // [q|k][token block]
-#pragma unroll
+#pragma unroll 1
     for (int which = 0; which < 2; ++which) {
+        asm volatile("" ::: "memory");                                    // the B operand is read from LDS each time: keep the reads in the loop
         const int nb = which * NHT + head;
         const QDev qq = A.q_qkv[branch][which];
         const v4i* wp = weights_of(which);
@@ -801,28 +798,15 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
                     if (A.tap_qkv) *(int*)(A.tap_qkv + (canon_row0 + tok) * (3 * C) + n0) = wd[qd];
                 }
             }
-            qk[which][tb] = (v4i){wd[0], wd[1], wd[2], wd[3]};
+            if (which) qk[1][tb] = (v4i){wd[0], wd[1], wd[2], wd[3]};
+            else qk[0][tb] = (v4i){wd[0], wd[1], wd[2], wd[3]};
         };
-        if (HOIST) {
-            v4i wf[KS];
+        v16i acc[NTB];
+        start(acc[0]);
+        if (NTB == 2) acc[NTB - 1] = acc[0];
+        chain(wp, acc, true);
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks) wf[ks] = wp[ks * 64];
-#pragma unroll
-            for (int tb = 0; tb < NTB; ++tb) {
-                v16i acc;
-                start(acc);
-#pragma unroll
-                for (int ks = 0; ks < KS; ++ks) acc = mfma32(wf[ks], bf[tb][ks], acc);
-                finish(tb, acc);
-            }
-        } else {
-            v16i acc[NTB];
-            start(acc[0]);
-            if (NTB == 2) acc[NTB - 1] = acc[0];
-            chain(wp, acc, true);
-#pragma unroll
-            for (int tb = 0; tb < NTB; ++tb) finish(tb, acc[tb]);
-        }
+        for (int tb = 0; tb < NTB; ++tb) finish(tb, acc[tb]);
     }
     v4i vt[2];
     {
@@ -854,28 +838,13 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
             }
             vt[tb] = (v4i){wd[0], wd[1], wd[2], wd[3]};
         };
-        if (HOIST) {
-            v4i wf[KS];
+        v16i acc[NTB];
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks) wf[ks] = wp[ks * 64];
+        for (int r = 0; r < 16; ++r) acc[0][r] = nc;
+        if (NTB == 2) acc[NTB - 1] = acc[0];
+        chain(wp, acc, false);
 #pragma unroll
-            for (int tb = 0; tb < NTB; ++tb) {
-                v16i acc;
-#pragma unroll
-                for (int r = 0; r < 16; ++r) acc[r] = nc;
-#pragma unroll
-                for (int ks = 0; ks < KS; ++ks) acc = mfma32(bf[tb][ks], wf[ks], acc);      // rows = tokens, columns = dims
-                finish(tb, acc);
-            }
-        } else {
-            v16i acc[NTB];
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[0][r] = nc;
-            if (NTB == 2) acc[NTB - 1] = acc[0];
-            chain(wp, acc, false);
-#pragma unroll
-            for (int tb = 0; tb < NTB; ++tb) finish(tb, acc[tb]);
-        }
+        for (int tb = 0; tb < NTB; ++tb) finish(tb, acc[tb]);
         cs = half_sum(cs);
         if (QS == 1) {
             if (g == 0) csum[wave][j] = -(A.qp[branch].zp * cs);
@@ -898,18 +867,21 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
     AttnCore core;
     core.poly = &A.poly;
     core.nzcsum = csum[wave];
-    core.bq = A.bias2 + ((size_t)(mask_type(G, w) * NHT + head) * TOK) * 64 + g * 4 * 64 + tb0 * 32 + j;
+    core.bq = A.bias2 + ((size_t)(mask_type(G, w) * NHT + head) * TOK) * 64 + g * 4 * 64 + j;
     core.m2 = A.m2[branch];
     core.qp = A.qp[branch];
     const size_t tbase = ((size_t)canon_slot * NHT + head) * TOK * TOK;
     core.tap_s = A.tap_s ? A.tap_s + tbase : nullptr;
     core.tap_p = A.tap_p ? A.tap_p + tbase : nullptr;
-    v16i o[NTB];
-    attention_core<TAPS, NTB>(qk[0], kf, vt, core, j, g, tb0, o);
     const int pack = branch ? A.out_pack : 0;                            // the low region's rows may be packed (dense, after the high region)
-    if (pack) attention_store<TAPS, NTB>(o, A.qo[branch], A.m_o[branch], j, g, tb0, head, C, A.out + (size_t)G.base_lo * C,
-                                         row0 - G.base_lo, A.tap_o, A.tap_code, canon_row0, pack);
-    else attention_store<TAPS, NTB>(o, A.qo[branch], A.m_o[branch], j, g, tb0, head, C, A.out, row0, A.tap_o, A.tap_code, canon_row0);
+    int8_t* out = A.out + (pack ? (size_t)G.base_lo * C : 0);
+    const int orow0 = row0 - (pack ? G.base_lo : 0);
+#pragma unroll 1
+    for (int ib = tb0; ib < tb0 + NTB; ++ib) {
+        asm volatile("" ::: "memory");
+        const v16i o = attention_core<TAPS>(NTB == 2 && ib ? qk[0][NTB - 1] : qk[0][0], kf, vt, core, j, g, ib);
+        attention_store<TAPS>(o, A.qo[branch], A.m_o[branch], j, g, ib, head, C, out, orow0, A.tap_o, A.tap_code, canon_row0, pack);
+    }
 }
 
 // ------------------------------------------------------------------ fused token kernel
