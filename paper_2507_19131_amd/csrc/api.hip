@@ -13,6 +13,7 @@
 
 #include "../../include/mixaq.h"
 #include "kernels.h"
+#include "arena.h"
 
 using namespace mixaq;
 
@@ -99,19 +100,6 @@ QDev make_qdev(mixaq_qparam p, int bits)
     return q;
 }
 
-// device buffer owned by a block
-template <typename T>
-int upload(std::vector<void*>& owned, const std::vector<T>& host, T** dev)
-{
-    void* p = nullptr;
-    size_t bytes = host.size() * sizeof(T);
-    HIP_TRY(hipMalloc(&p, bytes ? bytes : 16));
-    owned.push_back(p);
-    if (bytes) HIP_TRY(hipMemcpy(p, host.data(), bytes, hipMemcpyHostToDevice));
-    *dev = (T*)p;
-    return MIXAQ_OK;
-}
-
 template <typename T>
 int download(const T* dev, size_t n, std::vector<T>& host)
 {
@@ -128,6 +116,8 @@ struct Linear {           // one shadow layer prepared for the device
     float* bias[2] = {nullptr, nullptr};
     int* negcorr[2] = {nullptr, nullptr};
     std::vector<int> colsum;   // sum_k W[n,k], kept on the host
+    std::vector<float> hm[2], hb[2];   // host copies of m, bias and negcorr, while the block is being built
+    std::vector<int> hnc[2];
 };
 
 }  // namespace
@@ -135,7 +125,7 @@ struct Linear {           // one shadow layer prepared for the device
 struct mixaq_block {
     mixaq_block_desc d;
     int Hp, Wp, nWc, nW;
-    std::vector<void*> owned;
+    Arena mem;                 // everything the block keeps on the device
     Linear qkv, proj, fc1, fc2;
     float* ln_gamma[2][2];     // [which LN][branch]
     float* ln_beta[2][2];
@@ -217,9 +207,7 @@ int prepare_linear(mixaq_block* blk, Linear& L, const int8_t* w_dev, const float
     L.K = K;
     L.N = N;
     L.colsum = colsum;
-    int8_t* wp = nullptr;
-    if ((rc = upload(blk->owned, packed, &wp))) return rc;
-    L.Wp = (v4i*)wp;
+    blk->mem.add(packed, &L.Wp);
     if (reg_order) {
         for (int nb = 0; nb < NB; ++nb)
             for (int ks = 0; ks < KS; ++ks)
@@ -228,8 +216,7 @@ int prepare_linear(mixaq_block* blk, Linear& L, const int8_t* w_dev, const float
                         int k = ks * 32 + (r / 4) * 8 + (lane / 32) * 4 + r % 4;
                         packed[(((size_t)nb * KS + ks) * 64 + lane) * 16 + r] = w[(size_t)(nb * 32 + lane % 32) * K + k];
                     }
-        if ((rc = upload(blk->owned, packed, &wp))) return rc;
-        L.Wp_reg = (v4i*)wp;
+        blk->mem.add(packed, &L.Wp_reg);
     }
     for (int br = 0; br < 2; ++br) {
         if ((rc = download(bias_dev[br], (size_t)N, b))) return rc;
@@ -240,9 +227,10 @@ int prepare_linear(mixaq_block* blk, Linear& L, const int8_t* w_dev, const float
             b[n] *= out_scale;
             nc[n] = -in_q[br].zero_point * colsum[n];
         }
-        if ((rc = upload(blk->owned, m, &L.m[br]))) return rc;
-        if ((rc = upload(blk->owned, b, &L.bias[br]))) return rc;
-        if ((rc = upload(blk->owned, nc, &L.negcorr[br]))) return rc;
+        blk->mem.add(m, &L.m[br]);
+        blk->mem.add(b, &L.bias[br]);
+        blk->mem.add(nc, &L.negcorr[br]);
+        L.hm[br] = m; L.hb[br] = b; L.hnc[br] = nc;
     }
     return MIXAQ_OK;
 }
@@ -394,7 +382,8 @@ int forward_impl(const mixaq_block* blk, const float* x, const int32_t* perm, co
         wa.x = x; wa.perm = perm; wa.scores = in_kernel_select ? scores : nullptr; wa.perm_out = perm_out ? perm_out : ws.perm;
         wa.y = y; wa.eps = d.ln_eps; wa.Wqkv = blk->qkv.Wp; wa.bias2 = blk->bias2; wa.out = ws.ao;
         wa.row_pix = ws.row_pix; wa.row_canon = ws.row_canon;
-        wa.out_pack = ft ? blk->ao_pack : 0;
+        wa.codes = ws.qkv;                                             // wide blocks only: 64 C bytes per window of the 147 C there
+        wa.out_pack = ft ? blk->ao_pack : PACK_FRAG;
         for (int br = 0; br < 2; ++br) {
             wa.params[br] = blk->win_params[br]; wa.q_in[br] = blk->q_in[br];
             for (int k = 0; k < 3; ++k) wa.q_qkv[br][k] = blk->q_qkv[br][k];
@@ -465,6 +454,7 @@ int forward_impl(const mixaq_block* blk, const float* x, const int32_t* perm, co
     mark(7);
     for (int r = 0; r < reps; ++r) launch_gemm(G, ga, EPI_FC1, st);
     fill(ga, blk->fc2, ws.g);
+    ga.Wp = blk->fc2.Wp_reg;                                           // FC1 leaves its codes in the order of its result registers
     ga.resid = ws.h; ga.y = y; ga.tap_acc = tp.acc_fc2; ga.tap_f = tp.y_win;
     mark(8);
     for (int r = 0; r < reps; ++r) launch_gemm(G, ga, EPI_FC2, st);
@@ -563,13 +553,13 @@ static int block_create(const mixaq_block_desc* desc, const mixaq_shared_params*
     if ((rc = prepare_linear(b, b->fc1, sh->w_fc1, sh->s_fc1, F, C, bias, qi, desc->weight_bits, true, GELU_SCALE))) return bail(rc);
     qi[0] = branch[0].a_fc2_in; qi[1] = branch[1].a_fc2_in; bias[0] = branch[0].b_fc2; bias[1] = branch[1].b_fc2;
     if ((rc = prepare_linear(b, b->fc2, sh->w_fc2, sh->s_fc2, C, F, bias, qi, desc->weight_bits, true))) return bail(rc);
-    std::vector<float> tmp;
+    std::vector<float> tmp, hln[2][4];                    // [branch][ln1 gamma, ln1 beta, ln2 gamma, ln2 beta]
     for (int br = 0; br < 2; ++br) {
         const float* src[4] = {branch[br].ln1_gamma, branch[br].ln1_beta, branch[br].ln2_gamma, branch[br].ln2_beta};
         float** dst[4] = {&b->ln_gamma[0][br], &b->ln_beta[0][br], &b->ln_gamma[1][br], &b->ln_beta[1][br]};
         for (int k = 0; k < 4; ++k) {
-            if ((rc = download(src[k], (size_t)C, tmp))) return bail(rc);
-            if ((rc = upload(b->owned, tmp, dst[k]))) return bail(rc);
+            if ((rc = download(src[k], (size_t)C, hln[br][k]))) return bail(rc);
+            b->mem.add(hln[br][k], dst[k]);
         }
         int bits = br == 0 ? desc->act_bits_high : desc->act_bits_low;
         b->q_in[br] = make_qdev(branch[br].a_qkv_in, bits);
@@ -586,9 +576,9 @@ static int block_create(const mixaq_block_desc* desc, const mixaq_shared_params*
     }
     if (desc->score_mode == 1) {
         if ((rc = download(sh->score_gamma, (size_t)C, tmp))) return bail(rc);
-        if ((rc = upload(b->owned, tmp, &b->score_gamma))) return bail(rc);
+        b->mem.add(tmp, &b->score_gamma);
         if ((rc = download(sh->score_beta, (size_t)C, tmp))) return bail(rc);
-        if ((rc = upload(b->owned, tmp, &b->score_beta))) return bail(rc);
+        b->mem.add(tmp, &b->score_beta);
     }
     // (relative position bias + shift mask) * log2(e), transposed to [type][head][key][query 64]
     {
@@ -613,48 +603,44 @@ static int block_create(const mixaq_block_desc* desc, const mixaq_shared_params*
                         tab[(((size_t)type * heads + h) * TOK + j) * 64 + i] = v > -1e30f ? v : -1e30f;
                     }
         }
-        if ((rc = upload(b->owned, tab, &b->bias2))) return bail(rc);
+        b->mem.add(tab, &b->bias2);
     }
     {
         std::vector<float> tab((size_t)GELU_K * 4);
         gelu_table(tab.data());
-        float* dev = nullptr;
-        if ((rc = upload(b->owned, tab, &dev))) return bail(rc);
-        b->gelu_tab = (const float4*)dev;
+        b->mem.add(tab, &b->gelu_tab);
     }
     b->fused_window = fused_window_supported(C);
     b->fused_token = fused_token_supported(C, desc->mlp_ratio);
-    auto gather_block = [&](const std::vector<std::pair<const void*, int>>& parts, float** dst) {
-        size_t words = 0;
-        for (auto& pt : parts) words += pt.second;
-        std::vector<float> blkp(words);
-        size_t off = 0;
-        for (auto& pt : parts) {
-            if (hipMemcpy(blkp.data() + off, pt.first, (size_t)pt.second * 4, hipMemcpyDeviceToHost) != hipSuccess)
-                return fail(MIXAQ_E_HIP, "copy of a parameter block failed");
-            off += pt.second;
+    if (b->fused_window)      // parameter blocks of the window kernel: LN1, then the QKV constants head by head
+        for (int br = 0; br < 2; ++br) {
+            std::vector<float> blkp = hln[br][0];
+            blkp.insert(blkp.end(), hln[br][1].begin(), hln[br][1].end());
+            const Linear& L = b->qkv;
+            for (int h = 0; h < heads; ++h)
+                for (int which = 0; which < 3; ++which) {
+                    const int n0 = which * C + h * HD;
+                    blkp.insert(blkp.end(), L.hm[br].begin() + n0, L.hm[br].begin() + n0 + HD);
+                    blkp.insert(blkp.end(), L.hb[br].begin() + n0, L.hb[br].begin() + n0 + HD);
+                    const size_t at = blkp.size();
+                    blkp.resize(at + HD);
+                    memcpy(&blkp[at], &L.hnc[br][n0], HD * 4);
+                }
+            b->mem.add(blkp, &b->win_params[br]);
         }
-        return upload(b->owned, blkp, dst);
-    };
-    if (b->fused_window)      // parameter blocks of the window kernel
-        for (int br = 0; br < 2; ++br)
-            if ((rc = gather_block({{b->ln_gamma[0][br], C}, {b->ln_beta[0][br], C}, {b->qkv.m[br], 3 * C}, {b->qkv.bias[br], 3 * C},
-                                    {b->qkv.negcorr[br], 3 * C}}, &b->win_params[br])))
-                return bail(rc);
     // Both fused kernels present: the low branch's attention-output codes cross between them packed (two or four
     // per byte, offset-binary); the projection of packed rows then starts at -(zp + offset) * colsum.
     if (b->fused_window && b->fused_token) b->ao_pack = pack_mode(desc->act_bits_low);
-    if (b->fused_token) {     // parameter blocks of the token kernel: device-to-device gathers of what was just uploaded
+    if (b->fused_token) {     // parameter blocks of the token kernel
         for (int br = 0; br < 2; ++br) {
             std::vector<float> blkp((size_t)8 * C + 3 * F);
             struct { const void* src; int n; } parts[11] = {
-                {b->proj.m[br], C}, {b->proj.bias[br], C}, {b->proj.negcorr[br], C}, {b->ln_gamma[1][br], C},
-                {b->ln_beta[1][br], C}, {b->fc2.m[br], C}, {b->fc2.bias[br], C}, {b->fc2.negcorr[br], C},
-                {b->fc1.m[br], F}, {b->fc1.bias[br], F}, {b->fc1.negcorr[br], F}};
+                {b->proj.hm[br].data(), C}, {b->proj.hb[br].data(), C}, {b->proj.hnc[br].data(), C}, {hln[br][2].data(), C},
+                {hln[br][3].data(), C}, {b->fc2.hm[br].data(), C}, {b->fc2.hb[br].data(), C}, {b->fc2.hnc[br].data(), C},
+                {b->fc1.hm[br].data(), F}, {b->fc1.hb[br].data(), F}, {b->fc1.hnc[br].data(), F}};
             size_t off = 0;
             for (auto& pt : parts) {
-                if (hipMemcpy(blkp.data() + off, pt.src, (size_t)pt.n * 4, hipMemcpyDeviceToHost) != hipSuccess)
-                    return bail(fail(MIXAQ_E_HIP, "copy of a parameter block failed"));
+                memcpy(blkp.data() + off, pt.src, (size_t)pt.n * 4);
                 off += pt.n;
             }
             if (br == 1 && b->ao_pack) {       // packed rows carry u = code + offset: the projection removes zp + offset
@@ -662,7 +648,7 @@ static int block_create(const mixaq_block_desc* desc, const mixaq_shared_params*
                 int* nc = (int*)blkp.data() + 2 * C;
                 for (int n = 0; n < C; ++n) nc[n] = -shift_by * b->proj.colsum[n];
             }
-            if ((rc = upload(b->owned, blkp, &b->tok_params[br]))) return bail(rc);
+            b->mem.add(blkp, &b->tok_params[br]);
         }
     }
     Workspace w;
@@ -675,6 +661,9 @@ static int block_create(const mixaq_block_desc* desc, const mixaq_shared_params*
             hipEventCreateWithFlags(&b->ev_join, hipEventDisableTiming) != hipSuccess)
             return bail(fail(MIXAQ_E_HIP, "creating the second stream of the stage failed"));
     }
+    HIP_TRY(b->mem.commit());
+    for (Linear* L : {&b->qkv, &b->proj, &b->fc1, &b->fc2})
+        for (int br = 0; br < 2; ++br) { L->hm[br] = {}; L->hb[br] = {}; L->hnc[br] = {}; }
     owner.b = nullptr;
     *out = b;
     return MIXAQ_OK;
@@ -683,7 +672,7 @@ static int block_create(const mixaq_block_desc* desc, const mixaq_shared_params*
 int mixaq_block_destroy(mixaq_block* blk)
 {
     if (!blk) return MIXAQ_OK;
-    for (void* p : blk->owned) (void)hipFree(p);
+    blk->mem.release();
     if (blk->ev_fork) (void)hipEventDestroy(blk->ev_fork);
     if (blk->ev_join) (void)hipEventDestroy(blk->ev_join);
     if (blk->side_stream) (void)hipStreamDestroy(blk->side_stream);

@@ -13,6 +13,7 @@
 
 #include "../../include/mixaq.h"
 #include "mixaq_dev.h"
+#include "arena.h"
 
 namespace mixaq { int fail(int code, const char* fmt, ...); }
 using namespace mixaq;
@@ -297,12 +298,12 @@ __global__ __launch_bounds__(256) void downsample_kernel(DsArgs A)
 struct mixaq_downsample {
     mixaq_downsample_desc d;
     int P = 0, K = 0, Kp = 0, Ho = 0, Wo = 0;
-    std::vector<void*> owned;
+    Arena mem;
     v4i* Wp = nullptr;
     float *m = nullptr, *bias = nullptr, *gamma = nullptr, *beta = nullptr;
     int* negcorr = nullptr;
     QDev q;
-    ~mixaq_downsample() { for (void* p : owned) (void)hipFree(p); }
+    ~mixaq_downsample() { mem.release(); }
 };
 
 namespace {
@@ -324,17 +325,6 @@ int ds_geometry(const mixaq_downsample_desc* d, int* P, int* K, int* Ho, int* Wo
     *Ho = (d->H + *P - 1) / *P;
     *Wo = (d->W + *P - 1) / *P;
     if ((long long)d->B * *Ho * *Wo > (1LL << 30)) return fail(MIXAQ_E_SHAPE, "map too large for 32-bit token indexing");
-    return MIXAQ_OK;
-}
-
-template <typename T>
-int ds_upload(mixaq_downsample* h, const std::vector<T>& host, T** dev)
-{
-    void* p = nullptr;
-    HIP_TRY(hipMalloc(&p, host.size() * sizeof(T) + 16));
-    h->owned.push_back(p);
-    HIP_TRY(hipMemcpy(p, host.data(), host.size() * sizeof(T), hipMemcpyHostToDevice));
-    *dev = (T*)p;
     return MIXAQ_OK;
 }
 
@@ -465,11 +455,13 @@ static int downsample_create(const mixaq_downsample_desc* desc, const mixaq_down
                     const int k = ks * 32 + (lane / 32) * 16 + e;
                     if (k < K) packed[(((size_t)nb * KS + ks) * 64 + lane) * 16 + e] = w[(size_t)(nb * 32 + lane % 32) * K + k];
                 }
-    int8_t* wp = nullptr;
-    if ((rc = ds_upload(h, packed, &wp)) || (rc = ds_upload(h, m, &h->m)) || (rc = ds_upload(h, bias, &h->bias)) ||
-        (rc = ds_upload(h, nc, &h->negcorr)) || (rc = ds_upload(h, ln_g, &h->gamma)) || (rc = ds_upload(h, ln_b, &h->beta)))
-        return bail(rc);
-    h->Wp = (v4i*)wp;
+    h->mem.add(packed, &h->Wp);
+    h->mem.add(m, &h->m);
+    h->mem.add(bias, &h->bias);
+    h->mem.add(nc, &h->negcorr);
+    h->mem.add(ln_g, &h->gamma);
+    h->mem.add(ln_b, &h->beta);
+    HIP_TRY(h->mem.commit());
     h->q.scale = p->a_in.scale;
     h->q.zp = p->a_in.zero_point;
     h->q.inv_s = 1.0f / p->a_in.scale;

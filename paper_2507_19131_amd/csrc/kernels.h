@@ -23,14 +23,14 @@ struct LnArgs {
     const float* beta[2];
     QDev q[2];
     float eps;
-    int8_t* out;                     // [rows,C]
+    int8_t* out;                     // operand fragments
     int* row_pix;                    // [rows] written by the gather, read otherwise
     int* row_canon;                  // [rows]
     int8_t* tap;                     // slot-major copy or NULL
 };
 
 struct GemmArgs {
-    const int8_t* A;                 // activations [rows,K] row-major
+    const int8_t* A;                 // activations, operand fragments (frag_offset; FC2: k in the order of the result registers)
     const v4i* Wp;                   // packed weights [N/32][K/32][64 lanes] x 16 bytes
     int K, N, nb_per_block;
     int kchunk;                      // bytes of K staged in LDS at a time (a divisor of K; set by the launcher)
@@ -38,7 +38,7 @@ struct GemmArgs {
     const float* bias[2];
     const int* negcorr[2];           // -zp_in * sum_k W[n,k]
     QDev q[2][3];                    // output quantizers (QKV: q,k,v; FC1: [0])
-    int8_t* out8;                    // [rows,N] codes (QKV, FC1)
+    int8_t* out8;                    // codes: [rows,N] (QKV), operand fragments of FC2 (FC1)
     float* outf;                     // [rows,N] (proj)
     const float* resid;              // [rows,N] (FC2)
     const float* x;                  // feature map, shortcut of the first residual (proj)
@@ -58,7 +58,7 @@ struct AttnArgs {
     float m2[2];                     // s_q*s_k/sqrt(d)*log2e
     float m_o[2];                    // s_p*s_v
     QDev qp[2], qo[2];
-    int8_t* out;                     // [rows,C]
+    int8_t* out;                     // operand fragments
     int32_t* tap_s;
     int8_t* tap_p;
     int32_t* tap_o;
@@ -72,8 +72,8 @@ struct WinArgs {                     // fused window kernel (gather + LN1 + QKV 
     const double* scores;            // ... the scores: every workgroup ranks its own window ([B,nW]; NULL = use perm)
     int* perm_out;                   // with scores: receives the selection list
     float* y;                        // with scores: pruned windows are forwarded here
-    // per branch one block of 32-bit words, staged in LDS by every workgroup:
-    // [LN1 gamma | LN1 beta] (C words each), then [qkv m | qkv bias | qkv negcorr] (3C words each; negcorr integers)
+    // per branch one block of 32-bit words, staged in LDS by every workgroup (the constants of its own heads only):
+    // [LN1 gamma | LN1 beta] (C words each), then per head [q|k|v][m | bias | negcorr] (32 words each; negcorr integers)
     const float* params[2];
     float eps;
     QDev q_in[2];
@@ -82,8 +82,9 @@ struct WinArgs {                     // fused window kernel (gather + LN1 + QKV 
     const float* bias2;
     float m2[2], m_o[2];
     QDev qp[2], qo[2];
-    int8_t* out;                     // attention output codes [rows,C]
-    int out_pack;                    // 0: int8 containers; 1, 2: the low region's rows packed (see unpack_codes)
+    int8_t* codes;                   // wide blocks: LN1 codes, operand fragments of 64 rows per slot (ln_window_kernel -> window_kernel)
+    int8_t* out;                     // attention output codes
+    int out_pack;                    // 0: int8 containers; 1, 2: the low region's rows packed (see unpack_codes); PACK_FRAG: fragments
     int* row_pix;
     int* row_canon;
     int8_t* tap_a1; int32_t* tap_acc; int8_t* tap_qkv; int32_t* tap_s; int8_t* tap_p; int32_t* tap_o; int8_t* tap_code;

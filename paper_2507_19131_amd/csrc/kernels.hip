@@ -7,6 +7,7 @@
 // Arithmetic that decides an integer code follows the pinned binary32 sequences
 // of mixaq_dev.h; reductions feeding a code run in binary64.
 #include <algorithm>
+#include <type_traits>
 #include "mixaq_dev.h"
 #include "kernels.h"
 
@@ -34,7 +35,10 @@ __device__ __forceinline__ void token_ln_stats(const float4 (&v)[NV], int C, flo
 {
     Moments m;
 #pragma unroll
-    for (int k = 0; k < NV; ++k) moments_add(m, v[k].x, v[k].y, v[k].z, v[k].w);
+    for (int k = 0; k < NV; ++k) {
+        if (NV > 8 && k % 4 == 0) __builtin_amdgcn_sched_barrier(0);
+        moments_add(m, v[k].x, v[k].y, v[k].z, v[k].w);
+    }
     const double s = group_sum<LPT>(m.s, first), q = group_sum<LPT>(m.q, first);
     mean = moments_mean(s, C);
     bool shaky;
@@ -54,6 +58,7 @@ __device__ __forceinline__ void token_ln_apply(float4 (&v)[NV], float mean, floa
 {
 #pragma unroll
     for (int k = 0; k < NV; ++k) {
+        if (NV > 8 && k % 4 == 0) __builtin_amdgcn_sched_barrier(0);     // long tokens: a few parameter reads in flight, not all of them
         int ch = (k * LPT + sub) * 4;
         float4 g = *(const float4*)(gamma + ch), b = *(const float4*)(beta + ch);
         v[k].x = fmaf((v[k].x - mean) * rstd, g.x, b.x);
@@ -140,6 +145,40 @@ __device__ __forceinline__ bool ranked_before(double rv, int v, double rw, int w
     const bool ahead = reverse ? (sv < sw) : (sv > sw);
     return ahead || (sv == sw && (nv != nw ? nw : v < w));
 }
+// Rank of window w of an image: how many of its windows come before it (order of importance).  The whole workgroup of NT
+// threads takes part and gets the same number; red: one int per wave, LDS.  Counted by ballot: four vector instructions per
+// candidate (the sorted order needs the NaN rules of ranked_before only when w's own score is NaN: a NaN candidate compares
+// false both ways, which ranks it behind every number).
+template <int NT>
+__device__ __forceinline__ int window_rank(const double* __restrict__ sc, int nW, int w, int tid, int* red)
+{
+    const double sw = sc[w];
+    int cnt = 0;
+    for (int base = 0; base < nW; base += 8 * NT) {                      // eight loads in flight per thread
+        double sv[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) sv[k] = sc[min(base + tid + k * NT, nW - 1)];
+        if (sw == sw) {
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const int u = base + tid + k * NT;
+                cnt += __popcll(__ballot(u < nW && (sv[k] > sw || (sv[k] == sw && u < w))));
+            }
+        } else {
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const int u = base + tid + k * NT;
+                cnt += __popcll(__ballot(u < nW && ranked_before(sv[k], u, sw, w, 0)));
+            }
+        }
+    }
+    if ((tid & 63) == 0) red[tid >> 6] = cnt;
+    __syncthreads();
+    int rank = 0;
+#pragma unroll
+    for (int k = 0; k < NT / 64; ++k) rank += red[k];
+    return __builtin_amdgcn_readfirstlane(rank);                          // the same in every lane: what follows from it stays scalar
+}
 constexpr int RANK_WPB = 16;                          // windows ranked per workgroup (4 per wave)
 __global__ __launch_bounds__(256) void select_rank_kernel(const double* __restrict__ scores, int nW, int reverse,
                                                           int* __restrict__ perm)
@@ -223,7 +262,6 @@ __global__ __launch_bounds__(256) void ln_quant_kernel(Geom G, LnArgs A)
         pix = 0;
     }
     const QDev q = A.q[branch];
-    int8_t* dst = A.out + (size_t)row * G.C;
     float4 v[NV];
     const bool real = canon >= 0 && pix >= 0;
     if (real) {
@@ -240,7 +278,7 @@ __global__ __launch_bounds__(256) void ln_quant_kernel(Geom G, LnArgs A)
         int code = pack4(quant_code(v[k].x, q), quant_code(v[k].y, q), quant_code(v[k].z, q), quant_code(v[k].w, q));
         if (canon < 0) code = 0;
         int ch = (k * LPT + sub) * 4;
-        *(int*)(dst + ch) = code;
+        *(int*)(A.out + frag_offset(row, ch, G.C / 32)) = code;
         if (A.tap && canon >= 0) *(int*)(A.tap + (size_t)canon * G.C + ch) = code;
     }
 }
@@ -250,16 +288,29 @@ __global__ __launch_bounds__(256) void ln_quant_kernel(Geom G, LnArgs A)
 // operand (rows = output channels), the activation rows are the B operand (columns
 // = tokens), so a lane owns one token and 16 output channels per 32-channel block.
 // A wave computes 64 rows x 32 channels at a time.
+// What the epilogue of one 32-channel block reads besides the sums; requested before the block's chain of products, so
+// that it travels under it.
+struct EpiConst { float4 m[4], bias[4]; };
 template <int EPI>
-__device__ __forceinline__ void epilogue(const GemmArgs& A, const Geom& G, int branch, int row, int nb, int g,
-                                         const v16i& acc, int pix, int canon, const float4* gelu_lds)
+__device__ __forceinline__ void epilogue_residual(const GemmArgs& A, int row, int nb, int g, int pix, float4 (&res)[4])
 {
-    const int N = A.N;
 #pragma unroll
     for (int qd = 0; qd < 4; ++qd) {
         const int n0 = nb * 32 + qd * 8 + g * 4;
-        const float4 m = *(const float4*)(A.m[branch] + n0);
-        const float4 bs = *(const float4*)(A.bias[branch] + n0);
+        if (EPI == EPI_PROJ) res[qd] = pix >= 0 ? *(const float4*)(A.x + (size_t)pix * A.N + n0) : make_float4(0.f, 0.f, 0.f, 0.f);
+        if (EPI == EPI_FC2) res[qd] = *(const float4*)(A.resid + (size_t)row * A.N + n0);
+    }
+}
+template <int EPI>
+__device__ __forceinline__ void epilogue(const GemmArgs& A, const Geom& G, int branch, int row, int nb, int g, const v16i& acc,
+                                         const EpiConst& ec, const float4 (&res)[4], int pix, int canon, const float4* gelu_lds)
+{
+    const int N = A.N;
+    int codes[4];
+#pragma unroll
+    for (int qd = 0; qd < 4; ++qd) {
+        const int n0 = nb * 32 + qd * 8 + g * 4;
+        const float4 m = ec.m[qd], bs = ec.bias[qd];
         const int a0 = acc[qd * 4 + 0], a1 = acc[qd * 4 + 1], a2 = acc[qd * 4 + 2], a3 = acc[qd * 4 + 3];
         float f0 = fmaf((float)a0, m.x, bs.x), f1 = fmaf((float)a1, m.y, bs.y);
         float f2 = fmaf((float)a2, m.z, bs.z), f3 = fmaf((float)a3, m.w, bs.w);
@@ -267,102 +318,136 @@ __device__ __forceinline__ void epilogue(const GemmArgs& A, const Geom& G, int b
         if (EPI == EPI_QKV || EPI == EPI_FC1) {
             if (EPI == EPI_FC1) { f0 = gelu_scaled(f0, gelu_lds); f1 = gelu_scaled(f1, gelu_lds); f2 = gelu_scaled(f2, gelu_lds); f3 = gelu_scaled(f3, gelu_lds); }
             const QDev& q = A.q[branch][EPI == EPI_QKV ? n0 / G.C : 0];
-            int code = pack4(quant_code(f0, q), quant_code(f1, q), quant_code(f2, q), quant_code(f3, q));
-            *(int*)(A.out8 + (size_t)row * N + n0) = code;
-            if (A.tap_code && canon >= 0) *(int*)(A.tap_code + (size_t)canon * N + n0) = code;
-        } else if (EPI == EPI_PROJ) {
-            float4 sc = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (pix >= 0) sc = *(const float4*)(A.x + (size_t)pix * N + n0);
-            float4 o = make_float4(f0 + sc.x, f1 + sc.y, f2 + sc.z, f3 + sc.w);
-            *(float4*)(A.outf + (size_t)row * N + n0) = o;
-            if (A.tap_f && canon >= 0) *(float4*)(A.tap_f + (size_t)canon * N + n0) = o;
-        } else {   // EPI_FC2: second residual and scatter back to the map
-            float4 h = *(const float4*)(A.resid + (size_t)row * N + n0);
-            float4 o = make_float4(f0 + h.x, f1 + h.y, f2 + h.z, f3 + h.w);
-            if (pix >= 0) *(float4*)(A.y + (size_t)pix * N + n0) = o;
+            codes[qd] = pack4(quant_code(f0, q), quant_code(f1, q), quant_code(f2, q), quant_code(f3, q));
+            if (EPI == EPI_QKV) *(int*)(A.out8 + (size_t)row * N + n0) = codes[qd];
+            if (A.tap_code && canon >= 0) *(int*)(A.tap_code + (size_t)canon * N + n0) = codes[qd];
+        } else {   // PROJ: first residual (the shortcut); FC2: second residual and scatter back to the map
+            const float4 o = make_float4(f0 + res[qd].x, f1 + res[qd].y, f2 + res[qd].z, f3 + res[qd].w);
+            if (EPI == EPI_PROJ) *(float4*)(A.outf + (size_t)row * N + n0) = o;
+            else if (pix >= 0) *(float4*)(A.y + (size_t)pix * N + n0) = o;
             if (A.tap_f && canon >= 0) *(float4*)(A.tap_f + (size_t)canon * N + n0) = o;
         }
     }
+    // FC1: the lane's 16 codes are one lane's 16 bytes of FC2's operand fragment (k in the order of the result registers)
+    if (EPI == EPI_FC1) *(v4i*)(A.out8 + (((size_t)(row >> 5) * (N / 32) + nb) * 64 + g * 32 + (row & 31)) * 16) = (v4i){codes[0], codes[1], codes[2], codes[3]};
 }
 
-// One workgroup per 64-row tile and group of output blocks (all of them once the tiles alone fill the chip; on few
-// rows, e.g. 20 row tiles at C = 768 and batch 1, groups of four).  The tile's activation rows are read once, 16 contiguous bytes per lane, and laid out in LDS as
-// MFMA operand fragments (the row-major codes read directly as operands are 16 bytes from each of 32 rows per
-// load, a quarter of every cache line touched); wave w computes the output blocks first + w, first + w + 4, ...
-// of the group: weight fragments stream through a ring of loads in flight, the B operand comes from LDS.
-// K up to 2048 stays whole in LDS for a 64-row tile, K up to 4096 for a 32-row tile; longer K passes in chunks.
+// One workgroup per tile of RT rows and group of output blocks (all of them once the tiles alone fill the chip; on few
+// rows, e.g. 37 row tiles at C = 768 and batch 1, groups of four, one per wave).  The activations come as MFMA operand
+// fragments ([32 rows][K slab][64 lanes][16 bytes], written so by their producers), so a tile is a contiguous run of
+// memory: it goes to LDS by direct loads, no register in between, all of them in flight together.  Wave w computes the
+// output blocks first + w, first + w + 4, ... of the group; its weight fragments stream through a ring of D loads that
+// starts before anything else and runs on across the output blocks.  What bounds it on few rows is the latency of that
+// stream: one CU holds four to eight such waves, so D is 16 where K allows (at 8 in flight fc2 with K = 3072 on 37 row
+// tiles took 19.4 us).  K up to 2048 stays whole in LDS for a 64-row tile, K up to 4096 for a 32-row tile; longer K
+// passes in chunks.
 constexpr int GEMM_TILE_MAX_K = 2048;      // 64 rows x K bytes of LDS
-// KMAX: bytes of K the instantiation's LDS holds per row (a longer K goes through in chunks of A.kchunk <= KMAX); RT: rows per tile,
-// 64 or, so that a long K fits LDS whole, 32
-template <int EPI, int KMAX, int RT = ROW_TILE>
-__global__ __launch_bounds__(256) void gemm_tile_kernel(Geom G, GemmArgs A)
+// KMAX: bytes of K the instantiation's LDS holds per row (a longer K goes through in chunks of A.kchunk <= KMAX, whole ring
+// turns each)
+template <int EPI, int KMAX, int RT, int D>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RT * KMAX <= 65536 ? 2 : 1))) void gemm_tile_kernel(Geom G, GemmArgs A)
 {
-    constexpr int RB = RT / 32;
+    constexpr int RB = RT / 32, PF = D % 4 == 0 ? 4 : 3;                // PF: LDS reads ahead
+    static_assert(D % PF == 0, "the LDS slots come round with the ring");
     __shared__ v4i afr[RT * KMAX / 16];                                // [row blocks][chunk slabs][64 lanes]
     __shared__ float4 gtab[EPI == EPI_FC1 ? GELU_K : 1];
-    constexpr int D = 8;                                               // weight fragments in flight per wave
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, j = lane & 31, g = lane >> 5;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, j = lane & 31, g = lane >> 5;
     const int row0 = blockIdx.x * RT;
     const int branch = row0 >= G.base_lo ? 1 : 0;
     const int K = A.K, ks_n = K / 32, NB = A.N / 32;
-    const int kch = A.kchunk, cs = kch / 32, n_ch = K / kch, per_row = kch / 16;       // chunk bytes (a divisor of K, at most KMAX), slabs per chunk, chunks
-    auto stage = [&](int ch) {     // piece (row r, 16-byte chunk q) -> fragment (r/32, q/2), lane (r%32, q%2)
-        for (int p = tid; p < RT * per_row; p += 256) {
-            const int r = p / per_row, q = p - r * per_row;
-            afr[((r >> 5) * cs + (q >> 1)) * 64 + (q & 1) * 32 + (r & 31)] = *(const v4i*)(A.A + (size_t)(row0 + r) * K + ch * kch + q * 16);
-        }
-    };
-    if (EPI == EPI_FC1) gelu_stage_table(gtab, A.gelu_tab, tid, 256);
-    const float4* gelu_lds = gtab;
+    const int cs = A.kchunk / 32, n_ch = K / A.kchunk;                 // slabs per chunk, chunks
+    const int nb_lo = blockIdx.y * A.nb_per_block, nb_hi = min(nb_lo + A.nb_per_block, NB);
+    const v4i* wp = A.Wp + (size_t)min(nb_lo + wave, NB - 1) * ks_n * 64 + lane;
     int pix[RB], canon[RB];
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
         canon[rb] = A.row_canon[row0 + rb * 32 + j];
         pix[rb] = (EPI == EPI_PROJ || EPI == EPI_FC2) ? A.row_pix[row0 + rb * 32 + j] : 0;
     }
+    v4i rw[D];
+#pragma unroll
+    for (int d = 0; d < D; ++d) rw[d] = wp[min(d, ks_n - 1) * 64];     // K may hold fewer than D slabs: the last one again (unused)
+    auto stage = [&](int ch) {                                         // one fragment of the tile per wave and turn
+        for (int f = wave; f < RB * cs; f += 4) {
+            const int rb = f >= cs ? 1 : 0;
+            const int8_t* src = A.A + ((size_t)(blockIdx.x * RB + rb) * ks_n + ch * cs + f - rb * cs) * 1024 + lane * 16;
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
+                                             (__attribute__((address_space(3))) void*)(afr + f * 64), 16, 0, 0);
+        }
+    };
     if (n_ch == 1) stage(0);                                           // the whole K stays for every output block
+    // what a block's start and epilogue read, requested ahead of its products (for the first block: with the tile)
+    int4 nc[4];
+    EpiConst ec;
+    float4 res[RB][4];
+    auto request = [&](int nb) {
+#pragma unroll
+        for (int qd = 0; qd < 4; ++qd) {
+            const int n0 = nb * 32 + qd * 8 + g * 4;
+            nc[qd] = *(const int4*)(A.negcorr[branch] + n0);
+            ec.m[qd] = *(const float4*)(A.m[branch] + n0);
+            ec.bias[qd] = *(const float4*)(A.bias[branch] + n0);
+        }
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) epilogue_residual<EPI>(A, row0 + rb * 32 + j, nb, g, pix[rb], res[rb]);
+    };
+    request(min(nb_lo + wave, NB - 1));
+    if (EPI == EPI_FC1) gelu_stage_table(gtab, A.gelu_tab, tid, 256);
+    const float4* gelu_lds = gtab;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                   // the direct loads have landed
     __syncthreads();
-    const int nb_lo = blockIdx.y * A.nb_per_block, nb_hi = min(nb_lo + A.nb_per_block, NB);
     for (int nb0 = nb_lo; nb0 < nb_hi; nb0 += 4) {                     // the same trips for every wave: barriers inside
         const int nb = min(nb0 + wave, NB - 1);
         const bool active = nb0 + wave < nb_hi;
-        const v4i* wp = A.Wp + (size_t)nb * ks_n * 64 + lane;
-        v4i rw[D];
-#pragma unroll
-        for (int d = 0; d < D; ++d) rw[d] = wp[min(d, ks_n - 1) * 64];  // K may hold fewer than D slabs: the last one again (unused)
+        const v4i* wnext = A.Wp + (size_t)min(nb0 + 4 + wave, NB - 1) * ks_n * 64 + lane;
+        if (nb0 > nb_lo) request(nb);
         v16i c0, c1;                                                     // c1: the second row block (RT = 64)
-        {   // accumulators start at -zp_in * colsum(W[n,:])
-            const int* nc = A.negcorr[branch] + nb * 32 + g * 4;
 #pragma unroll
-            for (int qd = 0; qd < 4; ++qd) {
-                int4 t = *(const int4*)(nc + qd * 8);
-                c0[qd * 4 + 0] = t.x; c0[qd * 4 + 1] = t.y; c0[qd * 4 + 2] = t.z; c0[qd * 4 + 3] = t.w;
-            }
-            c1 = c0;
+        for (int qd = 0; qd < 4; ++qd) {                                 // accumulators start at -zp_in * colsum(W[n,:])
+            c0[qd * 4 + 0] = nc[qd].x; c0[qd * 4 + 1] = nc[qd].y; c0[qd * 4 + 2] = nc[qd].z; c0[qd * 4 + 3] = nc[qd].w;
         }
+        c1 = c0;
 #pragma unroll 1
         for (int ch = 0; ch < n_ch; ++ch) {
             if (n_ch > 1) {
                 if (ch > 0 || nb0 > nb_lo) __syncthreads();             // the previous chunk is no longer read
                 stage(ch);
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
                 __syncthreads();
             }
-#pragma unroll 1
-            for (int k0 = 0; k0 < cs; k0 += D) {
+            // One turn of the ring: D fragments are used, the D after them requested.  Every step is product, request into
+            // the slot just used, next LDS read, in this order: left free, the scheduler moves the requests up, the slots of
+            // the next turn need registers of their own, and the copies at the turn's end wait for every load in flight.
+            v4i b[PF][RB];
+#pragma unroll
+            for (int d = 0; d < PF; ++d)
+#pragma unroll
+                for (int rb = 0; rb < RB; ++rb) b[d][rb] = afr[(rb * cs + min(d, cs - 1)) * 64 + lane];
+            auto turn = [&](int k0, auto full) {
+                const bool last = ch * cs + k0 + D >= ks_n;              // the ring turns to the next output block's weights
+                const v4i* wsrc = last ? wnext : wp + (size_t)(ch * cs + k0 + D) * 64;
+                const int left = last ? ks_n - 1 : ks_n - 1 - (ch * cs + k0 + D);
 #pragma unroll
                 for (int d = 0; d < D; ++d) {
-                    const v4i w = rw[d];
-                    rw[d] = wp[min(ch * cs + k0 + D + d, ks_n - 1) * 64]; // past the end: the last slab again (unused)
-                    if (k0 + d < cs) {                                   // wave-uniform: the last turn may be partial
-                        c0 = mfma32(w, afr[(k0 + d) * 64 + lane], c0);
-                        if (RB == 2) c1 = mfma32(w, afr[(cs + k0 + d) * 64 + lane], c1);
+                    if (decltype(full)::value || k0 + d < cs) {          // wave-uniform: the last turn may be partial
+                        c0 = mfma32(rw[d], b[d % PF][0], c0);
+                        if (RB == 2) c1 = mfma32(rw[d], b[d % PF][RB - 1], c1);
                     }
+                    rw[d] = wsrc[min(d, left) * 64];                     // past the end: the last slab again (unused)
+#pragma unroll
+                    for (int rb = 0; rb < RB; ++rb) b[d % PF][rb] = afr[(rb * cs + min(k0 + d + PF, cs - 1)) * 64 + lane];
+                    __builtin_amdgcn_sched_barrier(0);
                 }
-            }
+            };
+            int k0 = 0;
+#pragma unroll 1
+            for (; k0 + D <= cs; k0 += D) turn(k0, std::true_type());
+            if (k0 < cs) turn(k0, std::false_type());
         }
+        wp = wnext;
         if (active) {
-            epilogue<EPI>(A, G, branch, row0 + j, nb, g, c0, pix[0], canon[0], gelu_lds);
-            if (RB == 2) epilogue<EPI>(A, G, branch, row0 + 32 + j, nb, g, c1, pix[RB - 1], canon[RB - 1], gelu_lds);
+            epilogue<EPI>(A, G, branch, row0 + j, nb, g, c0, ec, res[0], pix[0], canon[0], gelu_lds);
+            if (RB == 2) epilogue<EPI>(A, G, branch, row0 + 32 + j, nb, g, c1, ec, res[RB - 1], pix[RB - 1], canon[RB - 1], gelu_lds);
         }
     }
 }
@@ -486,6 +571,7 @@ __device__ __forceinline__ void attention_store(const v16i& o, const QDev& qo, f
                                  quant_code((float)a2 * m_o, qo), quant_code((float)a3 * m_o, qo));
                 const int ch = head * HD + d0;
                 if (pack == 0) *(int*)(out + (size_t)(row0 + qi) * C + ch) = code[qd];
+                else if (pack == PACK_FRAG) *(int*)(out + frag_offset(row0 + qi, ch, C / 32)) = code[qd];
                 size_t ci = (canon_row0 + qi) * C + ch;
                 if (TAPS && tap_o) *(int4*)(tap_o + ci) = make_int4(a0, a1, a2, a3);
                 if (TAPS && tap_code) *(int*)(tap_code + ci) = code[qd];
@@ -581,7 +667,72 @@ __global__ __launch_bounds__(256) void attn_kernel(Geom G, AttnArgs A)
 #pragma unroll 1
     for (int ib = 0; ib < 2; ++ib) {
         const v16i o = attention_core<true>(ib ? qf[1] : qf[0], kf, vt, core, j, g, ib);
-        attention_store<true>(o, A.qo[branch], A.m_o[branch], j, g, ib, head, G.C, A.out, row0, A.tap_o, A.tap_code, (size_t)canon_slot * TOK);
+        attention_store<true>(o, A.qo[branch], A.m_o[branch], j, g, ib, head, G.C, A.out, row0, A.tap_o, A.tap_code, (size_t)canon_slot * TOK, PACK_FRAG);
+    }
+}
+
+// ------------------------------------------------------------------ LN1 of wide blocks
+// Gather (shift folded in) + LN1 + quantize of the windows' tokens into MFMA operand fragments, per slot 64 token rows
+// (49 and zeros), for the window kernel's CODES form; row bookkeeping, selection and pruned windows as there.  One
+// workgroup per window and 256 / LPT tokens: few windows still make hundreds of workgroups.
+template <int LPT, int NV, bool SCORED>
+__global__ __launch_bounds__(256) void ln_window_kernel(Geom G, WinArgs A)
+{
+    constexpr int TP = 256 / LPT, C = LPT * NV * 4, KS = C / 32;
+    __shared__ int red[4];
+    const int tid = threadIdx.x, sub = tid % LPT, t = blockIdx.y * TP + tid / LPT, widx = blockIdx.x;
+    int branch = 0, row0 = 0, canon_slot = 0, slot = widx, w, bimg;
+    bool pruned = false;
+    if (SCORED) {
+        bimg = widx / G.nW;
+        w = widx - bimg * G.nW;
+        const int rank = window_rank<256>(A.scores + (size_t)bimg * G.nW, G.nW, w, tid, red);
+        if (tid == 0 && blockIdx.y == 0) A.perm_out[(size_t)bimg * G.nW + rank] = w;
+        canon_slot = bimg * G.nW + rank;
+        pruned = rank >= G.k_hi + G.k_lo;
+        if (rank < G.k_hi) { slot = bimg * G.k_hi + rank; row0 = slot * TOK; }
+        else { branch = 1; slot = bimg * G.k_lo + rank - G.k_hi; row0 = G.base_lo + slot * TOK; slot += G.B * G.k_hi; }
+    } else if (widx < G.n_slots) {
+        slot_info(G, widx, branch, row0, canon_slot);
+        w = A.perm[canon_slot];
+        bimg = canon_slot / G.nW;
+    } else {
+        const int kept = G.k_hi + G.k_lo, q = widx - G.n_slots;
+        bimg = q / (G.nW - kept);
+        w = A.perm[bimg * G.nW + kept + (q - bimg * (G.nW - kept))];
+        pruned = true;
+    }
+    if (blockIdx.x == 0 && blockIdx.y == 0) {                             // the rows that pad each region to whole tiles belong to no window
+        for (int r = G.rows_hi + tid; r < G.base_lo; r += 256) { A.row_pix[r] = -1; A.row_canon[r] = -1; }
+        for (int r = G.base_lo + G.rows_lo + tid; r < G.rows_total; r += 256) { A.row_pix[r] = -1; A.row_canon[r] = -1; }
+    }
+    int pix = -1;
+    if (t < TOK) {
+        const int wr = w / G.nWc, wc = w - wr * G.nWc, tr = t / WS, tc = t - tr * WS;
+        int pr = wr * WS + tr + G.shift; if (pr >= G.Hp) pr -= G.Hp;
+        int pc = wc * WS + tc + G.shift; if (pc >= G.Wp) pc -= G.Wp;
+        pix = (pr < G.H && pc < G.W) ? (bimg * G.H + pr) * G.W + pc : -1;
+    }
+    float4 v[NV];
+#pragma unroll
+    for (int k = 0; k < NV; ++k) v[k] = pix >= 0 ? *(const float4*)(A.x + (size_t)pix * C + (k * LPT + sub) * 4) : make_float4(0.f, 0.f, 0.f, 0.f);
+    if (pruned) {                                                         // Sec. 3.4: the features are forwarded
+        if (pix >= 0) {
+#pragma unroll
+            for (int k = 0; k < NV; ++k) *(float4*)(A.y + (size_t)pix * C + (k * LPT + sub) * 4) = v[k];
+        }
+        return;
+    }
+    const int canon = canon_slot * TOK + t;
+    if (sub == 0 && t < TOK) { A.row_pix[row0 + t] = pix; A.row_canon[row0 + t] = canon; }
+    if (pix >= 0) token_layernorm<LPT, NV>(v, C, A.eps, A.params[branch], A.params[branch] + C, sub);   // padding enters as LN output 0
+    const QDev q = A.q_in[branch];
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+        const int ch = (k * LPT + sub) * 4;
+        const int code = t < TOK ? pack4(quant_code(v[k].x, q), quant_code(v[k].y, q), quant_code(v[k].z, q), quant_code(v[k].w, q)) : 0;
+        *(int*)(A.codes + frag_offset(slot * 64 + t, ch, KS)) = code;
+        if (A.tap_a1 && t < TOK) *(int*)(A.tap_a1 + (size_t)canon * C + ch) = code;
     }
 }
 
@@ -606,23 +757,26 @@ struct WinCfg {
 // to 128 registers instead of 160, one of a pair 80 instead of 100.  A workgroup of six or twelve waves only gets a second
 // place on a CU when its share per SIMD, rounded up, fits twice: 360 windows at C = 192 ran in two rounds of one workgroup
 // per CU (24.6 us), now in one round (20.8 us); C = 256, 1444 windows: 83 -> 72 us.
-constexpr int win_waves_per_eu(int NH, int HG, int QS) { return QS == 2 ? (NH * HG > 8 ? 4 : 6) : NH * HG > 8 ? 3 : NH == 3 ? 5 : 4; }
+constexpr int win_waves_per_eu(int NH, int HG, int QS, bool CODES) { return CODES ? (NH * HG < 32 ? 4 : 2) : QS == 2 ? (NH * HG > 8 ? 4 : 6) : NH * HG > 8 ? 3 : NH == 3 ? 5 : 4; }
 
-// word offsets inside the window kernel's parameter block of one branch (see WinArgs::params)
-template <int C> struct WinPrm {
-    static constexpr int LN_G = 0, LN_B = C, M = 2 * C, B = 5 * C, NC = 8 * C, WORDS = 11 * C;
+// The window kernel's parameter block of one branch (see WinArgs::params), as a workgroup of NH heads holds it in LDS:
+// LN1 gamma and beta (not with CODES), then the QKV epilogue constants of its own heads, per head [q|k|v][m|bias|-zp*colsum][32 dims]
+template <int C, int NH, bool CODES> struct WinPrm {
+    static constexpr int LN_G = 0, LN_B = C, HEADS = CODES ? 0 : 2 * C, PER_HEAD = 9 * HD, WORDS = HEADS + NH * PER_HEAD;
 };
 
-template <int NH, bool TAPS, bool SCORED, int HG = 1, int QS = 1>
-__global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(win_waves_per_eu(NH, HG, QS)))) void window_kernel(Geom G, WinArgs A)
+// CODES: the LN1 codes come ready from ln_window_kernel (wide blocks, whose heads are spread over many workgroups: each of
+// them would repeat the whole gather and LayerNorm); the workgroup is given a slot and there are no pruned ones.
+template <int NH, bool TAPS, bool SCORED, int HG = 1, int QS = 1, bool CODES = false>
+__global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(win_waves_per_eu(NH, HG, QS, CODES)))) void window_kernel(Geom G, WinArgs A)
 {
     constexpr int NHT = NH * HG;                                         // heads of the block; this workgroup runs NH of them
     constexpr int NW = NH * QS, NTB = 2 / QS;                            // waves; token blocks a wave projects and attends for
-    constexpr int C = NHT * 32, KS = NHT, LPT = WinCfg<NH, HG, QS>::LPT, NV = WinCfg<NH, HG, QS>::NV, NT = NW * 64;
+    constexpr int C = NHT * 32, KS = NHT, LPT = WinCfg<NH, HG, QS>::LPT, NV = CODES ? 1 : WinCfg<NH, HG, QS>::NV, NT = NW * 64;
     constexpr int GPW = WinCfg<NH, HG, QS>::GPW;
-    using PR = WinPrm<C>;
+    using PR = WinPrm<C, NH, CODES>;
     const int widx = HG == 1 ? blockIdx.x : blockIdx.x / HG, hg = HG == 1 ? 0 : blockIdx.x % HG;
-    static_assert(NW * GPW >= TOK, "one pass must cover the window");
+    static_assert(CODES || NW * GPW >= TOK, "one pass must cover the window");
     __shared__ v4i a1s[2 * KS * 64];                                     // LN1 codes as fragments [token block][k slab][lane]
     __shared__ __attribute__((aligned(16))) float prm[PR::WORDS];        // this branch's LN1 affine and QKV epilogue constants
     __shared__ __attribute__((aligned(16))) int csum[NW][HD];
@@ -632,11 +786,21 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, j = lane & 31, g = lane >> 5;
     const int hw = QS == 1 ? wave : wave >> 1, tb0 = QS == 1 ? 0 : wave & 1;   // head inside the workgroup, first token block
     const int head = hg * NH + hw;
-    constexpr int RING = KS < 6 ? KS : 6;                                // weight fragments in flight
+    // Weight fragments in flight.  STREAM (long K): the fragments of q, k and v are one stream that starts under the LayerNorm
+    // phase and runs on across the epilogues.
+    constexpr bool STREAM = KS >= 12;
+    constexpr int RING = !STREAM ? (KS < 6 ? KS : 6) : KS == 12 ? 6 : KS < 32 ? 8 : 16;
+    static_assert(!STREAM || KS % RING == 0, "each chain starts at ring slot 0");
+    v4i ring[RING];
     auto weights_of = [&](int which) { return A.Wqkv + (size_t)(which * NHT + head) * KS * 64 + lane; };
     // SCORED: the workgroup is given a window and finds its own place in the selection (its rank
     // under the total order of the scores); otherwise it is given a slot and looks the window up.
-    int branch = 0, row0 = 0, canon_slot = 0, w, bimg;
+    int branch = 0, row0 = 0, canon_slot = 0, w, bimg = 0;
+    if (STREAM && CODES) {
+        const v4i* wp = weights_of(0);
+#pragma unroll
+        for (int d = 0; d < RING; ++d) ring[d] = wp[d * 64];
+    }
     if (SCORED) {
         bimg = widx / G.nW;
         w = widx - bimg * G.nW;
@@ -662,16 +826,16 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
     }
     // The rows that pad each region to whole tiles belong to no window: the first workgroup marks them
     // (pixel -1, slot-major row -1) for the kernels of the seven-kernel path, which read the marks of every row.
-    if (blockIdx.x == 0) {
+    if (!CODES && blockIdx.x == 0) {
         for (int r = G.rows_hi + tid; r < G.base_lo; r += NT) { A.row_pix[r] = -1; A.row_canon[r] = -1; }
         for (int r = G.base_lo + G.rows_lo + tid; r < G.rows_total; r += NT) { A.row_pix[r] = -1; A.row_canon[r] = -1; }
     }
     int* a1w = (int*)a1s;
     // dword index of (token slot s, channel c with c%4==0) in the fragment layout (k = channel, natural order)
     auto frag_dw = [&](int s, int c) { return ((((s >> 5) * KS + (c >> 5)) * 64 + ((c & 31) >> 4) * 32 + (s & 31)) << 2) + ((c & 15) >> 2); };
-    for (int i = tid; i < 15 * (C / 4); i += NT) a1w[frag_dw(TOK + i / (C / 4), (i % (C / 4)) * 4)] = 0;
+    if (!CODES) for (int i = tid; i < 15 * (C / 4); i += NT) a1w[frag_dw(TOK + i / (C / 4), (i % (C / 4)) * 4)] = 0;
     const int grp = lane / LPT, sub = lane - grp * LPT, first = lane - sub;
-    const int t = grp < GPW ? wave * GPW + grp : TOK;                    // lanes beyond the last whole group idle
+    const int t = !CODES && grp < GPW ? wave * GPW + grp : TOK;          // lanes beyond the last whole group idle
     int pix = -1;
     float4 v[NV];
     if (t < TOK) {                                                       // gather: the loads need the window only
@@ -686,27 +850,7 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
         }
     }
     if (SCORED) {
-        const double* sc = A.scores + (size_t)bimg * G.nW;
-        const double sw = sc[w];
-        int cnt = 0;
-        for (int base = 0; base < G.nW; base += 8 * NT) {                // eight loads in flight per thread
-            double sv[8];
-#pragma unroll
-            for (int k = 0; k < 8; ++k) { const int u = base + tid + k * NT; sv[k] = sc[min(u, G.nW - 1)]; }
-#pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                const int u = base + tid + k * NT;
-                cnt += (u < G.nW && ranked_before(sv[k], u, sw, w, 0)) ? 1 : 0;
-            }
-        }
-#pragma unroll
-        for (int o = 32; o >= 1; o >>= 1) cnt += __shfl_xor(cnt, o, 64);
-        if (lane == 0) red[wave] = cnt;
-        __syncthreads();
-        int rank = 0;
-#pragma unroll
-        for (int k = 0; k < NW; ++k) rank += red[k];
-        rank = __builtin_amdgcn_readfirstlane(rank);                      // the same in every lane: what follows from it stays scalar
+        const int rank = window_rank<NT>(A.scores + (size_t)bimg * G.nW, G.nW, w, tid, red);
         if (tid == 0 && hg == 0) A.perm_out[(size_t)bimg * G.nW + rank] = w;
         if (rank >= G.k_hi + G.k_lo) {                                    // pruned (Sec. 3.4): forward the features
             if (pix >= 0 && hg == 0) {
@@ -725,12 +869,26 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
         constexpr int PV = PR::WORDS / 4, PVT = (PV + NT - 1) / NT;
         float4 pv[PVT];
 #pragma unroll
-        for (int k = 0; k < PVT; ++k) pv[k] = src[min(tid + k * NT, PV - 1)];
+        for (int k = 0; k < PVT; ++k) {
+            const int i = min(tid + k * NT, PV - 1);
+            pv[k] = src[HG > 1 && i >= PR::HEADS / 4 ? i + hg * (NH * PR::PER_HEAD / 4) + (CODES ? 2 * C / 4 : 0) : i];
+        }
+        if (CODES) {                                                      // operand fragments straight to LDS
+            const int wv = __builtin_amdgcn_readfirstlane(wave);
+            for (int f = wv; f < 2 * KS; f += NW)
+                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(A.codes + ((size_t)widx * 2 * KS + f) * 1024 + lane * 16),
+                                                 (__attribute__((address_space(3))) void*)(a1s + f * 64), 16, 0, 0);
+        }
+        if (STREAM && !CODES) {
+            const v4i* wp = weights_of(0);
+#pragma unroll
+            for (int d = 0; d < RING; ++d) ring[d] = wp[d * 64];
+        }
 #pragma unroll
         for (int k = 0; k < PVT; ++k) if (tid + k * NT < PV) ((float4*)prm)[tid + k * NT] = pv[k];
     }
+    if (CODES) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");           // the direct loads have landed
     __syncthreads();                                                     // parameter block visible
-    const int* prmi = (const int*)prm;
     if (t < TOK) {
         const int canon = canon_slot * TOK + t;
         if (sub == 0 && hg == 0) { A.row_pix[row0 + t] = pix; A.row_canon[row0 + t] = canon; }
@@ -743,28 +901,42 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
         const QDev q = A.q_in[branch];
 #pragma unroll
         for (int k = 0; k < NV; ++k) {
+            if (NV > 8 && k % 4 == 0) __builtin_amdgcn_sched_barrier(0);
             const int ch = (k * LPT + sub) * 4;
             int code = pack4(quant_code(v[k].x, q), quant_code(v[k].y, q), quant_code(v[k].z, q), quant_code(v[k].w, q));
             a1w[frag_dw(t, ch)] = code;
             if (TAPS && A.tap_a1 && hg == 0) *(int*)(A.tap_a1 + (size_t)canon * C + ch) = code;
         }
     }
-    __syncthreads();
+    if (!CODES) __syncthreads();
     // The B operand (LN1 fragments) is read from LDS inside the chain and the weight fragments come through a short ring of
     // loads: held in registers instead (24 to 64 of them) they cost the kernel its fourth and fifth wave per SIMD.
-    // acc[tb] += (weights as A operand ? W * act^T : act * W^T) over the whole K
-    auto chain = [&](const v4i* wp, v16i* acc, bool weights_first) {
-        v4i ring[RING];
+    // acc[tb] += (weights as A operand ? W * act^T : act * W^T) over the whole K; next: where the stream goes on
+    auto chain = [&](const v4i* wp, const v4i* next, v16i* acc, bool weights_first) {
+        constexpr int PF = STREAM ? 3 : 1;                                // LDS reads ahead (the scheduler's own business otherwise)
+        v4i xv[PF][NTB];
+        auto operand = [&](int ks) {
 #pragma unroll
-        for (int d = 0; d < RING; ++d) ring[d] = wp[d * 64];
+            for (int tb = 0; tb < NTB; ++tb) xv[ks % PF][tb] = a1s[((tb0 + tb) * KS + ks) * 64 + lane];
+        };
+        if (STREAM) {
+#pragma unroll
+            for (int d = 0; d < PF; ++d) operand(d);
+        } else {
+#pragma unroll
+            for (int d = 0; d < RING; ++d) ring[d] = wp[d * 64];
+        }
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
+            if (!STREAM) operand(ks);
             const v4i wv = ring[ks % RING];
-            if (ks + RING < KS) ring[ks % RING] = wp[(ks + RING) * 64];
 #pragma unroll
-            for (int tb = 0; tb < NTB; ++tb) {
-                const v4i xv = a1s[((tb0 + tb) * KS + ks) * 64 + lane];
-                acc[tb] = weights_first ? mfma32(wv, xv, acc[tb]) : mfma32(xv, wv, acc[tb]);
+            for (int tb = 0; tb < NTB; ++tb) acc[tb] = weights_first ? mfma32(wv, xv[ks % PF][tb], acc[tb]) : mfma32(xv[ks % PF][tb], wv, acc[tb]);
+            if (ks + RING < KS) ring[ks % RING] = wp[(ks + RING) * 64];
+            else if (STREAM && next) ring[ks % RING] = next[(ks + RING - KS) * 64];
+            if (STREAM) {                                                 // product, request into the slot just used, LDS read: see gemm_tile_kernel
+                if (ks + PF < KS) operand(ks + PF);
+                __builtin_amdgcn_sched_barrier(0);
             }
         }
     };
@@ -774,12 +946,13 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
     for (int which = 0; which < 2; ++which) {
         asm volatile("" ::: "memory");                                    // the B operand is read from LDS each time: keep the reads in the loop
         const int nb = which * NHT + head;
+        const float* pm = prm + PR::HEADS + hw * PR::PER_HEAD + which * (3 * HD);
         const QDev qq = A.q_qkv[branch][which];
         const v4i* wp = weights_of(which);
         auto start = [&](v16i& acc) {                                     // accumulators start at -zp * colsum
 #pragma unroll
             for (int qd = 0; qd < 4; ++qd) {
-                const int4 t4 = *(const int4*)(prmi + PR::NC + nb * 32 + qd * 8 + g * 4);
+                const int4 t4 = *(const int4*)((const int*)pm + 2 * HD + qd * 8 + g * 4);
                 acc[qd * 4 + 0] = t4.x; acc[qd * 4 + 1] = t4.y; acc[qd * 4 + 2] = t4.z; acc[qd * 4 + 3] = t4.w;
             }
         };
@@ -789,7 +962,7 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
 #pragma unroll
             for (int qd = 0; qd < 4; ++qd) {
                 const int n0 = nb * 32 + qd * 8 + g * 4;
-                const float4 m = *(const float4*)(prm + PR::M + n0), bs = *(const float4*)(prm + PR::B + n0);
+                const float4 m = *(const float4*)(pm + qd * 8 + g * 4), bs = *(const float4*)(pm + HD + qd * 8 + g * 4);
                 const int a0 = acc[qd * 4 + 0], a1 = acc[qd * 4 + 1], a2 = acc[qd * 4 + 2], a3 = acc[qd * 4 + 3];
                 wd[qd] = pack4(quant_code(fmaf((float)a0, m.x, bs.x), qq), quant_code(fmaf((float)a1, m.y, bs.y), qq),
                                quant_code(fmaf((float)a2, m.z, bs.z), qq), quant_code(fmaf((float)a3, m.w, bs.w), qq));
@@ -804,7 +977,7 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
         v16i acc[NTB];
         start(acc[0]);
         if (NTB == 2) acc[NTB - 1] = acc[0];
-        chain(wp, acc, true);
+        chain(wp, weights_of(which + 1), acc, true);
 #pragma unroll
         for (int tb = 0; tb < NTB; ++tb) finish(tb, acc[tb]);
     }
@@ -812,8 +985,9 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
     {
         const int nb = 2 * NHT + head, n = nb * 32 + j;                   // this lane's output channel (dim j of the head)
         const v4i* wp = weights_of(2);
-        const float m = prm[PR::M + n], bs = prm[PR::B + n];
-        const int nc = prmi[PR::NC + n];
+        const float* pm = prm + PR::HEADS + hw * PR::PER_HEAD + 2 * (3 * HD) + j;
+        const float m = pm[0], bs = pm[HD];
+        const int nc = __float_as_int(pm[2 * HD]);
         const QDev qv = A.q_qkv[branch][2];
         int cs = 0;
         auto finish = [&](int tb, const v16i& acc) {
@@ -842,7 +1016,7 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[0][r] = nc;
         if (NTB == 2) acc[NTB - 1] = acc[0];
-        chain(wp, acc, false);
+        chain(wp, nullptr, acc, false);
 #pragma unroll
         for (int tb = 0; tb < NTB; ++tb) finish(tb, acc[tb]);
         cs = half_sum(cs);
@@ -873,9 +1047,11 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
     const size_t tbase = ((size_t)canon_slot * NHT + head) * TOK * TOK;
     core.tap_s = A.tap_s ? A.tap_s + tbase : nullptr;
     core.tap_p = A.tap_p ? A.tap_p + tbase : nullptr;
-    const int pack = branch ? A.out_pack : 0;                            // the low region's rows may be packed (dense, after the high region)
-    int8_t* out = A.out + (pack ? (size_t)G.base_lo * C : 0);
-    const int orow0 = row0 - (pack ? G.base_lo : 0);
+    // the low region's rows may be packed (dense, after the high region); operand fragments are the same for both branches
+    const int pack = A.out_pack == PACK_FRAG || branch ? A.out_pack : 0;
+    const bool dense = pack == 1 || pack == 2;
+    int8_t* out = A.out + (dense ? (size_t)G.base_lo * C : 0);
+    const int orow0 = row0 - (dense ? G.base_lo : 0);
 #pragma unroll 1
     for (int ib = tb0; ib < tb0 + NTB; ++ib) {
         asm volatile("" ::: "memory");
@@ -1417,12 +1593,18 @@ static void launch_gemm_e(const Geom& G, const GemmArgs& A0, hipStream_t st)
     const int groups = std::max(1, std::min((NB + 3) / 4, (512 + nt - 1) / nt));
     A.nb_per_block = ((NB + groups - 1) / groups + 3) / 4 * 4;
     const dim3 grid(nt, (NB + A.nb_per_block - 1) / A.nb_per_block);
-    if (half && A.K <= 1024) hipLaunchKernelGGL((gemm_tile_kernel<EPI, 1024, 32>), grid, dim3(256), 0, st, G, A);
-    else if (half && A.K <= 3072) hipLaunchKernelGGL((gemm_tile_kernel<EPI, 3072, 32>), grid, dim3(256), 0, st, G, A);
-    else if (half) hipLaunchKernelGGL((gemm_tile_kernel<EPI, 4096, 32>), grid, dim3(256), 0, st, G, A);
-    else if (A.K <= 384) hipLaunchKernelGGL((gemm_tile_kernel<EPI, 384>), grid, dim3(256), 0, st, G, A);
-    else if (A.K <= 1024 || A.K > GEMM_TILE_MAX_K) hipLaunchKernelGGL((gemm_tile_kernel<EPI, 1024>), grid, dim3(256), 0, st, G, A);   // above 4096: chunks of 1024
-    else hipLaunchKernelGGL((gemm_tile_kernel<EPI, GEMM_TILE_MAX_K>), grid, dim3(256), 0, st, G, A);
+#define GEMM_CASE(KMAX, RT, D) hipLaunchKernelGGL((gemm_tile_kernel<EPI, KMAX, RT, D>), grid, dim3(256), 0, st, G, A)
+    // ring length: whole turns of 16 or 12 fragments where K has them
+    const bool d16 = A.K % 512 == 0;
+    if (half && A.K <= 1024) { if (d16) GEMM_CASE(1024, 32, 16); else GEMM_CASE(1024, 32, 12); }
+    else if (half && A.K <= 3072) { if (d16) GEMM_CASE(3072, 32, 16); else GEMM_CASE(3072, 32, 12); }
+    else if (half) GEMM_CASE(4096, 32, 16);
+    else if (A.K <= 384) GEMM_CASE(384, 64, 6);
+    else if (A.K <= 1024) { if (d16) GEMM_CASE(1024, 64, 16); else GEMM_CASE(1024, 64, 12); }
+    else if (A.K > GEMM_TILE_MAX_K) GEMM_CASE(1024, 64, 8);           // above 4096: chunks of 1024
+    else if (d16) GEMM_CASE(GEMM_TILE_MAX_K, 64, 16);
+    else GEMM_CASE(GEMM_TILE_MAX_K, 64, 12);
+#undef GEMM_CASE
 }
 
 void launch_gemm(const Geom& G, const GemmArgs& A, int epi, hipStream_t st)
@@ -1436,9 +1618,7 @@ void launch_gemm(const Geom& G, const GemmArgs& A, int epi, hipStream_t st)
 }
 
 // the window kernel (gather + LN1 + QKV + attention) and the token kernel (proj + LN2 + FFN + scatter) are chosen separately
-// (a window kernel for C = 768, two workgroups of twelve heads per window, was measured at 37.5 us against 42 us for the three
-// kernels it replaces on 24 windows, and the whole stage came out slower: not enabled)
-bool fused_window_supported(int C) { return C == 96 || C == 128 || C == 192 || C == 256 || C == 384; }
+bool fused_window_supported(int C) { return channels_supported(C); }
 bool fused_token_supported(int C, int mlp_ratio) { return (C == 96 || C == 128 || C == 192 || C == 256 || C == 384) && mlp_ratio == 4; }
 
 // C = 384: up to this many windows, two workgroups share a window's heads, each with a pair of waves per head (twelve
@@ -1456,6 +1636,24 @@ void launch_window(const Geom& G, const WinArgs& A, hipStream_t st)
     // the computed slots come first and the pruned windows of the list after them
     const int n_wg = G.B * G.nW;
     if (n_wg == 0) return;
+    // wide blocks: LN1 by a kernel of its own, then the heads of a window over several workgroups
+#define WIDE_CASE(C_, LPT, NV, NH, HG, QS)                                                                                \
+    if (G.C == C_) {                                                                                                      \
+        const dim3 lgrid(n_wg, 64 * LPT / 256);                                                                           \
+        if (A.scores) hipLaunchKernelGGL((ln_window_kernel<LPT, NV, true>), lgrid, dim3(256), 0, st, G, A);               \
+        else hipLaunchKernelGGL((ln_window_kernel<LPT, NV, false>), lgrid, dim3(256), 0, st, G, A);                       \
+        if (G.n_slots == 0) return;                                                                                       \
+        WinArgs W = A;                                                                                                    \
+        if (A.scores) W.perm = A.perm_out;                                                                                \
+        const dim3 grid(G.n_slots * HG), block(NH * QS * 64);                                                             \
+        if (A.taps) hipLaunchKernelGGL((window_kernel<NH, true, false, HG, QS, true>), grid, block, 0, st, G, W);         \
+        else hipLaunchKernelGGL((window_kernel<NH, false, false, HG, QS, true>), grid, block, 0, st, G, W);               \
+        return;                                                                                                           \
+    }
+    WIDE_CASE(512, 32, 4, 4, 4, 2)
+    WIDE_CASE(768, 64, 3, 4, 6, 2)
+    WIDE_CASE(1024, 64, 4, 4, 8, 2)
+#undef WIDE_CASE
 #define WIN_CASE(NH, HG, QS)                                                                                              \
     {                                                                                                                     \
         const dim3 grid(n_wg * HG), block(NH * QS * 64);                                                                  \

@@ -113,6 +113,14 @@ __device__ __forceinline__ float gelu_scaled(float xs, const float4* lds)
 __host__ __device__ constexpr int pack_mode(int bits) { return bits <= 2 ? 2 : bits <= 4 ? 1 : 0; }
 __host__ __device__ constexpr int pack_offset(int mode) { return mode == 2 ? 2 : mode == 1 ? 8 : 0; }
 
+// A third form, for the kernels that multiply whole tiles of rows: MFMA operand fragments, one byte per code.  Rows in
+// groups of 32, per group and slab of 32 channels 64 lanes x 16 bytes: lane = half * 32 + row, byte = channel of the half.
+constexpr int PACK_FRAG = 3;
+__device__ __forceinline__ size_t frag_offset(int row, int ch, int slabs)
+{
+    return (((size_t)(row >> 5) * slabs + (ch >> 5)) * 64 + ((ch & 31) >> 4) * 32 + (row & 31)) * 16 + (ch & 15);
+}
+
 // the 16 codes (offset-binary, one per byte, in channel order) of channels 32*ks + 16*half .. +15 of one packed row
 __device__ __forceinline__ v4i unpack_codes(const int8_t* packed_row, int mode, int ks, int half)
 {
