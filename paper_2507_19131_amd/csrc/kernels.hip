@@ -78,20 +78,23 @@ __device__ __forceinline__ void token_layernorm(float4 (&v)[NV], int C, float ep
 }
 
 // ------------------------------------------------------------------ K0 score
-// One workgroup (256 threads) per window of the un-shifted grid.
-template <int LPT, int NV>
-__global__ __launch_bounds__(256) void score_kernel(Geom G, const float* __restrict__ x, int mode, float eps,
-                                                    const float* __restrict__ gamma, const float* __restrict__ beta,
-                                                    double* __restrict__ scores)
+// One workgroup of NT threads per window of the un-shifted grid, LPT lanes per token.  The loads of PC passes over the
+// tokens are issued together, before any arithmetic.  Memory bound once there are windows enough to fill the chip (NT =
+// 256); wide maps have few windows, each of them a chain of round trips for its one workgroup, so from C = 384 it gets 1024
+// threads that have the whole window in flight at once (24 windows at C = 768: 7.5 -> 4.0 us).
+template <int LPT, int NV, int NT>
+__global__ __launch_bounds__(NT) void score_kernel(Geom G, const float* __restrict__ x, int mode, float eps,
+                                                   const float* __restrict__ gamma, const float* __restrict__ beta,
+                                                   double* __restrict__ scores)
 {
     const int wid = blockIdx.x;                       // b*nW + w
     const int b = wid / G.nW, w = wid - b * G.nW;
     const int wr = w / G.nWc, wc = w - wr * G.nWc;
     const int grp = threadIdx.x / LPT, sub = threadIdx.x % LPT;
-    constexpr int TP = 256 / LPT;
+    constexpr int TP = NT / LPT;
     double acc = 0.0;
     constexpr int PASSES = (TOK + TP - 1) / TP;
-    constexpr int PC = LPT <= 16 ? PASSES : 2;        // passes whose loads are issued together, before any arithmetic
+    constexpr int PC = LPT <= 16 || NT > 256 ? PASSES : 2;
 #pragma unroll 1
     for (int p0 = 0; p0 < PASSES; p0 += PC) {
         float4 v[PC][NV];
@@ -101,7 +104,7 @@ __global__ __launch_bounds__(256) void score_kernel(Geom G, const float* __restr
             const int t = grp + (p0 + p) * TP, pr = wr * WS + t / WS, pc = wc * WS + t % WS;
             in[p] = t < TOK && pr < G.H && pc < G.W;  // uniform inside a token group
             if (in[p]) {
-                const float* px = x + ((size_t)(b * G.H + pr) * G.W + pc) * G.C;
+                const float* px = x + ((size_t)(b * G.H + pr) * G.W + pc) * (LPT * NV * 4);
 #pragma unroll
                 for (int k = 0; k < NV; ++k) v[p][k] = *(const float4*)(px + (k * LPT + sub) * 4);
             }
@@ -109,19 +112,25 @@ __global__ __launch_bounds__(256) void score_kernel(Geom G, const float* __restr
 #pragma unroll
         for (int p = 0; p < PC; ++p) {
             if (in[p]) {
-                if (mode == 1) token_layernorm<LPT, NV>(v[p], G.C, eps, gamma, beta, sub);
+                if (mode == 1) token_layernorm<LPT, NV>(v[p], LPT * NV * 4, eps, gamma, beta, sub);
 #pragma unroll
-                for (int k = 0; k < NV; ++k)
-                    acc += ((double)v[p][k].x * (double)v[p][k].x + (double)v[p][k].y * (double)v[p][k].y) +
-                           ((double)v[p][k].z * (double)v[p][k].z + (double)v[p][k].w * (double)v[p][k].w);
+                for (int k = 0; k < NV; ++k) {
+                    const double d0 = v[p][k].x, d1 = v[p][k].y, d2 = v[p][k].z, d3 = v[p][k].w;
+                    acc += __builtin_fma(d0, d0, d1 * d1) + __builtin_fma(d2, d2, d3 * d3);
+                }
             }
         }
     }
     acc = group_sum<64>(acc);
-    __shared__ double part[4];
+    __shared__ double part[NT / 64];
     if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = acc;
     __syncthreads();
-    if (threadIdx.x == 0) scores[wid] = (part[0] + part[1]) + (part[2] + part[3]);
+    if (threadIdx.x == 0) {
+        double s = 0.0;
+#pragma unroll
+        for (int k = 0; k < NT / 64; ++k) s += part[k];
+        scores[wid] = s;
+    }
 }
 
 // ------------------------------------------------------------------ K1 select
@@ -1516,7 +1525,8 @@ template <int LPT, int NV>
 static void launch_score_t(const Geom& G, const float* x, int mode, float eps, const float* gm, const float* bt,
                            double* scores, hipStream_t st)
 {
-    hipLaunchKernelGGL((score_kernel<LPT, NV>), dim3(G.B * G.nW), dim3(256), 0, st, G, x, mode, eps, gm, bt, scores);
+    constexpr int NT = LPT * NV * 4 >= 384 ? 1024 : 256;
+    hipLaunchKernelGGL((score_kernel<LPT, NV, NT>), dim3(G.B * G.nW), dim3(NT), 0, st, G, x, mode, eps, gm, bt, scores);
 }
 template <int LPT, int NV>
 static void launch_ln_t(const Geom& G, const LnArgs& A, bool gather, hipStream_t st)
