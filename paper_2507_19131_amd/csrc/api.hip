@@ -110,8 +110,8 @@ int download(const T* dev, size_t n, std::vector<T>& host)
 
 struct Linear {           // one shadow layer prepared for the device
     int K = 0, N = 0;
-    v4i* Wp = nullptr;         // k bytes of a lane half in natural order (operand read from row-major memory)
-    v4i* Wp_reg = nullptr;     // k bytes in the order of MFMA result registers (operand chained from registers)
+    v4i* Wp = nullptr;         // packed weights; the k bytes of a lane half in natural order (QKV, projection) or in the order
+                               // of MFMA result registers (FC1, FC2: the operand is a lane's own 16 results)
     float* m[2] = {nullptr, nullptr};
     float* bias[2] = {nullptr, nullptr};
     int* negcorr[2] = {nullptr, nullptr};
@@ -197,27 +197,18 @@ int prepare_linear(mixaq_block* blk, Linear& L, const int8_t* w_dev, const float
         }
     }
     const int NB = N / 32, KS = K / 32;
-    std::vector<int8_t> packed((size_t)N * K);
+    int8_t* packed = blk->mem.take<int8_t>((size_t)N * K, &L.Wp);
     for (int nb = 0; nb < NB; ++nb)
         for (int ks = 0; ks < KS; ++ks)
-            for (int lane = 0; lane < 64; ++lane) {
-                const int8_t* src = &w[(size_t)(nb * 32 + lane % 32) * K + ks * 32 + (lane / 32) * 16];
-                memcpy(&packed[(((size_t)nb * KS + ks) * 64 + lane) * 16], src, 16);
+            for (int lane = 0; lane < 64; ++lane, packed += 16) {
+                const int8_t* src = &w[(size_t)(nb * 32 + lane % 32) * K + ks * 32];
+                if (!reg_order) memcpy(packed, src + (lane / 32) * 16, 16);
+                else
+                    for (int q = 0; q < 4; ++q) memcpy(packed + q * 4, src + q * 8 + (lane / 32) * 4, 4);
             }
     L.K = K;
     L.N = N;
     L.colsum = colsum;
-    blk->mem.add(packed, &L.Wp);
-    if (reg_order) {
-        for (int nb = 0; nb < NB; ++nb)
-            for (int ks = 0; ks < KS; ++ks)
-                for (int lane = 0; lane < 64; ++lane)
-                    for (int r = 0; r < 16; ++r) {
-                        int k = ks * 32 + (r / 4) * 8 + (lane / 32) * 4 + r % 4;
-                        packed[(((size_t)nb * KS + ks) * 64 + lane) * 16 + r] = w[(size_t)(nb * 32 + lane % 32) * K + k];
-                    }
-        blk->mem.add(packed, &L.Wp_reg);
-    }
     for (int br = 0; br < 2; ++br) {
         if ((rc = download(bias_dev[br], (size_t)N, b))) return rc;
         std::vector<float> m(N);
@@ -419,7 +410,7 @@ int forward_impl(const mixaq_block* blk, const float* x, const int32_t* perm, co
     if (ft) {
         TokArgs ta = {};
         ta.ao = ws.ao; ta.x = x; ta.y = y; ta.row_pix = ws.row_pix; ta.row_canon = ws.row_canon; ta.eps = d.ln_eps;
-        ta.Wproj = blk->proj.Wp; ta.W1 = blk->fc1.Wp_reg; ta.W2 = blk->fc2.Wp_reg;
+        ta.Wproj = blk->proj.Wp; ta.W1 = blk->fc1.Wp; ta.W2 = blk->fc2.Wp;
         ta.ao_pack = blk->ao_pack;
         for (int br = 0; br < 2; ++br) {
             ta.params[br] = blk->tok_params[br];
@@ -454,7 +445,6 @@ int forward_impl(const mixaq_block* blk, const float* x, const int32_t* perm, co
     mark(7);
     for (int r = 0; r < reps; ++r) launch_gemm(G, ga, EPI_FC1, st);
     fill(ga, blk->fc2, ws.g);
-    ga.Wp = blk->fc2.Wp_reg;                                           // FC1 leaves its codes in the order of its result registers
     ga.resid = ws.h; ga.y = y; ga.tap_acc = tp.acc_fc2; ga.tap_f = tp.y_win;
     mark(8);
     for (int r = 0; r < reps; ++r) launch_gemm(G, ga, EPI_FC2, st);
@@ -542,6 +532,7 @@ static int block_create(const mixaq_block_desc* desc, const mixaq_shared_params*
     b->nWc = b->Wp / WS; b->nW = (b->Hp / WS) * b->nWc;
     const int C = desc->C, F = C * desc->mlp_ratio, heads = desc->heads;
     BlockOwner owner{b};
+    b->mem.reserve((size_t)4 * C * C + 2 * (size_t)F * C + (size_t)heads * 4 * TOK * 64 * 4 + (size_t)C * 800 + 65536);
     auto bail = [&](int code) { return code; };          // the owner destroys the block
     mixaq_qparam qi[2];
     const float* bias[2];

@@ -30,7 +30,7 @@ struct LnArgs {
 };
 
 struct GemmArgs {
-    const int8_t* A;                 // activations, operand fragments (frag_offset; FC2: k in the order of the result registers)
+    const int8_t* A;                 // activations, operand fragments (FC1, FC2: k in the order of the result registers)
     const v4i* Wp;                   // packed weights [N/32][K/32][64 lanes] x 16 bytes
     int K, N, nb_per_block;
     int kchunk;                      // bytes of K staged in LDS at a time (a divisor of K; set by the launcher)

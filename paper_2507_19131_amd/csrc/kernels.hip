@@ -287,7 +287,7 @@ __global__ __launch_bounds__(256) void ln_quant_kernel(Geom G, LnArgs A)
         int code = pack4(quant_code(v[k].x, q), quant_code(v[k].y, q), quant_code(v[k].z, q), quant_code(v[k].w, q));
         if (canon < 0) code = 0;
         int ch = (k * LPT + sub) * 4;
-        *(int*)(A.out + frag_offset(row, ch, G.C / 32)) = code;
+        *(int*)(A.out + (GATHER ? frag_offset(row, ch, G.C / 32) : frag_offset_reg(row, ch, G.C / 32))) = code;   // the k order of the next layer's weights
         if (A.tap && canon >= 0) *(int*)(A.tap + (size_t)canon * G.C + ch) = code;
     }
 }

@@ -121,6 +121,12 @@ __device__ __forceinline__ size_t frag_offset(int row, int ch, int slabs)
     return (((size_t)(row >> 5) * slabs + (ch >> 5)) * 64 + ((ch & 31) >> 4) * 32 + (row & 31)) * 16 + (ch & 15);
 }
 
+// the same with the 32 channels of a slab in the order of MFMA result registers (byte r of a half: channel mfma_row(r, half))
+__device__ __forceinline__ size_t frag_offset_reg(int row, int ch, int slabs)
+{
+    return (((size_t)(row >> 5) * slabs + (ch >> 5)) * 64 + ((ch >> 2) & 1) * 32 + (row & 31)) * 16 + ((ch & 31) >> 3) * 4 + (ch & 3);
+}
+
 // the 16 codes (offset-binary, one per byte, in channel order) of channels 32*ks + 16*half .. +15 of one packed row
 __device__ __forceinline__ v4i unpack_codes(const int8_t* packed_row, int mode, int ks, int half)
 {
