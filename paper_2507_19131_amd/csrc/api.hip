@@ -597,7 +597,7 @@ static int block_create(const mixaq_block_desc* desc, const mixaq_shared_params*
         b->mem.add(tab, &b->bias2);
     }
     {
-        std::vector<float> tab((size_t)GELU_K * 4);
+        std::vector<float> tab((size_t)GELU_TAB * 4, 0.0f);
         gelu_table(tab.data());
         b->mem.add(tab, &b->gelu_tab);
     }

@@ -1307,7 +1307,7 @@ __global__ __launch_bounds__(NH * 64) void token_wide_kernel(Geom G, TokArgs A)
     __shared__ v4i gs[2][NH * RB * 64];                                // [buffer][hidden block of the chunk][row block][lane]
     __shared__ double part[2][NH][32 * RB];
     __shared__ __attribute__((aligned(16))) float prm[PR::WORDS];
-    __shared__ float4 gtab[GELU_K];
+    __shared__ float4 gtab[GELU_TAB];
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, j = lane & 31, g = lane >> 5;
     const int row_base = blockIdx.x * (32 * RB);
     const int branch = row_base >= G.base_lo ? 1 : 0;                 // a tile never straddles the regions: scalar
@@ -1333,33 +1333,55 @@ __global__ __launch_bounds__(NH * 64) void token_wide_kernel(Geom G, TokArgs A)
         pix[rb] = valid[rb] ? A.row_pix[row] : -1;
         canon[rb] = (TAPS && valid[rb]) ? (size_t)A.row_canon[row] : 0;
     }
-    // stage the attention codes of the tile: piece p = (row r, 16-byte chunk q) -> fragment (r/32, q/2), lane (r%32, q%2)
+    // Staging: the attention codes of the tile as operand fragments, the parameter block and the GELU table.  What is a plain
+    // copy goes straight to LDS and everything is requested before anything is waited for (piece by piece, load and LDS
+    // write in a loop, the staging was a chain of round trips: 3.3 us of a tile's 14 at C = 192).
+    const int swave = __builtin_amdgcn_readfirstlane(wave);
+    auto to_lds = [&](const void* src, void* dst) {                    // 64 lanes x 16 bytes; src per lane, dst the wave's 1 KB
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src, (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
+    };
     const int pack = branch ? A.ao_pack : 0;                           // packed low-branch codes: scalar per tile
-    for (int p = tid; p < 32 * RB * (C / 16); p += NT) {
-        const int r = p / (C / 16), q = p - r * (C / 16);
-        actf[((r >> 5) * KS + (q >> 1)) * 64 + (q & 1) * 32 + (r & 31)] =
-            pack ? unpack_codes(A.ao + (size_t)G.base_lo * C + (size_t)(row_base - G.base_lo + r) * (C >> pack), pack, q >> 1, q & 1)
-                 : *(const v4i*)(A.ao + (size_t)(row_base + r) * C + q * 16);
+    v4i pc[RB];
+    if (pack) {
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb)                                // fragment (rb, slab = wave), lane (half g, row j)
+            pc[rb] = unpack_codes(A.ao + (size_t)G.base_lo * C + (size_t)(row_base - G.base_lo + rb * 32 + j) * (C >> pack), pack, wave, g);
+    } else {
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb)
+            to_lds(A.ao + (size_t)(row_base + rb * 32 + j) * C + swave * 32 + g * 16, actf + (rb * KS + swave) * 64);
     }
-    {
-        const float4* psrc = (const float4*)A.params[branch];
-        for (int p = tid; p < PR::WORDS / 4; p += NT) ((float4*)prm)[p] = psrc[p];
-    }
-    gelu_stage_table(gtab, A.gelu_tab, tid, NT);
-    // acc[rb] += W * operand^T over one phase.  Weights come from the ring (slot0 = ring slot of the phase's first
-    // fragment); after fragment i is used, the fragment RING places further down the stream is requested: from this
-    // phase (cur) or from the start of the next one (nxt, NULL at the end of the stream).  Operand fragment i of
-    // row block rb: b[(rb*rb_stride + i*i_stride)*64 + lane].
-    auto run = [&](int slot0, const v4i* cur, const v4i* nxt, const v4i* b, int rb_stride, int i_stride, v16i* acc) {
+    for (int p = swave; p < PR::WORDS / 256; p += NH) to_lds(A.params[branch] + p * 256 + lane * 4, prm + p * 256);
+    if (PR::WORDS % 256 && tid < PR::WORDS % 256 / 4) ((float4*)prm)[PR::WORDS / 256 * 64 + tid] = ((const float4*)A.params[branch])[PR::WORDS / 256 * 64 + tid];
+    if (swave >= NH - 2) to_lds(A.gelu_tab + (swave - (NH - 2)) * 64 + lane, gtab + (swave - (NH - 2)) * 64);
+    // acc[rb] += W * operand^T over one phase.  Weights come from the ring (SLOT0 = ring slot of the phase's first
+    // fragment); after fragment i is used, the fragment RING places further down the stream is requested into its slot: from
+    // this phase (cur) or from the start of the next one (nxt; LAST: the end of the stream).  Operand fragment i of row
+    // block rb: b[(rb*rb_stride + i*i_stride)*64 + lane], read PF steps ahead.  The steps keep their order (product, request,
+    // LDS read): see gemm_tile_kernel.
+    auto run = [&](auto SLOT0, auto LAST, const v4i* cur, const v4i* nxt, const v4i* b, int rb_stride, int i_stride, v16i* acc) {
+        constexpr int PF = 2;
+        v4i bq[PF][RB];
+        auto operand = [&](int i) {
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb) bq[i % PF][rb] = b[(rb * rb_stride + i * i_stride) * 64 + lane];
+        };
+#pragma unroll
+        for (int i = 0; i < PF; ++i) operand(i);
 #pragma unroll
         for (int i = 0; i < KS; ++i) {
-            const v4i wv = ring[(slot0 + i) % RING];
-            if (i + RING < KS) ring[(slot0 + i) % RING] = cur[(i + RING) * 64];
-            else if (nxt) ring[(slot0 + i) % RING] = nxt[(i + RING - KS) * 64];
+            constexpr int S0 = decltype(SLOT0)::value;
 #pragma unroll
-            for (int rb = 0; rb < RB; ++rb) acc[rb] = mfma32(wv, b[(rb * rb_stride + i * i_stride) * 64 + lane], acc[rb]);
+            for (int rb = 0; rb < RB; ++rb) acc[rb] = mfma32(ring[(S0 + i) % RING], bq[i % PF][rb], acc[rb]);
+            if (i + RING < KS) ring[(S0 + i) % RING] = cur[(i + RING) * 64];
+            else if (!decltype(LAST)::value) ring[(S0 + i) % RING] = nxt[(i + RING - KS) * 64];
+            if (i + PF < KS) operand(i + PF);
+            __builtin_amdgcn_sched_barrier(0);
         }
     };
+    using Even = std::integral_constant<int, 0>;
+    using Odd = std::integral_constant<int, SLOT_ODD>;
+    using More = std::false_type;
     auto start = [&](v16i* acc, int off) {                             // accumulators start at -zp * colsum
 #pragma unroll
         for (int qd = 0; qd < 4; ++qd) {
@@ -1375,12 +1397,17 @@ __global__ __launch_bounds__(NH * 64) void token_wide_kernel(Geom G, TokArgs A)
 #pragma unroll
         for (int qd = 0; qd < 4; ++qd)
             sc[rb][qd] = pix[rb] >= 0 ? *(const float4*)(A.x + (size_t)pix[rb] * C + nb * 32 + qd * 8 + g * 4) : make_float4(0.f, 0.f, 0.f, 0.f);
+    if (pack) {
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) actf[(rb * KS + wave) * 64 + lane] = pc[rb];
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                   // the direct loads have landed
     __syncthreads();                                                  // staged codes, parameters and table visible
     float h[RB][16];
     {   // output projection + first residual
         v16i acc[RB];
         start(acc, PR::P_NC + nb * 32);
-        run(0, wproj, w1_of(0), actf, KS, 1, acc);
+        run(Even(), More(), wproj, w1_of(0), actf, KS, 1, acc);
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
@@ -1488,7 +1515,7 @@ __global__ __launch_bounds__(NH * 64) void token_wide_kernel(Geom G, TokArgs A)
     {   // chunk 0: FC1 + GELU
         v16i acc[RB];
         start(acc, PR::F1_NC + wave * 32);
-        run(SLOT_ODD, w1_of(0), w1_of(1), actf, KS, 1, acc);
+        run(Odd(), More(), w1_of(0), w1_of(1), actf, KS, 1, acc);
         gelu_chunk(0, acc);
     }
     __syncthreads();                                                  // chunk 0 of the hidden codes complete
@@ -1496,12 +1523,12 @@ __global__ __launch_bounds__(NH * 64) void token_wide_kernel(Geom G, TokArgs A)
     for (int ch = 1; ch < 4; ++ch) {
         v16i acc[RB];
         start(acc, PR::F1_NC + (ch * NH + wave) * 32);
-        run(0, w1_of(ch), w2_of(ch - 1), actf, KS, 1, acc);                                   // FC1 of chunk ch
-        run(SLOT_ODD, w2_of(ch - 1), ch < 3 ? w1_of(ch + 1) : w2_of(3), gs[(ch - 1) & 1], 1, RB, acc2);   // FC2 of chunk ch-1, under ...
+        run(Even(), More(), w1_of(ch), w2_of(ch - 1), actf, KS, 1, acc);                                   // FC1 of chunk ch
+        run(Odd(), More(), w2_of(ch - 1), ch < 3 ? w1_of(ch + 1) : w2_of(3), gs[(ch - 1) & 1], 1, RB, acc2);   // FC2 of chunk ch-1, under ...
         gelu_chunk(ch, acc);                                                                  // ... this arithmetic
         __syncthreads();                                              // chunk ch complete, chunk ch-1 no longer read
     }
-    run(0, w2_of(3), nullptr, gs[1], 1, RB, acc2);                     // FC2 of the last chunk
+    run(Even(), std::true_type(), w2_of(3), nullptr, gs[1], 1, RB, acc2);                     // FC2 of the last chunk
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb)
 #pragma unroll

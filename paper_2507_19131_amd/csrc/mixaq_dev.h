@@ -84,6 +84,7 @@ __device__ __forceinline__ float exp2_pinned(float y, const PolyCoef& P)
 // result uses inv_s / 2^GELU_LOG2K.  This saves the multiply that would form the table index.
 constexpr int GELU_LOG2K = 4;
 constexpr int GELU_K = 6 << GELU_LOG2K;                       // intervals on [0,6)
+constexpr int GELU_TAB = (GELU_K + 63) / 64 * 64;            // entries of the stored table (whole 1 KB pieces; zeros behind the intervals)
 constexpr float GELU_SCALE = (float)(1 << GELU_LOG2K);
 __device__ __forceinline__ void gelu_stage_table(float4* lds, const float4* tab, int tid, int nthreads)
 {
