@@ -24,6 +24,7 @@ struct DsArgs {
     const float* x;
     float* y;
     int B, H, W, Cin, P, K, Kp, N, Ho, Wo, tokens;
+    FastDiv by_map, by_row;           // by Ho Wo, by Wo
     const v4i* Wp;                    // [N/32][Kp/32][64 lanes] x 16 bytes, natural k order, zero beyond K
     const float* m;                   // a_in.scale * s_w[n]
     const float* bias;                // [N] (zeros when the layer has none)
@@ -69,101 +70,261 @@ __device__ __forceinline__ float4 ds_values(const DsArgs& A, int b, int i, int j
     return v;
 }
 
-// Patch merging of the usual widths (C_in = 4 LPT NV4, LPT lanes per token, 4 NV4 = NV float4 per lane: C_in a
-// multiple of 48 or 64 up to 512).  One workgroup (4 waves) per 32 output tokens and per group of output blocks.
-// Phase 1: LPT lanes hold the 4 C_in inputs of a token in registers (NV independent 16-byte loads per lane, the
-// neighbour of each known at compile time), LayerNorm statistics in binary64 over the lane group, quantize, codes
-// to LDS as MFMA operand fragments; 256 / LPT tokens per pass.  Phase 2: wave w computes the output blocks
-// first + w, first + w + 4, ... of its group: the weight fragments stream through a ring of loads in flight.
-template <int LPT, int NV, bool TAPS>
-__global__ __launch_bounds__(256) void merge_kernel(DsArgs A, int blocks_per_group)
+constexpr int MERGE_CUS = 256;                  // 8 XCDs of 32
+// fragments in flight per wave: a part of the slabs that every split keeps whole
+constexpr int merge_ring(int KS) { return KS % 3 == 0 ? (KS >= 48 ? 12 : 6) : 8; }
+constexpr int merge_max_split(int KS) { return KS / merge_ring(KS) >= 4 ? 4 : 2; }
+
+// Patch merging of the usual widths (C_in = LPT NV: 96, 128, 192, 256, 384, 512), one workgroup per 32 output tokens and
+// per group of output blocks.
+// Phase 1: LPT lanes per token, a quarter of them per neighbour, NV float4 each; the workgroup grows with C_in so that
+// a lane's share of the 32 tokens is 48 or 64 floats, which it requests all at once: the kernel waits once for memory,
+// and 128 registers leave room for sixteen waves per CU.  LayerNorm statistics in one binary64 pass over the lane group,
+// quantize, codes to LDS as MFMA operand fragments (slabs and halves a little apart, so that the lanes of a wave spread
+// over the banks).
+// Phase 2: wave w takes the output blocks first + w, first + w + waves, ... of its group; the weight fragments stream
+// through a ring of loads in flight that starts before the barrier.  On a small grid `split` waves share the slabs of one
+// output block (whole numbers: any order gives the same sums) and add up through LDS.  The tokens are the rows of the
+// product and the output channels its columns, so a store writes whole 128-byte lines and a lane needs one m and one bias.
+// Bound: memory on large maps (4 x 256 x 256 x 128: 59 -> 39 us with the input in the cache; before, 64 floats per lane and
+// the hoisted gamma and beta took 224 registers, two waves per SIMD, and the vector unit idled two thirds of the time), the
+// chain load - statistics - codes - products of one workgroup per CU on small ones (50 x 84 x 384: 21.2 -> 12.1 us).
+template <int LPT, int NV, int NT, bool TAPS>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void merge_kernel(DsArgs A, int by_xcd, int groups, int per, int split)
 {
-    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    constexpr int TP = 256 / LPT, PER = NV / 4, KSN = NV * LPT / 8, RING = KSN % 8 == 0 ? 8 : 6;
-    static_assert(NV % 4 == 0 && (LPT & (LPT - 1)) == 0 && LPT <= 64 && KSN % RING == 0, "lane groups inside a wave, whole ring turns");
-    v4i* frag = (v4i*)smem;                                   // [KSN][64]
-    int* fragw = (int*)smem;
+    constexpr int CIN = LPT * NV, K = 4 * CIN, KS = K / 32, LQ = LPT / 4, TP = NT / LPT, PASSES = 32 / TP, NW = NT / 64;
+    constexpr int RING = merge_ring(KS), HALF = 34, SLAB = KS % 16 == 0 ? 69 : 68;        // strides in 16-byte units
+    static_assert(KS % RING == 0 && (LPT & (LPT - 1)) == 0 && LPT <= 64 && PASSES * NV <= 16, "lane groups inside a wave, whole ring turns");
+    __shared__ v4i frag[(KS + 1) * SLAB];                     // one slab more: the operand of the step after the last is read, not used
+    int* fragw = (int*)frag;
+    int tile, group = 0;
+    if (by_xcd) {                                             // the groups of a tile on one XCD: its inputs come through one L2
+        const int slot = blockIdx.x >> 3;                     // (33 tiles of C_in = 384 in 6 groups: 15.0 -> 12.1 us)
+        tile = slot / groups * 8 + (blockIdx.x & 7);
+        group = slot % groups;
+        if (tile * 32 >= A.tokens) return;
+    } else {
+        tile = groups == 1 ? blockIdx.x : blockIdx.x / groups;
+        group = groups == 1 ? 0 : blockIdx.x % groups;
+    }
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const int grp = tid / LPT, sub = tid % LPT;
-#pragma unroll 1
-    for (int p0 = 0; p0 < 32; p0 += TP) {
-        const int jt = p0 + grp, tok = blockIdx.x * 32 + jt;
-        const bool valid = tok < A.tokens;
-        const int b = tok / (A.Ho * A.Wo), rem = tok - b * (A.Ho * A.Wo), i = rem / A.Wo, j = rem - i * A.Wo;
-        float4 v[NV];
+    {
+        const int grp = tid / LPT, q = (tid % LPT) / LQ, ch0 = (tid % LQ) * 4;
+        float4 v[PASSES][NV];
+        bool valid[PASSES], inside[PASSES];
 #pragma unroll
-        for (int k = 0; k < NV; ++k) {                        // element k of the lane: neighbour k / PER, channels ((k % PER) LPT + sub) 4 ..
-            const int q = k / PER, r = 2 * i + (q & 1), c = 2 * j + (q >> 1);
-            v[k] = (valid && r < A.H && c < A.W)
-                       ? *(const float4*)(A.x + (((size_t)b * A.H + r) * A.W + c) * A.Cin + ((k % PER) * LPT + sub) * 4)
-                       : make_float4(0.f, 0.f, 0.f, 0.f);
+        for (int p = 0; p < PASSES; ++p) {
+            const int tok = tile * 32 + p * TP + grp;
+            valid[p] = tok < A.tokens;
+            const int b = A.by_map(tok), rem = tok - b * A.by_map.d, i = A.by_row(rem), j = rem - i * A.by_row.d;
+            const int r = 2 * i + (q & 1), c = 2 * j + (q >> 1);
+            inside[p] = valid[p] && r < A.H && c < A.W;
+            const float* src = A.x + (inside[p] ? (((size_t)b * A.H + r) * A.W + c) * CIN : 0) + ch0;
+#pragma unroll
+            for (int k = 0; k < NV; ++k) v[p][k] = *(const float4*)(src + k * (LQ * 4));
         }
-        double s = 0.0;
+        const float* gamma = A.gamma + q * CIN + ch0;
+        const float* beta = A.beta + q * CIN + ch0;
+        float mean[PASSES], rstd[PASSES];
 #pragma unroll
-        for (int k = 0; k < NV; ++k) s += ((double)v[k].x + (double)v[k].y) + ((double)v[k].z + (double)v[k].w);
+        for (int p = 0; p < PASSES; ++p) {
+            if (!__all(inside[p])) {                          // the edge of an odd map, the last tile
 #pragma unroll
-        for (int o = LPT / 2; o >= 1; o >>= 1) s += __shfl_xor(s, o, 64);
-        const float mean = (float)(s / (double)A.K);
-        double qv = 0.0;
-#pragma unroll
-        for (int k = 0; k < NV; ++k) {
-            const double a0 = (double)v[k].x - (double)mean, a1 = (double)v[k].y - (double)mean;
-            const double a2 = (double)v[k].z - (double)mean, a3 = (double)v[k].w - (double)mean;
-            qv += (a0 * a0 + a1 * a1) + (a2 * a2 + a3 * a3);
-        }
-#pragma unroll
-        for (int o = LPT / 2; o >= 1; o >>= 1) qv += __shfl_xor(qv, o, 64);
-        const float var = (float)(qv / (double)A.K);
-        const float rstd = 1.0f / sqrtf(var + A.eps);
-#pragma unroll
-        for (int k = 0; k < NV; ++k) {
-            const int k0 = (k * LPT + sub) * 4;
-            int code = 0;
-            if (valid) {
-                const float4 gm = *(const float4*)(A.gamma + k0), bt = *(const float4*)(A.beta + k0);
-                code = pack4(quant_code(fmaf((v[k].x - mean) * rstd, gm.x, bt.x), A.q), quant_code(fmaf((v[k].y - mean) * rstd, gm.y, bt.y), A.q),
-                             quant_code(fmaf((v[k].z - mean) * rstd, gm.z, bt.z), A.q), quant_code(fmaf((v[k].w - mean) * rstd, gm.w, bt.w), A.q));
-                if (TAPS && A.tap_codes && blockIdx.y == 0) *(int*)(A.tap_codes + (size_t)tok * A.K + k0) = code;
+                for (int k = 0; k < NV; ++k) {
+                    v[p][k].x = inside[p] ? v[p][k].x : 0.f; v[p][k].y = inside[p] ? v[p][k].y : 0.f;
+                    v[p][k].z = inside[p] ? v[p][k].z : 0.f; v[p][k].w = inside[p] ? v[p][k].w : 0.f;
+                }
             }
-            fragw[(((k0 >> 5) * 64 + ((k0 & 31) >> 4) * 32 + jt) << 2) + ((k0 & 15) >> 2)] = code;
+            Moments mo;
+#pragma unroll
+            for (int k = 0; k < NV; ++k) moments_add(mo, v[p][k].x, v[p][k].y, v[p][k].z, v[p][k].w);
+            const double s = lanes_sum<LPT>(mo.s);
+            mean[p] = moments_mean(s, K);
+            bool shaky;
+            double cs = moments_centred(s, lanes_sum<LPT>(mo.q), mean[p], K, shaky);
+            if (__any(shaky)) {
+                double t = 0.0;
+#pragma unroll
+                for (int k = 0; k < NV; ++k) t += centred_squares(v[p][k].x, v[p][k].y, v[p][k].z, v[p][k].w, mean[p]);
+                cs = lanes_sum<LPT>(t);
+            }
+            rstd[p] = moments_rstd(cs, K, A.eps);
+        }
+#pragma unroll
+        for (int k = 0; k < NV; ++k) {
+            const float4 gm = *(const float4*)(gamma + k * (LQ * 4)), bt = *(const float4*)(beta + k * (LQ * 4));
+            const int k0 = q * CIN + ch0 + k * (LQ * 4);
+#pragma unroll
+            for (int p = 0; p < PASSES; ++p) {
+                const int jt = p * TP + grp;
+                const int code = pack4(quant_code(fmaf((v[p][k].x - mean[p]) * rstd[p], gm.x, bt.x), A.q), quant_code(fmaf((v[p][k].y - mean[p]) * rstd[p], gm.y, bt.y), A.q),
+                                       quant_code(fmaf((v[p][k].z - mean[p]) * rstd[p], gm.z, bt.z), A.q), quant_code(fmaf((v[p][k].w - mean[p]) * rstd[p], gm.w, bt.w), A.q));
+                if (TAPS && A.tap_codes && valid[p] && group == 0) *(int*)(A.tap_codes + (size_t)(tile * 32 + jt) * K + k0) = code;
+                fragw[(((k0 >> 5) * SLAB + ((k0 & 31) >> 4) * HALF + jt) << 2) + ((k0 & 15) >> 2)] = code;
+            }
+            if (k & 1) __builtin_amdgcn_sched_barrier(0);     // not all of gamma and beta in registers at once
         }
     }
-    __syncthreads();
-    const int j = lane & 31, g = lane >> 5;
-    const int tok = blockIdx.x * 32 + j;
-    const bool valid = tok < A.tokens;
-    const int first = blockIdx.y * blocks_per_group, last = min(first + blocks_per_group, A.N / 32);
-    for (int nb = first + wave; nb < last; nb += 4) {
-        const v4i* wp = A.Wp + (size_t)nb * KSN * 64 + lane;
-        v4i ring[RING];
+    const int j = lane & 31, g = lane >> 5, part = wave % split, len = KS / split;
+    const int first = group * per, units = (min(first + per, A.N / 32) - first) * split;
+    int nb = first + (wave < units ? wave / split : 0);
+    const v4i* wp = A.Wp + ((size_t)nb * KS + part * len) * 64 + lane;
+    v4i ring[RING];
 #pragma unroll
-        for (int d = 0; d < RING; ++d) ring[d] = wp[d * 64];
+    for (int d = 0; d < RING; ++d) ring[d] = wp[d * 64];
+    __syncthreads();
+    const v4i* fs = frag + part * len * SLAB + g * HALF + j;
+    auto store = [&](const v16i& acc, float m, float bias) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int tok = tile * 32 + mfma_row(r, g);
+            if (tok < A.tokens) {
+                const size_t at = (size_t)tok * A.N + nb * 32 + j;
+                A.y[at] = fmaf((float)acc[r], m, bias);
+                if (TAPS && A.tap_acc) A.tap_acc[at] = acc[r];
+            }
+        }
+    };
+    v16i acc;
+    for (int u = wave; u < units; u += NW) {                  // one turn where split > 1
+        const float m = A.m[nb * 32 + j], bias = A.bias[nb * 32 + j];
+        const int nc = part == 0 ? A.negcorr[nb * 32 + j] : 0;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[r] = nc;
+        const v4i* wnext = u + NW < units ? wp + (size_t)NW * KS * 64 : wp;               // behind the last turn: loaded, not used
+        v4i f = fs[0];
+#pragma unroll 1
+        for (int k0 = 0; k0 < len; k0 += RING) {
+            const v4i* wn = k0 + RING < len ? wp + (k0 + RING) * 64 : wnext;
+#pragma unroll
+            for (int d = 0; d < RING; ++d) {
+                const v4i fn = fs[(k0 + d + 1) * SLAB];
+                acc = mfma32(f, ring[d], acc);
+                ring[d] = wn[d * 64];
+                f = fn;
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        if (split == 1) {
+            store(acc, m, bias);
+            nb += NW;
+        }
+        wp = wnext;
+    }
+    if (split > 1) {                                          // uniform over the grid
+        int* sums = (int*)frag + (wave / split * (split - 1) + (part ? part - 1 : 0)) * 1024 + lane;
+        __syncthreads();                                      // the operand fragments have been read
+        if (wave < units && part)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) sums[r * 64] = acc[r];
+        __syncthreads();
+        if (wave < units && part == 0) {
+            for (int t = 0; t < split - 1; ++t)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[r] += sums[t * 1024 + r * 64];
+            store(acc, A.m[nb * 32 + j], A.bias[nb * 32 + j]);
+        }
+    }
+}
+
+// a load of four floats that need not lie on a 16-byte boundary (rows of 3 W floats do not)
+typedef float f4_any __attribute__((ext_vector_type(4), aligned(4)));
+
+// Patch embedding of 4x4x3 patches into 32 NB channels (96 and 128: the widths of Swin's first stages).  One wave per 32
+// output tokens, nothing shared but the constants of the channels: lane = (token, half), a half holds two of the four patch
+// rows (24 inputs in six loads of 16 bytes; the weights are packed in that order: 16 + 8 codes of each half
+// and zeros), so the codes are MFMA operands where they were computed, and the 32 NB outputs of a token end in two lanes,
+// which makes the LayerNorm one binary64 sum in registers and one exchange.
+// Bound: memory, once the map is large (4 x 1024 x 1024 into 128: 47.8 us with a tile's codes and outputs through LDS and
+// three barriers, 31.8 us now, 5.8 TB/s with the image from the cache); at 800 x 1344 into 96 (15.0 -> 10.8 us) one chain of
+// waits per wave, two waves per SIMD.  The 128 registers of four waves per SIMD need the two barriers against hoisting below.
+template <int NB, bool TAPS>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void embed_kernel(DsArgs A)
+{
+    constexpr int N = NB * 32;
+    __shared__ float4 par[5][N / 4];                          // m, bias, gamma, beta, -zp * sum of the weights
+    const int tid = threadIdx.x, lane = tid & 63, j = lane & 31, g = lane >> 5;
+    const int tok = (blockIdx.x * 4 + (tid >> 6)) * 32 + j;
+    const bool valid = tok < A.tokens;
+    const int b = A.by_map(tok), rem = tok - b * A.by_map.d, pi = A.by_row(rem), pj = rem - pi * A.by_row.d;
+    float v[24];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int r = pi * 4 + g * 2 + h, c = pj * 4;
+        const bool inside = valid && r < A.H;
+        const bool whole = inside && c + 4 <= A.W;
+        const float* row = A.x + (inside ? (((size_t)b * A.H + r) * A.W + c) * 3 : 0);
+#pragma unroll
+        for (int t = 0; t < 3; ++t) {
+            const f4_any w = *(const f4_any*)((whole ? row : A.m) + t * 4);          // A.m: any 12 floats
+            v[h * 12 + t * 4 + 0] = w.x; v[h * 12 + t * 4 + 1] = w.y; v[h * 12 + t * 4 + 2] = w.z; v[h * 12 + t * 4 + 3] = w.w;
+        }
+        if (!__all(whole)) {                                  // a patch over the edge of the map: pixel by pixel, zeros beyond
+#pragma unroll
+            for (int t = 0; t < 12; ++t) v[h * 12 + t] = inside && c + t / 3 < A.W ? row[t] : 0.f;
+        }
+    }
+    v4i wf[NB][2];
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) wf[nb][ks] = A.Wp[(nb * 2 + ks) * 64 + lane];
+    for (int e = tid; e < 5 * (N / 4); e += 256) {
+        const int which = e / (N / 4), at = e - which * (N / 4);
+        const float* src = which == 0 ? A.m : which == 1 ? A.bias : which == 2 ? A.gamma : which == 3 ? A.beta : (const float*)A.negcorr;
+        par[which][at] = ((const float4*)src)[at];
+    }
+    v4i code[2] = {};
+#pragma unroll
+    for (int t = 0; t < 6; ++t) {
+        const int c = pack4(quant_code(v[t * 4 + 0], A.q), quant_code(v[t * 4 + 1], A.q), quant_code(v[t * 4 + 2], A.q), quant_code(v[t * 4 + 3], A.q));
+        code[t >> 2][t & 3] = c;
+        if (TAPS && A.tap_codes && valid) *(int*)(A.tap_codes + (size_t)tok * 48 + g * 24 + t * 4) = c;
+    }
+    __syncthreads();
+    float f[NB * 16];
+    Moments mo;
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+        __builtin_amdgcn_sched_barrier(0);                    // one block's constants and sums in registers at a time
         v16i acc;
 #pragma unroll
         for (int qd = 0; qd < 4; ++qd) {
-            const int4 t4 = *(const int4*)(A.negcorr + nb * 32 + qd * 8 + g * 4);
+            const int4 t4 = ((const int4*)par[4])[nb * 8 + qd * 2 + g];
             acc[qd * 4 + 0] = t4.x; acc[qd * 4 + 1] = t4.y; acc[qd * 4 + 2] = t4.z; acc[qd * 4 + 3] = t4.w;
         }
-#pragma unroll 1
-        for (int k0 = 0; k0 < KSN; k0 += RING) {
-#pragma unroll
-            for (int d = 0; d < RING; ++d) {
-                const v4i wv = ring[d];
-                ring[d] = wp[min(k0 + RING + d, KSN - 1) * 64];           // past the end: the last fragment again, unused
-                acc = mfma32(wv, frag[(k0 + d) * 64 + lane], acc);
-            }
-        }
+        acc = mfma32(wf[nb][0], code[0], acc);
+        acc = mfma32(wf[nb][1], code[1], acc);
 #pragma unroll
         for (int qd = 0; qd < 4; ++qd) {
-            const int n0 = nb * 32 + qd * 8 + g * 4;
-            const float4 m = *(const float4*)(A.m + n0), bs = *(const float4*)(A.bias + n0);
-            if (valid) {
-                *(float4*)(A.y + (size_t)tok * A.N + n0) =
-                    make_float4(fmaf((float)acc[qd * 4 + 0], m.x, bs.x), fmaf((float)acc[qd * 4 + 1], m.y, bs.y),
-                                fmaf((float)acc[qd * 4 + 2], m.z, bs.z), fmaf((float)acc[qd * 4 + 3], m.w, bs.w));
-                if (TAPS && A.tap_acc) *(int4*)(A.tap_acc + (size_t)tok * A.N + n0) = make_int4(acc[qd * 4], acc[qd * 4 + 1], acc[qd * 4 + 2], acc[qd * 4 + 3]);
-            }
+            const float4 m = par[0][nb * 8 + qd * 2 + g], bs = par[1][nb * 8 + qd * 2 + g];
+            float* o = f + nb * 16 + qd * 4;
+            o[0] = fmaf((float)acc[qd * 4 + 0], m.x, bs.x); o[1] = fmaf((float)acc[qd * 4 + 1], m.y, bs.y);
+            o[2] = fmaf((float)acc[qd * 4 + 2], m.z, bs.z); o[3] = fmaf((float)acc[qd * 4 + 3], m.w, bs.w);
+            moments_add(mo, o[0], o[1], o[2], o[3]);
+            if (TAPS && A.tap_acc && valid)
+                *(int4*)(A.tap_acc + (size_t)tok * N + nb * 32 + qd * 8 + g * 4) = make_int4(acc[qd * 4], acc[qd * 4 + 1], acc[qd * 4 + 2], acc[qd * 4 + 3]);
         }
+    }
+    const double s = half_sum(mo.s);
+    const float mean = moments_mean(s, N);
+    bool shaky;
+    double cs = moments_centred(s, half_sum(mo.q), mean, N, shaky);
+    if (__any(shaky)) {
+        double t = 0.0;
+#pragma unroll
+        for (int k = 0; k < NB * 4; ++k) t += centred_squares(f[k * 4], f[k * 4 + 1], f[k * 4 + 2], f[k * 4 + 3], mean);
+        cs = half_sum(t);
+    }
+    const float rstd = moments_rstd(cs, N, A.eps);
+    if (!valid) return;
+    float* out = A.y + (size_t)tok * N + g * 4;
+#pragma unroll
+    for (int k = 0; k < NB * 4; ++k) {
+        if (k % 4 == 0) __builtin_amdgcn_sched_barrier(0);
+        const float4 gm = par[2][k * 2 + g], bt = par[3][k * 2 + g];
+        *(float4*)(out + k * 8) = make_float4(fmaf((f[k * 4 + 0] - mean) * rstd, gm.x, bt.x), fmaf((f[k * 4 + 1] - mean) * rstd, gm.y, bt.y),
+                                              fmaf((f[k * 4 + 2] - mean) * rstd, gm.z, bt.z), fmaf((f[k * 4 + 3] - mean) * rstd, gm.w, bt.w));
     }
 }
 
@@ -298,6 +459,7 @@ __global__ __launch_bounds__(256) void downsample_kernel(DsArgs A)
 struct mixaq_downsample {
     mixaq_downsample_desc d;
     int P = 0, K = 0, Kp = 0, Ho = 0, Wo = 0;
+    FastDiv by_map, by_row;
     Arena mem;
     v4i* Wp = nullptr;
     float *m = nullptr, *bias = nullptr, *gamma = nullptr, *beta = nullptr;
@@ -328,6 +490,8 @@ int ds_geometry(const mixaq_downsample_desc* d, int* P, int* K, int* Ho, int* Wo
     return MIXAQ_OK;
 }
 
+bool embed_in_registers(const mixaq_downsample_desc& d) { return d.kind == 0 && d.patch == 4 && d.C_in == 3 && (d.N == 96 || d.N == 128); }
+
 size_t ds_lds_bytes(const mixaq_downsample* h) { return (size_t)h->Kp * 32 + (h->d.kind == 0 ? (size_t)32 * h->d.N * 4 : 0); }
 
 int ds_forward(const mixaq_downsample* h, const float* x, float* y, void* stream, int8_t* tap_codes, int32_t* tap_acc)
@@ -338,33 +502,42 @@ int ds_forward(const mixaq_downsample* h, const float* x, float* y, void* stream
     A.x = x; A.y = y;
     A.B = h->d.B; A.H = h->d.H; A.W = h->d.W; A.Cin = h->d.C_in; A.P = h->P; A.K = h->K; A.Kp = h->Kp; A.N = h->d.N;
     A.Ho = h->Ho; A.Wo = h->Wo; A.tokens = h->d.B * h->Ho * h->Wo;
+    A.by_map = h->by_map; A.by_row = h->by_row;
     A.Wp = h->Wp; A.m = h->m; A.bias = h->bias; A.negcorr = h->negcorr; A.gamma = h->gamma; A.beta = h->beta;
     A.q = h->q; A.eps = h->d.ln_eps; A.tap_codes = tap_codes; A.tap_acc = tap_acc;
     const dim3 grid((A.tokens + 31) / 32);
     const size_t lds = ds_lds_bytes(h);
     hipStream_t st = (hipStream_t)stream;
-    // patch merging of the usual widths: lanes per token and registers per lane from C_in; the output blocks are split
-    // into groups of at least four (one per wave) over more workgroups while the grid has fewer than about 512
-    int lpt = 0, nv = 0;
-    if (h->d.kind == 1) {
-        for (int n : {12, 16})
-            for (int l : {8, 16, 32})
-                if (!lpt && A.Cin == n * l) { lpt = l; nv = n; }
+    const bool taps = tap_codes || tap_acc;
+    // patch merging of the usual widths: the output blocks are split into groups while that leaves a CU of its own to each
+    // workgroup, XCD by XCD (every group repeats phase 1, so a second workgroup on a CU costs more than the shorter phase 2
+    // gives: 128 tiles of C_in = 96 in 2 groups 6.8 us, in 4 groups 9.2 us), and the slabs of a block over the waves that have
+    // no block of their own
+#define MERGE_CASE(L, V, NT)                                                                                          \
+    if (h->d.kind == 1 && A.Cin == L * V) {                                                                           \
+        const int NB = A.N / 32, tiles = (int)grid.x;                                                                 \
+        const int room = tiles < 8 ? MERGE_CUS / tiles : MERGE_CUS / 8 / ((tiles + 7) / 8);                           \
+        const int most = std::max(1, std::min(NB, room)), per = (NB + most - 1) / most, groups = (NB + per - 1) / per;  \
+        int split = 1;                                                                                                \
+        while (split < merge_max_split(L * V / 8) && per * split * 2 <= NT / 64) split *= 2;                          \
+        const int by_xcd = tiles >= 8 && groups > 1;                                                                  \
+        const dim3 grid2((by_xcd ? (tiles + 7) / 8 * 8 : tiles) * groups);                                            \
+        if (taps) hipLaunchKernelGGL((merge_kernel<L, V, NT, true>), grid2, dim3(NT), 0, st, A, by_xcd, groups, per, split); \
+        else hipLaunchKernelGGL((merge_kernel<L, V, NT, false>), grid2, dim3(NT), 0, st, A, by_xcd, groups, per, split);   \
+        HIP_TRY(hipGetLastError());                                                                                   \
+        return MIXAQ_OK;                                                                                              \
     }
-    if (lpt) {
-        const int NB = A.N / 32, tiles = (int)grid.x;
-        int groups = std::max(1, std::min(NB / 4, (512 + tiles - 1) / tiles));
-        const int per = ((NB + groups - 1) / groups + 3) / 4 * 4;
-        groups = (NB + per - 1) / per;
-        const dim3 grid2(tiles, groups);
-        const bool taps = tap_codes || tap_acc;
-#define MERGE_CASE(L, V)                                                                                          \
-    if (lpt == L && nv == V) {                                                                                    \
-        if (taps) hipLaunchKernelGGL((merge_kernel<L, V, true>), grid2, dim3(256), (size_t)A.Kp * 32, st, A, per);  \
-        else hipLaunchKernelGGL((merge_kernel<L, V, false>), grid2, dim3(256), (size_t)A.Kp * 32, st, A, per);     \
-    }
-        MERGE_CASE(8, 12) MERGE_CASE(16, 12) MERGE_CASE(32, 12) MERGE_CASE(8, 16) MERGE_CASE(16, 16) MERGE_CASE(32, 16)
+    MERGE_CASE(32, 3, 256) MERGE_CASE(32, 4, 256) MERGE_CASE(64, 3, 512) MERGE_CASE(64, 4, 512) MERGE_CASE(64, 6, 1024) MERGE_CASE(64, 8, 1024)
 #undef MERGE_CASE
+    if (embed_in_registers(h->d)) {
+        const dim3 grid4((A.tokens + 127) / 128);
+        if (A.N == 96) {
+            if (taps) hipLaunchKernelGGL((embed_kernel<3, true>), grid4, dim3(256), 0, st, A);
+            else hipLaunchKernelGGL((embed_kernel<3, false>), grid4, dim3(256), 0, st, A);
+        } else {
+            if (taps) hipLaunchKernelGGL((embed_kernel<4, true>), grid4, dim3(256), 0, st, A);
+            else hipLaunchKernelGGL((embed_kernel<4, false>), grid4, dim3(256), 0, st, A);
+        }
     } else if (h->d.kind == 0 && A.P == 4 && A.Cin == 3) hipLaunchKernelGGL((downsample_kernel<0, 4, 3>), grid, dim3(256), lds, st, A);
     else if (h->d.kind == 0) hipLaunchKernelGGL(downsample_kernel<0>, grid, dim3(256), lds, st, A);
     else hipLaunchKernelGGL(downsample_kernel<1>, grid, dim3(256), lds, st, A);
@@ -424,6 +597,7 @@ static int downsample_create(const mixaq_downsample_desc* desc, const mixaq_down
     LayerOwner owner{h};
     auto bail = [&](int code) { return code; };          // the owner frees the layer
     h->d = *desc; h->P = P; h->K = K; h->Kp = Kp; h->Ho = Ho; h->Wo = Wo;
+    h->by_map = FastDiv(Ho * Wo); h->by_row = FastDiv(Wo);
     std::vector<int8_t> w((size_t)N * K);
     std::vector<float> s(N), bias(N, 0.0f), ln_g(n_ln), ln_b(n_ln);
     if (hipMemcpy(w.data(), p->w, w.size(), hipMemcpyDeviceToHost) != hipSuccess ||
@@ -447,12 +621,14 @@ static int downsample_create(const mixaq_downsample_desc* desc, const mixaq_down
         nc[n] = (int)(-(long long)p->a_in.zero_point * cs);
     }
     const int NB = N / 32, KS = Kp / 32;
+    const bool halves = embed_in_registers(*desc);
     std::vector<int8_t> packed((size_t)N * Kp, 0);
     for (int nb = 0; nb < NB; ++nb)
         for (int ks = 0; ks < KS; ++ks)
             for (int lane = 0; lane < 64; ++lane)
                 for (int e = 0; e < 16; ++e) {
-                    const int k = ks * 32 + (lane / 32) * 16 + e;
+                    // of the halves: 16 k each per slab, or 24 each in all (embed_kernel)
+                    const int k = !halves ? ks * 32 + (lane / 32) * 16 + e : ks * 16 + e < K / 2 ? (lane / 32) * (K / 2) + ks * 16 + e : K;
                     if (k < K) packed[(((size_t)nb * KS + ks) * 64 + lane) * 16 + e] = w[(size_t)(nb * 32 + lane % 32) * K + k];
                 }
     h->mem.add(packed, &h->Wp);

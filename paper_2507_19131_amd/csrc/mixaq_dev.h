@@ -208,8 +208,11 @@ __device__ __forceinline__ double moments_centred(double s, double q, float mean
     shaky = v * 64.0 < q;
     return v;
 }
+// (the second pass of shaky tokens; its inputs are made opaque, or the compiler keeps their conversions to binary64 from the
+// first pass in registers for it: twice the token, in spills)
 __device__ __forceinline__ double centred_squares(float x0, float x1, float x2, float x3, float mean)
 {
+    asm("" : "+v"(x0), "+v"(x1), "+v"(x2), "+v"(x3));
     const double a = (double)x0 - (double)mean, b = (double)x1 - (double)mean;
     const double c = (double)x2 - (double)mean, d = (double)x3 - (double)mean;
     return (a * a + b * b) + (c * c + d * d);
@@ -225,6 +228,20 @@ __device__ __forceinline__ v16i mfma32(v4i a, v4i b, v16i c)
 }
 // row of the 32x32 result held in register r by a lane of half g
 __device__ __forceinline__ int mfma_row(int r, int g) { return (r >> 2) * 8 + g * 4 + (r & 3); }
+
+// n / d for 0 <= n < 2^31 and a divisor the host knows: a high product, an add and a shift in place of the some twenty-five
+// instructions of a division
+struct FastDiv {
+    unsigned mul = 0, shift = 0;
+    int d = 1;
+    FastDiv() = default;
+    explicit FastDiv(int divisor) : d(divisor)
+    {
+        while ((1u << shift) < (unsigned)divisor) ++shift;
+        mul = (unsigned)(((1ull << 32) * ((1ull << shift) - (unsigned)divisor)) / (unsigned)divisor + 1);
+    }
+    __device__ __forceinline__ int operator()(int n) const { return (int)((__umulhi(mul, (unsigned)n) + (unsigned)n) >> shift); }
+};
 
 // Geometry of one forward call.  Rows of the gathered activation matrices: the
 // high group of all images first (slot = b*k_hi + j), padded to a multiple of
