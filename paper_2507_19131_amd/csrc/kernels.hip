@@ -784,7 +784,11 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
     constexpr int C = NHT * 32, KS = NHT, LPT = WinCfg<NH, HG, QS>::LPT, NV = CODES ? 1 : WinCfg<NH, HG, QS>::NV, NT = NW * 64;
     constexpr int GPW = WinCfg<NH, HG, QS>::GPW;
     using PR = WinPrm<C, NH, CODES>;
-    const int widx = HG == 1 ? blockIdx.x : blockIdx.x / HG, hg = HG == 1 ? 0 : blockIdx.x % HG;
+    // the workgroups of a window on one XCD, whose L2 then reads the window once (1444 windows at C = 256: 339 -> 335 us the
+    // pair); with CODES, one after another
+    const int widx = HG == 1 ? blockIdx.x : CODES ? blockIdx.x / HG : blockIdx.x / (8 * HG) * 8 + blockIdx.x % 8;
+    const int hg = HG == 1 ? 0 : CODES ? blockIdx.x % HG : blockIdx.x / 8 % HG;
+    if (HG > 1 && !CODES && widx >= G.B * G.nW) return;
     static_assert(CODES || NW * GPW >= TOK, "one pass must cover the window");
     __shared__ v4i a1s[2 * KS * 64];                                     // LN1 codes as fragments [token block][k slab][lane]
     __shared__ __attribute__((aligned(16))) float prm[PR::WORDS];        // this branch's LN1 affine and QKV epilogue constants
@@ -1658,15 +1662,17 @@ void launch_gemm(const Geom& G, const GemmArgs& A, int epi, hipStream_t st)
 bool fused_window_supported(int C) { return channels_supported(C); }
 bool fused_token_supported(int C, int mlp_ratio) { return (C == 96 || C == 128 || C == 192 || C == 256 || C == 384) && mlp_ratio == 4; }
 
-// C = 384: up to this many windows, two workgroups share a window's heads, each with a pair of waves per head (twelve
-// waves: 15.7 instead of 16.8 us on 96 windows with one wave per head, and 22.8 us for one twelve-head workgroup per window)
-constexpr int WINDOW_SPLIT_SMALL = 128;
 // Up to this many windows a pair of waves shares a head.  The pair form has the shorter chain of dependent steps
 // (a workgroup alone on its CU: 9.5 instead of 11.2 us at C = 96) but 15 % more vector and 80 % more scalar
 // instructions per window, so it loses once the CUs are full (1392 windows at C = 96: 31 instead of 28.3 us;
-// 5476 at C = 128: 113 instead of 101 us).  At C = 192 it wins on 360 windows (22.8 instead of 25.4 us); at
-// C = 256 it measures the same on 1444 windows and is not instantiated.
+// 5476 at C = 128: 113 instead of 101 us).  At C = 192 it wins on 360 windows (22.8 instead of 25.4 us).
 constexpr int WINDOW_PAIR_SMALL = 256, WINDOW_PAIR_SMALL_6 = 512;
+// Up to this many windows two workgroups share a window's heads (each gathers and normalizes the whole window): a wave then has
+// fewer neighbours on its SIMD.  The pair of blocks on 96 windows: 41.4 -> 40.5 us at C = 128, 51.9 -> 48.5 us at C = 192
+// (130 windows: 54.5 -> 56.4), at C = 384 15.7 instead of 16.8 us a kernel.  C = 256 always: sixteen waves
+// of one workgroup, or eight of twice the registers, leave a CU half empty, three workgroups of eight fill it (6 windows:
+// 62.8 -> 51.4 us the pair, 300: 106 -> 95, 1444: 351 -> 335, 2750: 680 -> 654).
+constexpr int WINDOW_SPLIT_SMALL = 96, WINDOW_SPLIT_SMALL_12 = 128;
 void launch_window(const Geom& G, const WinArgs& A, hipStream_t st)
 {
     // every window gets a workgroup: with scores it finds its own rank (and may turn out pruned), otherwise
@@ -1693,7 +1699,7 @@ void launch_window(const Geom& G, const WinArgs& A, hipStream_t st)
 #undef WIDE_CASE
 #define WIN_CASE(NH, HG, QS)                                                                                              \
     {                                                                                                                     \
-        const dim3 grid(n_wg * HG), block(NH * QS * 64);                                                                  \
+        const dim3 grid(HG > 1 ? (n_wg + 7) / 8 * 8 * HG : n_wg), block(NH * QS * 64);                                     \
         if (A.scores) {   /* no entry point takes scores and taps together */                                            \
             hipLaunchKernelGGL((window_kernel<NH, false, true, HG, QS>), grid, block, 0, st, G, A);                       \
         } else {                                                                                                          \
@@ -1707,14 +1713,16 @@ void launch_window(const Geom& G, const WinArgs& A, hipStream_t st)
             if (n_wg <= WINDOW_PAIR_SMALL) { WIN_CASE(3, 1, 2); }
             WIN_CASE(3, 1, 1);
         case 4:
+            if (n_wg <= WINDOW_SPLIT_SMALL) { WIN_CASE(2, 2, 2); }
             if (n_wg <= WINDOW_PAIR_SMALL) { WIN_CASE(4, 1, 2); }
             WIN_CASE(4, 1, 1);
         case 6:
+            if (n_wg <= WINDOW_SPLIT_SMALL) { WIN_CASE(3, 2, 2); }
             if (n_wg <= WINDOW_PAIR_SMALL_6) { WIN_CASE(6, 1, 2); }
             WIN_CASE(6, 1, 1);
-        case 8: WIN_CASE(8, 1, 1);
+        case 8: WIN_CASE(4, 2, 2);
         case 12:
-            if (n_wg <= WINDOW_SPLIT_SMALL) { WIN_CASE(6, 2, 2); }
+            if (n_wg <= WINDOW_SPLIT_SMALL_12) { WIN_CASE(6, 2, 2); }
             WIN_CASE(12, 1, 1);
         default: break;
     }
