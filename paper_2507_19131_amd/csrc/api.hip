@@ -245,6 +245,14 @@ int check_qparam(const mixaq_qparam& q, int bits, const char* name)
 // with at most this many windows in all, on the fused kernels (config 3, 2 x 96 windows at C = 384: 0.36 instead of
 // 0.41 ms per stage pass; 2 x 1392 windows at C = 96: 10 % faster; 4 x 1392: 4 %, no longer taken).
 constexpr int STAGE_SPLIT_MAX_WINDOWS = 4096;
+// Fork and join cost 25 to 30 us, so the stage has to be long enough: from about 2000 windows over all its blocks on (at
+// C = 96, whose kernels are shorter, 2667).  Two blocks on 112 windows: 76 us as two chains, 53 as one at C = 192; six blocks
+// on 240 windows at C = 384: 388 and 364; on 504: 633 and 711; two blocks on 1008 windows at C = 192: 178 and 191.
+constexpr long long STAGE_SPLIT_MIN_WORK = 2000LL * 128;
+bool stage_split_pays(const mixaq_block* b, int n_blocks)
+{
+    return (long long)n_blocks * b->d.B * b->nW * std::min(b->d.C, 128) >= STAGE_SPLIT_MIN_WORK;
+}
 bool stage_splits(const mixaq_block* b)
 {
     return b->d.B >= 2 && b->d.B * b->nW <= STAGE_SPLIT_MAX_WINDOWS && b->fused_window && b->fused_token;
@@ -749,7 +757,7 @@ int mixaq_stage_forward(mixaq_block* const* blocks, int32_t n_blocks, const floa
     }
     int rc = mixaq_score_windows(blocks[0], x, scores, stream);
     if (rc) return rc;
-    // A batch of small maps (stage_splits) runs as two chains of blocks, one per half of the images, the second on the
+    // A batch of small maps (stage_splits, stage_split_pays) runs as two chains of blocks, one per half of the images, the second on the
     // first block's side stream: the images are independent through the whole stage, every kernel of such a map leaves
     // CUs idle, and the window kernel of one half runs beside the token kernel of the other.  Not under stream capture.
     hipStream_t st = (hipStream_t)stream;
@@ -757,7 +765,7 @@ int mixaq_stage_forward(mixaq_block* const* blocks, int32_t n_blocks, const floa
     Part parts[2];
     int n_parts = 1;
     hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
-    bool split = n_blocks > 1 && b0->side_stream != nullptr;
+    bool split = n_blocks > 1 && b0->side_stream != nullptr && stage_split_pays(b0, n_blocks);
     for (int i = 0; split && i < n_blocks; ++i) split = blocks[i]->fused_window && blocks[i]->fused_token;
     if (split) {
         if (hipStreamIsCapturing(st, &capturing) != hipSuccess) {
