@@ -1130,7 +1130,7 @@ __global__ __launch_bounds__(NH * 64) __attribute__((amdgpu_waves_per_eu(tok_wav
         const v4i* w1 = A.W1 + (size_t)wave * KS * 64 + lane;
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
-            aof[ks] = pack ? unpack_codes(pp, pack, ks, g) : *(const v4i*)(ap + ks * 32);
+            aof[ks] = pack ? expand_codes(packed_codes(pp, pack, ks, g), pack, g) : *(const v4i*)(ap + ks * 32);
             wpf[ks] = wp[ks * 64];
             if (EARLY_W1) w1f[ks] = w1[ks * 64];
         }
@@ -1294,7 +1294,7 @@ __global__ __launch_bounds__(NH * 64) __attribute__((amdgpu_waves_per_eu(tok_wav
 // every weight fragment, which divides the L2 -> CU weight traffic per row by RB), one wave per 32-channel block.
 // Built for a small register footprint: the per-branch parameter block sits in LDS, the weight fragments of the whole kernel form ONE stream
 // per wave (projection block, then per chunk the FC1 block and the FC2 fragments) that is requested RING
-// fragments ahead across every phase boundary, and with twelve waves h is parked in the output map between the
+// fragments ahead across every phase boundary, and with two row blocks h is parked in the output map between the
 // first and the second residual (the same thread writes and re-reads the same address) instead of in registers.
 // The FFN runs in four chunks of NH hidden blocks: FC1 + GELU + quantize of a chunk goes to one of two LDS buffers,
 // then FC2 accumulates that chunk.
@@ -1302,8 +1302,8 @@ template <int NH, int RB, bool TAPS>
 __global__ __launch_bounds__(NH * 64) void token_wide_kernel(Geom G, TokArgs A)
 {
     constexpr int C = NH * 32, KS = NH, HB = 4 * NH, F = 4 * C, NT = NH * 64;
-    constexpr int RING = NH == 6 ? 6 : 8;                              // fragments in flight per wave
-    constexpr bool PARK_H = (NH >= 12 || RB >= 4) && !TAPS;          // taps need h of padded tokens too, which have no pixel
+    constexpr int RING = NH == 6 ? 6 : RB == 1 ? 12 : 8;               // fragments in flight per wave
+    constexpr bool PARK_H = RB >= 2 && !TAPS;                         // taps need h of padded tokens too, which have no pixel
     static_assert((2 * KS) % RING == 0 && RING <= KS, "phases 2k start at ring slot 0, phases 2k+1 at slot KS % RING");
     constexpr int SLOT_ODD = KS % RING;
     using PR = TokPrm<C>;
@@ -1319,14 +1319,12 @@ __global__ __launch_bounds__(NH * 64) void token_wide_kernel(Geom G, TokArgs A)
     const int* prmi = (const int*)prm;
     // The wave's weight stream, phase by phase (every phase has KS = NH fragments): projection block, FC1 block of
     // chunk 0, then per chunk c = 1..3 the FC1 block of chunk c followed by the FC2 fragments of chunk c-1, and the
-    // FC2 fragments of chunk 3 at the end.  FC2 of a chunk is issued one chunk late so that its matrix work runs
-    // under the GELU arithmetic of the next chunk.
+    // FC2 fragments of chunk 3 at the end.  FC2 of a chunk is issued one chunk late, with the GELU arithmetic of the next chunk
+    // between its steps: the weights then arrive (64 bytes per clock and CU bound this kernel at C = 384) while it runs
+    // (C = 384, 32-row tiles 24.0 -> 23.4 us, 64-row tiles 39.5 -> 38.6; C = 192 26.1 -> 25.5).
     const v4i* wproj = A.Wproj + (size_t)nb * KS * 64 + lane;
     auto w1_of = [&](int chunk) { return A.W1 + ((size_t)(chunk * NH + wave) * KS) * 64 + lane; };
     auto w2_of = [&](int chunk) { return A.W2 + ((size_t)nb * HB + chunk * NH) * 64 + lane; };
-    v4i ring[RING];
-#pragma unroll
-    for (int d = 0; d < RING; ++d) ring[d] = wproj[d * 64];            // the stream starts before anything else
     int pix[RB];
     bool valid[RB];
     size_t canon[RB];
@@ -1334,7 +1332,7 @@ __global__ __launch_bounds__(NH * 64) void token_wide_kernel(Geom G, TokArgs A)
     for (int rb = 0; rb < RB; ++rb) {
         const int row = row_base + rb * 32 + j;
         valid[rb] = branch ? (row - G.base_lo < G.rows_lo) : (row < G.rows_hi);
-        pix[rb] = valid[rb] ? A.row_pix[row] : -1;
+        pix[rb] = A.row_pix[row];
         canon[rb] = (TAPS && valid[rb]) ? (size_t)A.row_canon[row] : 0;
     }
     // Staging: the attention codes of the tile as operand fragments, the parameter block and the GELU table.  What is a plain
@@ -1345,25 +1343,34 @@ __global__ __launch_bounds__(NH * 64) void token_wide_kernel(Geom G, TokArgs A)
         __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src, (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
     };
     const int pack = branch ? A.ao_pack : 0;                           // packed low-branch codes: scalar per tile
-    v4i pc[RB];
-    if (pack) {
+    int2 pc[RB];
+    if (!pack) {
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb)                                // fragment (rb, slab = wave), lane (half g, row j)
-            pc[rb] = unpack_codes(A.ao + (size_t)G.base_lo * C + (size_t)(row_base - G.base_lo + rb * 32 + j) * (C >> pack), pack, wave, g);
-    } else {
-#pragma unroll
-        for (int rb = 0; rb < RB; ++rb)
             to_lds(A.ao + (size_t)(row_base + rb * 32 + j) * C + swave * 32 + g * 16, actf + (rb * KS + swave) * 64);
     }
-    for (int p = swave; p < PR::WORDS / 256; p += NH) to_lds(A.params[branch] + p * 256 + lane * 4, prm + p * 256);
+    if (pack) {
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb)
+            pc[rb] = packed_codes(A.ao + (size_t)G.base_lo * C + (size_t)(row_base - G.base_lo + rb * 32 + j) * (C >> pack), pack, wave, g);
+    }
+#pragma unroll
+    for (int p0 = 0; p0 < PR::WORDS / 256; p0 += NH)                   // unrolled: the number of loads behind another one is known
+        if (p0 + NH <= PR::WORDS / 256 || p0 + swave < PR::WORDS / 256)
+            to_lds(A.params[branch] + (p0 + swave) * 256 + lane * 4, prm + (p0 + swave) * 256);
     if (PR::WORDS % 256 && tid < PR::WORDS % 256 / 4) ((float4*)prm)[PR::WORDS / 256 * 64 + tid] = ((const float4*)A.params[branch])[PR::WORDS / 256 * 64 + tid];
     if (swave >= NH - 2) to_lds(A.gelu_tab + (swave - (NH - 2)) * 64 + lane, gtab + (swave - (NH - 2)) * 64);
+    asm volatile("" ::: "memory");                                     // the weight stream is requested behind them
+    v4i ring[RING];
+#pragma unroll
+    for (int d = 0; d < RING; ++d) ring[d] = wproj[d * 64];
+    asm volatile("" ::: "memory");
     // acc[rb] += W * operand^T over one phase.  Weights come from the ring (SLOT0 = ring slot of the phase's first
     // fragment); after fragment i is used, the fragment RING places further down the stream is requested into its slot: from
     // this phase (cur) or from the start of the next one (nxt; LAST: the end of the stream).  Operand fragment i of row
     // block rb: b[(rb*rb_stride + i*i_stride)*64 + lane], read PF steps ahead.  The steps keep their order (product, request,
     // LDS read): see gemm_tile_kernel.
-    auto run = [&](auto SLOT0, auto LAST, const v4i* cur, const v4i* nxt, const v4i* b, int rb_stride, int i_stride, v16i* acc) {
+    auto run = [&](auto SLOT0, auto LAST, const v4i* cur, const v4i* nxt, const v4i* b, int rb_stride, int i_stride, v16i* acc, auto between) {
         constexpr int PF = 2;
         v4i bq[PF][RB];
         auto operand = [&](int i) {
@@ -1380,12 +1387,14 @@ __global__ __launch_bounds__(NH * 64) void token_wide_kernel(Geom G, TokArgs A)
             if (i + RING < KS) ring[(S0 + i) % RING] = cur[(i + RING) * 64];
             else if (!decltype(LAST)::value) ring[(S0 + i) % RING] = nxt[(i + RING - KS) * 64];
             if (i + PF < KS) operand(i + PF);
+            between(i);
             __builtin_amdgcn_sched_barrier(0);
         }
     };
     using Even = std::integral_constant<int, 0>;
     using Odd = std::integral_constant<int, SLOT_ODD>;
     using More = std::false_type;
+    auto nothing = [](int) {};
     auto start = [&](v16i* acc, int off) {                             // accumulators start at -zp * colsum
 #pragma unroll
         for (int qd = 0; qd < 4; ++qd) {
@@ -1395,23 +1404,30 @@ __global__ __launch_bounds__(NH * 64) void token_wide_kernel(Geom G, TokArgs A)
 #pragma unroll
         for (int rb = 1; rb < RB; ++rb) acc[rb] = acc[0];
     };
-    float4 sc[RB][4];                                                  // shortcut of the first residual, in flight during the projection
-#pragma unroll
-    for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-        for (int qd = 0; qd < 4; ++qd)
-            sc[rb][qd] = pix[rb] >= 0 ? *(const float4*)(A.x + (size_t)pix[rb] * C + nb * 32 + qd * 8 + g * 4) : make_float4(0.f, 0.f, 0.f, 0.f);
     if (pack) {
 #pragma unroll
-        for (int rb = 0; rb < RB; ++rb) actf[(rb * KS + wave) * 64 + lane] = pc[rb];
+        for (int rb = 0; rb < RB; ++rb) actf[(rb * KS + wave) * 64 + lane] = expand_codes(pc[rb], pack, g);
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                   // the direct loads have landed
     __syncthreads();                                                  // staged codes, parameters and table visible
+    // Shortcut of the first residual, in flight during the projection (requested before the barrier, its loads waited for the
+    // pixel index behind the whole ring, one more round trip: C = 384, 96 windows, a pair of blocks 80.8 -> 76.2 us, with h no
+    // longer parked on 32-row tiles).  Rows without a pixel are not stored: any values do, except for taps.
+    float4 sc[RB][4];
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+        pix[rb] = valid[rb] ? pix[rb] : -1;
+#pragma unroll
+        for (int qd = 0; qd < 4; ++qd) {
+            const float4 v = *(const float4*)(A.x + (size_t)max(pix[rb], 0) * C + nb * 32 + qd * 8 + g * 4);
+            sc[rb][qd] = !TAPS || pix[rb] >= 0 ? v : make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+    }
     float h[RB][16];
     {   // output projection + first residual
         v16i acc[RB];
         start(acc, PR::P_NC + nb * 32);
-        run(Even(), More(), wproj, w1_of(0), actf, KS, 1, acc);
+        run(Even(), More(), wproj, w1_of(0), actf, KS, 1, acc, nothing);
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
@@ -1494,45 +1510,48 @@ __global__ __launch_bounds__(NH * 64) void token_wide_kernel(Geom G, TokArgs A)
     v16i acc2[RB];
     start(acc2, PR::F2_NC + nb * 32);
     const QDev qg = A.q_fc2in[branch];
-    // GELU + quantize of the FC1 sums of hidden block ch*NH + wave -> LDS buffer ch & 1
-    auto gelu_chunk = [&](int ch, const v16i* acc) {
-        const int hb = ch * NH + wave;
-#pragma unroll
-        for (int rb = 0; rb < RB; ++rb) {
-            int wd[4];
-#pragma unroll
-            for (int qd = 0; qd < 4; ++qd) {
-                const int n0 = hb * 32 + qd * 8 + g * 4;
-                const float4 m = *(const float4*)(prm + PR::F1_M + n0), bs = *(const float4*)(prm + PR::F1_B + n0);
-                wd[qd] = pack4(quant_code(gelu_scaled(fmaf((float)acc[rb][qd * 4 + 0], m.x, bs.x), gtab), qg),
-                               quant_code(gelu_scaled(fmaf((float)acc[rb][qd * 4 + 1], m.y, bs.y), gtab), qg),
-                               quant_code(gelu_scaled(fmaf((float)acc[rb][qd * 4 + 2], m.z, bs.z), gtab), qg),
-                               quant_code(gelu_scaled(fmaf((float)acc[rb][qd * 4 + 3], m.w, bs.w), gtab), qg));
-                if (TAPS && valid[rb]) {
-                    if (A.tap_acc_fc1) *(int4*)(A.tap_acc_fc1 + canon[rb] * F + n0) = make_int4(acc[rb][qd * 4], acc[rb][qd * 4 + 1], acc[rb][qd * 4 + 2], acc[rb][qd * 4 + 3]);
-                    if (A.tap_g) *(int*)(A.tap_g + canon[rb] * F + n0) = wd[qd];
-                }
-            }
-            gs[ch & 1][(wave * RB + rb) * 64 + lane] = (v4i){wd[0], wd[1], wd[2], wd[3]};
+    // GELU + quantize of four of the FC1 sums of hidden block ch*NH + wave, and the block's codes -> LDS buffer ch & 1
+    int wd[RB][4];
+    auto gelu_part = [&](int ch, int rb, int qd, const v16i* acc) {
+        const int n0 = (ch * NH + wave) * 32 + qd * 8 + g * 4;
+        const float4 m = *(const float4*)(prm + PR::F1_M + n0), bs = *(const float4*)(prm + PR::F1_B + n0);
+        wd[rb][qd] = pack4(quant_code(gelu_scaled(fmaf((float)acc[rb][qd * 4 + 0], m.x, bs.x), gtab), qg),
+                           quant_code(gelu_scaled(fmaf((float)acc[rb][qd * 4 + 1], m.y, bs.y), gtab), qg),
+                           quant_code(gelu_scaled(fmaf((float)acc[rb][qd * 4 + 2], m.z, bs.z), gtab), qg),
+                           quant_code(gelu_scaled(fmaf((float)acc[rb][qd * 4 + 3], m.w, bs.w), gtab), qg));
+        if (TAPS && valid[rb]) {
+            if (A.tap_acc_fc1) *(int4*)(A.tap_acc_fc1 + canon[rb] * F + n0) = make_int4(acc[rb][qd * 4], acc[rb][qd * 4 + 1], acc[rb][qd * 4 + 2], acc[rb][qd * 4 + 3]);
+            if (A.tap_g) *(int*)(A.tap_g + canon[rb] * F + n0) = wd[rb][qd];
         }
+    };
+    auto gelu_store = [&](int ch) {
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) gs[ch & 1][(wave * RB + rb) * 64 + lane] = (v4i){wd[rb][0], wd[rb][1], wd[rb][2], wd[rb][3]};
     };
     {   // chunk 0: FC1 + GELU
         v16i acc[RB];
         start(acc, PR::F1_NC + wave * 32);
-        run(Odd(), More(), w1_of(0), w1_of(1), actf, KS, 1, acc);
-        gelu_chunk(0, acc);
+        run(Odd(), More(), w1_of(0), w1_of(1), actf, KS, 1, acc, nothing);
+#pragma unroll
+        for (int u = 0; u < 4 * RB; ++u) gelu_part(0, u / 4, u % 4, acc);
+        gelu_store(0);
     }
     __syncthreads();                                                  // chunk 0 of the hidden codes complete
 #pragma unroll 1
     for (int ch = 1; ch < 4; ++ch) {
         v16i acc[RB];
         start(acc, PR::F1_NC + (ch * NH + wave) * 32);
-        run(Even(), More(), w1_of(ch), w2_of(ch - 1), actf, KS, 1, acc);                                   // FC1 of chunk ch
-        run(Odd(), More(), w2_of(ch - 1), ch < 3 ? w1_of(ch + 1) : w2_of(3), gs[(ch - 1) & 1], 1, RB, acc2);   // FC2 of chunk ch-1, under ...
-        gelu_chunk(ch, acc);                                                                  // ... this arithmetic
+        run(Even(), More(), w1_of(ch), w2_of(ch - 1), actf, KS, 1, acc, nothing);                          // FC1 of chunk ch
+        run(Odd(), More(), w2_of(ch - 1), ch < 3 ? w1_of(ch + 1) : w2_of(3), gs[(ch - 1) & 1], 1, RB, acc2,   // FC2 of chunk ch-1, and
+            [&](int i) {                                                                      // between its steps ...
+#pragma unroll
+                for (int u = 0; u < 4 * RB; ++u)
+                    if ((u + 1) * KS / (4 * RB) - 1 == i) gelu_part(ch, u / 4, u % 4, acc);   // ... GELU of chunk ch
+            });
+        gelu_store(ch);
         __syncthreads();                                              // chunk ch complete, chunk ch-1 no longer read
     }
-    run(Even(), std::true_type(), w2_of(3), nullptr, gs[1], 1, RB, acc2);                     // FC2 of the last chunk
+    run(Even(), std::true_type(), w2_of(3), nullptr, gs[1], 1, RB, acc2, nothing);                     // FC2 of the last chunk
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb)
 #pragma unroll

@@ -128,14 +128,15 @@ __device__ __forceinline__ size_t frag_offset_reg(int row, int ch, int slabs)
     return (((size_t)(row >> 5) * slabs + (ch >> 5)) * 64 + ((ch >> 2) & 1) * 32 + (row & 31)) * 16 + ((ch & 31) >> 3) * 4 + (ch & 3);
 }
 
-// the 16 codes (offset-binary, one per byte, in channel order) of channels 32*ks + 16*half .. +15 of one packed row
-__device__ __forceinline__ v4i unpack_codes(const int8_t* packed_row, int mode, int ks, int half)
+// the 16 codes (offset-binary, one per byte, in channel order) of channels 32*ks + 16*half .. +15 of one packed row: the eight
+// bytes that hold them, and the codes (apart, so that the load can be in flight)
+__device__ __forceinline__ int2 packed_codes(const int8_t* packed_row, int mode, int ks, int half)
 {
-    if (mode == 1) {
-        const int2 w = *(const int2*)(packed_row + ks * 16 + half * 8);
-        return (v4i){w.x & 0x0f0f0f0f, w.y & 0x0f0f0f0f, (w.x >> 4) & 0x0f0f0f0f, (w.y >> 4) & 0x0f0f0f0f};
-    }
-    const int2 w = *(const int2*)(packed_row + ks * 8);
+    return *(const int2*)(packed_row + (mode == 1 ? ks * 16 + half * 8 : ks * 8));
+}
+__device__ __forceinline__ v4i expand_codes(int2 w, int mode, int half)
+{
+    if (mode == 1) return (v4i){w.x & 0x0f0f0f0f, w.y & 0x0f0f0f0f, (w.x >> 4) & 0x0f0f0f0f, (w.y >> 4) & 0x0f0f0f0f};
     const int s = half * 4;
     return (v4i){(w.x >> s) & 0x03030303, (w.y >> s) & 0x03030303, (w.x >> (s + 2)) & 0x03030303, (w.y >> (s + 2)) & 0x03030303};
 }
