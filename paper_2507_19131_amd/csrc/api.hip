@@ -632,7 +632,7 @@ static int block_create(const mixaq_block_desc* desc, const mixaq_shared_params*
     if (b->fused_window && b->fused_token) b->ao_pack = pack_mode(desc->act_bits_low);
     if (b->fused_token) {     // parameter blocks of the token kernel
         for (int br = 0; br < 2; ++br) {
-            std::vector<float> blkp((size_t)8 * C + 3 * F);
+            std::vector<float> blkp(((size_t)8 * C + 3 * F + 255) / 256 * 256, 0.0f);      // whole 1 KB pieces: see token_stage
             struct { const void* src; int n; } parts[11] = {
                 {b->proj.hm[br].data(), C}, {b->proj.hb[br].data(), C}, {b->proj.hnc[br].data(), C}, {hln[br][2].data(), C},
                 {hln[br][3].data(), C}, {b->fc2.hm[br].data(), C}, {b->fc2.hb[br].data(), C}, {b->fc2.hnc[br].data(), C},

@@ -1074,235 +1074,49 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
 }
 
 // ------------------------------------------------------------------ fused token kernel
-// One workgroup per tile of 32 gathered rows, one wave per 32-channel block (NH = C/32 = 3, 4 or 8 waves; six and
-// twelve waves run the wide form below):
-//   proj + first residual (wave w owns channels 32w..32w+31, h stays in registers) -> LN2 with
-//   statistics exchanged through LDS -> quantize -> FC1 (each wave 4 hidden blocks) + GELU +
-//   quantize, codes to LDS as fragments -> FC2 + second residual -> scatter to the map.
-// Latency is hidden by issuing loads a phase ahead: the per-branch parameter block (epilogue
-// constants, LN2 affine) is staged in LDS once, weight fragments of the next MFMA chain are
-// requested before the current epilogue starts.
-// waves per SIMD the token kernel is compiled for: two workgroups per CU with eight waves each, four and five with
-// four and three waves; measured: one more resident workgroup at eight waves takes the kernel from 122 to 96 us
-// on 70756 rows, five waves per SIMD at three waves per workgroup gain nothing
-constexpr int tok_waves_per_eu(int) { return 4; }
+// One workgroup per tile of 32*RB gathered rows (RB 32-row blocks share every weight fragment), one wave per 32-channel
+// block (NH = C/32 = 3, 4, 6, 8 or 12 waves):
+//   proj + first residual (wave w owns channels 32w..32w+31) -> LN2 with statistics exchanged through LDS -> quantize -> FC1 +
+//   GELU + quantize, codes to LDS as fragments -> FC2 + second residual -> scatter to the map.
+// The weight fragments of the whole kernel form ONE stream per wave that is requested RING fragments ahead across every phase
+// boundary; the per-branch parameter block and the GELU table sit in LDS.  The FFN runs in four chunks of NH hidden blocks: FC1 +
+// GELU + quantize of a chunk goes to one of two LDS buffers, then FC2 accumulates that chunk.  With two row blocks h is parked in
+// the output map between the first and the second residual (the same thread writes and re-reads the same address).
+// Bound: vector instructions (GELU) at C = 96 and 128 on large maps, the weights at 64 bytes per clock and CU at C = 384, the
+// chain of phases on few tiles.  Against a form with the chunks unrolled and FC1's weights a block ahead, which the three, four
+// and eight waves had: stage of two blocks on 8 x 1392 windows at C = 96 715 -> 692 us, 5476 at C = 128 456 -> 442, 1444 at
+// C = 256 342 -> 331; 64 windows at C = 256 58.9 -> 52.7.
+// Waves per SIMD it is compiled for: 128 registers take it all without spills up to eight waves (three, four and eight waves
+// want up to 124 by themselves; at five waves per SIMD the spills at C = 96 cost more than the fifth wave gives), twelve need 160 and have a CU to themselves.
+constexpr int tok_waves_per_eu(int NH) { return NH == 12 ? 3 : 4; }
 // word offsets inside the parameter block of one branch (see TokArgs::params)
 template <int C> struct TokPrm {
     static constexpr int F = 4 * C;
     static constexpr int P_M = 0, P_B = C, P_NC = 2 * C, LN_G = 3 * C, LN_B = 4 * C, F2_M = 5 * C, F2_B = 6 * C,
-                         F2_NC = 7 * C, F1_M = 8 * C, F1_B = 8 * C + F, F1_NC = 8 * C + 2 * F, WORDS = 8 * C + 3 * F;
+                         F2_NC = 7 * C, F1_M = 8 * C, F1_B = 8 * C + F, F1_NC = 8 * C + 2 * F, WORDS = (8 * C + 3 * F + 255) / 256 * 256;   // whole 1 KB pieces
 };
 
-template <int NH, bool TAPS>
-__global__ __launch_bounds__(NH * 64) __attribute__((amdgpu_waves_per_eu(tok_waves_per_eu(NH), tok_waves_per_eu(NH)))) void token_kernel(Geom G, TokArgs A)
+// 64 lanes x 16 bytes from memory straight into LDS (src per lane, dst the wave's 1 KB)
+__device__ __forceinline__ void to_lds(const void* src, void* dst)
 {
-    constexpr int C = NH * 32, KS = NH, HB = 4 * NH, F = 4 * C, NT = NH * 64;
-    using PR = TokPrm<C>;
-    constexpr int PV = PR::WORDS / 4, PVT = (PV + NT - 1) / NT;       // float4 of the block, per thread
-    constexpr int D2 = 4;                                            // FC2 weight fragments in flight
-    constexpr bool EARLY_W1 = NH <= 4;                               // first FC1 weights requested at entry (register room permitting)
-    __shared__ v4i a2s[KS * 64];
-    __shared__ v4i gs[HB * 64];
-    __shared__ double part[2][NH][32];
-    __shared__ __attribute__((aligned(16))) float prm[PR::WORDS];
-    __shared__ float4 gtab[GELU_K];
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, j = lane & 31, g = lane >> 5;
-    const int tile = blockIdx.x;
-    const int row = tile * 32 + j;
-    const int branch = tile * 32 >= G.base_lo ? 1 : 0;                 // a tile never straddles the regions: scalar
-    const bool valid = branch ? (row - G.base_lo < G.rows_lo) : (row < G.rows_hi);
-    const int nb = wave;
-    // ---- loads that depend on nothing: parameter block, attention codes, first weight fragments
-    static_assert(PVT <= 3, "the parameter block is staged with at most three loads per thread");
-    const float4* psrc = (const float4*)A.params[branch];
-    const float4 pv0 = psrc[tid];                                     // PV >= NT always; out-of-range threads re-read the last vector
-    const float4 pv1 = psrc[min(tid + NT, PV - 1)];
-    const float4 pv2 = psrc[min(tid + 2 * NT, PV - 1)];
-    const int pix = valid ? A.row_pix[row] : -1;
-    const size_t canon = (TAPS && valid) ? (size_t)A.row_canon[row] : 0;
-    const bool tap_ok = TAPS && valid;
-    v4i aof[KS], wpf[KS], w1f[KS];
-    {
-        const int pack = branch ? A.ao_pack : 0;                       // packed low-branch codes: scalar per tile
-        const int8_t* ap = A.ao + (size_t)row * C + g * 16;
-        const int8_t* pp = A.ao + (size_t)G.base_lo * C + (size_t)(row - G.base_lo) * (C >> pack);
-        const v4i* wp = A.Wproj + (size_t)nb * KS * 64 + lane;
-        const v4i* w1 = A.W1 + (size_t)wave * KS * 64 + lane;
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src, (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
+}
+// requests the branch's parameter block and the GELU table of a token kernel of NH waves
+template <int NH>
+__device__ __forceinline__ void token_stage(const float* params, const float4* gelu_tab, float* prm, float4* gtab, int wave, int lane)
+{
+    constexpr int PIECES = TokPrm<NH * 32>::WORDS / 256;
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            aof[ks] = pack ? expand_codes(packed_codes(pp, pack, ks, g), pack, g) : *(const v4i*)(ap + ks * 32);
-            wpf[ks] = wp[ks * 64];
-            if (EARLY_W1) w1f[ks] = w1[ks * 64];
-        }
-    }
-    gelu_stage_table(gtab, A.gelu_tab, tid, NT);
-    const float4* gelu_lds = gtab;
-    ((float4*)prm)[tid] = pv0;
-    if (PVT > 1 && tid + NT < PV) ((float4*)prm)[tid + NT] = pv1;
-    if (PVT > 2 && tid + 2 * NT < PV) ((float4*)prm)[tid + 2 * NT] = pv2;
-    float4 sc[4];
-#pragma unroll
-    for (int qd = 0; qd < 4; ++qd)
-        sc[qd] = pix >= 0 ? *(const float4*)(A.x + (size_t)pix * C + nb * 32 + qd * 8 + g * 4) : make_float4(0.f, 0.f, 0.f, 0.f);
-    __syncthreads();                                                  // parameter block visible
-    const int* prmi = (const int*)prm;
-    float h[16];
-    {   // output projection + first residual
-        v16i acc;
-#pragma unroll
-        for (int qd = 0; qd < 4; ++qd) {
-            const int4 t4 = *(const int4*)(prmi + PR::P_NC + nb * 32 + qd * 8 + g * 4);
-            acc[qd * 4 + 0] = t4.x; acc[qd * 4 + 1] = t4.y; acc[qd * 4 + 2] = t4.z; acc[qd * 4 + 3] = t4.w;
-        }
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) acc = mfma32(wpf[ks], aof[ks], acc);
-        if (!EARLY_W1) {                                              // wide blocks: the first FC1 weights follow the projection chain
-            const v4i* w1 = A.W1 + (size_t)wave * KS * 64 + lane;
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks) w1f[ks] = w1[ks * 64];
-        }
-#pragma unroll
-        for (int qd = 0; qd < 4; ++qd) {
-            const int n0 = nb * 32 + qd * 8 + g * 4;
-            const float4 m = *(const float4*)(prm + PR::P_M + n0), bs = *(const float4*)(prm + PR::P_B + n0);
-            h[qd * 4 + 0] = fmaf((float)acc[qd * 4 + 0], m.x, bs.x) + sc[qd].x;
-            h[qd * 4 + 1] = fmaf((float)acc[qd * 4 + 1], m.y, bs.y) + sc[qd].y;
-            h[qd * 4 + 2] = fmaf((float)acc[qd * 4 + 2], m.z, bs.z) + sc[qd].z;
-            h[qd * 4 + 3] = fmaf((float)acc[qd * 4 + 3], m.w, bs.w) + sc[qd].w;
-            if (tap_ok) {
-                if (A.tap_acc_proj) *(int4*)(A.tap_acc_proj + canon * C + n0) = make_int4(acc[qd * 4], acc[qd * 4 + 1], acc[qd * 4 + 2], acc[qd * 4 + 3]);
-                if (A.tap_h) *(float4*)(A.tap_h + canon * C + n0) = make_float4(h[qd * 4], h[qd * 4 + 1], h[qd * 4 + 2], h[qd * 4 + 3]);
-            }
-        }
-    }
-    {   // LN2: binary64 partial sums per (wave, token) through LDS, then normalise and quantize
-        Moments m;
-#pragma unroll
-        for (int r = 0; r < 16; r += 4) moments_add(m, h[r], h[r + 1], h[r + 2], h[r + 3]);
-        m.s = half_sum(m.s);
-        m.q = half_sum(m.q);
-        if (g == 0) { part[0][wave][j] = m.s; part[1][wave][j] = m.q; }
-        __syncthreads();
-        double s = 0.0, q = 0.0;
-#pragma unroll
-        for (int w2 = 0; w2 < NH; ++w2) { s += part[0][w2][j]; q += part[1][w2][j]; }
-        const float mean = moments_mean(s, C);
-        bool shaky;
-        double var = moments_centred(s, q, mean, C, shaky);
-        if (__any(shaky)) {                                            // every wave sees the same 32 tokens' sums: uniform over the workgroup
-            q = 0.0;
-#pragma unroll
-            for (int r = 0; r < 16; r += 4) q += centred_squares(h[r], h[r + 1], h[r + 2], h[r + 3], mean);
-            q = half_sum(q);
-            __syncthreads();                                          // the sums have been read
-            if (g == 0) part[1][wave][j] = q;
-            __syncthreads();
-            var = 0.0;
-#pragma unroll
-            for (int w2 = 0; w2 < NH; ++w2) var += part[1][w2][j];
-        }
-        const float rstd = moments_rstd(var, C, A.eps);
-        const QDev qa = A.q_fc1in[branch];
-        int wd[4];
-#pragma unroll
-        for (int qd = 0; qd < 4; ++qd) {
-            const int n0 = nb * 32 + qd * 8 + g * 4;
-            const float4 gm = *(const float4*)(prm + PR::LN_G + n0), bt = *(const float4*)(prm + PR::LN_B + n0);
-            wd[qd] = pack4(quant_code(fmaf((h[qd * 4 + 0] - mean) * rstd, gm.x, bt.x), qa),
-                           quant_code(fmaf((h[qd * 4 + 1] - mean) * rstd, gm.y, bt.y), qa),
-                           quant_code(fmaf((h[qd * 4 + 2] - mean) * rstd, gm.z, bt.z), qa),
-                           quant_code(fmaf((h[qd * 4 + 3] - mean) * rstd, gm.w, bt.w), qa));
-            if (tap_ok && A.tap_a2) *(int*)(A.tap_a2 + canon * C + n0) = wd[qd];
-        }
-        a2s[nb * 64 + lane] = (v4i){wd[0], wd[1], wd[2], wd[3]};       // k slab nb, byte r = channel 32nb + mfma_row(r,g)
-    }
-    __syncthreads();
-    v4i w2q[D2];                                                      // first FC2 weight fragments, requested during FC1
-    const v4i* w2p = A.W2 + (size_t)nb * HB * 64 + lane;
-    {   // FC1 + GELU + quantize for hidden blocks wave, wave+NH, ...
-        v4i af[KS];
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) af[ks] = a2s[ks * 64 + lane];
-        const QDev qg = A.q_fc2in[branch];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int hb = wave + NH * i;
-            v16i acc;
-#pragma unroll
-            for (int qd = 0; qd < 4; ++qd) {
-                const int4 t4 = *(const int4*)(prmi + PR::F1_NC + hb * 32 + qd * 8 + g * 4);
-                acc[qd * 4 + 0] = t4.x; acc[qd * 4 + 1] = t4.y; acc[qd * 4 + 2] = t4.z; acc[qd * 4 + 3] = t4.w;
-            }
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks) acc = mfma32(w1f[ks], af[ks], acc);
-            if (i < 3) {                                              // weights of the next hidden block
-                const v4i* w1 = A.W1 + (size_t)(hb + NH) * KS * 64 + lane;
-#pragma unroll
-                for (int ks = 0; ks < KS; ++ks) w1f[ks] = w1[ks * 64];
-            } else {
-#pragma unroll
-                for (int d = 0; d < D2; ++d) w2q[d] = w2p[d * 64];
-            }
-            int wd[4];
-#pragma unroll
-            for (int qd = 0; qd < 4; ++qd) {
-                const int n0 = hb * 32 + qd * 8 + g * 4;
-                const float4 m = *(const float4*)(prm + PR::F1_M + n0), bs = *(const float4*)(prm + PR::F1_B + n0);
-                wd[qd] = pack4(quant_code(gelu_scaled(fmaf((float)acc[qd * 4 + 0], m.x, bs.x), gelu_lds), qg),
-                               quant_code(gelu_scaled(fmaf((float)acc[qd * 4 + 1], m.y, bs.y), gelu_lds), qg),
-                               quant_code(gelu_scaled(fmaf((float)acc[qd * 4 + 2], m.z, bs.z), gelu_lds), qg),
-                               quant_code(gelu_scaled(fmaf((float)acc[qd * 4 + 3], m.w, bs.w), gelu_lds), qg));
-                if (tap_ok) {
-                    if (A.tap_acc_fc1) *(int4*)(A.tap_acc_fc1 + canon * F + n0) = make_int4(acc[qd * 4], acc[qd * 4 + 1], acc[qd * 4 + 2], acc[qd * 4 + 3]);
-                    if (A.tap_g) *(int*)(A.tap_g + canon * F + n0) = wd[qd];
-                }
-            }
-            gs[hb * 64 + lane] = (v4i){wd[0], wd[1], wd[2], wd[3]};
-        }
-    }
-    __syncthreads();
-    {   // FC2 + second residual + scatter
-        v16i acc;
-#pragma unroll
-        for (int qd = 0; qd < 4; ++qd) {
-            const int4 t4 = *(const int4*)(prmi + PR::F2_NC + nb * 32 + qd * 8 + g * 4);
-            acc[qd * 4 + 0] = t4.x; acc[qd * 4 + 1] = t4.y; acc[qd * 4 + 2] = t4.z; acc[qd * 4 + 3] = t4.w;
-        }
-#pragma unroll
-        for (int hb = 0; hb < HB; ++hb) {
-            const v4i w = w2q[hb % D2];
-            if (hb + D2 < HB) w2q[hb % D2] = w2p[(hb + D2) * 64];
-            acc = mfma32(w, gs[hb * 64 + lane], acc);
-        }
-#pragma unroll
-        for (int qd = 0; qd < 4; ++qd) {
-            const int n0 = nb * 32 + qd * 8 + g * 4;
-            const float4 m = *(const float4*)(prm + PR::F2_M + n0), bs = *(const float4*)(prm + PR::F2_B + n0);
-            float4 o4 = make_float4(fmaf((float)acc[qd * 4 + 0], m.x, bs.x) + h[qd * 4 + 0], fmaf((float)acc[qd * 4 + 1], m.y, bs.y) + h[qd * 4 + 1],
-                                    fmaf((float)acc[qd * 4 + 2], m.z, bs.z) + h[qd * 4 + 2], fmaf((float)acc[qd * 4 + 3], m.w, bs.w) + h[qd * 4 + 3]);
-            if (pix >= 0) *(float4*)(A.y + (size_t)pix * C + n0) = o4;
-            if (tap_ok) {
-                if (A.tap_acc_fc2) *(int4*)(A.tap_acc_fc2 + canon * C + n0) = make_int4(acc[qd * 4], acc[qd * 4 + 1], acc[qd * 4 + 2], acc[qd * 4 + 3]);
-                if (A.tap_y) *(float4*)(A.tap_y + canon * C + n0) = o4;
-            }
-        }
-    }
+    for (int p0 = 0; p0 < PIECES; p0 += NH)
+        if (p0 + NH <= PIECES || p0 + wave < PIECES) to_lds(params + (p0 + wave) * 256 + lane * 4, prm + (p0 + wave) * 256);
+    if (wave >= NH - 2) to_lds(gelu_tab + (wave - (NH - 2)) * 64 + lane, gtab + (wave - (NH - 2)) * 64);
 }
 
-// ------------------------------------------------------------------ fused token kernel, wide form
-// For six and twelve waves (C = 192, 384): one workgroup per tile of 32*RB gathered rows (RB 32-row blocks share
-// every weight fragment, which divides the L2 -> CU weight traffic per row by RB), one wave per 32-channel block.
-// Built for a small register footprint: the per-branch parameter block sits in LDS, the weight fragments of the whole kernel form ONE stream
-// per wave (projection block, then per chunk the FC1 block and the FC2 fragments) that is requested RING
-// fragments ahead across every phase boundary, and with two row blocks h is parked in the output map between the
-// first and the second residual (the same thread writes and re-reads the same address) instead of in registers.
-// The FFN runs in four chunks of NH hidden blocks: FC1 + GELU + quantize of a chunk goes to one of two LDS buffers,
-// then FC2 accumulates that chunk.
 template <int NH, int RB, bool TAPS>
-__global__ __launch_bounds__(NH * 64) void token_wide_kernel(Geom G, TokArgs A)
+__global__ __launch_bounds__(NH * 64) __attribute__((amdgpu_waves_per_eu(tok_waves_per_eu(NH)))) void token_kernel(Geom G, TokArgs A)
 {
-    constexpr int C = NH * 32, KS = NH, HB = 4 * NH, F = 4 * C, NT = NH * 64;
-    constexpr int RING = NH == 6 ? 6 : RB == 1 ? 12 : 8;               // fragments in flight per wave
+    constexpr int C = NH * 32, KS = NH, HB = 4 * NH, F = 4 * C;
+    constexpr int RING = NH < 8 ? NH : NH == 12 && RB == 1 ? 12 : 8;               // fragments in flight per wave
     constexpr bool PARK_H = RB >= 2 && !TAPS;                         // taps need h of padded tokens too, which have no pixel
     static_assert((2 * KS) % RING == 0 && RING <= KS, "phases 2k start at ring slot 0, phases 2k+1 at slot KS % RING");
     constexpr int SLOT_ODD = KS % RING;
@@ -1325,23 +1139,10 @@ __global__ __launch_bounds__(NH * 64) void token_wide_kernel(Geom G, TokArgs A)
     const v4i* wproj = A.Wproj + (size_t)nb * KS * 64 + lane;
     auto w1_of = [&](int chunk) { return A.W1 + ((size_t)(chunk * NH + wave) * KS) * 64 + lane; };
     auto w2_of = [&](int chunk) { return A.W2 + ((size_t)nb * HB + chunk * NH) * 64 + lane; };
-    int pix[RB];
-    bool valid[RB];
-    size_t canon[RB];
-#pragma unroll
-    for (int rb = 0; rb < RB; ++rb) {
-        const int row = row_base + rb * 32 + j;
-        valid[rb] = branch ? (row - G.base_lo < G.rows_lo) : (row < G.rows_hi);
-        pix[rb] = A.row_pix[row];
-        canon[rb] = (TAPS && valid[rb]) ? (size_t)A.row_canon[row] : 0;
-    }
     // Staging: the attention codes of the tile as operand fragments, the parameter block and the GELU table.  What is a plain
     // copy goes straight to LDS and everything is requested before anything is waited for (piece by piece, load and LDS
     // write in a loop, the staging was a chain of round trips: 3.3 us of a tile's 14 at C = 192).
     const int swave = __builtin_amdgcn_readfirstlane(wave);
-    auto to_lds = [&](const void* src, void* dst) {                    // 64 lanes x 16 bytes; src per lane, dst the wave's 1 KB
-        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src, (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
-    };
     const int pack = branch ? A.ao_pack : 0;                           // packed low-branch codes: scalar per tile
     int2 pc[RB];
     if (!pack) {
@@ -1354,12 +1155,17 @@ __global__ __launch_bounds__(NH * 64) void token_wide_kernel(Geom G, TokArgs A)
         for (int rb = 0; rb < RB; ++rb)
             pc[rb] = packed_codes(A.ao + (size_t)G.base_lo * C + (size_t)(row_base - G.base_lo + rb * 32 + j) * (C >> pack), pack, wave, g);
     }
+    int pix[RB];
+    bool valid[RB];
+    size_t canon[RB];
 #pragma unroll
-    for (int p0 = 0; p0 < PR::WORDS / 256; p0 += NH)                   // unrolled: the number of loads behind another one is known
-        if (p0 + NH <= PR::WORDS / 256 || p0 + swave < PR::WORDS / 256)
-            to_lds(A.params[branch] + (p0 + swave) * 256 + lane * 4, prm + (p0 + swave) * 256);
-    if (PR::WORDS % 256 && tid < PR::WORDS % 256 / 4) ((float4*)prm)[PR::WORDS / 256 * 64 + tid] = ((const float4*)A.params[branch])[PR::WORDS / 256 * 64 + tid];
-    if (swave >= NH - 2) to_lds(A.gelu_tab + (swave - (NH - 2)) * 64 + lane, gtab + (swave - (NH - 2)) * 64);
+    for (int rb = 0; rb < RB; ++rb) {
+        const int row = row_base + rb * 32 + j;
+        valid[rb] = branch ? (row - G.base_lo < G.rows_lo) : (row < G.rows_hi);
+        pix[rb] = A.row_pix[row];
+        canon[rb] = (TAPS && valid[rb]) ? (size_t)A.row_canon[row] : 0;
+    }
+    token_stage<NH>(A.params[branch], A.gelu_tab, prm, gtab, swave, lane);
     asm volatile("" ::: "memory");                                     // the weight stream is requested behind them
     v4i ring[RING];
 #pragma unroll
@@ -1546,7 +1352,7 @@ __global__ __launch_bounds__(NH * 64) void token_wide_kernel(Geom G, TokArgs A)
             [&](int i) {                                                                      // between its steps ...
 #pragma unroll
                 for (int u = 0; u < 4 * RB; ++u)
-                    if ((u + 1) * KS / (4 * RB) - 1 == i) gelu_part(ch, u / 4, u % 4, acc);   // ... GELU of chunk ch
+                    if (((u + 1) * KS + 4 * RB - 1) / (4 * RB) - 1 == i) gelu_part(ch, u / 4, u % 4, acc);   // ... GELU of chunk ch
             });
         gelu_store(ch);
         __syncthreads();                                              // chunk ch complete, chunk ch-1 no longer read
@@ -1748,31 +1554,23 @@ void launch_window(const Geom& G, const WinArgs& A, hipStream_t st)
 #undef WIN_CASE
 }
 
-constexpr int TOKEN_WIDE_SMALL = 128;        // C = 384: up to this many 64-row tiles the wide token kernel runs on 32-row tiles
+constexpr int TOKEN_WIDE_SMALL = 128;        // C = 384: up to this many 64-row tiles the token kernel runs on 32-row tiles
 void launch_token(const Geom& G, const TokArgs& A, hipStream_t st)
 {
     if (G.rows_total == 0) return;
-    const int NHr = G.C / 32;
-#define TOK_CASE(NH)                                                                                              \
-    if (A.taps) hipLaunchKernelGGL((token_kernel<NH, true>), dim3(G.rows_total / 32), dim3(NH * 64), 0, st, G, A); \
-    else hipLaunchKernelGGL((token_kernel<NH, false>), dim3(G.rows_total / 32), dim3(NH * 64), 0, st, G, A);      \
-    break
-    // twelve heads: the wide form, 64-row tiles once there are enough of them to give every second CU one, else 32-row tiles
-    if (NHr == 12 && G.rows_total / 64 > TOKEN_WIDE_SMALL) {
-        if (A.taps) hipLaunchKernelGGL((token_wide_kernel<12, 2, true>), dim3(G.rows_total / 64), dim3(12 * 64), 0, st, G, A);
-        else hipLaunchKernelGGL((token_wide_kernel<12, 2, false>), dim3(G.rows_total / 64), dim3(12 * 64), 0, st, G, A);
-    } else if (NHr == 12) {
-        if (A.taps) hipLaunchKernelGGL((token_wide_kernel<12, 1, true>), dim3(G.rows_total / 32), dim3(12 * 64), 0, st, G, A);
-        else hipLaunchKernelGGL((token_wide_kernel<12, 1, false>), dim3(G.rows_total / 32), dim3(12 * 64), 0, st, G, A);
-    } else if (NHr == 6) {    // six waves: the wide form on 32-row tiles (28.9 instead of 32.3 us on 552 tiles; at 3, 4 and 8 waves the plain kernel wins)
-        if (A.taps) hipLaunchKernelGGL((token_wide_kernel<6, 1, true>), dim3(G.rows_total / 32), dim3(6 * 64), 0, st, G, A);
-        else hipLaunchKernelGGL((token_wide_kernel<6, 1, false>), dim3(G.rows_total / 32), dim3(6 * 64), 0, st, G, A);
-    } else {
-        switch (NHr) {
-            case 3: TOK_CASE(3);
-            case 4: TOK_CASE(4);
-            default: TOK_CASE(8);
-        }
+#define TOK_CASE(NH, RB)                                                                                                             \
+    if (A.taps) hipLaunchKernelGGL((token_kernel<NH, RB, true>), dim3(G.rows_total / (32 * RB)), dim3(NH * 64), 0, st, G, A); \
+    else hipLaunchKernelGGL((token_kernel<NH, RB, false>), dim3(G.rows_total / (32 * RB)), dim3(NH * 64), 0, st, G, A)
+    switch (G.C / 32) {
+        case 3: TOK_CASE(3, 1); break;
+        case 4: TOK_CASE(4, 1); break;
+        case 6: TOK_CASE(6, 1); break;
+        case 8: TOK_CASE(8, 1); break;
+        default:
+            // 64-row tiles once there are enough of them to give every second CU one, else 32-row tiles (with fewer waves the
+            // registers of a second row block cost more than its weights save)
+            if (G.rows_total / 64 > TOKEN_WIDE_SMALL) { TOK_CASE(12, 2); }
+            else { TOK_CASE(12, 1); }
     }
 #undef TOK_CASE
 }
