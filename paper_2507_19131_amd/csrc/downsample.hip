@@ -79,8 +79,7 @@ constexpr int merge_max_split(int KS) { return KS / merge_ring(KS) >= 4 ? 4 : 2;
 // per group of output blocks.
 // Phase 1: LPT lanes per token, a quarter of them per neighbour, NV float4 each; the workgroup grows with C_in so that
 // a lane's share of the 32 tokens is 48 or 64 floats, which it requests all at once: the kernel waits once for memory,
-// and 128 registers leave room for sixteen waves per CU.  LayerNorm statistics in one binary64 pass over the lane group,
-// quantize, codes to LDS as MFMA operand fragments (slabs and halves a little apart, so that the lanes of a wave spread
+// and 128 registers leave room for sixteen waves per CU.  LayerNorm statistics in binary64 over the lane group, quantize, codes to LDS as MFMA operand fragments (slabs and halves a little apart, so that the lanes of a wave spread
 // over the banks).
 // Phase 2: wave w takes the output blocks first + w, first + w + waves, ... of its group; the weight fragments stream
 // through a ring of loads in flight that starts before the barrier.  On a small grid `split` waves share the slabs of one
@@ -135,20 +134,13 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void me
                     v[p][k].z = inside[p] ? v[p][k].z : 0.f; v[p][k].w = inside[p] ? v[p][k].w : 0.f;
                 }
             }
-            Moments mo;
+            double s = 0.0, sq = 0.0;
 #pragma unroll
-            for (int k = 0; k < NV; ++k) moments_add(mo, v[p][k].x, v[p][k].y, v[p][k].z, v[p][k].w);
-            const double s = lanes_sum<LPT>(mo.s);
-            mean[p] = moments_mean(s, K);
-            bool shaky;
-            double cs = moments_centred(s, lanes_sum<LPT>(mo.q), mean[p], K, shaky);
-            if (__any(shaky)) {
-                double t = 0.0;
+            for (int k = 0; k < NV; ++k) s += sum4(v[p][k].x, v[p][k].y, v[p][k].z, v[p][k].w);
+            mean[p] = ln_mean(lanes_sum<LPT>(s), K);
 #pragma unroll
-                for (int k = 0; k < NV; ++k) t += centred_squares(v[p][k].x, v[p][k].y, v[p][k].z, v[p][k].w, mean[p]);
-                cs = lanes_sum<LPT>(t);
-            }
-            rstd[p] = moments_rstd(cs, K, A.eps);
+            for (int k = 0; k < NV; ++k) sq += centred4(v[p][k].x, v[p][k].y, v[p][k].z, v[p][k].w, mean[p]);
+            rstd[p] = ln_rstd(lanes_sum<LPT>(sq), K, A.eps);
         }
 #pragma unroll
         for (int k = 0; k < NV; ++k) {
@@ -234,7 +226,7 @@ typedef float f4_any __attribute__((ext_vector_type(4), aligned(4)));
 // output tokens, nothing shared but the constants of the channels: lane = (token, half), a half holds two of the four patch
 // rows (24 inputs in six loads of 16 bytes; the weights are packed in that order: 16 + 8 codes of each half
 // and zeros), so the codes are MFMA operands where they were computed, and the 32 NB outputs of a token end in two lanes,
-// which makes the LayerNorm one binary64 sum in registers and one exchange.
+// whose LayerNorm sums need one exchange each.
 // Bound: memory, once the map is large (4 x 1024 x 1024 into 128: 47.8 us with a tile's codes and outputs through LDS and
 // three barriers, 31.8 us now, 5.8 TB/s with the image from the cache); at 800 x 1344 into 96 (15.0 -> 10.8 us) one chain of
 // waits per wave, two waves per SIMD.  The 128 registers of four waves per SIMD need the two barriers against hoisting below.
@@ -283,7 +275,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void e
     }
     __syncthreads();
     float f[NB * 16];
-    Moments mo;
+    double s = 0.0;
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
         __builtin_amdgcn_sched_barrier(0);                    // one block's constants and sums in registers at a time
@@ -301,22 +293,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void e
             float* o = f + nb * 16 + qd * 4;
             o[0] = fmaf((float)acc[qd * 4 + 0], m.x, bs.x); o[1] = fmaf((float)acc[qd * 4 + 1], m.y, bs.y);
             o[2] = fmaf((float)acc[qd * 4 + 2], m.z, bs.z); o[3] = fmaf((float)acc[qd * 4 + 3], m.w, bs.w);
-            moments_add(mo, o[0], o[1], o[2], o[3]);
+            s += sum4(o[0], o[1], o[2], o[3]);
             if (TAPS && A.tap_acc && valid)
                 *(int4*)(A.tap_acc + (size_t)tok * N + nb * 32 + qd * 8 + g * 4) = make_int4(acc[qd * 4], acc[qd * 4 + 1], acc[qd * 4 + 2], acc[qd * 4 + 3]);
         }
     }
-    const double s = half_sum(mo.s);
-    const float mean = moments_mean(s, N);
-    bool shaky;
-    double cs = moments_centred(s, half_sum(mo.q), mean, N, shaky);
-    if (__any(shaky)) {
-        double t = 0.0;
+    const float mean = ln_mean(half_sum(s), N);
+    double sq = 0.0;
 #pragma unroll
-        for (int k = 0; k < NB * 4; ++k) t += centred_squares(f[k * 4], f[k * 4 + 1], f[k * 4 + 2], f[k * 4 + 3], mean);
-        cs = half_sum(t);
-    }
-    const float rstd = moments_rstd(cs, N, A.eps);
+    for (int k = 0; k < NB * 4; ++k) sq += centred4(f[k * 4], f[k * 4 + 1], f[k * 4 + 2], f[k * 4 + 3], mean);
+    const float rstd = ln_rstd(half_sum(sq), N, A.eps);
     if (!valid) return;
     float* out = A.y + (size_t)tok * N + g * 4;
 #pragma unroll

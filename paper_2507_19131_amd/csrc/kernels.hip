@@ -29,27 +29,23 @@ __device__ __forceinline__ double group_sum(double v, int first = 0)
 
 // LayerNorm of one token spread over LPT lanes (NV float4 per lane; channel of
 // element e of vector k on lane i: (k*LPT + i)*4 + e).  Mean and variance in
-// binary64, rounded once (see Moments).
+// binary64, rounded once (see ln_stats.h).
 template <int LPT, int NV>
 __device__ __forceinline__ void token_ln_stats(const float4 (&v)[NV], int C, float eps, float& mean, float& rstd, int first = 0)
 {
-    Moments m;
+    double s = 0.0, q = 0.0;
 #pragma unroll
     for (int k = 0; k < NV; ++k) {
         if (NV > 8 && k % 4 == 0) __builtin_amdgcn_sched_barrier(0);
-        moments_add(m, v[k].x, v[k].y, v[k].z, v[k].w);
+        s += sum4(v[k].x, v[k].y, v[k].z, v[k].w);
     }
-    const double s = group_sum<LPT>(m.s, first), q = group_sum<LPT>(m.q, first);
-    mean = moments_mean(s, C);
-    bool shaky;
-    double var = moments_centred(s, q, mean, C, shaky);
-    if (shaky) {                                                 // the same in every lane of the token
-        var = 0.0;
+    mean = ln_mean(group_sum<LPT>(s, first), C);
 #pragma unroll
-        for (int k = 0; k < NV; ++k) var += centred_squares(v[k].x, v[k].y, v[k].z, v[k].w, mean);
-        var = group_sum<LPT>(var, first);
+    for (int k = 0; k < NV; ++k) {
+        if (NV > 8 && k % 4 == 0) __builtin_amdgcn_sched_barrier(0);
+        q += centred4(v[k].x, v[k].y, v[k].z, v[k].w, mean);
     }
-    rstd = moments_rstd(var, C, eps);
+    rstd = ln_rstd(group_sum<LPT>(q, first), C, eps);
 }
 
 template <int LPT, int NV>
@@ -277,7 +273,7 @@ __global__ __launch_bounds__(256) void ln_quant_kernel(Geom G, LnArgs A)
         const float* src = GATHER ? A.src + (size_t)pix * G.C : A.src + (size_t)row * G.C;
 #pragma unroll
         for (int k = 0; k < NV; ++k) v[k] = *(const float4*)(src + (k * LPT + sub) * 4);
-        token_layernorm<LPT, NV>(v, G.C, A.eps, A.gamma[branch], A.beta[branch], sub);
+        token_layernorm<LPT, NV>(v, LPT * NV * 4, A.eps, A.gamma[branch], A.beta[branch], sub);
     } else {
 #pragma unroll
         for (int k = 0; k < NV; ++k) v[k] = make_float4(0.f, 0.f, 0.f, 0.f);   // padding enters as LN output 0
@@ -1254,50 +1250,34 @@ __global__ __launch_bounds__(NH * 64) __attribute__((amdgpu_waves_per_eu(tok_wav
     }
     {   // LN2: binary64 partial sums per (wave, token) through LDS, then normalise and quantize
         float mean[RB];
-        double var[RB];
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) {
-            Moments m;
+            double s = 0.0;
 #pragma unroll
-            for (int r = 0; r < 16; r += 4) moments_add(m, h[rb][r], h[rb][r + 1], h[rb][r + 2], h[rb][r + 3]);
-            m.s = half_sum(m.s);
-            m.q = half_sum(m.q);
-            if (g == 0) { part[0][wave][rb * 32 + j] = m.s; part[1][wave][rb * 32 + j] = m.q; }
+            for (int r = 0; r < 16; r += 4) s += sum4(h[rb][r], h[rb][r + 1], h[rb][r + 2], h[rb][r + 3]);
+            s = half_sum(s);
+            if (g == 0) part[0][wave][rb * 32 + j] = s;
         }
         __syncthreads();                                              // also: every wave is done reading the attention codes
-        bool any_shaky = false;
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) {
             double s = 0.0, q = 0.0;
 #pragma unroll
-            for (int w2i = 0; w2i < NH; ++w2i) { s += part[0][w2i][rb * 32 + j]; q += part[1][w2i][rb * 32 + j]; }
-            mean[rb] = moments_mean(s, C);
-            bool shaky;
-            var[rb] = moments_centred(s, q, mean[rb], C, shaky);
-            any_shaky |= shaky;
+            for (int w2i = 0; w2i < NH; ++w2i) s += part[0][w2i][rb * 32 + j];
+            mean[rb] = ln_mean(s, C);
+#pragma unroll
+            for (int r = 0; r < 16; r += 4) q += centred4(h[rb][r], h[rb][r + 1], h[rb][r + 2], h[rb][r + 3], mean[rb]);
+            q = half_sum(q);
+            if (g == 0) part[1][wave][rb * 32 + j] = q;
         }
-        if (__any(any_shaky)) {                                        // every wave sees the same tokens' sums: uniform over the workgroup
-            __syncthreads();                                          // the sums have been read
-#pragma unroll
-            for (int rb = 0; rb < RB; ++rb) {
-                double q = 0.0;
-#pragma unroll
-                for (int r = 0; r < 16; r += 4) q += centred_squares(h[rb][r], h[rb][r + 1], h[rb][r + 2], h[rb][r + 3], mean[rb]);
-                q = half_sum(q);
-                if (g == 0) part[1][wave][rb * 32 + j] = q;
-            }
-            __syncthreads();
-#pragma unroll
-            for (int rb = 0; rb < RB; ++rb) {
-                var[rb] = 0.0;
-#pragma unroll
-                for (int w2i = 0; w2i < NH; ++w2i) var[rb] += part[1][w2i][rb * 32 + j];
-            }
-        }
+        __syncthreads();
         const QDev qa = A.q_fc1in[branch];
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) {
-            const float rstd = moments_rstd(var[rb], C, A.eps);
+            double q = 0.0;
+#pragma unroll
+            for (int w2i = 0; w2i < NH; ++w2i) q += part[1][w2i][rb * 32 + j];
+            const float rstd = ln_rstd(q, C, A.eps);
             int wd[4];
 #pragma unroll
             for (int qd = 0; qd < 4; ++qd) {

@@ -4,6 +4,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include "ln_stats.h"
 
 namespace mixaq {
 
@@ -183,42 +184,6 @@ __device__ __forceinline__ double lanes_sum(double v)
     if (W >= 64) v = half_sum(v);
     return v;
 }
-
-// ---- LayerNorm statistics of one token, binary64 -------------------------------------------------
-// One pass: sum and sum of squares together (convert, add, fused multiply-add: three vector instructions per element
-// where mean first, centred squares second takes five, and one exchange between the lanes or waves of a token instead of
-// two).  sum (x - mean)^2 = q - mean (2 s - C mean) for the ROUNDED mean, so the result is the one of the two-pass form up
-// to the cancellation in that subtraction, at most 64 times 2^-52 relative: where the token's mean is so large that more
-// would cancel, moments_shaky says so and the caller takes the centred squares in a second pass.
-struct Moments { double s = 0.0, q = 0.0; };
-__device__ __forceinline__ void moments_add(Moments& m, float a, float b, float c, float d)
-{
-    const double ad = a, bd = b, cd = c, dd = d;
-    m.s += (ad + bd) + (cd + dd);
-    m.q = __builtin_fma(ad, ad, m.q);
-    m.q = __builtin_fma(bd, bd, m.q);
-    m.q = __builtin_fma(cd, cd, m.q);
-    m.q = __builtin_fma(dd, dd, m.q);
-}
-__device__ __forceinline__ float moments_mean(double s, int C) { return (float)(s * (1.0 / (double)C)); }
-// the centred sum of squares; shaky: too much of it cancelled
-__device__ __forceinline__ double moments_centred(double s, double q, float mean, int C, bool& shaky)
-{
-    const double m = mean;
-    const double v = __builtin_fma(-m, __builtin_fma(-(double)C, m, s + s), q);
-    shaky = v * 64.0 < q;
-    return v;
-}
-// (the second pass of shaky tokens; its inputs are made opaque, or the compiler keeps their conversions to binary64 from the
-// first pass in registers for it: twice the token, in spills)
-__device__ __forceinline__ double centred_squares(float x0, float x1, float x2, float x3, float mean)
-{
-    asm("" : "+v"(x0), "+v"(x1), "+v"(x2), "+v"(x3));
-    const double a = (double)x0 - (double)mean, b = (double)x1 - (double)mean;
-    const double c = (double)x2 - (double)mean, d = (double)x3 - (double)mean;
-    return (a * a + b * b) + (c * c + d * d);
-}
-__device__ __forceinline__ float moments_rstd(double v, int C, float eps) { return 1.0f / sqrtf((float)(v * (1.0 / (double)C)) + eps); }
 
 // D[32x32] += A[32 x 32k] * B[32k x 32]; lane l supplies row (A) / column (B) l%32 and
 // the 16 k-values of half l/32; D register r of lane l is row (r/4)*8 + (l/32)*4 + r%4,

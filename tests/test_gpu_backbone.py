@@ -162,3 +162,31 @@ def test_config4_backbone_chain():
         assert not np.isnan(g).any()
         assert err <= 1e-3 * rms
         bi += 1
+
+
+def test_a_token_does_not_depend_on_its_neighbours():
+    """A token's LayerNorm is a function of the token: the bits of the others stay when one token of every 32 (the tokens of a
+    wave of the patch embedding) is replaced by one whose mean is many standard deviations.  A form that lets one token's
+    cancellation choose the formula of its neighbours shows about once in 1e7 tokens (the rounding of the variance to
+    binary32 has to tell the two apart), hence 1e8 of them."""
+    B, H, W, N = 4, 1024, 1024, 96
+    inp = synth.make_downsample_inputs(synth.DownSpec(0, B, H, W, 3, N), 110)
+    inp.bias = inp.bias + np.float32(8.0)                            # mean about 6 standard deviations
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(111)
+    gd = GpuDown(inp)
+    try:
+        differ = torch.zeros((), dtype=torch.int64, device="cuda")
+        for it in range(400):
+            a = torch.randn((B, H, W, 3), generator=gen, device="cuda")
+            b = a.clone()
+            b.view(B, H, W // 128, 128, 3)[:, :, :, :4] = 0.0          # the first token of every 32: its 96 outputs are nearly equal
+            ya, _, _ = gd.forward(a)
+            yb, _, _ = gd.forward(b)
+            same = (ya == yb).view(-1, 32, N)
+            differ += (~same[:, 1:]).any(dim=2).sum()
+            if it % 100 == 99:
+                print("tokens compared", (it + 1) * B * (H // 4) * (W // 4) * 31 // 32, "different", int(differ), flush=True)
+        assert int(differ) == 0
+    finally:
+        gd.close()

@@ -1,0 +1,122 @@
+"""The binary64 statistics of a LayerNorm token (csrc/ln_stats.h), compiled for the host from the lines the kernels use and
+compared with exact arithmetic, in the kernels' orders of summation.  CPU only."""
+import os
+import subprocess
+import textwrap
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2507_19131_amd", "csrc")
+
+PROGRAM = textwrap.dedent(r'''
+    #include <cstdio>
+    #include <cmath>
+    #include <functional>
+    #include <random>
+    #include <vector>
+    #include <quadmath.h>
+    #include "ln_stats.h"
+    using namespace mixaq;
+    typedef __float128 Q;
+    typedef std::vector<float> Tok;
+
+    // a reduction over the C values of a token: term(4 values) per lane and vector, lane sums, then across the lanes
+    struct Order { int C, lanes; bool tree; };          // tree: butterfly over the lanes; otherwise lane after lane
+    static double reduce(const Tok& x, Order o, const std::function<double(const float*, double)>& add)
+    {
+        const int NV = o.C / (4 * o.lanes);
+        std::vector<double> p(o.lanes, 0.0);
+        for (int k = 0; k < NV; ++k)
+            for (int i = 0; i < o.lanes; ++i) p[i] = add(&x[(k * o.lanes + i) * 4], p[i]);
+        if (!o.tree) {
+            double t = 0.0;
+            for (double v : p) t += v;
+            return t;
+        }
+        for (int w = 1; w < o.lanes; w *= 2) {
+            std::vector<double> q = p;
+            for (int i = 0; i < o.lanes; ++i) p[i] = q[i] + q[i ^ w];
+        }
+        return p[0];
+    }
+    int main()
+    {
+        std::mt19937_64 gen(7);
+        // the quotient: the bits of a division
+        long bad = 0;
+        std::uniform_real_distribution<double> mant(1.0, 2.0);
+        for (int C : {96, 128, 192, 256, 384, 512, 768, 1024, 1536, 2048})
+            for (int t = 0; t < 300000; ++t) {
+                const double v = std::ldexp(mant(gen), (int)(gen() % 200) - 100) * ((gen() & 1) ? 1 : -1);
+                bad += over_channels(v, C) != v / (double)C;
+            }
+        std::printf("quotient %ld\n", bad);
+        // the centred sum: relative error in units of 2^-53 against what its roundings allow, and of the one-pass form for comparison
+        std::normal_distribution<float> normal(0.0f, 1.0f);
+        const Order orders[] = {{96, 8, true}, {96, 3, false}, {96, 6, false}, {128, 8, true}, {192, 16, true}, {192, 6, false}, {256, 8, false},
+                                {384, 32, true}, {384, 12, false}, {768, 64, true}, {1024, 64, true}, {2048, 64, true}};
+        for (const Order& o : orders)
+            for (double ratio : {0.0, 0.3, 1.0, 7.0, 100.0}) {
+                double worst = 0.0, worst_one = 0.0, sq = 0.0, sq_plain = 0.0, mean_err = 0.0;
+                const int n = 3000;
+                for (int t = 0; t < n; ++t) {
+                    Tok x(o.C);
+                    for (float& v : x) v = normal(gen) + (float)ratio;
+                    const double s = reduce(x, o, [](const float* v, double a) { return a + sum4(v[0], v[1], v[2], v[3]); });
+                    const float mean = ln_mean(s, o.C);
+                    const double c = reduce(x, o, [&](const float* v, double a) { return a + centred4(v[0], v[1], v[2], v[3], mean); });
+                    const double m = mean;
+                    const double plain = reduce(x, o, [&](const float* v, double a) {        // every product rounded on its own
+                        const double d0 = v[0] - m, d1 = v[1] - m, d2 = v[2] - m, d3 = v[3] - m;
+                        return a + ((d0 * d0 + d1 * d1) + (d2 * d2 + d3 * d3));
+                    });
+                    double q = reduce(x, o, [](const float* v, double a) {
+                        for (int e = 0; e < 4; ++e) a = std::fma((double)v[e], (double)v[e], a);
+                        return a;
+                    });
+                    q = std::fma(-m, std::fma(-(double)o.C, m, s + s), q);
+                    Q exact = 0, sum = 0;
+                    for (float v : x) { const Q d = (Q)v - (Q)mean; exact += d * d; sum += v; }
+                    const double e = (double)fabsq(((Q)c - exact) / exact) * 0x1p53, ep = (double)fabsq(((Q)plain - exact) / exact) * 0x1p53;
+                    worst = std::fmax(worst, e);
+                    worst_one = std::fmax(worst_one, (double)fabsq(((Q)q - exact) / exact) * 0x1p53);
+                    sq += e * e;
+                    sq_plain += ep * ep;
+                    mean_err = std::fmax(mean_err, (double)fabsq(((Q)s - sum)));
+                }
+                // subtraction (squared: two), square, three additions inside a vector (the first is the fused one), one per vector of a
+                // lane, then the lanes
+                const int depth = 3 + 2 + o.C / (4 * o.lanes) + (o.tree ? (int)std::round(std::log2((double)o.lanes)) : o.lanes);
+                std::printf("order %d %d %d ratio %g bound %d worst %.17g onepass %.17g rms %.17g plain %.17g\n", o.C, o.lanes, (int)o.tree, ratio, depth,
+                            worst, worst_one, std::sqrt(sq / n), std::sqrt(sq_plain / n));
+            }
+        return 0;
+    }
+''')
+
+
+@pytest.fixture(scope="module")
+def measured(tmp_path_factory):
+    d = tmp_path_factory.mktemp("ln_stats")
+    src, exe = d / "ln.cpp", d / "ln"
+    src.write_text(PROGRAM)
+    subprocess.run(["g++", "-O2", "-ffp-contract=off", "-I", CSRC, "-o", str(exe), str(src), "-lquadmath"], check=True)
+    return subprocess.run([str(exe)], check=True, capture_output=True, text=True).stdout.splitlines()
+
+
+def test_quotient_by_the_width_is_the_division(measured):
+    assert measured[0] == "quotient 0"
+
+
+def test_variance_keeps_its_precision_whatever_the_mean(measured):
+    """Every term of the centred sum is positive, so its relative error is at most one rounding (2^-53) per operation on the
+    way of a term, at any mean; and it is no larger than with every product rounded on its own.  The one-pass form (sum and
+    sum of squares) is the planted mistake: at mean = 7 standard deviations it is far outside the same bound."""
+    rows = [dict(zip(["C", "lanes", "tree", "ratio", "bound", "worst", "onepass", "rms", "plain"],
+                     [float(t) for t in (line.split()[1:4] + line.split()[5::2])])) for line in measured[1:]]
+    assert len(rows) == 60
+    for r in rows:
+        assert r["worst"] <= r["bound"], r
+        assert r["rms"] <= 1.02 * r["plain"], r                # the two differ by a rounding less here; 3000 tokens see 2 %
+    assert min(r["onepass"] for r in rows if r["ratio"] == 7.0) > 2 * max(r["bound"] for r in rows)
