@@ -134,6 +134,7 @@ struct mixaq_block {
     float* bias2 = nullptr;
     QDev q_in[2], q_qkv[2][3], q_p[2], q_ao[2], q_fc1in[2], q_fc2in[2];
     float m2[2], m_o[2];
+    bool exp_floor = false;    // the softmax exponents need their floor (see exp2_pinned)
     float* tok_params[2] = {nullptr, nullptr};   // parameter blocks of the fused token kernel
     float* win_params[2] = {nullptr, nullptr};   // parameter blocks of the fused window kernel
     int ao_pack = 0;           // packing of the low branch's attention-output codes between the two fused kernels
@@ -391,6 +392,7 @@ int forward_impl(const mixaq_block* blk, const float* x, const int32_t* perm, co
         wa.tap_a1 = tp.a_qkv_in; wa.tap_acc = tp.acc_qkv; wa.tap_qkv = tp.qkv; wa.tap_s = tp.acc_s; wa.tap_p = tp.p;
         wa.tap_o = tp.acc_o; wa.tap_code = tp.a_proj_in;
         wa.poly = pinned_coefficients();
+        wa.floor = blk->exp_floor;
         wa.taps = taps != nullptr;
         mark(9);
         for (int r = 0; r < reps; ++r) launch_window(G, wa, st);       // also forwards pruned windows
@@ -410,6 +412,7 @@ int forward_impl(const mixaq_block* blk, const float* x, const int32_t* perm, co
         aa.qkv = ws.qkv; aa.perm = perm; aa.bias2 = blk->bias2; aa.out = ws.ao;
         for (int br = 0; br < 2; ++br) { aa.m2[br] = blk->m2[br]; aa.m_o[br] = blk->m_o[br]; aa.qp[br] = blk->q_p[br]; aa.qo[br] = blk->q_ao[br]; }
         aa.poly = pinned_coefficients();
+        aa.floor = blk->exp_floor;
         aa.tap_s = tp.acc_s; aa.tap_p = tp.p; aa.tap_o = tp.acc_o; aa.tap_code = tp.a_proj_in;
         mark(4);
         for (int r = 0; r < reps; ++r) launch_attn(G, aa, st);
@@ -579,6 +582,12 @@ static int block_create(const mixaq_block_desc* desc, const mixaq_shared_params*
         if ((rc = download(sh->score_beta, (size_t)C, tmp))) return bail(rc);
         b->mem.add(tmp, &b->score_beta);
     }
+    // Logits are finite without the floor where the table and the largest product (|S| <= 32 * 128 * 128) are at most LOGIT_MAX;
+    // a bias that shuts a pair out altogether (-infinity), anything else that is no ordinary number, and quantizers for which a
+    // probability of 2^-99 is not zero take the floor.
+    constexpr float LOGIT_MAX = 1e30f, STEPS_MAX = 0x1p60f;
+    for (int br = 0; br < 2; ++br)
+        if (!(b->m2[br] * (float)(HD * 128 * 128) <= LOGIT_MAX) || b->q_p[br].inv_s > STEPS_MAX) b->exp_floor = true;
     // (relative position bias + shift mask) * log2(e), transposed to [type][head][key][query 64]
     {
         std::vector<float> rpb;
@@ -597,9 +606,9 @@ static int block_create(const mixaq_block_desc* desc, const mixaq_shared_params*
                             token_src(b, wr, wc, j, &rj, &cj);
                             if (!(std::abs(ri - rj) < WS && std::abs(ci - cj) < WS)) v = v + MASK_VALUE;
                         }
-                        // a bias that shuts a pair out altogether (-infinity, or not a number) becomes a finite one: see exp2_pinned
                         v = v * LOG2E_F;
-                        tab[(((size_t)type * heads + h) * TOK + j) * 64 + i] = v > -1e30f ? v : -1e30f;
+                        tab[(((size_t)type * heads + h) * TOK + j) * 64 + i] = v;
+                        if (!(std::fabs(v) <= LOGIT_MAX)) b->exp_floor = true;
                     }
         }
         b->mem.add(tab, &b->bias2);

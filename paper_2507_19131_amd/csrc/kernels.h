@@ -64,6 +64,7 @@ struct AttnArgs {
     int32_t* tap_o;
     int8_t* tap_code;
     PolyCoef poly;
+    bool floor;                      // the exponents need their floor: see exp2_pinned
 };
 
 struct WinArgs {                     // fused window kernel (gather + LN1 + QKV + attention)
@@ -89,6 +90,7 @@ struct WinArgs {                     // fused window kernel (gather + LN1 + QKV 
     int* row_canon;
     int8_t* tap_a1; int32_t* tap_acc; int8_t* tap_qkv; int32_t* tap_s; int8_t* tap_p; int32_t* tap_o; int8_t* tap_code;
     PolyCoef poly;
+    bool floor;                      // the exponents need their floor: see exp2_pinned
     bool taps;                       // any tap pointer set
 };
 

@@ -476,6 +476,7 @@ struct AttnCore {
     float m2;
     QDev qp;
     const int* nzcsum;        // [HD], LDS
+    bool floor;               // see exp2_pinned; scalar
     int32_t* tap_s;           // already offset to this (slot, head): [49][49]
     int8_t* tap_p;
 };
@@ -508,6 +509,13 @@ __device__ __forceinline__ v16i attention_core(const v4i& qf, const v4i (&kf)[2]
                 lg[kb][r] = v;
             }
         mx = half_max(mx);
+        if (A.floor) {                                                    // infinities and NaN of the table or the products end here
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) lg[kb][r] = fmaxf(lg[kb][r] - mx, EXP2_FLOOR);
+            mx = 0.0f;
+        }
         double den = 0.0;
 #pragma unroll
         for (int kb = 0; kb < 2; ++kb)
@@ -663,6 +671,7 @@ __global__ __launch_bounds__(256) void attn_kernel(Geom G, AttnArgs A)
     AttnCore core;
     core.nzcsum = csum[wave];
     core.poly = &A.poly;
+    core.floor = A.floor;
     core.bq = A.bias2 + ((size_t)(mtype * G.heads + head) * TOK) * 64 + g * 4 * 64 + j;
     core.m2 = A.m2[branch];
     core.qp = A.qp[branch];
@@ -1049,6 +1058,7 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
     __builtin_amdgcn_wave_barrier();
     AttnCore core;
     core.poly = &A.poly;
+    core.floor = A.floor;
     core.nzcsum = csum[wave];
     core.bq = A.bias2 + ((size_t)(mask_type(G, w) * NHT + head) * TOK) * 64 + g * 4 * 64 + j;
     core.m2 = A.m2[branch];

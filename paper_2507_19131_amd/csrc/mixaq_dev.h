@@ -55,9 +55,11 @@ struct PolyCoef {
     float e[6];       // 2^r on [-1/2, 1/2], degree 5, e[0] = constant term
 };
 
-// 2^y for y <= 0: split, degree-5 polynomial, exact scaling.  The definition holds y at -100 from below; the code leaves
-// that out: a term under 2^-99 changes neither the denominator of its row (which is at least 1: the row's maximum
-// contributes 2^0, and binary64 cannot see 49 such terms beside it) nor a code.  y must be finite (the bias table is).
+// 2^y for y <= 0, finite: split, degree-5 polynomial, exact scaling.  The definition holds y at EXP2_FLOOR from below; the
+// code leaves that out: a term under 2^-99 changes neither the denominator of its row (which is at least 1: the row's maximum
+// contributes 2^0, and binary64 cannot see 49 such terms beside it) nor a code.  Where a logit may not be finite, or the
+// probabilities' step is so small that such a term would make a code, the caller applies the floor (AttnCore::floor).
+constexpr float EXP2_FLOOR = -100.0f;
 __device__ __forceinline__ float exp2_pinned(float y, const PolyCoef& P)
 {
     float n = rintf(y);

@@ -387,3 +387,41 @@ def test_degenerate_inputs(kind):
     for n in gh.INT_TAPS:
         assert res[n] == 0, (n, res)
     assert res["y_bit_identical"], res
+
+
+@pytest.mark.parametrize("kind", ["plus_inf", "minus_inf", "nan", "overflow", "huge", "products", "tiny_step"])
+@pytest.mark.parametrize("C,heads,fused", [(96, 3, True), (96, 3, False), (384, 12, True), (768, 24, None)])
+def test_logits_that_are_no_ordinary_numbers(C, heads, fused, kind):
+    """Infinities, NaN and overflowing values in the relative position bias, products of q and k that overflow the logits, and
+    probability steps below 2^-100: the softmax's exponents are held at their floor, as the definition says, and every tap is
+    the oracle's."""
+    spec, inp, x, k = _case(2, 14, 21, C, heads, 3, 0.5, 81, blobs=True)
+    rng = np.random.default_rng(82)
+    rpb = inp.shared.rel_pos_bias.copy()
+    some = rng.random(rpb.shape) < 0.02
+    if kind == "plus_inf":
+        rpb[some] = np.inf                       # some rows with one or two of them, some with none
+    elif kind == "minus_inf":
+        rpb[some] = -np.inf
+        rpb[0, 3, :] = -np.inf                   # a row that shuts every key out
+    elif kind == "nan":
+        rpb[some] = np.nan
+    elif kind == "overflow":
+        rpb[some] = 3e38                         # finite, infinite times log2(e)
+    elif kind == "huge":
+        rpb[some] = 2e38
+        rpb[rng.random(rpb.shape) < 0.02] = -2e38
+    elif kind == "products":                     # q and k in steps of about 1e17: the largest products overflow, the others do not
+        inp.shared.s_qkv = inp.shared.s_qkv.copy()
+        inp.shared.s_qkv[:2 * C] *= np.float32(1e19)
+        for br in inp.branches:
+            for n in ("a_q", "a_k"):
+                br.q[n] = (br.q[n][0] * 1e19, 0)
+    else:
+        for br in inp.branches:
+            br.q["a_p"] = (2.0 ** -101, 0)       # every probability but 2^-100 and less saturates
+    inp.shared.rel_pos_bias = rpb
+    print("logits", kind, "C", C, "fused", fused, flush=True)
+    res = gh.compare_block(inp, x, k, fused=fused)
+    print(res, flush=True)
+    gh.assert_parity(res)
