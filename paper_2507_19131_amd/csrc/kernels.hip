@@ -75,9 +75,9 @@ __device__ __forceinline__ void token_layernorm(float4 (&v)[NV], int C, float ep
 
 // ------------------------------------------------------------------ K0 score
 // One workgroup of NT threads per window of the un-shifted grid, LPT lanes per token.  The loads of PC passes over the
-// tokens are issued together, before any arithmetic.  Memory bound once there are windows enough to fill the chip (NT =
-// 256); wide maps have few windows, each of them a chain of round trips for its one workgroup, so from C = 384 it gets 1024
-// threads that have the whole window in flight at once (24 windows at C = 768: 7.5 -> 4.0 us).
+// tokens are issued together, before any arithmetic.  Memory bound once there are windows enough to fill the chip; wide maps
+// have few windows, each of them a chain of round trips for its one workgroup, so from C = 384 it gets 1024 threads that have
+// the whole window in flight at once (see launch_score_t).
 template <int LPT, int NV, int NT>
 __global__ __launch_bounds__(NT) void score_kernel(Geom G, const float* __restrict__ x, int mode, float eps,
                                                    const float* __restrict__ gamma, const float* __restrict__ beta,
@@ -1367,12 +1367,22 @@ __global__ __launch_bounds__(NH * 64) __attribute__((amdgpu_waves_per_eu(tok_wav
 }
 
 // ------------------------------------------------------------------ launchers
+// From C = 384 a window is taken by 1024 threads (256 threads -> 1024, launch to launch on fresh maps).  Raw score: equal where
+// the launch itself is what takes the time (24 windows at C = 768 6.5 us both), better or equal beyond (384 windows at 768 12.5 ->
+// 11.7, 3200 at 384 41.8 -> 39.1, 900 at 1024 30.8 -> 30.5).  With the scoring LayerNorm the window's arithmetic is spread wider
+// (24 windows at 768 11.0 -> 7.5, 100 at 1024 14.1 -> 9.3, 900 at 384 17.6 -> 16.6), until the map no longer fits the chip in
+// about one round and the waiting of the larger workgroups costs more (1600 windows at 384 28.4 -> 28.6, 1444 at 512 34.0 ->
+// 36.1, 900 at 768 30.3 -> 36.2, 900 at 1024 39.1 -> 45.0): the line is drawn at windows times channels.
+constexpr long long SCORE_WIDE_LN_MAX = 512 * 1024;
 template <int LPT, int NV>
 static void launch_score_t(const Geom& G, const float* x, int mode, float eps, const float* gm, const float* bt,
                            double* scores, hipStream_t st)
 {
-    constexpr int NT = LPT * NV * 4 >= 384 ? 1024 : 256;
-    hipLaunchKernelGGL((score_kernel<LPT, NV, NT>), dim3(G.B * G.nW), dim3(NT), 0, st, G, x, mode, eps, gm, bt, scores);
+    constexpr bool WIDE = LPT * NV * 4 >= 384;
+    if (WIDE && (mode == 0 || (long long)G.B * G.nW * G.C <= SCORE_WIDE_LN_MAX))
+        hipLaunchKernelGGL((score_kernel<LPT, NV, WIDE ? 1024 : 256>), dim3(G.B * G.nW), dim3(WIDE ? 1024 : 256), 0, st, G, x, mode, eps, gm, bt, scores);
+    else
+        hipLaunchKernelGGL((score_kernel<LPT, NV, 256>), dim3(G.B * G.nW), dim3(256), 0, st, G, x, mode, eps, gm, bt, scores);
 }
 template <int LPT, int NV>
 static void launch_ln_t(const Geom& G, const LnArgs& A, bool gather, hipStream_t st)

@@ -425,3 +425,17 @@ def test_logits_that_are_no_ordinary_numbers(C, heads, fused, kind):
     res = gh.compare_block(inp, x, k, fused=fused)
     print(res, flush=True)
     gh.assert_parity(res)
+
+
+@pytest.mark.parametrize("B,H,W,C,mode", [(9, 56, 63, 768, 1), (10, 56, 63, 768, 1), (10, 56, 63, 768, 0), (4, 130, 140, 384, 1), (5, 82, 91, 1024, 1)])
+def test_scores_of_wide_maps_on_both_sides_of_the_workgroup_size(B, H, W, C, mode):
+    """Wide maps are scored by 1024 threads per window, large ones with the scoring LayerNorm by 256."""
+    import oracle_api as O
+    spec, inp, x, k = _case(B, H, W, C, C // 32, 0, 0.5, 45, blobs=True, mode=mode)
+    print("scores", B, H, W, C, "mode", mode, "windows times channels", B * spec.nW * C, flush=True)
+    with gh.GpuBlock(inp) as gb:
+        scores, perm = gb.score_select(torch.from_numpy(x).cuda(), k)
+        torch.cuda.synchronize()
+    want = O.score_windows(inp, x)
+    assert np.max(np.abs(scores.cpu().numpy() - want) / want) <= 1e-12
+    assert np.array_equal(perm.cpu().numpy(), O.select_windows(want, k))
