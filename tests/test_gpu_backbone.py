@@ -77,6 +77,21 @@ def test_downsample_matches_oracle(kind, B, H, W, C_in, N, bits, wbits):
     assert torch.equal(y, y2)
 
 
+@pytest.mark.parametrize("B,H,W,N,bits,wbits", [
+    (1, 64, 96, 128, 8, 8),
+    (2, 50, 45, 128, 4, 4),         # sizes that are not multiples of the patch
+    (1, 5, 7, 128, 8, 8),           # four tokens
+    (3, 33, 514, 128, 6, 8),        # the last patch of a row and the last wave are partial
+    (1, 3, 130, 96, 8, 8),          # a single row of patches, all of them over the edge
+    (1, 64, 96, 192, 8, 8),         # other widths: the general kernel with its patch known at compile time
+    (2, 50, 45, 192, 4, 4),
+    (1, 37, 41, 160, 8, 4),
+    (1, 41, 37, 32, 8, 8),
+])
+def test_patch_embedding_widths_match_oracle(B, H, W, N, bits, wbits):
+    test_downsample_matches_oracle(0, B, H, W, 3, N, bits, wbits)
+
+
 def test_downsample_error_paths():
     sp = synth.DownSpec(1, 1, 14, 14, 96, 192)
     inp = synth.make_downsample_inputs(sp, 7)

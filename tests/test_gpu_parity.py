@@ -44,7 +44,8 @@ SMALL = [
 ]
 
 
-# both implementations where both exist: the fused kernels cover C <= 384, the seven-kernel path every width
+# both implementations: the two fused kernels (C <= 384) and the seven-kernel path; the default path of the wider blocks is in
+# WIDE_CASES
 BLOCK_CASES = [case + (fused,) for case in SMALL for fused in (True, False) if not (fused and case[3] > 384)]
 
 
@@ -67,7 +68,7 @@ BIAS_CASES = [(C, heads, bits, wbits, shift, fused)
 def test_independent_biases_per_branch(C, heads, bits, wbits, shift, fused):
     """PTQ variant (Sec. 4.3, PTQ setup): the low branch has biases of its own, visibly different from the
     high branch's; every tap must follow the bias of the row's branch (both implementations up to C = 384, the
-    seven-kernel path, the only one there, at C = 768)."""
+    seven-kernel path at C = 768)."""
     spec, inp, x, k = _case(2, 20, 27, C, heads, shift, 0.4, 51, blobs=True, bits=bits, wbits=wbits,
                             per_branch_bias=True, bias_std=0.1)
     for n in ("b_qkv", "b_proj", "b_fc1", "b_fc2"):
@@ -255,8 +256,7 @@ def test_activation_pruning_matches_oracle(shift, kh_frac, kl_frac, fused):
 @pytest.mark.parametrize("C,heads", [(96, 3), (128, 4), (384, 12), (768, 24)])
 @pytest.mark.parametrize("shift,kh_frac,kl_frac", [(0, 0.5, -1), (3, 0.25, 0.5), (3, 0.0, 0.0)])
 def test_forward_from_scores_matches_oracle(C, heads, shift, kh_frac, kl_frac):
-    """The selection taken inside the first kernel from the stage's scores (fused path) or by the
-    select kernel (seven-kernel path, C = 768) gives the oracle's block output."""
+    """The selection taken inside the first kernel from the stage's scores gives the oracle's block output."""
     import oracle_api as O
     spec, inp, x, _ = _case(2, 26, 33, C, heads, shift, 0.5, 41, blobs=True)
     nW = spec.nW
@@ -439,3 +439,51 @@ def test_scores_of_wide_maps_on_both_sides_of_the_workgroup_size(B, H, W, C, mod
     want = O.score_windows(inp, x)
     assert np.max(np.abs(scores.cpu().numpy() - want) / want) <= 1e-12
     assert np.array_equal(perm.cpu().numpy(), O.select_windows(want, k))
+
+
+WIDE_CASES = [
+    # B, H, W, C, shift, keep, bits, kwargs: the default path of the wide blocks (LN1, then a window's heads over several workgroups)
+    (2, 21, 28, 512, 3, 0.4, (7, 3), {}),
+    (1, 7, 7, 512, 0, 1.0, (8, 4), {}),                               # a single window
+    (3, 33, 40, 512, 3, 0.0, (4, 2), dict(wbits=4)),                  # 90 windows, everything low
+    (1, 14, 21, 1024, 3, 0.5, (8, 4), {}),
+    (2, 20, 27, 1024, 0, 0.3, (4, 2), dict(wbits=4, per_branch_bias=True)),
+    (2, 20, 27, 768, 3, 1.0, (6, 3), dict(mode=1)),
+    (1, 20, 27, 512, 3, 0.5, (8, 4), dict(mlp_ratio=3)),
+]
+
+
+@pytest.mark.parametrize("B,H,W,C,shift,keep,bits,kw", WIDE_CASES)
+def test_wide_blocks_on_their_default_path(B, H, W, C, shift, keep, bits, kw):
+    spec, inp, x, k = _case(B, H, W, C, C // 32, shift, keep, 46, bits=bits, blobs=True, **kw)
+    print("wide block", B, H, W, C, shift, keep, bits, kw, flush=True)
+    res = gh.compare_block(inp, x, k)
+    print(res, flush=True)
+    gh.assert_parity(res)
+
+
+@pytest.mark.parametrize("C,heads", [(512, 16), (1024, 32)])
+@pytest.mark.parametrize("shift,kh_frac,kl_frac", [(0, 0.5, -1), (3, 0.25, 0.5), (3, 0.0, 0.0)])
+def test_wide_blocks_from_scores_and_lists_with_pruning(C, heads, shift, kh_frac, kl_frac):
+    """Selection inside the call and from a list, pruned windows forwarded, at the widths the case above does not cover."""
+    import oracle_api as O
+    spec, inp, x, _ = _case(2, 26, 33, C, heads, shift, 0.5, 47, blobs=True)
+    nW = spec.nW
+    kh = int(kh_frac * nW)
+    kl = nW - kh if kl_frac < 0 else int(kl_frac * nW)
+    print("wide block, scores", C, shift, kh, kl, flush=True)
+    dev = torch.device("cuda:0")
+    xt = torch.from_numpy(x).to(dev)
+    with gh.GpuBlock(inp) as gb:
+        scores = torch.empty((2, nW), dtype=torch.float64, device=dev)
+        M.mixaq_score_windows(gb.blk, xt, scores)
+        y = torch.full_like(xt, float("nan"))
+        perm = torch.full((2, nW), -1, dtype=torch.int32, device=dev)
+        M.mixaq_block_forward_scored(gb.blk, xt, scores, kh, kl, y, gb.ws, perm_out=perm)
+        y_list = gb.forward_pruned(xt, perm, kh, kl)
+        torch.cuda.synchronize()
+    o_perm = O.select_windows(O.score_windows(inp, x), kh, k_low=kl)
+    assert np.array_equal(perm.cpu().numpy(), o_perm)
+    oy, _ = O.block_forward(inp, x, o_perm, kh, k_low=kl, threads=16)
+    assert np.array_equal(y.cpu().numpy(), oy)
+    assert torch.equal(y, y_list)

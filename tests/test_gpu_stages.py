@@ -132,9 +132,9 @@ def test_stage_entry_point_with_a_ratio_per_pair_and_pruning(fused):
 
 @pytest.mark.parametrize("B,C,heads", [(2, 384, 12), (3, 96, 3), (5, 192, 6)])
 def test_stage_on_a_batch_of_small_maps_runs_as_two_chains(B, C, heads):
-    """A batch of small maps (at most 4096 windows in all) goes through the stage call as two chains of blocks, one per
-    half of the images (uneven halves for an odd batch), the second on the library's side stream; the result is the
-    oracle's, the same bits as block after block on the whole batch, and repeated calls agree."""
+    """A batch of small maps whose blocks own what two chains need (a side stream, a workspace in two parts) but whose stage
+    is too short to fork: the result is the oracle's, the same bits as block after block on the whole batch, and repeated
+    calls agree.  The stages that do fork: test_forked_stage_with_uneven_halves_pruning_and_streams."""
     spec = synth.BlockSpec(B, 30, 37, C, heads)
     shifts = [0, 3, 0, 3]
     assert B * spec.nW <= 4096
@@ -205,7 +205,7 @@ def test_two_chains_at_config2_shape_on_two_maps():
 def test_stage_on_a_side_stream_matches_the_default_stream(B):
     """All work of a call is ordered on the stream it is given: a stage run on a second stream (default
     priority) while the default stream is kept busy gives the same bits, and is complete as soon as that
-    stream is; with a batch also when the call runs as two chains (the second on the library's own stream)."""
+    stream is (also where the call forks: test_forked_stage_with_uneven_halves_pruning_and_streams)."""
     wl = synth.workload("cfg2")
     st = wl["stages"][0]
     spec = synth.BlockSpec(B, 60, 75, 96, 3)
@@ -244,8 +244,8 @@ BENCH_STAGES = [("cfg1", 0), ("cfg2", 0), ("cfg3", 0), ("cfg4", 1), ("cfg4", 2),
 @pytest.mark.parametrize("name,stage", BENCH_STAGES, ids=[f"{n}-stage{s + 1}" for n, s in BENCH_STAGES])
 def test_stage_call_as_the_benchmark_launches_it(name, stage):
     """Every benchmark workload at full size through mixaq_stage_forward, the one call a benchmark step makes
-    (score, selection inside the first block's first kernel, list handed on to the later blocks; config 3's two
-    maps go through it as two chains, config 4's last stage on the seven-kernel path)."""
+    (score, selection inside the first block's first kernel, list handed on to the later blocks; config 4's last stage with
+    LN1 as a kernel of its own and the separate kernels of the second half)."""
     wl = synth.workload(name)
     st = wl["stages"][stage]
     spec, shifts = st["spec"], st["shifts"]
@@ -279,7 +279,7 @@ def test_stage_call_as_the_benchmark_launches_it(name, stage):
 
 
 def test_random_sweep_of_stage_calls():
-    """Thirty seeded random stage calls: width, batch (one or two chains), map size, 1-4 blocks, bit widths, score mode,
+    """Thirty seeded random stage calls: width, batch, map size, 1-4 blocks, bit widths, score mode,
     shared or independent biases and, per pair, any split into high, low and pruned windows (none and all included);
     maps and selection lists must equal the oracle's bit for bit."""
     dev = torch.device("cuda:0")
@@ -326,8 +326,8 @@ def test_random_sweep_of_stage_calls():
 
 @pytest.mark.parametrize("name", ["cfg2", "cfg3"])
 def test_repeated_stage_calls_are_bit_stable(name):
-    """The same stage call a hundred times over (one chain at config 2, two chains at config 3): every result has the
-    bits of the first, which a missing barrier or a race between the chains would not survive."""
+    """The same stage call a hundred times over: every result has the bits of the first, which a missing barrier would not
+    survive (two chains: test_repeated_forked_stage_calls_are_bit_stable)."""
     wl = synth.workload(name)
     st = wl["stages"][0]
     spec, shifts = st["spec"], st["shifts"]
@@ -398,3 +398,138 @@ def test_stage_call_can_be_captured_in_a_graph():
     finally:
         for gb in blocks:
             gb.close()
+
+
+# (B, H, W, C, heads, blocks): windows enough over all blocks that the stage call forks; uneven halves where the batch is odd
+FORKED = [(3, 82, 137, 96, 3, 4), (2, 68, 81, 128, 4, 9), (5, 75, 66, 192, 6, 4), (3, 60, 65, 256, 8, 8), (3, 68, 81, 384, 12, 6)]
+
+
+@pytest.mark.parametrize("B,H,W,C,heads,n_blocks", FORKED)
+@pytest.mark.parametrize("own_stream", [False, True])
+def test_forked_stage_with_uneven_halves_pruning_and_streams(B, H, W, C, heads, n_blocks, own_stream):
+    """The stage call as two chains: uneven halves for an odd batch, pruned windows in some pairs and none in others, on the
+    default stream or on one of the caller's while the default stream is kept busy (complete as soon as that stream is);
+    the same bits as block after block on the whole batch on one stream, and the oracle's."""
+    spec = synth.BlockSpec(B, H, W, C, heads, act_bits_low=2 if C == 128 else 4)
+    assert gh.stage_forks(spec, n_blocks)
+    nW, pairs = spec.nW, (n_blocks + 1) // 2
+    shifts = [0, 3] * pairs
+    k_high = [[nW // 2, nW // 3, 0][p % 3] for p in range(pairs)]
+    k_low = [[nW - nW // 2, nW // 3, nW // 2][p % 3] for p in range(pairs)]
+    dev = torch.device("cuda:0")
+    x_np = synth.make_feature_map(spec, 310, blobs=True)
+    inputs = [synth.make_block_inputs(spec, 311 + i) for i in range(n_blocks)]
+    x = torch.from_numpy(x_np).to(dev)
+    print("forked stage", B, H, W, "C", C, "blocks", n_blocks, "own stream", own_stream, flush=True)
+    blocks = [gh.GpuBlock(inp, shift) for inp, shift in zip(inputs, shifts)]
+    try:
+        y, tmp = torch.full_like(x, float("nan")), torch.full_like(x, float("nan"))
+        scores = torch.empty((B, nW), dtype=torch.float64, device=dev)
+        perm = torch.full((B, nW), -1, dtype=torch.int32, device=dev)
+        handles = [gb.blk for gb in blocks]
+        ws = M.alloc_workspace(blocks[0].blk)
+        stream = torch.cuda.Stream() if own_stream else None
+        busy = torch.empty(1 << 26, device=dev)
+        torch.cuda.synchronize()
+        if own_stream:
+            for _ in range(8):
+                busy.normal_()                                      # keeps the default stream occupied meanwhile
+        M.mixaq_stage_forward(handles, x, k_high, k_low, y, tmp, scores, perm, ws, stream=stream)
+        if own_stream:
+            stream.synchronize()
+            y_own = y.cpu().numpy()                                 # complete as soon as ITS stream is
+        torch.cuda.synchronize()
+        y_gpu, perm_gpu = y.cpu().numpy(), perm.cpu().numpy()
+        assert not own_stream or np.array_equal(y_own, y_gpu)
+        cur = x                                                     # block after block on the whole batch, one stream
+        for i, gb in enumerate(blocks):
+            cur = gb.forward_pruned(cur, perm, k_high[i // 2], k_low[i // 2])
+        torch.cuda.synchronize()
+        assert np.array_equal(cur.cpu().numpy(), y_gpu)
+    finally:
+        for gb in blocks:
+            gb.close()
+    if own_stream:
+        return                                                      # the oracle has seen these bits in the other half of the cases
+    sc_o = O.score_windows(inputs[0], x_np)
+    cur = x_np
+    for i, (inp, shift) in enumerate(zip(inputs, shifts)):
+        perm_o = O.select_windows(sc_o, k_high[i // 2], k_low=k_low[i // 2])
+        assert np.array_equal(perm_gpu, perm_o)
+        cur, _ = O.block_forward(inp, cur, perm_o, k_high[i // 2], shift, threads=16, k_low=k_low[i // 2])
+    assert np.array_equal(y_gpu, cur)
+
+
+@pytest.mark.parametrize("B,H,W,C,heads,n_blocks", [FORKED[0], FORKED[4]])
+def test_repeated_forked_stage_calls_are_bit_stable(B, H, W, C, heads, n_blocks):
+    """A stage call that runs as two chains, a hundred times over on two alternating maps: every result has the bits of its
+    map's first, which a race between the chains or with the call before would not survive."""
+    spec = synth.BlockSpec(B, H, W, C, heads)
+    assert gh.stage_forks(spec, n_blocks)
+    dev = torch.device("cuda:0")
+    xs = [torch.from_numpy(synth.make_feature_map(spec, 330 + i, blobs=True)).to(dev) for i in range(2)]
+    blocks = [gh.GpuBlock(synth.make_block_inputs(spec, 340 + i), 3 * (i % 2)) for i in range(n_blocks)]
+    try:
+        k, pairs = spec.nW // 2, (n_blocks + 1) // 2
+        y, tmp = torch.empty_like(xs[0]), torch.empty_like(xs[0])
+        scores = torch.empty((B, spec.nW), dtype=torch.float64, device=dev)
+        perm = torch.empty((B, spec.nW), dtype=torch.int32, device=dev)
+        handles = [gb.blk for gb in blocks]
+        first = []
+        for x in xs:
+            M.mixaq_stage_forward(handles, x, [k] * pairs, None, y, tmp, scores, perm, blocks[0].ws)
+            torch.cuda.synchronize()
+            first.append((y.clone(), perm.clone()))
+        print("repeating a forked stage call", B, H, W, "C", C, flush=True)
+        for it in range(100):
+            y.fill_(float("nan"))
+            M.mixaq_stage_forward(handles, xs[it % 2], [k] * pairs, None, y, tmp, scores, perm, blocks[0].ws)
+            if it % 5 == 4:
+                assert torch.equal(y, first[it % 2][0]) and torch.equal(perm, first[it % 2][1]), it
+        torch.cuda.synchronize()
+    finally:
+        for gb in blocks:
+            gb.close()
+
+
+def test_random_sweep_of_forked_stage_calls():
+    """Six seeded random stage calls that run as two chains: width, batch, map size, precision and, per pair, any split into
+    high, low and pruned windows; maps and lists must equal the oracle's bit for bit."""
+    dev = torch.device("cuda:0")
+    for case in range(6):
+        rng = np.random.default_rng(64000 + case)
+        C, heads = [(96, 3), (128, 4), (192, 6)][case % 3]
+        B, n_blocks = int(rng.integers(2, 7)), int(rng.integers(2, 7))
+        hi = int(rng.integers(4, 9))
+        windows = 1.05 * 2000 * 128 / min(C, 128) / n_blocks / B * float(rng.uniform(1.0, 1.3))
+        rows = max(2, int(np.sqrt(windows * rng.uniform(0.6, 1.6))))
+        cols = max(2, -(-int(windows) // rows) + 1)
+        spec = synth.BlockSpec(B, 7 * rows - int(rng.integers(0, 7)), 7 * cols - int(rng.integers(0, 7)), C, heads, act_bits_high=hi,
+                               act_bits_low=int(rng.integers(2, hi + 1)), weight_bits=int(rng.choice([4, 8])), score_mode=int(rng.integers(0, 2)))
+        assert gh.stage_forks(spec, n_blocks), case
+        pairs = (n_blocks + 1) // 2
+        k_high = [int(rng.integers(0, spec.nW + 1)) for _ in range(pairs)]
+        k_low = [spec.nW - kh if rng.integers(0, 2) else int(rng.integers(0, spec.nW - kh + 1)) for kh in k_high]
+        print("forked sweep case", case, "B", B, spec.H, spec.W, "C", C, "blocks", n_blocks, "k_high", k_high, "k_low", k_low, flush=True)
+        x_np = synth.make_feature_map(spec, 65000 + case, blobs=True)
+        inputs = [synth.make_block_inputs(spec, 66000 + 10 * case + i, per_branch_bias=bool(rng.integers(0, 2))) for i in range(n_blocks)]
+        x = torch.from_numpy(x_np).to(dev)
+        blocks = [gh.GpuBlock(inp, 3 * (i % 2)) for i, inp in enumerate(inputs)]
+        try:
+            y, tmp = torch.full_like(x, float("nan")), torch.empty_like(x)
+            scores = torch.empty((B, spec.nW), dtype=torch.float64, device=dev)
+            perm = torch.full((B, spec.nW), -1, dtype=torch.int32, device=dev)
+            for _ in range(2):
+                M.mixaq_stage_forward([gb.blk for gb in blocks], x, k_high, k_low, y, tmp, scores, perm, blocks[0].ws)
+            torch.cuda.synchronize()
+            y_gpu, perm_gpu = y.cpu().numpy(), perm.cpu().numpy()
+        finally:
+            for gb in blocks:
+                gb.close()
+        sc_o = O.score_windows(inputs[0], x_np)
+        cur = x_np
+        for i, inp in enumerate(inputs):
+            perm_o = O.select_windows(sc_o, k_high[i // 2], k_low=k_low[i // 2])
+            cur, _ = O.block_forward(inp, cur, perm_o, k_high[i // 2], 3 * (i % 2), threads=16, k_low=k_low[i // 2])
+        assert np.array_equal(perm_gpu, perm_o), case
+        assert np.array_equal(y_gpu, cur), case
