@@ -1451,6 +1451,8 @@ static void launch_gemm_e(const Geom& G, const GemmArgs& A0, hipStream_t st)
     // 32-row tiles: a long K stays whole in LDS (K = 3072 on 19 row tiles: 16.3 us; 64-row tiles in chunks of 1024: 27.8 us);
     // a narrow layer on few rows gets twice the workgroups (the projection at C = 768 on 19 row tiles: 8.1 instead of 10.7 us;
     // with 72 or 96 output blocks the wider layers have workgroups enough and lose: 13.2 and 13.8 instead of 12.4 and 13.2 us)
+    // (only FC2 has K = mlp_ratio C; the other layers have K = C <= 1024, and QKV never as few as 32 output blocks there)
+    constexpr bool LONG_K = EPI == EPI_FC2;
     const bool half = (A.K > GEMM_TILE_MAX_K && A.K <= 4096) || (tiles <= 32 && NB <= 32 && A.K > 384 && A.K <= 1024);
     A.kchunk = A.K;
     if (A.K > 4096)                                                   // chunks of whole ring turns (256 bytes of K each): the largest such size up to
@@ -1462,14 +1464,23 @@ static void launch_gemm_e(const Geom& G, const GemmArgs& A0, hipStream_t st)
 #define GEMM_CASE(KMAX, RT, D) hipLaunchKernelGGL((gemm_tile_kernel<EPI, KMAX, RT, D>), grid, dim3(256), 0, st, G, A)
     // ring length: whole turns of 16 or 12 fragments where K has them
     const bool d16 = A.K % 512 == 0;
-    if (half && A.K <= 1024) { if (d16) GEMM_CASE(1024, 32, 16); else GEMM_CASE(1024, 32, 12); }
-    else if (half && A.K <= 3072) { if (d16) GEMM_CASE(3072, 32, 16); else GEMM_CASE(3072, 32, 12); }
-    else if (half) GEMM_CASE(4096, 32, 16);
-    else if (A.K <= 384) GEMM_CASE(384, 64, 6);
-    else if (A.K <= 1024) { if (d16) GEMM_CASE(1024, 64, 16); else GEMM_CASE(1024, 64, 12); }
-    else if (A.K > GEMM_TILE_MAX_K) GEMM_CASE(1024, 64, 8);           // above 4096: chunks of 1024
-    else if (d16) GEMM_CASE(GEMM_TILE_MAX_K, 64, 16);
-    else GEMM_CASE(GEMM_TILE_MAX_K, 64, 12);
+    if constexpr (LONG_K)
+        if (A.K > 1024) {
+            if (half && A.K <= 3072) { if (d16) GEMM_CASE(3072, 32, 16); else GEMM_CASE(3072, 32, 12); }
+            else if (half) GEMM_CASE(4096, 32, 16);
+            else if (A.K > GEMM_TILE_MAX_K) GEMM_CASE(1024, 64, 8);   // above 4096: chunks of 1024
+            else if (d16) GEMM_CASE(GEMM_TILE_MAX_K, 64, 16);
+            else GEMM_CASE(GEMM_TILE_MAX_K, 64, 12);
+            return;
+        }
+    if constexpr (EPI != EPI_QKV)
+        if (half) {
+            if (d16) GEMM_CASE(1024, 32, 16); else GEMM_CASE(1024, 32, 12);
+            return;
+        }
+    if (A.K <= 384) GEMM_CASE(384, 64, 6);
+    else if (d16) GEMM_CASE(1024, 64, 16);
+    else GEMM_CASE(1024, 64, 12);
 #undef GEMM_CASE
 }
 
