@@ -184,8 +184,9 @@ int mixaq_block_forward_scored(const mixaq_block *blk, const float *x, const dou
  * that hold the stage's scores and selection list afterwards.  The workspace must satisfy
  * mixaq_block_workspace_bytes of the stage's blocks (equal shapes give equal sizes).  All work is
  * ordered on `stream`; nothing is allocated.  A batch of small maps (B >= 2, at most 4096 windows in
- * all, fused kernels) runs as two chains of blocks, one per half of the images (they are independent
- * through the whole stage): the second chain is enqueued on a stream of the library's own that
+ * all, fused kernels) whose stage is long enough (n_blocks * B*nW * min(C, 128) >= 256000: fork and
+ * join cost as much as a short stage would gain) runs as two chains of blocks, one per half of the
+ * images (they are independent through the whole stage): the second chain is enqueued on a stream of the library's own that
  * starts after the work already on `stream` and that `stream` waits for before the call's work
  * counts as done, so the caller sees the same ordering as without it; under stream capture the
  * stage stays on `stream` alone.  MIXAQ_E_SHAPE if the blocks disagree on the shape or a count is
@@ -287,11 +288,11 @@ int mixaq_sample_ratios(int32_t n, double s_min, double s_max, double upper, con
                         size_t *n_used, double *ratios);
 
 /* Chooses between the two implementations of the forward call: the fused kernels (a window
- * kernel for gather/LN1/QKV/attention, a token kernel per 32- or 64-row tile for
- * proj/LN2/FFN/scatter: C <= 384, the token kernel with mlp_ratio 4; each is the default where it
- * is supported) and the seven-kernel path that handles every supported shape.  Both give the
- * same bits.  enable = 0 selects the seven-kernel path; enabling on a shape no fused kernel
- * covers returns MIXAQ_E_SHAPE. */
+ * kernel for gather/LN1/QKV/attention at every width, from C = 512 on with LN1 as a kernel before
+ * it; a token kernel per 32- or 64-row tile for proj/LN2/FFN/scatter: C <= 384, mlp_ratio 4; each
+ * is the default where it is supported) and the seven-kernel path that handles every supported
+ * shape.  Both give the same bits.  enable = 0 selects the seven-kernel path, enable != 0 the
+ * default again; the window kernel covers every supported width, so no shape is refused. */
 int mixaq_block_set_fused(mixaq_block *blk, int32_t enable);
 
 /* Measurement aid for benchmarks (not part of the paper's method): one forward
@@ -299,7 +300,8 @@ int mixaq_block_set_fused(mixaq_block *blk, int32_t enable);
  * recomputes the same result) between two HIP events on `stream`; synchronises
  * the stream and writes the mean duration of each kernel in milliseconds to the
  * HOST array kernel_ms[MIXAQ_NUM_KERNELS] (0 for kernels that did not run, e.g.
- * score and select when perm is given).  perm / scores as in mixaq_block_forward /
+ * score and select when perm is given).  From C = 512 on the entry of the window kernel is the sum of
+ * its two kernels (LN1, then QKV + attention), launched alternately.  perm / scores as in mixaq_block_forward /
  * mixaq_block_forward_scored (at most one non-NULL).  mixaq_kernel_name(i) names entry i. */
 #define MIXAQ_NUM_KERNELS 11
 int mixaq_block_forward_profile(const mixaq_block *blk, const float *x, const int32_t *perm, const double *scores,

@@ -242,13 +242,25 @@ int check_qparam(const mixaq_qparam& q, int bits, const char* name)
     return MIXAQ_OK;
 }
 
-// Two chains pay while the kernels of the stage leave CUs idle for part of their time: a batch of at least two maps
-// with at most this many windows in all, on the fused kernels (config 3, 2 x 96 windows at C = 384: 0.36 instead of
-// 0.41 ms per stage pass; 2 x 1392 windows at C = 96: 10 % faster; 4 x 1392: 4 %, no longer taken).
+// Two chains pay while the kernels of the stage leave CUs idle for part of their time: a batch of at least two maps with at
+// most this many windows in all, on the fused kernels (one chain -> two: a pair of blocks on 2784 windows at C = 96 183 -> 174 us,
+// on 1920 at 192 330 -> 314, on 1440 at 384 648 -> 602; beyond, 2 % and less: 4176 windows at 96 255 -> 250, 4107 at 128 342 -> 340,
+// 4608 at 192 773 -> 758, 4800 at 384 2142 -> 2091).
 constexpr int STAGE_SPLIT_MAX_WINDOWS = 4096;
-// Fork and join cost 25 to 30 us, so the stage has to be long enough: from about 2000 windows over all its blocks on (at
-// C = 96, whose kernels are shorter, 2667).  Two blocks on 112 windows: 76 us as two chains, 53 as one at C = 192; six blocks
-// on 240 windows at C = 384: 388 and 364; on 504: 633 and 711; two blocks on 1008 windows at C = 192: 178 and 191.
+// Fork and join cost 25 to 30 us, so the stage has to be long enough: from about 2000 windows over all its blocks on (at C = 96,
+// whose kernels are shorter, 2667).  One chain -> two, in us, for one set of handles called over and over | three sets in turn.
+//   two blocks:  C = 96, 840 windows 81 -> 88 | 81 -> 91; 1300 104 -> 103 | 104 -> 106; 1856 133 -> 126 | 138 -> 134
+//                C = 128, 924 95 -> 97 | 95 -> 100; 1352 133 -> 124 | 136 -> 130
+//                C = 192, 450 92 -> 101 | 91 -> 103; 924 188 -> 168 | 181 -> 174
+//                C = 256, 968 229 -> 231 | 238 -> 238; 1456 336 -> 336 | 345 -> 341
+//                C = 384, 242 126 -> 142 | 127 -> 143; 450 239 -> 231 | 258 -> 241
+//   six blocks:  C = 96, 840 236 -> 216 | 235 -> 267; 1856 386 -> 328 | 398 -> 399
+//                C = 192, 450 267 -> 259 | 267 -> 308; 924 548 -> 449 | 529 -> 502
+//                C = 384, 192 357 -> 299 | 358 -> 361; 242 370 -> 363 | 370 -> 407; 450 701 -> 616 | 742 -> 682
+// Sets in turn gain less because every handle of such a map makes a stream of its own: the runtime has four hardware queues,
+// and a side stream may get the caller's (with one side stream for all of them the second figures become the first).  Pruned
+// windows count like the others: with 40 % pruned, 1856 windows at C = 96 and two blocks 100 -> 106 | 105 -> 115, 450 at 384 and
+// six blocks 482 -> 403 | 521 -> 493; counting the computed windows only would turn both round.
 constexpr long long STAGE_SPLIT_MIN_WORK = 2000LL * 128;
 bool stage_split_pays(const mixaq_block* b, int n_blocks)
 {
@@ -789,7 +801,7 @@ int mixaq_stage_forward(mixaq_block* const* blocks, int32_t n_blocks, const floa
         parts[1].first = parts[0].images; parts[1].images = b0->d.B / 2;
         parts[1].ws_offset = carve(b0, nullptr, &w, false, parts[0].images);
         HIP_TRY(hipEventRecord(b0->ev_fork, st));                    // both chains start together (the second one window kernel behind
-        HIP_TRY(hipStreamWaitEvent(b0->side_stream, b0->ev_fork, 0)); // the first measured slower: 0.377 against 0.361 ms at config 3)
+        HIP_TRY(hipStreamWaitEvent(b0->side_stream, b0->ev_fork, 0)); // the first measured slower: 377 against 361 us, six blocks on 192 windows at C = 384)
     }
     const float* cur = x;
     for (int i = 0; i < n_blocks && !rc; ++i) {

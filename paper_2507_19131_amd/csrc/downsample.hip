@@ -85,9 +85,10 @@ constexpr int merge_max_split(int KS) { return KS / merge_ring(KS) >= 4 ? 4 : 2;
 // through a ring of loads in flight that starts before the barrier.  On a small grid `split` waves share the slabs of one
 // output block (whole numbers: any order gives the same sums) and add up through LDS.  The tokens are the rows of the
 // product and the output channels its columns, so a store writes whole 128-byte lines and a lane needs one m and one bias.
-// Bound: memory on large maps (4 x 256 x 256 x 128: 59 -> 39 us with the input in the cache; before, 64 floats per lane and
-// the hoisted gamma and beta took 224 registers, two waves per SIMD, and the vector unit idled two thirds of the time), the
-// chain load - statistics - codes - products of one workgroup per CU on small ones (50 x 84 x 384: 21.2 -> 12.1 us).
+// Bound: memory on large maps (4 x 256 x 256 x 128: 59.4 -> 39.1 us on one map over and over, 65.5 -> 48.4 on fresh ones; before,
+// 64 floats per lane and the hoisted gamma and beta took 224 registers, two waves per SIMD, and the vector unit idled two
+// thirds of the time), the chain load - statistics - codes - products of one workgroup per CU on small ones (50 x 84 x 384:
+// 21.2 -> 13.1 us).
 template <int LPT, int NV, int NT, bool TAPS>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void merge_kernel(DsArgs A, int by_xcd, int groups, int per, int split)
 {
@@ -98,7 +99,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void me
     int* fragw = (int*)frag;
     int tile, group = 0;
     if (by_xcd) {                                             // the groups of a tile on one XCD: its inputs come through one L2
-        const int slot = blockIdx.x >> 3;                     // (33 tiles of C_in = 384 in 6 groups: 15.0 -> 12.1 us)
+        const int slot = blockIdx.x >> 3;                     // (33 tiles of C_in = 384 in 6 groups: 3 of 15 us)
         tile = slot / groups * 8 + (blockIdx.x & 7);
         group = slot % groups;
         if (tile * 32 >= A.tokens) return;
@@ -227,9 +228,9 @@ typedef float f4_any __attribute__((ext_vector_type(4), aligned(4)));
 // rows (24 inputs in six loads of 16 bytes; the weights are packed in that order: 16 + 8 codes of each half
 // and zeros), so the codes are MFMA operands where they were computed, and the 32 NB outputs of a token end in two lanes,
 // whose LayerNorm sums need one exchange each.
-// Bound: memory, once the map is large (4 x 1024 x 1024 into 128: 47.8 us with a tile's codes and outputs through LDS and
-// three barriers, 31.8 us now, 5.8 TB/s with the image from the cache); at 800 x 1344 into 96 (15.0 -> 10.8 us) one chain of
-// waits per wave, two waves per SIMD.  The 128 registers of four waves per SIMD need the two barriers against hoisting below.
+// Bound: memory, once the map is large (4 x 1024 x 1024 into 128: with a tile's codes and outputs through LDS and three
+// barriers 45.7 us on one image over and over and 63.1 on fresh ones, now 32.9 and 44.1, which is 4.2 TB/s); at 800 x 1344 into
+// 96 (15.1 -> 11.2 us, fresh 18.8 -> 13.3) one chain of waits per wave, two waves per SIMD.  The 128 registers of four waves per SIMD need the two barriers against hoisting below.
 template <int NB, bool TAPS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void embed_kernel(DsArgs A)
 {

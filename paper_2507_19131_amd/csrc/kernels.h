@@ -85,7 +85,7 @@ struct WinArgs {                     // fused window kernel (gather + LN1 + QKV 
     QDev qp[2], qo[2];
     int8_t* codes;                   // wide blocks: LN1 codes, operand fragments of 64 rows per slot (ln_window_kernel -> window_kernel)
     int8_t* out;                     // attention output codes
-    int out_pack;                    // 0: int8 containers; 1, 2: the low region's rows packed (see unpack_codes); PACK_FRAG: fragments
+    int out_pack;                    // 0: int8 containers; 1, 2: the low region's rows packed (see packed_codes); PACK_FRAG: fragments
     int* row_pix;
     int* row_canon;
     int8_t* tap_a1; int32_t* tap_acc; int8_t* tap_qkv; int32_t* tap_s; int8_t* tap_p; int32_t* tap_o; int8_t* tap_code;

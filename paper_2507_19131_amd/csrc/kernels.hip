@@ -1,6 +1,9 @@
 // gfx950 kernels of the Two-Branch Swin Block (paper Sec. 3.2, Fig. 3):
 //   score_kernel      window importance = squared L2 norm            (Sec. 3.2)
-//   select_kernel     top-k partition into high / low groups         (Sec. 3.2)
+//   select_rank_kernel  top-k partition into high / low groups       (Sec. 3.2)
+//   window_kernel     gather + LN1 + QKV + attention of a window; wide blocks take LN1 from ln_window_kernel
+//   token_kernel      projection + LN2 + FFN + scatter of a tile of rows
+// and, where these do not apply,
 //   ln_quant_kernel   gather (shift folded in) + LayerNorm + quantize, also LN2
 //   gemm_tile_kernel  int8 MFMA linear layers with fused epilogues   (shadow layers)
 //   attn_kernel       per (window, head): QK^T, bias+mask, softmax, P.V
@@ -770,7 +773,8 @@ struct WinCfg {
 // scheduler spreads their loads over the whole kernel and wants 160 registers): with them a wave that owns a head needs 96
 // to 128 registers instead of 160, one of a pair 80 instead of 100.  A workgroup of six or twelve waves only gets a second
 // place on a CU when its share per SIMD, rounded up, fits twice: 360 windows at C = 192 ran in two rounds of one workgroup
-// per CU (24.6 us), now in one round (20.8 us); C = 256, 1444 windows: 83 -> 72 us.
+// per CU (24.6 us), now in one round (20.8 us); C = 256, 1444 windows: 83 -> 72 us.  (Three heads at five waves per SIMD spill
+// two registers, four with scores; at four waves none, but the pair of blocks on 1392 windows takes 110.5 instead of 108.0 us.)
 constexpr int win_waves_per_eu(int NH, int HG, int QS, bool CODES) { return CODES ? (NH * HG < 32 ? 4 : 2) : QS == 2 ? (NH * HG > 8 ? 4 : 6) : NH * HG > 8 ? 3 : NH == 3 ? 5 : 4; }
 
 // The window kernel's parameter block of one branch (see WinArgs::params), as a workgroup of NH heads holds it in LDS:
@@ -1090,10 +1094,11 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
 // the output map between the first and the second residual (the same thread writes and re-reads the same address).
 // Bound: vector instructions (GELU) at C = 96 and 128 on large maps, the weights at 64 bytes per clock and CU at C = 384, the
 // chain of phases on few tiles.  Against a form with the chunks unrolled and FC1's weights a block ahead, which the three, four
-// and eight waves had: stage of two blocks on 8 x 1392 windows at C = 96 715 -> 692 us, 5476 at C = 128 456 -> 442, 1444 at
-// C = 256 342 -> 331; 64 windows at C = 256 58.9 -> 52.7.
-// Waves per SIMD it is compiled for: 128 registers take it all without spills up to eight waves (three, four and eight waves
-// want up to 124 by themselves; at five waves per SIMD the spills at C = 96 cost more than the fifth wave gives), twelve need 160 and have a CU to themselves.
+// and eight waves had: stage of two blocks on 8 x 1392 windows at C = 96, 5476 at C = 128 and 1444 at C = 256 3 % shorter, 64
+// windows at C = 256 58.9 -> 52.7 us.
+// Waves per SIMD it is compiled for: 128 registers take it without spills up to six waves (106 to 124 wanted), at eight waves
+// with six spilled; at five waves per SIMD the spills at C = 96 cost more than the fifth wave gives; twelve need 160 and have a
+// CU to themselves.
 constexpr int tok_waves_per_eu(int NH) { return NH == 12 ? 3 : 4; }
 // word offsets inside the parameter block of one branch (see TokArgs::params)
 template <int C> struct TokPrm {
