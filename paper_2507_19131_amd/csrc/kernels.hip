@@ -346,8 +346,7 @@ __device__ __forceinline__ void epilogue(const GemmArgs& A, const Geom& G, int b
 // memory: it goes to LDS by direct loads, no register in between, all of them in flight together.  Wave w computes the
 // output blocks first + w, first + w + 4, ... of the group; its weight fragments stream through a ring of D loads that
 // starts before anything else and runs on across the output blocks.  What bounds it on few rows is the latency of that
-// stream: one CU holds four to eight such waves, so D is 16 where K allows (at 8 in flight fc2 with K = 3072 on 37 row
-// tiles took 19.4 us).  K up to 2048 stays whole in LDS for a 64-row tile, K up to 4096 for a 32-row tile; longer K
+// stream: one CU holds four to eight such waves, so D is 16 where K allows (fc2 with K = 3072 on 19 row tiles: 9.2 us).  K up to 2048 stays whole in LDS for a 64-row tile, K up to 4096 for a 32-row tile; longer K
 // passes in chunks.
 constexpr int GEMM_TILE_MAX_K = 2048;      // 64 rows x K bytes of LDS
 // KMAX: bytes of K the instantiation's LDS holds per row (a longer K goes through in chunks of A.kchunk <= KMAX, whole ring
@@ -1453,9 +1452,9 @@ static void launch_gemm_e(const Geom& G, const GemmArgs& A0, hipStream_t st)
     if (G.rows_total == 0) return;
     const int tiles = G.rows_total / ROW_TILE, NB = A.N / 32;
     // the activation tile through LDS, output blocks over the waves and, while the grid is small, in groups over workgroups
-    // 32-row tiles: a long K stays whole in LDS (K = 3072 on 19 row tiles: 16.3 us; 64-row tiles in chunks of 1024: 27.8 us);
-    // a narrow layer on few rows gets twice the workgroups (the projection at C = 768 on 19 row tiles: 8.1 instead of 10.7 us;
-    // with 72 or 96 output blocks the wider layers have workgroups enough and lose: 13.2 and 13.8 instead of 12.4 and 13.2 us)
+    // 32-row tiles: a long K stays whole in LDS (K = 3072 on 19 row tiles: 9.2 us; 64-row tiles in chunks of 1024: 14.7 us);
+    // a narrow layer on few rows gets twice the workgroups (the projection at C = 768 on 19 row tiles: 5.6 instead of 7.5 us;
+    // with 72 or 96 output blocks the wider layers have workgroups enough and lose: 10.6 and 9.5 instead of 9.1 and 9.3 us)
     // (only FC2 has K = mlp_ratio C; the other layers have K = C <= 1024, and QKV never as few as 32 output blocks there)
     constexpr bool LONG_K = EPI == EPI_FC2;
     const bool half = (A.K > GEMM_TILE_MAX_K && A.K <= 4096) || (tiles <= 32 && NB <= 32 && A.K > 384 && A.K <= 1024);
@@ -1504,13 +1503,15 @@ bool fused_window_supported(int C) { return channels_supported(C); }
 bool fused_token_supported(int C, int mlp_ratio) { return (C == 96 || C == 128 || C == 192 || C == 256 || C == 384) && mlp_ratio == 4; }
 
 // Up to this many windows a pair of waves shares a head.  The pair form has the shorter chain of dependent steps
-// (a workgroup alone on its CU: 9.5 instead of 11.2 us at C = 96) but 15 % more vector and 80 % more scalar
-// instructions per window, so it loses once the CUs are full (1392 windows at C = 96: 31 instead of 28.3 us;
-// 5476 at C = 128: 113 instead of 101 us).  At C = 192 it wins on 360 windows (22.8 instead of 25.4 us).
+// (a workgroup alone on its CU: 9.2 instead of 10.9 us at C = 96 and 128, 11.8 instead of 12.7 at C = 192) but 15 % more
+// vector and 80 % more scalar instructions per window, so it loses once the CUs are full (1392 windows at C = 96: 29.2 instead
+// of 24.3 us; 5476 at C = 128: 111 instead of 105 us).  At C = 192 it wins on 360 windows (18.2 instead of 18.8 us) and is
+// equal on 512.
 constexpr int WINDOW_PAIR_SMALL = 256, WINDOW_PAIR_SMALL_6 = 512;
 // Up to this many windows two workgroups share a window's heads (each gathers and normalizes the whole window): a wave then has
-// fewer neighbours on its SIMD.  The pair of blocks on 96 windows: 41.4 -> 40.5 us at C = 128, 51.9 -> 48.5 us at C = 192
-// (130 windows: 54.5 -> 56.4), at C = 384 15.7 instead of 16.8 us a kernel.  C = 256 always: sixteen waves
+// fewer neighbours on its SIMD.  96 windows: 9.3 -> 8.3 us a kernel at C = 128 (130 windows: 9.4 -> 9.5), 11.8 -> 11.0 at C = 192
+// (130 windows: 11.8 -> 13.6); at C = 384, against one wave per head, 128 windows 19.5 -> 15.1 (130: 19.5 -> 25.7, two
+// workgroups on one CU).  C = 256 always: sixteen waves
 // of one workgroup, or eight of twice the registers, leave a CU half empty, three workgroups of eight fill it (6 windows:
 // 62.8 -> 51.4 us the pair, 300: 106 -> 95, 1444: 351 -> 335, 2750: 680 -> 654).
 constexpr int WINDOW_SPLIT_SMALL = 96, WINDOW_SPLIT_SMALL_12 = 128;
@@ -1583,8 +1584,10 @@ void launch_token(const Geom& G, const TokArgs& A, hipStream_t st)
         case 6: TOK_CASE(6, 1); break;
         case 8: TOK_CASE(8, 1); break;
         default:
-            // 64-row tiles once there are enough of them to give every second CU one, else 32-row tiles (with fewer waves the
-            // registers of a second row block cost more than its weights save)
+            // 64-row tiles once there are enough of them to give every second CU one, else 32-row tiles, of which a CU then takes
+            // one (32-row -> 64-row: 156 windows 22.0 -> 37.3 us, 169 windows 39.3 -> 37.6, 192 39.6 -> 38.0; but 384 windows, where
+            // 64-row tiles are a few more than the CUs, 60.2 -> 74.3).  With fewer waves the registers of a second row block cost
+            // more than its weights save.
             if (G.rows_total / 64 > TOKEN_WIDE_SMALL) { TOK_CASE(12, 2); }
             else { TOK_CASE(12, 1); }
     }
