@@ -630,27 +630,26 @@ static int block_create(const mixaq_block_desc* desc, const mixaq_shared_params*
         gelu_table(tab.data());
         b->mem.add(tab, &b->gelu_tab);
     }
-    b->fused_window = fused_window_supported(C);
+    b->fused_window = true;   // every width has a form of the window kernel
     b->fused_token = fused_token_supported(C, desc->mlp_ratio);
-    if (b->fused_window)      // parameter blocks of the window kernel: LN1, then the QKV constants head by head
-        for (int br = 0; br < 2; ++br) {
-            std::vector<float> blkp = hln[br][0];
-            blkp.insert(blkp.end(), hln[br][1].begin(), hln[br][1].end());
-            const Linear& L = b->qkv;
-            for (int h = 0; h < heads; ++h)
-                for (int which = 0; which < 3; ++which) {
-                    const int n0 = which * C + h * HD;
-                    blkp.insert(blkp.end(), L.hm[br].begin() + n0, L.hm[br].begin() + n0 + HD);
-                    blkp.insert(blkp.end(), L.hb[br].begin() + n0, L.hb[br].begin() + n0 + HD);
-                    const size_t at = blkp.size();
-                    blkp.resize(at + HD);
-                    memcpy(&blkp[at], &L.hnc[br][n0], HD * 4);
-                }
-            b->mem.add(blkp, &b->win_params[br]);
-        }
+    for (int br = 0; br < 2; ++br) {      // parameter blocks of the window kernel: LN1, then the QKV constants head by head
+        std::vector<float> blkp = hln[br][0];
+        blkp.insert(blkp.end(), hln[br][1].begin(), hln[br][1].end());
+        const Linear& L = b->qkv;
+        for (int h = 0; h < heads; ++h)
+            for (int which = 0; which < 3; ++which) {
+                const int n0 = which * C + h * HD;
+                blkp.insert(blkp.end(), L.hm[br].begin() + n0, L.hm[br].begin() + n0 + HD);
+                blkp.insert(blkp.end(), L.hb[br].begin() + n0, L.hb[br].begin() + n0 + HD);
+                const size_t at = blkp.size();
+                blkp.resize(at + HD);
+                memcpy(&blkp[at], &L.hnc[br][n0], HD * 4);
+            }
+        b->mem.add(blkp, &b->win_params[br]);
+    }
     // Both fused kernels present: the low branch's attention-output codes cross between them packed (two or four
     // per byte, offset-binary); the projection of packed rows then starts at -(zp + offset) * colsum.
-    if (b->fused_window && b->fused_token) b->ao_pack = pack_mode(desc->act_bits_low);
+    if (b->fused_token) b->ao_pack = pack_mode(desc->act_bits_low);
     if (b->fused_token) {     // parameter blocks of the token kernel
         for (int br = 0; br < 2; ++br) {
             std::vector<float> blkp(((size_t)8 * C + 3 * F + 255) / 256 * 256, 0.0f);      // whole 1 KB pieces: see token_stage
@@ -853,11 +852,8 @@ int mixaq_block_forward_static(const mixaq_block* blk, const float* x, const int
 int mixaq_block_set_fused(mixaq_block* blk, int32_t enable)
 {
     if (!blk) return fail(MIXAQ_E_NULL, "block is NULL");
-    const bool w_ok = fused_window_supported(blk->d.C), t_ok = fused_token_supported(blk->d.C, blk->d.mlp_ratio);
-    if (enable && !w_ok && !t_ok)
-        return fail(MIXAQ_E_SHAPE, "no fused kernel covers C = %d, mlp_ratio = %d", blk->d.C, blk->d.mlp_ratio);
-    blk->fused_window = enable != 0 && w_ok;
-    blk->fused_token = enable != 0 && t_ok;
+    blk->fused_window = enable != 0;
+    blk->fused_token = enable != 0 && fused_token_supported(blk->d.C, blk->d.mlp_ratio);
     return MIXAQ_OK;
 }
 

@@ -116,7 +116,6 @@ struct TokArgs {                     // fused token kernel (proj + LN2 + FFN + s
 };
 
 bool channels_supported(int C);
-bool fused_window_supported(int C);
 bool fused_token_supported(int C, int mlp_ratio);
 void launch_window(const Geom& G, const WinArgs& A, hipStream_t st);
 void launch_token(const Geom& G, const TokArgs& A, hipStream_t st);

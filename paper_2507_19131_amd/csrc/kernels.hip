@@ -1499,7 +1499,6 @@ void launch_gemm(const Geom& G, const GemmArgs& A, int epi, hipStream_t st)
 }
 
 // the window kernel (gather + LN1 + QKV + attention) and the token kernel (proj + LN2 + FFN + scatter) are chosen separately
-bool fused_window_supported(int C) { return channels_supported(C); }
 bool fused_token_supported(int C, int mlp_ratio) { return (C == 96 || C == 128 || C == 192 || C == 256 || C == 384) && mlp_ratio == 4; }
 
 // Up to this many windows a pair of waves shares a head.  The pair form has the shorter chain of dependent steps

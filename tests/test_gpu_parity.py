@@ -487,3 +487,24 @@ def test_wide_blocks_from_scores_and_lists_with_pruning(C, heads, shift, kh_frac
     oy, _ = O.block_forward(inp, x, o_perm, kh, k_low=kl, threads=16)
     assert np.array_equal(y.cpu().numpy(), oy)
     assert torch.equal(y, y_list)
+
+
+@pytest.mark.parametrize("C,heads,mlp_ratio", [(96, 3, 4), (384, 12, 3), (768, 24, 4)])
+def test_switching_between_the_implementations_and_back(C, heads, mlp_ratio):
+    """mixaq_block_set_fused is accepted in both directions at every width and gives the same bits; 1 is the default again."""
+    spec, inp, x, k = _case(2, 20, 27, C, heads, 3, 0.5, 48, blobs=True, mlp_ratio=mlp_ratio)
+    xt = torch.from_numpy(x).cuda()
+    print("switching", C, mlp_ratio, flush=True)
+    with gh.GpuBlock(inp) as gb:
+        outs, names = [], []
+        for enable in (None, 0, 1):
+            if enable is not None:
+                M.mixaq_block_set_fused(gb.blk, enable)
+            outs.append(gb.forward(xt, None, k))
+            y = torch.empty_like(xt)
+            ms = M.mixaq_block_forward_profile(gb.blk, xt, None, k, y, gb.ws, repeats=1)
+            names.append({n for n, v in ms.items() if v > 0})
+        torch.cuda.synchronize()
+    assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
+    assert names[0] == names[2] and "window_ln1_qkv_attention" in names[0]
+    assert "window_ln1_qkv_attention" not in names[1] and "qkv_gemm" in names[1]
