@@ -140,7 +140,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void me
             for (int k = 0; k < NV; ++k) s += sum4(v[p][k].x, v[p][k].y, v[p][k].z, v[p][k].w);
             mean[p] = ln_mean(lanes_sum<LPT>(s), K);
 #pragma unroll
-            for (int k = 0; k < NV; ++k) sq += centred4(v[p][k].x, v[p][k].y, v[p][k].z, v[p][k].w, mean[p]);
+            for (int k = 0; k < NV; ++k) sq += centred4<true>(v[p][k].x, v[p][k].y, v[p][k].z, v[p][k].w, mean[p]);
             rstd[p] = ln_rstd(lanes_sum<LPT>(sq), K, A.eps);
         }
 #pragma unroll
@@ -302,7 +302,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void e
     const float mean = ln_mean(half_sum(s), N);
     double sq = 0.0;
 #pragma unroll
-    for (int k = 0; k < NB * 4; ++k) sq += centred4(f[k * 4], f[k * 4 + 1], f[k * 4 + 2], f[k * 4 + 3], mean);
+    for (int k = 0; k < NB * 4; ++k) sq += centred4<NB != 3>(f[k * 4], f[k * 4 + 1], f[k * 4 + 2], f[k * 4 + 3], mean);
     const float rstd = ln_rstd(half_sum(sq), N, A.eps);
     if (!valid) return;
     float* out = A.y + (size_t)tok * N + g * 4;

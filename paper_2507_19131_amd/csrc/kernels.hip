@@ -46,7 +46,7 @@ __device__ __forceinline__ void token_ln_stats(const float4 (&v)[NV], int C, flo
 #pragma unroll
     for (int k = 0; k < NV; ++k) {
         if (NV > 8 && k % 4 == 0) __builtin_amdgcn_sched_barrier(0);
-        q += centred4(v[k].x, v[k].y, v[k].z, v[k].w, mean);
+        q += centred4<true>(v[k].x, v[k].y, v[k].z, v[k].w, mean);
     }
     rstd = ln_rstd(group_sum<LPT>(q, first), C, eps);
 }
@@ -1280,7 +1280,7 @@ __global__ __launch_bounds__(NH * 64) __attribute__((amdgpu_waves_per_eu(tok_wav
             for (int w2i = 0; w2i < NH; ++w2i) s += part[0][w2i][rb * 32 + j];
             mean[rb] = ln_mean(s, C);
 #pragma unroll
-            for (int r = 0; r < 16; r += 4) q += centred4(h[rb][r], h[rb][r + 1], h[rb][r + 2], h[rb][r + 3], mean[rb]);
+            for (int r = 0; r < 16; r += 4) q += centred4<false>(h[rb][r], h[rb][r + 1], h[rb][r + 2], h[rb][r + 3], mean[rb]);
             q = half_sum(q);
             if (g == 0) part[1][wave][rb * 32 + j] = q;
         }

@@ -65,7 +65,7 @@ PROGRAM = textwrap.dedent(r'''
                     for (float& v : x) v = normal(gen) + (float)ratio;
                     const double s = reduce(x, o, [](const float* v, double a) { return a + sum4(v[0], v[1], v[2], v[3]); });
                     const float mean = ln_mean(s, o.C);
-                    const double c = reduce(x, o, [&](const float* v, double a) { return a + centred4(v[0], v[1], v[2], v[3], mean); });
+                    const double c = reduce(x, o, [&](const float* v, double a) { return a + centred4<true>(v[0], v[1], v[2], v[3], mean); });
                     const double m = mean;
                     const double plain = reduce(x, o, [&](const float* v, double a) {        // every product rounded on its own
                         const double d0 = v[0] - m, d1 = v[1] - m, d2 = v[2] - m, d3 = v[3] - m;
