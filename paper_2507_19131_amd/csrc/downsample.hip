@@ -229,8 +229,9 @@ typedef float f4_any __attribute__((ext_vector_type(4), aligned(4)));
 // and zeros), so the codes are MFMA operands where they were computed, and the 32 NB outputs of a token end in two lanes,
 // whose LayerNorm sums need one exchange each.
 // Bound: memory, once the map is large (4 x 1024 x 1024 into 128: with a tile's codes and outputs through LDS and three
-// barriers 45.7 us on one image over and over and 63.1 on fresh ones, now 32.9 and 44.1, which is 4.2 TB/s); at 800 x 1344 into
-// 96 (15.1 -> 11.0 us, fresh 18.8 -> 13.2) one chain of waits per wave, two waves per SIMD.  The 128 registers of four waves per SIMD need the two barriers against hoisting below.
+// barriers 45.7 us on one image over and over and 63.1 on fresh ones, now 33.3 and 43.9, which is 4.2 TB/s); at 800 x 1344 into
+// 96 (15.1 -> 11.0 us, fresh 18.8 -> 13.2) one chain of waits per wave, two waves per SIMD.  The 128 registers of four waves per
+// SIMD need the two barriers against hoisting below.
 template <int NB, bool TAPS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void embed_kernel(DsArgs A)
 {
