@@ -79,8 +79,8 @@ constexpr int merge_max_split(int KS) { return KS / merge_ring(KS) >= 4 ? 4 : 2;
 // per group of output blocks.
 // Phase 1: LPT lanes per token, a quarter of them per neighbour, NV float4 each; the workgroup grows with C_in so that
 // a lane's share of the 32 tokens is 48 or 64 floats, which it requests all at once: the kernel waits once for memory,
-// and 128 registers leave room for sixteen waves per CU.  LayerNorm statistics in binary64 over the lane group, quantize, codes to LDS as MFMA operand fragments (slabs and halves a little apart, so that the lanes of a wave spread
-// over the banks).
+// and 128 registers leave room for sixteen waves per CU.  LayerNorm statistics in binary64 over the lane group, quantize,
+// codes to LDS as MFMA operand fragments (slabs and halves a little apart, so that the lanes of a wave spread over the banks).
 // Phase 2: wave w takes the output blocks first + w, first + w + waves, ... of its group; the weight fragments stream
 // through a ring of loads in flight that starts before the barrier.  On a small grid `split` waves share the slabs of one
 // output block (whole numbers: any order gives the same sums) and add up through LDS.  The tokens are the rows of the

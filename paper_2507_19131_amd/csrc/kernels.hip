@@ -346,8 +346,8 @@ __device__ __forceinline__ void epilogue(const GemmArgs& A, const Geom& G, int b
 // memory: it goes to LDS by direct loads, no register in between, all of them in flight together.  Wave w computes the
 // output blocks first + w, first + w + 4, ... of the group; its weight fragments stream through a ring of D loads that
 // starts before anything else and runs on across the output blocks.  What bounds it on few rows is the latency of that
-// stream: one CU holds four to eight such waves, so D is 16 where K allows (fc2 with K = 3072 on 19 row tiles: 9.2 us).  K up to 2048 stays whole in LDS for a 64-row tile, K up to 4096 for a 32-row tile; longer K
-// passes in chunks.
+// stream: one CU holds four to eight such waves, so D is 16 where K allows (fc2 with K = 3072 on 19 row tiles: 9.2 us).
+// K up to 2048 stays whole in LDS for a 64-row tile, K up to 4096 for a 32-row tile; longer K passes in chunks.
 constexpr int GEMM_TILE_MAX_K = 2048;      // 64 rows x K bytes of LDS
 // KMAX: bytes of K the instantiation's LDS holds per row (a longer K goes through in chunks of A.kchunk <= KMAX, whole ring
 // turns each)
