@@ -2,6 +2,7 @@
 // parameter packing at create time, workspace layout and the launch sequence.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -125,6 +126,7 @@ struct Linear {           // one shadow layer prepared for the device
 struct mixaq_block {
     mixaq_block_desc d;
     int Hp, Wp, nWc, nW;
+    FastDiv by_nW, by_nWc;
     Arena mem;                 // everything the block keeps on the device
     Linear qkv, proj, fc1, fc2;
     float* ln_gamma[2][2];     // [which LN][branch]
@@ -134,7 +136,7 @@ struct mixaq_block {
     float* bias2 = nullptr;
     QDev q_in[2], q_qkv[2][3], q_p[2], q_ao[2], q_fc1in[2], q_fc2in[2];
     float m2[2], m_o[2];
-    bool exp_floor = false;    // the softmax exponents need their floor (see exp2_pinned)
+    int exp_floor[2] = {3, 3}; // per branch, which softmax exponents need their floor: bit 0 unmasked windows, bit 1 windows with masked pairs
     float* tok_params[2] = {nullptr, nullptr};   // parameter blocks of the fused token kernel
     float* win_params[2] = {nullptr, nullptr};   // parameter blocks of the fused window kernel
     int ao_pack = 0;           // packing of the low branch's attention-output codes between the two fused kernels
@@ -281,6 +283,8 @@ void make_geom(const mixaq_block* b, int k_hi, int k_lo, Geom* G, int images = 0
     G->rows_lo = nB * G->k_lo * TOK;
     G->base_lo = round_up(G->rows_hi, REGION_ALIGN);
     G->rows_total = G->base_lo + round_up(G->rows_lo, REGION_ALIGN);
+    G->by_nW = b->by_nW; G->by_nWc = b->by_nWc;
+    G->by_hi = FastDiv(std::max(k_hi, 1)); G->by_lo = FastDiv(std::max(k_lo, 1));
 }
 
 struct Workspace {
@@ -400,11 +404,10 @@ int forward_impl(const mixaq_block* blk, const float* x, const int32_t* perm, co
             wa.params[br] = blk->win_params[br]; wa.q_in[br] = blk->q_in[br];
             for (int k = 0; k < 3; ++k) wa.q_qkv[br][k] = blk->q_qkv[br][k];
             wa.m2[br] = blk->m2[br]; wa.m_o[br] = blk->m_o[br]; wa.qp[br] = blk->q_p[br]; wa.qo[br] = blk->q_ao[br];
+            wa.floor[br] = blk->exp_floor[br];
         }
         wa.tap_a1 = tp.a_qkv_in; wa.tap_acc = tp.acc_qkv; wa.tap_qkv = tp.qkv; wa.tap_s = tp.acc_s; wa.tap_p = tp.p;
         wa.tap_o = tp.acc_o; wa.tap_code = tp.a_proj_in;
-        wa.poly = pinned_coefficients();
-        wa.floor = blk->exp_floor;
         wa.taps = taps != nullptr;
         mark(9);
         for (int r = 0; r < reps; ++r) launch_window(G, wa, st);       // also forwards pruned windows
@@ -422,9 +425,7 @@ int forward_impl(const mixaq_block* blk, const float* x, const int32_t* perm, co
         for (int r = 0; r < reps; ++r) launch_gemm(G, ga, EPI_QKV, st);
         AttnArgs aa = {};
         aa.qkv = ws.qkv; aa.perm = perm; aa.bias2 = blk->bias2; aa.out = ws.ao;
-        for (int br = 0; br < 2; ++br) { aa.m2[br] = blk->m2[br]; aa.m_o[br] = blk->m_o[br]; aa.qp[br] = blk->q_p[br]; aa.qo[br] = blk->q_ao[br]; }
-        aa.poly = pinned_coefficients();
-        aa.floor = blk->exp_floor;
+        for (int br = 0; br < 2; ++br) { aa.m2[br] = blk->m2[br]; aa.m_o[br] = blk->m_o[br]; aa.qp[br] = blk->q_p[br]; aa.qo[br] = blk->q_ao[br]; aa.floor[br] = blk->exp_floor[br]; }
         aa.tap_s = tp.acc_s; aa.tap_p = tp.p; aa.tap_o = tp.acc_o; aa.tap_code = tp.a_proj_in;
         mark(4);
         for (int r = 0; r < reps; ++r) launch_attn(G, aa, st);
@@ -553,6 +554,7 @@ static int block_create(const mixaq_block_desc* desc, const mixaq_shared_params*
     b->d = *desc;
     b->Hp = round_up(desc->H, WS); b->Wp = round_up(desc->W, WS);
     b->nWc = b->Wp / WS; b->nW = (b->Hp / WS) * b->nWc;
+    b->by_nW = FastDiv(b->nW); b->by_nWc = FastDiv(b->nWc);
     const int C = desc->C, F = C * desc->mlp_ratio, heads = desc->heads;
     BlockOwner owner{b};
     b->mem.reserve((size_t)4 * C * C + 2 * (size_t)F * C + (size_t)heads * 4 * TOK * 64 * 4 + (size_t)C * 800 + 65536);
@@ -594,34 +596,62 @@ static int block_create(const mixaq_block_desc* desc, const mixaq_shared_params*
         if ((rc = download(sh->score_beta, (size_t)C, tmp))) return bail(rc);
         b->mem.add(tmp, &b->score_beta);
     }
-    // Logits are finite without the floor where the table and the largest product (|S| <= 32 * 128 * 128) are at most LOGIT_MAX;
-    // a bias that shuts a pair out altogether (-infinity), anything else that is no ordinary number, and quantizers for which a
-    // probability of 2^-99 is not zero take the floor.
-    constexpr float LOGIT_MAX = 1e30f, STEPS_MAX = 0x1p60f;
-    for (int br = 0; br < 2; ++br)
-        if (!(b->m2[br] * (float)(HD * 128 * 128) <= LOGIT_MAX) || b->q_p[br].inv_s > STEPS_MAX) b->exp_floor = true;
-    // (relative position bias + shift mask) * log2(e), transposed to [type][head][key][query 64]
+    // (relative position bias + shift mask) * log2(e), transposed to [type][head][key][query 64], and which softmax exponents need
+    // their floor (see exp2_pinned).  The products of a branch lie in [-P, P], P = 32 * 2^(2 bits - 2) steps of m2, so an unmasked
+    // logit is at most 2 P and the span of its table row below the row's maximum: no floor while that is under 99 (1 is left for the
+    // roundings).  A masked pair is worth -100 log2(e) or less, e^-100 of a probability, which neither changes a denominator (at
+    // least 1) nor makes a code: any value that keeps its exponent far below 2^-53 and above 2^-126 gives the same bits.  Where the
+    // products are narrow enough its table entry is 90 below the row's largest unmasked one, and such windows need no floor either
+    // (it costs 51 vector instructions per query block); otherwise they take it.  Anything that is no ordinary number takes it too.
     {
+        constexpr float MASKED_BELOW = 90.0f, MASKED_SPAN = 34.0f, STEPS_MAX = 0x1p40f;   // exponents of masked pairs: -90 +- 34
+        float span[2];                                       // 2 P
+        bool narrow = true;
+        for (int br = 0; br < 2; ++br) {
+            span[br] = 2.0f * HD * (float)(1 << (2 * (br == 0 ? desc->act_bits_high : desc->act_bits_low) - 2)) * b->m2[br];
+            narrow = narrow && span[br] <= MASKED_SPAN && b->q_p[br].inv_s <= STEPS_MAX;
+        }
         std::vector<float> rpb;
         if ((rc = download(sh->rel_pos_bias, (size_t)heads * TOK * TOK, rpb))) return bail(rc);
         std::vector<float> tab((size_t)4 * heads * TOK * 64, 0.0f);
         const int nWr = b->Hp / WS;
+        std::vector<std::pair<size_t, float>> raised;
+        float widest = 0.0f;                                 // of the unmasked entries of a row, over all rows
         for (int type = 0; type < 4; ++type) {
             int wr = (type & 2) ? nWr - 1 : 0, wc = (type & 1) ? b->nWc - 1 : 0;
             for (int h = 0; h < heads; ++h)
-                for (int i = 0; i < TOK; ++i)
+                for (int i = 0; i < TOK; ++i) {
+                    float row[TOK], row_min = INFINITY, row_max = -INFINITY;
+                    bool masked[TOK], ordinary = true;
                     for (int j = 0; j < TOK; ++j) {
                         float v = rpb[((size_t)h * TOK + i) * TOK + j];
+                        masked[j] = false;
                         if (desc->shift > 0) {
                             int ri, ci, rj, cj;
                             token_src(b, wr, wc, i, &ri, &ci);
                             token_src(b, wr, wc, j, &rj, &cj);
-                            if (!(std::abs(ri - rj) < WS && std::abs(ci - cj) < WS)) v = v + MASK_VALUE;
+                            masked[j] = !(std::abs(ri - rj) < WS && std::abs(ci - cj) < WS);
+                            if (masked[j]) v = v + MASK_VALUE;
                         }
-                        v = v * LOG2E_F;
-                        tab[(((size_t)type * heads + h) * TOK + j) * 64 + i] = v;
-                        if (!(std::fabs(v) <= LOGIT_MAX)) b->exp_floor = true;
+                        row[j] = v = v * LOG2E_F;
+                        ordinary = ordinary && std::isfinite(v);
+                        if (!masked[j]) { row_min = std::min(row_min, v); row_max = std::max(row_max, v); }
                     }
+                    widest = ordinary ? std::max(widest, row_max - row_min) : INFINITY;
+                    for (int j = 0; j < TOK; ++j) {
+                        const size_t at = (((size_t)type * heads + h) * TOK + j) * 64 + i;
+                        tab[at] = row[j];
+                        if (!masked[j]) continue;
+                        narrow = narrow && row[j] <= row_max - MASKED_BELOW;      // not where a large bias makes up for the mask
+                        if (narrow) raised.push_back({at, row_max - MASKED_BELOW});
+                    }
+                }
+        }
+        if (narrow && std::isfinite(widest)) for (const auto& r : raised) tab[r.first] = r.second;
+        else narrow = false;
+        for (int br = 0; br < 2; ++br) {
+            const bool wide = !(span[br] + widest <= -EXP2_FLOOR - 1.0f);
+            b->exp_floor[br] = (wide ? 1 : 0) | (wide || !narrow ? 2 : 0);
         }
         b->mem.add(tab, &b->bias2);
     }

@@ -6,13 +6,6 @@ namespace mixaq {
 
 enum { EPI_QKV = 0, EPI_PROJ = 1, EPI_FC1 = 2, EPI_FC2 = 3 };
 
-// the pinned coefficients of 2^r (host side fills kernel arguments with them)
-inline PolyCoef pinned_coefficients()
-{
-    PolyCoef P = {{0x1.000002p+0f, 0x1.62e430p-1f, 0x1.ebf906p-3f, 0x1.c6aeccp-5f, 0x1.3d107cp-7f, 0x1.5f48c8p-10f}};
-    return P;
-}
-
 // Host side: the GELU_K x 4 coefficient table of gelu_pinned (api.hip uploads it once per block).
 void gelu_table(float* tab);
 
@@ -63,8 +56,7 @@ struct AttnArgs {
     int8_t* tap_p;
     int32_t* tap_o;
     int8_t* tap_code;
-    PolyCoef poly;
-    bool floor;                      // the exponents need their floor: see exp2_pinned
+    int floor[2];                    // which exponents need their floor: bit 0 windows without, bit 1 windows with masked pairs
 };
 
 struct WinArgs {                     // fused window kernel (gather + LN1 + QKV + attention)
@@ -89,8 +81,7 @@ struct WinArgs {                     // fused window kernel (gather + LN1 + QKV 
     int* row_pix;
     int* row_canon;
     int8_t* tap_a1; int32_t* tap_acc; int8_t* tap_qkv; int32_t* tap_s; int8_t* tap_p; int32_t* tap_o; int8_t* tap_code;
-    PolyCoef poly;
-    bool floor;                      // the exponents need their floor: see exp2_pinned
+    int floor[2];                    // which exponents need their floor: bit 0 windows without, bit 1 windows with masked pairs
     bool taps;                       // any tap pointer set
 };
 

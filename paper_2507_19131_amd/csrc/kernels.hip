@@ -17,24 +17,27 @@
 namespace mixaq {
 
 // ------------------------------------------------------------------ helpers
-// sum over a group of W consecutive lanes (the group does not straddle a wave); every lane of the
-// group gets the same bits: a butterfly for powers of two, a fixed-order gather otherwise
-// (first = the group's first lane).
+// sum over a group of W consecutive lanes (the group does not straddle a wave; first = its first lane); every lane of the
+// group gets the same bits: a butterfly for powers of two; otherwise W = 3 * 2^k, a butterfly over the aligned subgroups of
+// 2^k lanes, then three shuffles (over all W lanes they were 24 permutes through the LDS pipe and eleven dependent additions at
+// W = 12).
 template <int W>
 __device__ __forceinline__ double group_sum(double v, int first = 0)
 {
-    if ((W & (W - 1)) == 0) return lanes_sum<W>(v);
-    double tot = __shfl(v, first, 64);
-#pragma unroll
-    for (int k = 1; k < W; ++k) tot += __shfl(v, first + k, 64);
-    return tot;
+    if constexpr ((W & (W - 1)) == 0) return lanes_sum<W>(v);
+    else {
+        constexpr int P = W & -W;
+        static_assert(W == 3 * P && P <= 4, "three aligned subgroups of one quad at most");
+        v = lanes_sum<P>(v);
+        return (__shfl(v, first, 64) + __shfl(v, first + P, 64)) + __shfl(v, first + 2 * P, 64);
+    }
 }
 
 // LayerNorm of one token spread over LPT lanes (NV float4 per lane; channel of
 // element e of vector k on lane i: (k*LPT + i)*4 + e).  Mean and variance in
 // binary64, rounded once (see ln_stats.h).
 template <int LPT, int NV>
-__device__ __forceinline__ void token_ln_stats(const float4 (&v)[NV], int C, float eps, float& mean, float& rstd, int first = 0)
+__device__ __forceinline__ void token_ln_stats(float4 (&v)[NV], int C, float eps, float& mean, float& rstd, int first = 0)
 {
     double s = 0.0, q = 0.0;
 #pragma unroll
@@ -87,8 +90,8 @@ __global__ __launch_bounds__(NT) void score_kernel(Geom G, const float* __restri
                                                    double* __restrict__ scores)
 {
     const int wid = blockIdx.x;                       // b*nW + w
-    const int b = wid / G.nW, w = wid - b * G.nW;
-    const int wr = w / G.nWc, wc = w - wr * G.nWc;
+    const int b = G.by_nW(wid), w = wid - b * G.nW;
+    const int wr = G.by_nWc(w), wc = w - wr * G.nWc;
     const int grp = threadIdx.x / LPT, sub = threadIdx.x % LPT;
     constexpr int TP = NT / LPT;
     double acc = 0.0;
@@ -237,7 +240,7 @@ __global__ __launch_bounds__(256) void bypass_kernel(Geom G, const int* __restri
     const int kept = G.k_hi + G.k_lo, n_pruned = G.nW - kept;
     const int b = blockIdx.x / n_pruned, jpos = kept + blockIdx.x % n_pruned;
     const int w = perm[b * G.nW + jpos];
-    const int wr = w / G.nWc, wc = w - wr * G.nWc;
+    const int wr = G.by_nWc(w), wc = w - wr * G.nWc;
     const int c4 = G.C / 4;
     for (int i = threadIdx.x; i < TOK * c4; i += 256) {
         const int t = i / c4, k = i - t * c4, tr = t / WS, tc = t - tr * WS;
@@ -269,7 +272,7 @@ __global__ __launch_bounds__(256) void ln_quant_kernel(Geom G, LnArgs A)
         canon = A.row_canon[row];
         pix = 0;
     }
-    const QDev q = A.q[branch];
+    const QDev q = in_vgpr(A.q[branch]);
     float4 v[NV];
     const bool real = canon >= 0 && pix >= 0;
     if (real) {
@@ -472,10 +475,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RT * KMAX <
 // (an integer multiply is a quarter-rate instruction; and starting the accumulators there costs no instruction, where
 // subtracting afterwards took one per output element).
 struct AttnCore {
-    const PolyCoef* poly;
     const float* bq;          // (bias + mask) * log2e of query j of query block 0 at key g*4, in the [49 keys][64 queries]
                               // table of this head and mask type: key k + g*4, query block ib is bq[k * 64 + ib * 32]
-    float m2;
+    float m2, c5;             // in vector registers, like qp's factor and addend
     QDev qp;
     const int* nzcsum;        // [HD], LDS
     bool floor;               // see exp2_pinned; scalar
@@ -511,7 +513,7 @@ __device__ __forceinline__ v16i attention_core(const v4i& qf, const v4i (&kf)[2]
                 lg[kb][r] = v;
             }
         mx = half_max(mx);
-        if (A.floor) {                                                    // infinities and NaN of the table or the products end here
+        if (A.floor) {                                                    // masked pairs, infinities and NaN end here
 #pragma unroll
             for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
@@ -522,13 +524,21 @@ __device__ __forceinline__ v16i attention_core(const v4i& qf, const v4i (&kf)[2]
 #pragma unroll
         for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int key = kb * 32 + (r >> 2) * 8 + (r & 3);
-                if (key < TOK) {
-                    const int kk = key + g * 4;
-                    float e = kk < TOK ? exp2_pinned(lg[kb][r] - mx, *A.poly) : 0.0f;
-                    lg[kb][r] = e;
-                    den += (double)e;
+            for (int r = 0; r < 16; r += 4) {
+                const int key = kb * 32 + (r >> 2) * 8;
+                if (key + 3 + 4 < TOK) {                                  // four keys, valid for both halves
+                    float y[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) y[e] = lg[kb][r + e] - mx;
+                    exp2_pinned<4>(y, A.c5);
+                    den += sum4(y[0], y[1], y[2], y[3]);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) lg[kb][r + e] = y[e];
+                } else if (key < TOK) {                                   // the last key, of the lower half only
+                    float y = lg[kb][r] - mx;
+                    exp2_pinned<1>(&y, A.c5);
+                    lg[kb][r] = key + g * 4 < TOK ? y : 0.0f;
+                    den += (double)lg[kb][r];
                 }
             }
         den = half_sum(den);
@@ -612,14 +622,14 @@ __device__ __forceinline__ void attention_store(const v16i& o, const QDev& qo, f
 __device__ __forceinline__ void slot_info(const Geom& G, int slot, int& branch, int& row0, int& canon_slot)
 {
     const int n_hi = G.B * G.k_hi;
-    if (slot < n_hi) { int b = slot / G.k_hi; branch = 0; row0 = slot * TOK; canon_slot = b * G.nW + (slot - b * G.k_hi); }
-    else { int s = slot - n_hi, b = s / G.k_lo; branch = 1; row0 = G.base_lo + s * TOK; canon_slot = b * G.nW + G.k_hi + (s - b * G.k_lo); }
+    if (slot < n_hi) { int b = G.by_hi(slot); branch = 0; row0 = slot * TOK; canon_slot = b * G.nW + (slot - b * G.k_hi); }
+    else { int s = slot - n_hi, b = G.by_lo(s); branch = 1; row0 = G.base_lo + s * TOK; canon_slot = b * G.nW + G.k_hi + (s - b * G.k_lo); }
 }
 
 __device__ __forceinline__ int mask_type(const Geom& G, int w)
 {
     if (G.shift == 0) return 0;
-    int wr = w / G.nWc, wc = w - wr * G.nWc;
+    int wr = G.by_nWc(w), wc = w - wr * G.nWc;
     return (wr == G.Hp / WS - 1 ? 2 : 0) + (wc == G.nWc - 1 ? 1 : 0);
 }
 
@@ -672,18 +682,18 @@ __global__ __launch_bounds__(256) void attn_kernel(Geom G, AttnArgs A)
     __builtin_amdgcn_wave_barrier();
     AttnCore core;
     core.nzcsum = csum[wave];
-    core.poly = &A.poly;
-    core.floor = A.floor;
+    core.floor = (A.floor[branch] >> (mtype != 0)) & 1;
+    core.c5 = in_vgpr(EXP2_C5);
     core.bq = A.bias2 + ((size_t)(mtype * G.heads + head) * TOK) * 64 + g * 4 * 64 + j;
-    core.m2 = A.m2[branch];
-    core.qp = A.qp[branch];
+    core.m2 = in_vgpr(A.m2[branch]);
+    core.qp = in_vgpr(A.qp[branch]);
     const size_t tb = ((size_t)canon_slot * G.heads + head) * TOK * TOK;
     core.tap_s = A.tap_s ? A.tap_s + tb : nullptr;
     core.tap_p = A.tap_p ? A.tap_p + tb : nullptr;
 #pragma unroll 1
     for (int ib = 0; ib < 2; ++ib) {
         const v16i o = attention_core<true>(ib ? qf[1] : qf[0], kf, vt, core, j, g, ib);
-        attention_store<true>(o, A.qo[branch], A.m_o[branch], j, g, ib, head, G.C, A.out, row0, A.tap_o, A.tap_code, (size_t)canon_slot * TOK, PACK_FRAG);
+        attention_store<true>(o, in_vgpr(A.qo[branch]), in_vgpr(A.m_o[branch]), j, g, ib, head, G.C, A.out, row0, A.tap_o, A.tap_code, (size_t)canon_slot * TOK, PACK_FRAG);
     }
 }
 
@@ -700,7 +710,7 @@ __global__ __launch_bounds__(256) void ln_window_kernel(Geom G, WinArgs A)
     int branch = 0, row0 = 0, canon_slot = 0, slot = widx, w, bimg;
     bool pruned = false;
     if (SCORED) {
-        bimg = widx / G.nW;
+        bimg = G.by_nW(widx);
         w = widx - bimg * G.nW;
         const int rank = window_rank<256>(A.scores + (size_t)bimg * G.nW, G.nW, w, tid, red);
         if (tid == 0 && blockIdx.y == 0) A.perm_out[(size_t)bimg * G.nW + rank] = w;
@@ -711,7 +721,7 @@ __global__ __launch_bounds__(256) void ln_window_kernel(Geom G, WinArgs A)
     } else if (widx < G.n_slots) {
         slot_info(G, widx, branch, row0, canon_slot);
         w = A.perm[canon_slot];
-        bimg = canon_slot / G.nW;
+        bimg = G.by_nW(canon_slot);
     } else {
         const int kept = G.k_hi + G.k_lo, q = widx - G.n_slots;
         bimg = q / (G.nW - kept);
@@ -724,7 +734,7 @@ __global__ __launch_bounds__(256) void ln_window_kernel(Geom G, WinArgs A)
     }
     int pix = -1;
     if (t < TOK) {
-        const int wr = w / G.nWc, wc = w - wr * G.nWc, tr = t / WS, tc = t - tr * WS;
+        const int wr = G.by_nWc(w), wc = w - wr * G.nWc, tr = t / WS, tc = t - tr * WS;
         int pr = wr * WS + tr + G.shift; if (pr >= G.Hp) pr -= G.Hp;
         int pc = wc * WS + tc + G.shift; if (pc >= G.Wp) pc -= G.Wp;
         pix = (pr < G.H && pc < G.W) ? (bimg * G.H + pr) * G.W + pc : -1;
@@ -742,7 +752,7 @@ __global__ __launch_bounds__(256) void ln_window_kernel(Geom G, WinArgs A)
     const int canon = canon_slot * TOK + t;
     if (sub == 0 && t < TOK) { A.row_pix[row0 + t] = pix; A.row_canon[row0 + t] = canon; }
     if (pix >= 0) token_layernorm<LPT, NV>(v, C, A.eps, A.params[branch], A.params[branch] + C, sub);   // padding enters as LN output 0
-    const QDev q = A.q_in[branch];
+    const QDev q = in_vgpr(A.q_in[branch]);
 #pragma unroll
     for (int k = 0; k < NV; ++k) {
         const int ch = (k * LPT + sub) * 4;
@@ -760,6 +770,12 @@ __global__ __launch_bounds__(256) void ln_window_kernel(Geom G, WinArgs A)
 //   gather (shift folded into the index map) + LN1 + quantize, shared through LDS as MFMA
 //   fragments -> per head: q, k (transposed product, lane = token) and v (plain product, lane =
 //   dim) straight into operand registers -> attention core -> codes of the attention output.
+// What bounds it on full CUs is the issue of instructions: a SIMD issues one vector instruction per four to five clocks for its
+// even and one for its odd wave slots, and only one of the two at a time may be other than a simple one (see in_vgpr); a wave
+// alone on its CU waits for the map, its weights and the bias.  Simple instructions in place of others in the softmax, no integer
+// divisions, sixteen bytes a lane where the token slots behind the window are cleared, and sums over three, six or twelve lanes
+// by quads: a pair of blocks on 4 x 256 x 256 x 128 458.6 -> 445.2 us, 2 x 50 x 84 x 384 (six blocks) 356.3 -> 347.4,
+// 100 x 168 x 192 88.3 -> 86.5, one block on 56 x 56 x 96 19.7 -> 18.9.
 template <int NH, int HG, int QS>
 struct WinCfg {
     // lanes per token in the LN phase: one per wave (3 ... 16), so that the 49 tokens fit one pass
@@ -823,17 +839,17 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
         for (int d = 0; d < RING; ++d) ring[d] = wp[d * 64];
     }
     if (SCORED) {
-        bimg = widx / G.nW;
+        bimg = G.by_nW(widx);
         w = widx - bimg * G.nW;
     } else if (widx < G.n_slots) {
         slot_info(G, widx, branch, row0, canon_slot);
         w = A.perm[canon_slot];
-        bimg = canon_slot / G.nW;
+        bimg = G.by_nW(canon_slot);
     } else {                              // workgroups past the computed slots: pruned windows (Sec. 3.4), features forwarded
         if (hg != 0) return;
         const int kept = G.k_hi + G.k_lo, q = widx - G.n_slots, b = q / (G.nW - kept);
         const int wp = A.perm[b * G.nW + kept + (q - b * (G.nW - kept))];
-        const int wr = wp / G.nWc, wc = wp - wr * G.nWc;
+        const int wr = G.by_nWc(wp), wc = wp - wr * G.nWc;
         for (int i = tid; i < TOK * (C / 4); i += NT) {
             const int tt = i / (C / 4), k = i - tt * (C / 4), tr = tt / WS, tc = tt - tr * WS;
             int pr = wr * WS + tr + G.shift; if (pr >= G.Hp) pr -= G.Hp;
@@ -854,13 +870,15 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
     int* a1w = (int*)a1s;
     // dword index of (token slot s, channel c with c%4==0) in the fragment layout (k = channel, natural order)
     auto frag_dw = [&](int s, int c) { return ((((s >> 5) * KS + (c >> 5)) * 64 + ((c & 31) >> 4) * 32 + (s & 31)) << 2) + ((c & 15) >> 2); };
-    if (!CODES) for (int i = tid; i < 15 * (C / 4); i += NT) a1w[frag_dw(TOK + i / (C / 4), (i % (C / 4)) * 4)] = 0;
+    static_assert(CODES || NT >= 32 * KS, "one pass must clear the token slots behind the window");
+    if (!CODES && tid < 32 * KS && (tid & 15) < 64 - TOK)                 // the fifteen of every half slab, sixteen bytes a lane
+        a1s[(KS + (tid >> 5)) * 64 + ((tid >> 4) & 1) * 32 + TOK - 32 + (tid & 15)] = (v4i){0, 0, 0, 0};
     const int grp = lane / LPT, sub = lane - grp * LPT, first = lane - sub;
     const int t = !CODES && grp < GPW ? wave * GPW + grp : TOK;          // lanes beyond the last whole group idle
     int pix = -1;
     float4 v[NV];
     if (t < TOK) {                                                       // gather: the loads need the window only
-        const int wr = w / G.nWc, wc = w - wr * G.nWc, tr = t / WS, tc = t - tr * WS;
+        const int wr = G.by_nWc(w), wc = w - wr * G.nWc, tr = t / WS, tc = t - tr * WS;
         int pr = wr * WS + tr + G.shift; if (pr >= G.Hp) pr -= G.Hp;
         int pc = wc * WS + tc + G.shift; if (pc >= G.Wp) pc -= G.Wp;
         pix = (pr < G.H && pc < G.W) ? (bimg * G.H + pr) * G.W + pc : -1;
@@ -919,13 +937,15 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
 #pragma unroll
             for (int k = 0; k < NV; ++k) v[k] = make_float4(0.f, 0.f, 0.f, 0.f);
         }
-        const QDev q = A.q_in[branch];
+        const QDev q = in_vgpr(A.q_in[branch]);
 #pragma unroll
         for (int k = 0; k < NV; ++k) {
             if (NV > 8 && k % 4 == 0) __builtin_amdgcn_sched_barrier(0);
             const int ch = (k * LPT + sub) * 4;
             int code = pack4(quant_code(v[k].x, q), quant_code(v[k].y, q), quant_code(v[k].z, q), quant_code(v[k].w, q));
-            a1w[frag_dw(t, ch)] = code;
+            // four vectors on, the fragment address is a constant further (32 channels are 1 KB of fragments, and a token's slabs
+            // follow one another in whole vectors of sixteen channels): at most four addresses are formed
+            a1w[frag_dw(t, ((k & 3) * LPT + sub) * 4) + (k >> 2) * LPT * 128] = code;
             if (TAPS && A.tap_a1 && hg == 0) *(int*)(A.tap_a1 + (size_t)canon * C + ch) = code;
         }
     }
@@ -962,13 +982,13 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
         }
     };
     const size_t canon_row0 = (size_t)canon_slot * TOK;
-    v4i qk[2][NTB];                                                      // [q|k][token block]
+    v4i qk[2][NTB] = {};                                                 // [q|k][token block]
 #pragma unroll 1
     for (int which = 0; which < 2; ++which) {
         asm volatile("" ::: "memory");                                    // the B operand is read from LDS each time: keep the reads in the loop
         const int nb = which * NHT + head;
         const float* pm = prm + PR::HEADS + hw * PR::PER_HEAD + which * (3 * HD);
-        const QDev qq = A.q_qkv[branch][which];
+        const QDev qq = in_vgpr(A.q_qkv[branch][which]);
         const v4i* wp = weights_of(which);
         auto start = [&](v16i& acc) {                                     // accumulators start at -zp * colsum
 #pragma unroll
@@ -992,8 +1012,8 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
                     if (A.tap_qkv) *(int*)(A.tap_qkv + (canon_row0 + tok) * (3 * C) + n0) = wd[qd];
                 }
             }
-            if (which) qk[1][tb] = (v4i){wd[0], wd[1], wd[2], wd[3]};
-            else qk[0][tb] = (v4i){wd[0], wd[1], wd[2], wd[3]};
+            qk[0][tb] = qk[1][tb];                                        // the second trip moves q to its place (a select costs twice a move)
+            qk[1][tb] = (v4i){wd[0], wd[1], wd[2], wd[3]};
         };
         v16i acc[NTB];
         start(acc[0]);
@@ -1009,7 +1029,7 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
         const float* pm = prm + PR::HEADS + hw * PR::PER_HEAD + 2 * (3 * HD) + j;
         const float m = pm[0], bs = pm[HD];
         const int nc = __float_as_int(pm[2 * HD]);
-        const QDev qv = A.q_qkv[branch][2];
+        const QDev qv = in_vgpr(A.q_qkv[branch][2]);
         int cs = 0;
         auto finish = [&](int tb, const v16i& acc) {
             int wd[4];
@@ -1059,13 +1079,14 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
     }
     __builtin_amdgcn_s_waitcnt(0xc07f);                                   // lgkmcnt(0): the wave's own csum entries are in LDS
     __builtin_amdgcn_wave_barrier();
+    const int mtype = mask_type(G, w);
     AttnCore core;
-    core.poly = &A.poly;
-    core.floor = A.floor;
+    core.floor = (A.floor[branch] >> (mtype != 0)) & 1;
+    core.c5 = in_vgpr(EXP2_C5);
     core.nzcsum = csum[wave];
-    core.bq = A.bias2 + ((size_t)(mask_type(G, w) * NHT + head) * TOK) * 64 + g * 4 * 64 + j;
-    core.m2 = A.m2[branch];
-    core.qp = A.qp[branch];
+    core.bq = A.bias2 + ((size_t)(mtype * NHT + head) * TOK) * 64 + g * 4 * 64 + j;
+    core.m2 = in_vgpr(A.m2[branch]);
+    core.qp = in_vgpr(A.qp[branch]);
     const size_t tbase = ((size_t)canon_slot * NHT + head) * TOK * TOK;
     core.tap_s = A.tap_s ? A.tap_s + tbase : nullptr;
     core.tap_p = A.tap_p ? A.tap_p + tbase : nullptr;
@@ -1078,7 +1099,7 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
     for (int ib = tb0; ib < tb0 + NTB; ++ib) {
         asm volatile("" ::: "memory");
         const v16i o = attention_core<TAPS>(NTB == 2 && ib ? qk[0][NTB - 1] : qk[0][0], kf, vt, core, j, g, ib);
-        attention_store<TAPS>(o, A.qo[branch], A.m_o[branch], j, g, ib, head, C, out, orow0, A.tap_o, A.tap_code, canon_row0, pack);
+        attention_store<TAPS>(o, in_vgpr(A.qo[branch]), in_vgpr(A.m_o[branch]), j, g, ib, head, C, out, orow0, A.tap_o, A.tap_code, canon_row0, pack);
     }
 }
 
@@ -1285,7 +1306,7 @@ __global__ __launch_bounds__(NH * 64) __attribute__((amdgpu_waves_per_eu(tok_wav
             if (g == 0) part[1][wave][rb * 32 + j] = q;
         }
         __syncthreads();
-        const QDev qa = A.q_fc1in[branch];
+        const QDev qa = in_vgpr(A.q_fc1in[branch]);
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) {
             double q = 0.0;
@@ -1309,7 +1330,7 @@ __global__ __launch_bounds__(NH * 64) __attribute__((amdgpu_waves_per_eu(tok_wav
     __syncthreads();
     v16i acc2[RB];
     start(acc2, PR::F2_NC + nb * 32);
-    const QDev qg = A.q_fc2in[branch];
+    const QDev qg = in_vgpr(A.q_fc2in[branch]);
     // GELU + quantize of four of the FC1 sums of hidden block ch*NH + wave, and the block's codes -> LDS buffer ch & 1
     int wd[RB][4];
     auto gelu_part = [&](int ch, int rb, int qd, const v16i* acc) {

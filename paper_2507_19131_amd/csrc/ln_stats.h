@@ -19,12 +19,12 @@ namespace mixaq {
 
 MIXAQ_HD double sum4(float a, float b, float c, float d) { return ((double)a + (double)b) + ((double)c + (double)d); }
 
-// REREAD: the four values are made opaque, or the compiler keeps their conversions to binary64 from the first pass in registers,
+// REREAD: the caller's four registers are made opaque (in place: a copy costs a move per element), or the compiler keeps their conversions to binary64 from the first pass in registers,
 // twice the token, in spills where the registers are full (the window kernel's forms of a pair of waves per head: up to 58).  The
 // token kernel and the 96-channel embedding have the room: a conversion less per element, 4 x 128 x 128 x 256 333.5 -> 330.6 us the
 // pair of blocks, 4 x 256 x 256 x 128 448.5 -> 446.0, embedding 800 x 1344 on fresh images 13.25 -> 13.05.
-template <bool REREAD>
-MIXAQ_HD double centred4(float x0, float x1, float x2, float x3, float mean)
+template <bool REREAD, class F>
+MIXAQ_HD double centred4(F& x0, F& x1, F& x2, F& x3, float mean)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
     if (REREAD) asm("" : "+v"(x0), "+v"(x1), "+v"(x2), "+v"(x3));

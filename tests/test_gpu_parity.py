@@ -427,6 +427,35 @@ def test_logits_that_are_no_ordinary_numbers(C, heads, fused, kind):
     gh.assert_parity(res)
 
 
+@pytest.mark.parametrize("span,kind", [(33.0, "bias"), (35.0, "bias"), (94.0, "plain"), (101.0, "plain"), (400.0, "plain"), (30.0, "made_up")])
+@pytest.mark.parametrize("C,heads,fused,bits", [(96, 3, True, (8, 4)), (96, 3, False, (8, 4)), (384, 12, True, (4, 2))])
+def test_exponents_around_the_lines_of_their_floor(C, heads, fused, bits, span, kind):
+    """Products of q and k that span `span` exponents with saturated codes, on both sides of the lines from which windows with
+    masked pairs (34) and all windows (99 with the bias) hold their exponents at the floor, and a bias that makes up for the mask
+    of some pairs.  Every tap is the oracle's."""
+    spec, inp, x, k = _case(2, 14, 21, C, heads, 3, 0.5, 83, blobs=True, bits=bits)
+    rng = np.random.default_rng(84)
+    steps = []
+    for br, b in zip(inp.branches, bits):        # span = 2 * 32 * 2^(2 b - 2) * s_q * s_k * log2(e) / sqrt(32)
+        s = float(np.sqrt(span * np.sqrt(32.0) / (1.442695 * 64 * 4.0 ** (b - 1))))
+        steps.append(s / br.q["a_q"][0])
+        br.q["a_q"], br.q["a_k"] = (s * 1.0625, 0), (s / 1.0625, 0)
+    inp.shared.s_qkv = inp.shared.s_qkv.copy()
+    inp.shared.s_qkv[:2 * C] *= np.float32(3.0 * max(steps))
+    rpb = inp.shared.rel_pos_bias.copy()
+    if kind == "bias":
+        rpb *= np.float32(4.0)
+    elif kind == "plain":
+        rpb *= np.float32(0.25)
+    else:
+        rpb[rng.random(rpb.shape) < 0.05] += np.float32(130.0)
+    inp.shared.rel_pos_bias = rpb
+    print("floor lines", span, kind, "C", C, "fused", fused, "bits", bits, flush=True)
+    res = gh.compare_block(inp, x, k, fused=fused)
+    print(res, flush=True)
+    gh.assert_parity(res)
+
+
 @pytest.mark.parametrize("B,H,W,C,mode", [(9, 56, 63, 768, 1), (10, 56, 63, 768, 1), (10, 56, 63, 768, 0), (4, 130, 140, 384, 1), (5, 82, 91, 1024, 1)])
 def test_scores_of_wide_maps_on_both_sides_of_the_workgroup_size(B, H, W, C, mode):
     """Wide maps are scored by 1024 threads per window, large ones with the scoring LayerNorm by 256."""
