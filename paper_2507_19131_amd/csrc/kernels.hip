@@ -1116,6 +1116,9 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
 // chain of phases on few tiles.  Against a form with the chunks unrolled and FC1's weights a block ahead, which the three, four
 // and eight waves had: stage of two blocks on 8 x 1392 windows at C = 96, 5476 at C = 128 and 1444 at C = 256 3 % shorter, 64
 // windows at C = 256 58.9 -> 52.7 us.
+// LN2's partial sums are read together and each by one half of the lanes, for both row blocks before either goes on, and the
+// parked h is requested ahead of the last products: 2 x 50 x 84 x 384 (six blocks) 347.4 -> 340.6 us, of 64-row tiles' 72 k clocks
+// these phases had taken 15 k and 7 k.
 // Waves per SIMD it is compiled for: 128 registers take it without spills up to six waves (106 to 124 wanted), at eight waves
 // with six spilled; at five waves per SIMD the spills at C = 96 cost more than the fifth wave gives; twelve need 160 and have a
 // CU to themselves.
@@ -1294,12 +1297,24 @@ __global__ __launch_bounds__(NH * 64) __attribute__((amdgpu_waves_per_eu(tok_wav
             if (g == 0) part[0][wave][rb * 32 + j] = s;
         }
         __syncthreads();                                              // also: every wave is done reading the attention codes
+        // sum of a row's partials: with an even number of waves each half of the lanes takes every second one, read together
+        auto total = [&](int which, int rb) {
+            constexpr bool HALVES = NH % 2 == 0;
+            constexpr int N = HALVES ? NH / 2 : NH;
+            double v[N];
+#pragma unroll
+            for (int k = 0; k < N; ++k) v[k] = part[which][HALVES ? 2 * k + g : k][rb * 32 + j];
+#pragma unroll
+            for (int d = 1; d < N; d *= 2)
+#pragma unroll
+                for (int k = 0; k + d < N; k += 2 * d) v[k] += v[k + d];
+            return HALVES ? half_sum(v[0]) : v[0];
+        };
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) mean[rb] = ln_mean(total(0, rb), C);
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) {
-            double s = 0.0, q = 0.0;
-#pragma unroll
-            for (int w2i = 0; w2i < NH; ++w2i) s += part[0][w2i][rb * 32 + j];
-            mean[rb] = ln_mean(s, C);
+            double q = 0.0;
 #pragma unroll
             for (int r = 0; r < 16; r += 4) q += centred4<false>(h[rb][r], h[rb][r + 1], h[rb][r + 2], h[rb][r + 3], mean[rb]);
             q = half_sum(q);
@@ -1307,21 +1322,20 @@ __global__ __launch_bounds__(NH * 64) __attribute__((amdgpu_waves_per_eu(tok_wav
         }
         __syncthreads();
         const QDev qa = in_vgpr(A.q_fc1in[branch]);
+        float rstd[RB];
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) rstd[rb] = ln_rstd(total(1, rb), C, A.eps);
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) {
-            double q = 0.0;
-#pragma unroll
-            for (int w2i = 0; w2i < NH; ++w2i) q += part[1][w2i][rb * 32 + j];
-            const float rstd = ln_rstd(q, C, A.eps);
             int wd[4];
 #pragma unroll
             for (int qd = 0; qd < 4; ++qd) {
                 const int n0 = nb * 32 + qd * 8 + g * 4;
                 const float4 gm = *(const float4*)(prm + PR::LN_G + n0), bt = *(const float4*)(prm + PR::LN_B + n0);
-                wd[qd] = pack4(quant_code(fmaf((h[rb][qd * 4 + 0] - mean[rb]) * rstd, gm.x, bt.x), qa),
-                               quant_code(fmaf((h[rb][qd * 4 + 1] - mean[rb]) * rstd, gm.y, bt.y), qa),
-                               quant_code(fmaf((h[rb][qd * 4 + 2] - mean[rb]) * rstd, gm.z, bt.z), qa),
-                               quant_code(fmaf((h[rb][qd * 4 + 3] - mean[rb]) * rstd, gm.w, bt.w), qa));
+                wd[qd] = pack4(quant_code(fmaf((h[rb][qd * 4 + 0] - mean[rb]) * rstd[rb], gm.x, bt.x), qa),
+                               quant_code(fmaf((h[rb][qd * 4 + 1] - mean[rb]) * rstd[rb], gm.y, bt.y), qa),
+                               quant_code(fmaf((h[rb][qd * 4 + 2] - mean[rb]) * rstd[rb], gm.z, bt.z), qa),
+                               quant_code(fmaf((h[rb][qd * 4 + 3] - mean[rb]) * rstd[rb], gm.w, bt.w), qa));
                 if (TAPS && valid[rb] && A.tap_a2) *(int*)(A.tap_a2 + canon[rb] * C + n0) = wd[qd];
             }
             actf[(rb * KS + nb) * 64 + lane] = (v4i){wd[0], wd[1], wd[2], wd[3]};   // k slab nb, byte r = channel 32nb + mfma_row(r,g)
@@ -1372,6 +1386,15 @@ __global__ __launch_bounds__(NH * 64) __attribute__((amdgpu_waves_per_eu(tok_wav
         gelu_store(ch);
         __syncthreads();                                              // chunk ch complete, chunk ch-1 no longer read
     }
+    if (PARK_H) {                                                     // the parked h travels under the last products
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+            for (int qd = 0; qd < 4; ++qd) {
+                const float4 v = *(const float4*)(A.y + (size_t)max(pix[rb], 0) * C + nb * 32 + qd * 8 + g * 4);
+                h[rb][qd * 4] = v.x; h[rb][qd * 4 + 1] = v.y; h[rb][qd * 4 + 2] = v.z; h[rb][qd * 4 + 3] = v.w;
+            }
+    }
     run(Even(), std::true_type(), w2_of(3), nullptr, gs[1], 1, RB, acc2, nothing);                     // FC2 of the last chunk
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb)
@@ -1379,8 +1402,7 @@ __global__ __launch_bounds__(NH * 64) __attribute__((amdgpu_waves_per_eu(tok_wav
         for (int qd = 0; qd < 4; ++qd) {   // second residual + scatter
             const int n0 = nb * 32 + qd * 8 + g * 4;
             const float4 m = *(const float4*)(prm + PR::F2_M + n0), bs = *(const float4*)(prm + PR::F2_B + n0);
-            float4 hh = make_float4(h[rb][qd * 4], h[rb][qd * 4 + 1], h[rb][qd * 4 + 2], h[rb][qd * 4 + 3]);
-            if (PARK_H) hh = pix[rb] >= 0 ? *(const float4*)(A.y + (size_t)pix[rb] * C + n0) : make_float4(0.f, 0.f, 0.f, 0.f);
+            const float4 hh = make_float4(h[rb][qd * 4], h[rb][qd * 4 + 1], h[rb][qd * 4 + 2], h[rb][qd * 4 + 3]);
             float4 o4 = make_float4(fmaf((float)acc2[rb][qd * 4 + 0], m.x, bs.x) + hh.x, fmaf((float)acc2[rb][qd * 4 + 1], m.y, bs.y) + hh.y,
                                     fmaf((float)acc2[rb][qd * 4 + 2], m.z, bs.z) + hh.z, fmaf((float)acc2[rb][qd * 4 + 3], m.w, bs.w) + hh.w);
             if (pix[rb] >= 0) *(float4*)(A.y + (size_t)pix[rb] * C + n0) = o4;
