@@ -133,7 +133,7 @@ struct mixaq_block {
     float* ln_beta[2][2];
     float* score_gamma = nullptr;
     float* score_beta = nullptr;
-    float* bias2 = nullptr;
+    float4* bias2 = nullptr;
     QDev q_in[2], q_qkv[2][3], q_p[2], q_ao[2], q_fc1in[2], q_fc2in[2];
     float m2[2], m_o[2];
     int exp_floor[2] = {3, 3}; // per branch, which softmax exponents need their floor: bit 0 unmasked windows, bit 1 windows with masked pairs
@@ -557,7 +557,7 @@ static int block_create(const mixaq_block_desc* desc, const mixaq_shared_params*
     b->by_nW = FastDiv(b->nW); b->by_nWc = FastDiv(b->nWc);
     const int C = desc->C, F = C * desc->mlp_ratio, heads = desc->heads;
     BlockOwner owner{b};
-    b->mem.reserve((size_t)4 * C * C + 2 * (size_t)F * C + (size_t)heads * 4 * TOK * 64 * 4 + (size_t)C * 800 + 65536);
+    b->mem.reserve((size_t)4 * C * C + 2 * (size_t)F * C + (size_t)heads * 4 * BIAS_QUADS * 64 * 16 + (size_t)C * 800 + 65536);
     auto bail = [&](int code) { return code; };          // the owner destroys the block
     mixaq_qparam qi[2];
     const float* bias[2];
@@ -596,7 +596,7 @@ static int block_create(const mixaq_block_desc* desc, const mixaq_shared_params*
         if ((rc = download(sh->score_beta, (size_t)C, tmp))) return bail(rc);
         b->mem.add(tmp, &b->score_beta);
     }
-    // (relative position bias + shift mask) * log2(e), transposed to [type][head][key][query 64], and which softmax exponents need
+    // (relative position bias + shift mask) * log2(e), transposed to [type][head][key quad][query 64][4], and which softmax exponents need
     // their floor (see exp2_pinned).  The products of a branch lie in [-P, P], P = 32 * 2^(2 bits - 2) steps of m2, so an unmasked
     // logit is at most 2 P and the span of its table row below the row's maximum: no floor while that is under 99 (1 is left for the
     // roundings).  A masked pair is worth -100 log2(e) or less, e^-100 of a probability, which neither changes a denominator (at
@@ -613,7 +613,7 @@ static int block_create(const mixaq_block_desc* desc, const mixaq_shared_params*
         }
         std::vector<float> rpb;
         if ((rc = download(sh->rel_pos_bias, (size_t)heads * TOK * TOK, rpb))) return bail(rc);
-        std::vector<float> tab((size_t)4 * heads * TOK * 64, 0.0f);
+        std::vector<float> tab((size_t)4 * heads * BIAS_QUADS * 64 * 4, 0.0f);
         const int nWr = b->Hp / WS;
         std::vector<std::pair<size_t, float>> raised;
         float widest = 0.0f;                                 // of the unmasked entries of a row, over all rows
@@ -639,7 +639,7 @@ static int block_create(const mixaq_block_desc* desc, const mixaq_shared_params*
                     }
                     widest = ordinary ? std::max(widest, row_max - row_min) : INFINITY;
                     for (int j = 0; j < TOK; ++j) {
-                        const size_t at = (((size_t)type * heads + h) * TOK + j) * 64 + i;
+                        const size_t at = ((((size_t)type * heads + h) * BIAS_QUADS + j / 4) * 64 + i) * 4 + j % 4;
                         tab[at] = row[j];
                         if (!masked[j]) continue;
                         narrow = narrow && row[j] <= row_max - MASKED_BELOW;      // not where a large bias makes up for the mask

@@ -47,7 +47,7 @@ struct GemmArgs {
 struct AttnArgs {
     const int8_t* qkv;               // [rows,3C]
     const int* perm;
-    const float* bias2;              // [4 mask types][heads][49 keys][64 queries], (bias+mask)*log2e
+    const float4* bias2;             // [4 mask types][heads][13 key quads][64 queries][4 keys], (bias+mask)*log2e
     float m2[2];                     // s_q*s_k/sqrt(d)*log2e
     float m_o[2];                    // s_p*s_v
     QDev qp[2], qo[2];
@@ -72,7 +72,7 @@ struct WinArgs {                     // fused window kernel (gather + LN1 + QKV 
     QDev q_in[2];
     const v4i* Wqkv;                 // packed, natural k order
     QDev q_qkv[2][3];
-    const float* bias2;
+    const float4* bias2;
     float m2[2], m_o[2];
     QDev qp[2], qo[2];
     int8_t* codes;                   // wide blocks: LN1 codes, operand fragments of 64 rows per slot (ln_window_kernel -> window_kernel)

@@ -475,8 +475,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RT * KMAX <
 // (an integer multiply is a quarter-rate instruction; and starting the accumulators there costs no instruction, where
 // subtracting afterwards took one per output element).
 struct AttnCore {
-    const float* bq;          // (bias + mask) * log2e of query j of query block 0 at key g*4, in the [49 keys][64 queries]
-                              // table of this head and mask type: key k + g*4, query block ib is bq[k * 64 + ib * 32]
+    const float4* bq;         // (bias + mask) * log2e of query j of query block 0 at keys g*4 ..+3, in the [13 key quads][64 queries][4]
+                              // table of this head and mask type: keys k + g*4 ..+3, query block ib are bq[k / 4 * 64 + ib * 32]
     float m2, c5;             // in vector registers, like qp's factor and addend
     QDev qp;
     const int* nzcsum;        // [HD], LDS
@@ -501,16 +501,24 @@ __device__ __forceinline__ v16i attention_core(const v4i& qf, const v4i (&kf)[2]
 #pragma unroll
         for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int key = kb * 32 + (r >> 2) * 8 + (r & 3);         // + g*4
-                float v = -INFINITY;
-                if (key < TOK) {                                          // valid for at least one half
-                    const int kk = key + g * 4;
-                    if (kk < TOK) v = fmaf((float)s[kb][r], A.m2, A.bq[key * 64 + ib * 32]);
-                    mx = fmaxf(mx, v);
-                    if (TAPS && kk < TOK && qi < TOK && A.tap_s) A.tap_s[qi * TOK + kk] = s[kb][r];
+            for (int r = 0; r < 16; r += 4) {
+                const int key = kb * 32 + (r >> 2) * 8;                   // + g*4
+                float b[4] = {0.f, 0.f, 0.f, 0.f};
+                if (key + 3 + 4 < TOK) {                                  // four keys, valid for both halves
+                    const float4 b4 = A.bq[(key / 4) * 64 + ib * 32];
+                    b[0] = b4.x; b[1] = b4.y; b[2] = b4.z; b[3] = b4.w;
+                } else if (key < TOK) b[0] = A.bq[(key / 4 - g) * 64 + ib * 32].x;   // the last key, of the lower half only
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int kk = key + e + g * 4;
+                    float v = -INFINITY;
+                    if (key + e < TOK) {                                  // valid for at least one half
+                        if (key + 7 < TOK || kk < TOK) v = fmaf((float)s[kb][r + e], A.m2, b[e]);
+                        mx = fmaxf(mx, v);
+                        if (TAPS && kk < TOK && qi < TOK && A.tap_s) A.tap_s[qi * TOK + kk] = s[kb][r + e];
+                    }
+                    lg[kb][r + e] = v;
                 }
-                lg[kb][r] = v;
             }
         mx = half_max(mx);
         if (A.floor) {                                                    // masked pairs, infinities and NaN end here
@@ -594,20 +602,28 @@ __device__ __forceinline__ void attention_store(const v16i& o, const QDev& qo, f
                 const int a0 = o[qd * 4 + 0], a1 = o[qd * 4 + 1], a2 = o[qd * 4 + 2], a3 = o[qd * 4 + 3];
                 code[qd] = pack4(quant_code((float)a0 * m_o, qo), quant_code((float)a1 * m_o, qo),
                                  quant_code((float)a2 * m_o, qo), quant_code((float)a3 * m_o, qo));
-                const int ch = head * HD + d0;
-                if (pack == 0) *(int*)(out + (size_t)(row0 + qi) * C + ch) = code[qd];
-                else if (pack == PACK_FRAG) *(int*)(out + frag_offset(row0 + qi, ch, C / 32)) = code[qd];
-                size_t ci = (canon_row0 + qi) * C + ch;
+                size_t ci = (canon_row0 + qi) * C + head * HD + d0;
                 if (TAPS && tap_o) *(int4*)(tap_o + ci) = make_int4(a0, a1, a2, a3);
                 if (TAPS && tap_code) *(int*)(tap_code + ci) = code[qd];
             }
-            if (pack == 1) {                       // out = first packed row of the region, row0 = row inside it
-                int8_t* rowp = out + (size_t)(row0 + qi) * (C / 2) + head * 16 + g * 4;
+            // The halves exchange, so that a lane stores its token's sixteen (packed: eight) consecutive bytes at once: four-byte
+            // stores cost a write request each.
+            if (pack == 0 || pack == PACK_FRAG) {
+                const auto lo = __builtin_amdgcn_permlane32_swap(code[0], code[2], false, false);   // dims 0..3, 4..7 | 16..19, 20..23
+                const auto hi = __builtin_amdgcn_permlane32_swap(code[1], code[3], false, false);   // 8..11, 12..15 | 24..27, 28..31
+                const v4i all = {(int)lo[0], (int)lo[1], (int)hi[0], (int)hi[1]};
+                const int ch = head * HD + g * 16;
+                if (pack == 0) *(v4i*)(out + (size_t)(row0 + qi) * C + ch) = all;
+                else *(v4i*)(out + frag_offset(row0 + qi, ch, C / 32)) = all;
+            } else if (pack == 1) {                // out = first packed row of the region, row0 = row inside it
+                int w[2];
 #pragma unroll
                 for (int p = 0; p < 2; ++p) {
                     const int lo = (code[2 * p] ^ 0x08080808) & 0x0f0f0f0f, hi = (code[2 * p + 1] ^ 0x08080808) & 0x0f0f0f0f;
-                    *(int*)(rowp + p * 8) = lo | (hi << 4);
+                    w[p] = lo | (hi << 4);
                 }
+                const auto both = __builtin_amdgcn_permlane32_swap(w[0], w[1], false, false);
+                *(int2*)(out + (size_t)(row0 + qi) * (C / 2) + head * 16 + g * 8) = make_int2((int)both[0], (int)both[1]);
             } else if (pack == 2) {
                 int w = 0;
 #pragma unroll
@@ -684,7 +700,7 @@ __global__ __launch_bounds__(256) void attn_kernel(Geom G, AttnArgs A)
     core.nzcsum = csum[wave];
     core.floor = (A.floor[branch] >> (mtype != 0)) & 1;
     core.c5 = in_vgpr(EXP2_C5);
-    core.bq = A.bias2 + ((size_t)(mtype * G.heads + head) * TOK) * 64 + g * 4 * 64 + j;
+    core.bq = A.bias2 + (size_t)(mtype * G.heads + head) * BIAS_QUADS * 64 + g * 64 + j;
     core.m2 = in_vgpr(A.m2[branch]);
     core.qp = in_vgpr(A.qp[branch]);
     const size_t tb = ((size_t)canon_slot * G.heads + head) * TOK * TOK;
@@ -1084,7 +1100,7 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
     core.floor = (A.floor[branch] >> (mtype != 0)) & 1;
     core.c5 = in_vgpr(EXP2_C5);
     core.nzcsum = csum[wave];
-    core.bq = A.bias2 + ((size_t)(mtype * NHT + head) * TOK) * 64 + g * 4 * 64 + j;
+    core.bq = A.bias2 + (size_t)(mtype * NHT + head) * BIAS_QUADS * 64 + g * 64 + j;
     core.m2 = in_vgpr(A.m2[branch]);
     core.qp = in_vgpr(A.qp[branch]);
     const size_t tbase = ((size_t)canon_slot * NHT + head) * TOK * TOK;

@@ -13,6 +13,7 @@ typedef int v16i __attribute__((ext_vector_type(16)));
 
 constexpr int WS = 7;            // window side
 constexpr int TOK = 49;          // tokens per window
+constexpr int BIAS_QUADS = (TOK + 3) / 4;   // key quads of the bias table
 constexpr int HD = 32;           // head dimension = one 32-wide MFMA block
 constexpr int ROW_TILE = 64;     // rows per GEMM tile
 constexpr int REGION_ALIGN = 128; // the branch regions of the row space are padded to this (the largest row tile of any kernel)
