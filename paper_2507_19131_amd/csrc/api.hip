@@ -9,6 +9,7 @@
 #include <cstring>
 #include <mutex>
 #include <new>
+#include <thread>
 #include <utility>
 #include <vector>
 
@@ -143,10 +144,7 @@ struct mixaq_block {
     const float4* gelu_tab = nullptr;            // cubic coefficients of the pinned GELU
     size_t ws_bytes = 0;
     size_t ws_fused_bytes = 0; // what the two fused kernels alone need
-    // Small maps in a batch (see mixaq_stage_forward): the stage runs as two chains, one per half of the images,
-    // the second on this stream between the two events; created with the block when the shape qualifies.
-    hipStream_t side_stream = nullptr;
-    hipEvent_t ev_fork = nullptr, ev_join = nullptr;
+    int side_device = -1;      // a batch of small maps: the device whose side streams the stage call may use (see SideStreams)
     bool fused_window = false; // the window kernel instead of gather/LN1 + QKV + attention kernels
     bool fused_token = false;  // the token kernel instead of proj + LN2 + FC1 + FC2 kernels
 };
@@ -178,6 +176,96 @@ int static_scratch(void** out)
     *out = ptr[dev];
     return MIXAQ_OK;
 }
+
+// Side streams for stages that run as two chains (see mixaq_stage_forward).  One per stream that callers use, not one per handle:
+// the runtime spreads streams over four hardware queues, and with one per handle the second chain of every fourth handle
+// shared the first one's queue (six blocks on 192 windows at C = 384, three sets of handles in turn: 361 us as two chains, 358 as
+// one; with a side stream per caller 300).  A side stream only ever waits for its caller's stream, so callers stay independent of one
+// another.  At most MAX of them per device; a further caller takes over the one unused for longest, or runs as one
+// chain if all are in the middle of a call.  They are created when a block that may use them is, or on a caller's first call, and are
+// given back with the last such block.
+class SideStreams {
+public:
+    struct Side {
+        hipStream_t caller = nullptr, stream = nullptr;
+        std::thread::id thread;                    // of the caller, where its stream's name means another stream in every thread
+        hipEvent_t fork = nullptr, join = nullptr;
+        int calls = 0;                             // in progress
+        unsigned long long used = 0;
+        std::mutex mu;                             // an event is recorded and waited for in one piece
+    };
+    static SideStreams& of(int device)
+    {
+        static SideStreams all[MAX_DEVICES];
+        return all[device];
+    }
+    int retain(hipStream_t caller)
+    {
+        std::lock_guard<std::mutex> lock(mu_);
+        if (!find(caller) && !make(caller)) return MIXAQ_E_HIP;
+        ++blocks_;
+        return MIXAQ_OK;
+    }
+    void release()
+    {
+        std::lock_guard<std::mutex> lock(mu_);
+        if (--blocks_ > 0) return;
+        for (Side& s : side_) {
+            if (s.join) (void)hipEventDestroy(s.join);
+            if (s.fork) (void)hipEventDestroy(s.fork);
+            if (s.stream) (void)hipStreamDestroy(s.stream);
+            s.join = s.fork = nullptr;
+            s.stream = s.caller = nullptr;
+        }
+    }
+    // the caller's side stream, or NULL; ended by done()
+    Side* begin(hipStream_t caller)
+    {
+        std::lock_guard<std::mutex> lock(mu_);
+        Side* s = find(caller);
+        if (!s) s = make(caller);
+        if (s) { ++s->calls; s->used = ++clock_; }
+        return s;
+    }
+    void done(Side* s)
+    {
+        std::lock_guard<std::mutex> lock(mu_);
+        --s->calls;
+    }
+
+private:
+    static constexpr int MAX = 4;
+    static bool per_thread(hipStream_t s) { return s == hipStreamPerThread; }
+    Side* find(hipStream_t caller)
+    {
+        for (Side& s : side_)
+            if (s.stream && s.caller == caller && (!per_thread(caller) || s.thread == std::this_thread::get_id())) return &s;
+        return nullptr;
+    }
+    Side* make(hipStream_t caller)
+    {
+        Side* s = nullptr;
+        for (Side& c : side_)
+            if (!c.calls && (!s || (s->stream && (!c.stream || c.used < s->used)))) s = &c;
+        if (!s) return nullptr;
+        if (!s->stream) {
+            if ((!s->fork && hipEventCreateWithFlags(&s->fork, hipEventDisableTiming) != hipSuccess) ||
+                (!s->join && hipEventCreateWithFlags(&s->join, hipEventDisableTiming) != hipSuccess) ||
+                hipStreamCreateWithFlags(&s->stream, hipStreamNonBlocking) != hipSuccess) {
+                (void)hipGetLastError();                     // not to be mistaken for a launch error later
+                s->stream = nullptr;
+                return nullptr;
+            }
+        }
+        s->caller = caller;
+        s->thread = std::this_thread::get_id();
+        return s;
+    }
+    std::mutex mu_;
+    Side side_[MAX];
+    int blocks_ = 0;
+    unsigned long long clock_ = 0;
+};
 
 // packs W[N,K] (row-major int8) into MFMA A-operand order and builds the per-branch epilogue constants
 int prepare_linear(mixaq_block* blk, Linear& L, const int8_t* w_dev, const float* s_dev, int N, int K,
@@ -249,24 +337,19 @@ int check_qparam(const mixaq_qparam& q, int bits, const char* name)
 // on 1920 at 192 330 -> 314, on 1440 at 384 648 -> 602; beyond, 2 % and less: 4176 windows at 96 255 -> 250, 4107 at 128 342 -> 340,
 // 4608 at 192 773 -> 758, 4800 at 384 2142 -> 2091).
 constexpr int STAGE_SPLIT_MAX_WINDOWS = 4096;
-// Fork and join cost 25 to 30 us, so the stage has to be long enough: from about 2000 windows over all its blocks on (at C = 96,
-// whose kernels are shorter, 2667).  One chain -> two, in us, for one set of handles called over and over | three sets in turn.
-//   two blocks:  C = 96, 840 windows 81 -> 88 | 81 -> 91; 1300 104 -> 103 | 104 -> 106; 1856 133 -> 126 | 138 -> 134
-//                C = 128, 924 95 -> 97 | 95 -> 100; 1352 133 -> 124 | 136 -> 130
-//                C = 192, 450 92 -> 101 | 91 -> 103; 924 188 -> 168 | 181 -> 174
-//                C = 256, 968 229 -> 231 | 238 -> 238; 1456 336 -> 336 | 345 -> 341
-//                C = 384, 242 126 -> 142 | 127 -> 143; 450 239 -> 231 | 258 -> 241
-//   six blocks:  C = 96, 840 236 -> 216 | 235 -> 267; 1856 386 -> 328 | 398 -> 399
-//                C = 192, 450 267 -> 259 | 267 -> 308; 924 548 -> 449 | 529 -> 502
-//                C = 384, 192 357 -> 299 | 358 -> 361; 242 370 -> 363 | 370 -> 407; 450 701 -> 616 | 742 -> 682
-// Sets in turn gain less because every handle of such a map makes a stream of its own: the runtime has four hardware queues,
-// and a side stream may get the caller's (with one side stream for all of them the second figures become the first).  Pruned
-// windows count like the others: with 40 % pruned, 1856 windows at C = 96 and two blocks 100 -> 106 | 105 -> 115, 450 at 384 and
-// six blocks 482 -> 403 | 521 -> 493; counting the computed windows only would turn both round.
-constexpr long long STAGE_SPLIT_MIN_WORK = 2000LL * 128;
+// Fork and join cost 25 to 30 us, so the stage has to be long enough: the line is drawn at windows times channels over all its
+// blocks.  One chain -> two, in us (three sets of handles in turn take the same, as they share the caller's side stream):
+//   two blocks:  C = 96, 256 windows 43 -> 77; 392 54 -> 78; 840 79 -> 84; 1352 104 -> 101
+//                C = 128, 920 95 -> 94        C = 192, 450 89 -> 100; 924 175 -> 170
+//                C = 256, 480 128 -> 128; 1012 245 -> 241      C = 384, 192 114 -> 117; 300 159 -> 140; 450 236 -> 232
+//   six blocks:  C = 96, 128 windows 110 -> 142; 392 166 -> 155        C = 128, 512 190 -> 171
+//                C = 192, 98 170 -> 176; 200 204 -> 200       C = 256, 220 225 -> 219
+//                C = 384, 40 215 -> 231; 70 217 -> 232; 192 335 -> 294
+// Pruned windows count like the others: their share shortens both forms.
+constexpr long long STAGE_SPLIT_MIN_WORK = 2200LL * 100;
 bool stage_split_pays(const mixaq_block* b, int n_blocks)
 {
-    return (long long)n_blocks * b->d.B * b->nW * std::min(b->d.C, 128) >= STAGE_SPLIT_MIN_WORK;
+    return (long long)n_blocks * b->d.B * b->nW * b->d.C >= STAGE_SPLIT_MIN_WORK;
 }
 bool stage_splits(const mixaq_block* b)
 {
@@ -705,10 +788,12 @@ static int block_create(const mixaq_block_desc* desc, const mixaq_shared_params*
     b->ws_fused_bytes = carve(b, nullptr, &w, true);
     if (stage_splits(b)) {                  // two chains: each half of the images has its own part of the workspace
         b->ws_bytes = std::max(b->ws_bytes, carve(b, nullptr, &w, false, (desc->B + 1) / 2) + carve(b, nullptr, &w, false, desc->B / 2));
-        if (hipStreamCreateWithFlags(&b->side_stream, hipStreamNonBlocking) != hipSuccess ||
-            hipEventCreateWithFlags(&b->ev_fork, hipEventDisableTiming) != hipSuccess ||
-            hipEventCreateWithFlags(&b->ev_join, hipEventDisableTiming) != hipSuccess)
-            return bail(fail(MIXAQ_E_HIP, "creating the second stream of the stage failed"));
+        int dev = -1;
+        HIP_TRY(hipGetDevice(&dev));
+        if (dev >= 0 && dev < MAX_DEVICES) {
+            if (SideStreams::of(dev).retain((hipStream_t)stream) != MIXAQ_OK) return bail(fail(MIXAQ_E_HIP, "creating the second stream of the stage failed"));
+            b->side_device = dev;
+        }
     }
     HIP_TRY(b->mem.commit());
     for (Linear* L : {&b->qkv, &b->proj, &b->fc1, &b->fc2})
@@ -722,9 +807,7 @@ int mixaq_block_destroy(mixaq_block* blk)
 {
     if (!blk) return MIXAQ_OK;
     blk->mem.release();
-    if (blk->ev_fork) (void)hipEventDestroy(blk->ev_fork);
-    if (blk->ev_join) (void)hipEventDestroy(blk->ev_join);
-    if (blk->side_stream) (void)hipStreamDestroy(blk->side_stream);
+    if (blk->side_device >= 0) SideStreams::of(blk->side_device).release();
     delete blk;
     return MIXAQ_OK;
 }
@@ -808,14 +891,14 @@ int mixaq_stage_forward(mixaq_block* const* blocks, int32_t n_blocks, const floa
     int rc = mixaq_score_windows(blocks[0], x, scores, stream);
     if (rc) return rc;
     // A batch of small maps (stage_splits, stage_split_pays) runs as two chains of blocks, one per half of the images, the second on the
-    // first block's side stream: the images are independent through the whole stage, every kernel of such a map leaves
+    // caller's side stream: the images are independent through the whole stage, every kernel of such a map leaves
     // CUs idle, and the window kernel of one half runs beside the token kernel of the other.  Not under stream capture.
     hipStream_t st = (hipStream_t)stream;
     const mixaq_block* b0 = blocks[0];
     Part parts[2];
     int n_parts = 1;
     hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
-    bool split = n_blocks > 1 && b0->side_stream != nullptr && stage_split_pays(b0, n_blocks);
+    bool split = n_blocks > 1 && b0->side_device >= 0 && stage_split_pays(b0, n_blocks);
     for (int i = 0; split && i < n_blocks; ++i) split = blocks[i]->fused_window && blocks[i]->fused_token;
     if (split) {
         if (hipStreamIsCapturing(st, &capturing) != hipSuccess) {
@@ -823,29 +906,43 @@ int mixaq_stage_forward(mixaq_block* const* blocks, int32_t n_blocks, const floa
             split = false;
         } else if (capturing != hipStreamCaptureStatusNone) split = false;
     }
+    SideStreams::Side* side = nullptr;
     if (split) {
+        int dev = -1;
+        if (hipGetDevice(&dev) == hipSuccess && dev == b0->side_device) side = SideStreams::of(dev).begin(st);
+    }
+    if (side) {
         Workspace w;
         n_parts = 2;
         parts[0].first = 0; parts[0].images = (b0->d.B + 1) / 2; parts[0].ws_offset = 0;
         parts[1].first = parts[0].images; parts[1].images = b0->d.B / 2;
         parts[1].ws_offset = carve(b0, nullptr, &w, false, parts[0].images);
-        HIP_TRY(hipEventRecord(b0->ev_fork, st));                    // both chains start together (the second one window kernel behind
-        HIP_TRY(hipStreamWaitEvent(b0->side_stream, b0->ev_fork, 0)); // the first measured slower: 377 against 361 us, six blocks on 192 windows at C = 384)
+        std::lock_guard<std::mutex> lock(side->mu);                  // both chains start together (the second one window kernel behind the
+        hipError_t e = hipEventRecord(side->fork, st);               // first measured slower: 377 against 361 us, six blocks on 192 windows at C = 384)
+        if (e == hipSuccess) e = hipStreamWaitEvent(side->stream, side->fork, 0);
+        if (e != hipSuccess) {
+            SideStreams::of(b0->side_device).done(side);
+            return fail(MIXAQ_E_HIP, "starting the second chain failed: %s", hipGetErrorString(e));
+        }
     }
     const float* cur = x;
     for (int i = 0; i < n_blocks && !rc; ++i) {
         float* dst = ((n_blocks - 1 - i) & 1) ? tmp : y;            // the last block writes y
         const int kh = k_high[i / 2], kl = k_low ? k_low[i / 2] : nW - kh;
         for (int p = 0; p < n_parts && !rc; ++p) {
-            void* sp = p == 0 ? stream : (void*)b0->side_stream;
+            void* sp = p == 0 ? stream : (void*)side->stream;
             if (i == 0) rc = forward_impl(blocks[0], cur, nullptr, scores, kh, kl, dst, workspace, workspace_bytes, sp, nullptr, nullptr, perm, false, parts[p]);
             else rc = forward_impl(blocks[i], cur, perm, nullptr, kh, kl, dst, workspace, workspace_bytes, sp, nullptr, nullptr, nullptr, false, parts[p]);
         }
         cur = dst;
     }
-    if (split) {                                                     // the side chain joins, also after an error in between
-        (void)hipEventRecord(b0->ev_join, b0->side_stream);
-        (void)hipStreamWaitEvent(st, b0->ev_join, 0);
+    if (side) {                                                      // the side chain joins, also after an error in between
+        {
+            std::lock_guard<std::mutex> lock(side->mu);
+            (void)hipEventRecord(side->join, side->stream);
+            (void)hipStreamWaitEvent(st, side->join, 0);
+        }
+        SideStreams::of(b0->side_device).done(side);
     }
     return rc;
 }

@@ -492,6 +492,54 @@ def test_repeated_forked_stage_calls_are_bit_stable(B, H, W, C, heads, n_blocks)
             gb.close()
 
 
+@pytest.mark.parametrize("threads", [1, 3])
+def test_forked_stages_on_more_streams_than_side_streams(threads):
+    """Stages that run as two chains on the default stream and on six of the callers' own (more than there are side streams), in
+    turn or from three threads at once, and again after all handles were destroyed and made anew: every result has the bits of
+    the same blocks run one after another on the whole batch."""
+    import threading
+    B, C, n_blocks = 2, 192, 6
+    spec = synth.BlockSpec(B, 82, 91, C, C // 32)
+    assert gh.stage_forks(spec, n_blocks)
+    dev = torch.device("cuda:0")
+    k, pairs = spec.nW // 2, n_blocks // 2
+    inputs = [synth.make_block_inputs(spec, 360 + i) for i in range(n_blocks)]
+    x = torch.from_numpy(synth.make_feature_map(spec, 361, blobs=True)).to(dev)
+    streams = [None] + [torch.cuda.Stream() for _ in range(6)]
+    print("forked stages on seven streams, threads", threads, flush=True)
+    for again in range(2):
+        blocks = [gh.GpuBlock(inp, 3 * (i % 2)) for i, inp in enumerate(inputs)]
+        try:
+            handles = [gb.blk for gb in blocks]
+            scores, perm = blocks[0].score_select(x, k)
+            want = x
+            for gb in blocks:
+                want = gb.forward(want, perm, k)
+            torch.cuda.synchronize()
+            bufs = [dict(y=torch.empty_like(x), tmp=torch.empty_like(x), ws=torch.empty_like(blocks[0].ws),
+                         scores=torch.empty_like(scores), perm=torch.empty_like(perm)) for _ in streams]
+            torch.cuda.synchronize()
+
+            def run(first):
+                for it in range(3):
+                    for i in range(first, len(streams), threads):
+                        b = bufs[i]
+                        M.mixaq_stage_forward(handles, x, [k] * pairs, None, b["y"], b["tmp"], b["scores"], b["perm"], b["ws"],
+                                              stream=streams[i])
+
+            workers = [threading.Thread(target=run, args=(t,)) for t in range(threads)]
+            for t in workers:
+                t.start()
+            for t in workers:
+                t.join()
+            torch.cuda.synchronize()
+            for b in bufs:
+                assert torch.equal(b["y"], want) and torch.equal(b["perm"], perm)
+        finally:
+            for gb in blocks:
+                gb.close()
+
+
 def test_random_sweep_of_forked_stage_calls():
     """Six seeded random stage calls that run as two chains: width, batch, map size, precision and, per pair, any split into
     high, low and pruned windows; maps and lists must equal the oracle's bit for bit."""
