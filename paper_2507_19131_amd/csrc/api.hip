@@ -332,11 +332,15 @@ int check_qparam(const mixaq_qparam& q, int bits, const char* name)
     return MIXAQ_OK;
 }
 
-// Two chains pay while the kernels of the stage leave CUs idle for part of their time: a batch of at least two maps with at
-// most this many windows in all, on the fused kernels (one chain -> two: a pair of blocks on 2784 windows at C = 96 183 -> 174 us,
-// on 1920 at 192 330 -> 314, on 1440 at 384 648 -> 602; beyond, 2 % and less: 4176 windows at 96 255 -> 250, 4107 at 128 342 -> 340,
-// 4608 at 192 773 -> 758, 4800 at 384 2142 -> 2091).
+// Two chains pay while the kernels of the stage leave CUs idle for part of their time (one chain -> two: a pair of blocks on 2784
+// windows at C = 96 183 -> 174 us, on 1920 at 192 330 -> 314, on 1440 at 384 648 -> 602), up to this many windows in all.
 constexpr int STAGE_SPLIT_MAX_WINDOWS = 4096;
+// Each chain of a larger batch takes its half of the images in rounds of at most half this many windows, whole images: the tail of
+// a kernel still runs beside the other chain's, and what a round reads again is nearer (a pair of blocks on 8 x 1392 windows at
+// C = 96 689 -> 660 us, 4 x 1369 at 128 449 -> 442, 16 x 360 at 192 932 -> 897, 16 x 361 at 256 1392 -> 1357, 64 x 96 at 384 2597 -> 2490;
+// as two halves without rounds 711 -> 697 and equal for the first two).  Not where the halves are uneven by more than an eighth
+// (5 x 1392 at 96 416 -> 419, 3 x 2500 464 -> 467).
+constexpr int STAGE_ROUND_WINDOWS = 5600;
 // Fork and join cost 25 to 30 us, so the stage has to be long enough: the line is drawn at windows times channels over all its
 // blocks.  One chain -> two, in us (three sets of handles in turn take the same, as they share the caller's side stream):
 //   two blocks:  C = 96, 256 windows 43 -> 77; 392 54 -> 78; 840 79 -> 84; 1352 104 -> 101
@@ -353,8 +357,17 @@ bool stage_split_pays(const mixaq_block* b, int n_blocks)
 }
 bool stage_splits(const mixaq_block* b)
 {
-    return b->d.B >= 2 && b->d.B * b->nW <= STAGE_SPLIT_MAX_WINDOWS && b->fused_window && b->fused_token;
+    const bool small = b->d.B * b->nW <= STAGE_SPLIT_MAX_WINDOWS, even = b->d.B % 2 == 0 || b->d.B >= 9;
+    return b->d.B >= 2 && (small || even) && b->fused_window && b->fused_token;
 }
+
+// rounds in which the two chains of such a stage go through their images
+int stage_rounds(const mixaq_block* b)
+{
+    const long long windows = (long long)b->d.B * b->nW;
+    return (int)std::min<long long>(b->d.B / 2, (windows + STAGE_ROUND_WINDOWS - 1) / STAGE_ROUND_WINDOWS);
+}
+int most_images_of_a_round(const mixaq_block* b) { return ((b->d.B + 1) / 2 + stage_rounds(b) - 1) / stage_rounds(b); }
 
 void make_geom(const mixaq_block* b, int k_hi, int k_lo, Geom* G, int images = 0)
 {
@@ -786,8 +799,8 @@ static int block_create(const mixaq_block_desc* desc, const mixaq_shared_params*
     Workspace w;
     b->ws_bytes = carve(b, nullptr, &w);
     b->ws_fused_bytes = carve(b, nullptr, &w, true);
-    if (stage_splits(b)) {                  // two chains: each half of the images has its own part of the workspace
-        b->ws_bytes = std::max(b->ws_bytes, carve(b, nullptr, &w, false, (desc->B + 1) / 2) + carve(b, nullptr, &w, false, desc->B / 2));
+    if (stage_splits(b)) {                  // two chains: each has its own part of the workspace, enough for its longest round
+        b->ws_bytes = std::max(b->ws_bytes, 2 * carve(b, nullptr, &w, false, most_images_of_a_round(b)));
         int dev = -1;
         HIP_TRY(hipGetDevice(&dev));
         if (dev >= 0 && dev < MAX_DEVICES) {
@@ -890,13 +903,13 @@ int mixaq_stage_forward(mixaq_block* const* blocks, int32_t n_blocks, const floa
     }
     int rc = mixaq_score_windows(blocks[0], x, scores, stream);
     if (rc) return rc;
-    // A batch of small maps (stage_splits, stage_split_pays) runs as two chains of blocks, one per half of the images, the second on the
+    // A batch (stage_splits, stage_split_pays) runs as two chains of blocks, one per half of the images, the second on the
     // caller's side stream: the images are independent through the whole stage, every kernel of such a map leaves
     // CUs idle, and the window kernel of one half runs beside the token kernel of the other.  Not under stream capture.
     hipStream_t st = (hipStream_t)stream;
     const mixaq_block* b0 = blocks[0];
-    Part parts[2];
-    int n_parts = 1;
+    int rounds = 1;
+    size_t ws_side = 0;                                              // where the side chain's part of the workspace starts
     hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
     bool split = n_blocks > 1 && b0->side_device >= 0 && stage_split_pays(b0, n_blocks);
     for (int i = 0; split && i < n_blocks; ++i) split = blocks[i]->fused_window && blocks[i]->fused_token;
@@ -913,10 +926,8 @@ int mixaq_stage_forward(mixaq_block* const* blocks, int32_t n_blocks, const floa
     }
     if (side) {
         Workspace w;
-        n_parts = 2;
-        parts[0].first = 0; parts[0].images = (b0->d.B + 1) / 2; parts[0].ws_offset = 0;
-        parts[1].first = parts[0].images; parts[1].images = b0->d.B / 2;
-        parts[1].ws_offset = carve(b0, nullptr, &w, false, parts[0].images);
+        rounds = stage_rounds(b0);
+        ws_side = carve(b0, nullptr, &w, false, most_images_of_a_round(b0));
         std::lock_guard<std::mutex> lock(side->mu);                  // both chains start together (the second one window kernel behind the
         hipError_t e = hipEventRecord(side->fork, st);               // first measured slower: 377 against 361 us, six blocks on 192 windows at C = 384)
         if (e == hipSuccess) e = hipStreamWaitEvent(side->stream, side->fork, 0);
@@ -925,16 +936,26 @@ int mixaq_stage_forward(mixaq_block* const* blocks, int32_t n_blocks, const floa
             return fail(MIXAQ_E_HIP, "starting the second chain failed: %s", hipGetErrorString(e));
         }
     }
-    const float* cur = x;
-    for (int i = 0; i < n_blocks && !rc; ++i) {
-        float* dst = ((n_blocks - 1 - i) & 1) ? tmp : y;            // the last block writes y
-        const int kh = k_high[i / 2], kl = k_low ? k_low[i / 2] : nW - kh;
-        for (int p = 0; p < n_parts && !rc; ++p) {
-            void* sp = p == 0 ? stream : (void*)side->stream;
-            if (i == 0) rc = forward_impl(blocks[0], cur, nullptr, scores, kh, kl, dst, workspace, workspace_bytes, sp, nullptr, nullptr, perm, false, parts[p]);
-            else rc = forward_impl(blocks[i], cur, perm, nullptr, kh, kl, dst, workspace, workspace_bytes, sp, nullptr, nullptr, nullptr, false, parts[p]);
+    for (int round = 0; round < rounds && !rc; ++round) {            // block by block, on both chains
+        const float* cur = x;
+        for (int i = 0; i < n_blocks && !rc; ++i) {
+            float* dst = ((n_blocks - 1 - i) & 1) ? tmp : y;        // the last block writes y
+            const int kh = k_high[i / 2], kl = k_low ? k_low[i / 2] : nW - kh;
+            for (int chain = 0; chain < (side ? 2 : 1) && !rc; ++chain) {
+                Part part;                                           // one chain: all images
+                if (side) {
+                    const int first = chain ? (b0->d.B + 1) / 2 : 0, images = chain ? b0->d.B / 2 : (b0->d.B + 1) / 2;
+                    const int from = (int)((long long)images * round / rounds), to = (int)((long long)images * (round + 1) / rounds);
+                    part.first = first + from;
+                    part.images = to - from;
+                    part.ws_offset = chain ? ws_side : 0;
+                }
+                void* sp = chain ? (void*)side->stream : stream;
+                if (i == 0) rc = forward_impl(blocks[0], cur, nullptr, scores, kh, kl, dst, workspace, workspace_bytes, sp, nullptr, nullptr, perm, false, part);
+                else rc = forward_impl(blocks[i], cur, perm, nullptr, kh, kl, dst, workspace, workspace_bytes, sp, nullptr, nullptr, nullptr, false, part);
+            }
+            cur = dst;
         }
-        cur = dst;
     }
     if (side) {                                                      // the side chain joins, also after an error in between
         {

@@ -492,6 +492,31 @@ def test_repeated_forked_stage_calls_are_bit_stable(B, H, W, C, heads, n_blocks)
             gb.close()
 
 
+@pytest.mark.parametrize("B,H,W,C,k_low", [(11, 161, 175, 96, None), (10, 161, 175, 96, 100), (6, 224, 220, 128, None), (3, 252, 371, 96, 200)])
+def test_stage_of_a_large_batch_in_rounds(B, H, W, C, k_low):
+    """More windows than two chains take at once: the chains go through their halves in rounds (uneven ones where the halves
+    are odd), pruned or not, or the stage stays on one chain (three images); the bits are those of block after block."""
+    spec = synth.BlockSpec(B, H, W, C, C // 32)
+    assert B * spec.nW > 5600
+    k = spec.nW // 2
+    dev = torch.device("cuda:0")
+    x = torch.randn((B, H, W, C), generator=torch.Generator(device=dev).manual_seed(370), device=dev)
+    print("stage in rounds", B, H, W, "C", C, "k_low", k_low, flush=True)
+    blocks = [gh.GpuBlock(synth.make_block_inputs(spec, 371 + i), 3 * (i % 2)) for i in range(2)]
+    try:
+        scores, perm = blocks[0].score_select(x, k)
+        want = x
+        for gb in blocks:
+            want = gb.forward(want, perm, k) if k_low is None else gh._forward_pruned(gb, want, perm, k, k_low)
+        y, tmp, s2, p2 = torch.full_like(x, float("nan")), torch.full_like(x, float("nan")), torch.empty_like(scores), torch.empty_like(perm)
+        M.mixaq_stage_forward([gb.blk for gb in blocks], x, [k], None if k_low is None else [k_low], y, tmp, s2, p2, blocks[0].ws)
+        torch.cuda.synchronize()
+        assert torch.equal(y, want) and torch.equal(p2, perm)
+    finally:
+        for gb in blocks:
+            gb.close()
+
+
 @pytest.mark.parametrize("threads", [1, 3])
 def test_forked_stages_on_more_streams_than_side_streams(threads):
     """Stages that run as two chains on the default stream and on six of the callers' own (more than there are side streams), in
