@@ -51,7 +51,7 @@ void gelu_table(float* tab)
             tab[4 * i + 1 + k] = (float)(acc * 0.5);
         }
     }
-    // the kernels work on values scaled by GELU_SCALE (see gelu_scaled): exact, a power of two
+    // the kernels work on values scaled by GELU_SCALE (see gelu_begin): exact, a power of two
     for (int e = 0; e < 4 * GELU_K; ++e) tab[e] *= GELU_SCALE;
 }
 }  // namespace mixaq
@@ -270,7 +270,7 @@ private:
 // packs W[N,K] (row-major int8) into MFMA A-operand order and builds the per-branch epilogue constants
 int prepare_linear(mixaq_block* blk, Linear& L, const int8_t* w_dev, const float* s_dev, int N, int K,
                    const float* const bias_dev[2], const mixaq_qparam in_q[2], int weight_bits, bool reg_order,
-                   float out_scale = 1.0f)   // a power of two folded into the epilogue constants (exact; see gelu_scaled)
+                   float out_scale = 1.0f)   // a power of two folded into the epilogue constants (exact; see gelu_begin)
 {
     std::vector<int8_t> w;
     std::vector<float> s, b;

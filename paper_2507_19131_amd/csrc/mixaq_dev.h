@@ -111,15 +111,29 @@ __device__ __forceinline__ void gelu_stage_table(float4* lds, const float4* tab,
 {
     for (int e = tid; e < GELU_K; e += nthreads) lds[e] = tab[e];
 }
-__device__ __forceinline__ float gelu_scaled(float xs, const float4* lds)
+// GELU and quantizer of four values in two halves: all four table reads are requested before the first is waited for (value after
+// value, a wave alone waited four times: block of 56 x 56 x 96 18.9 -> 18.6 us, 2 x 50 x 84 x 384 293 -> 287.5, backbone 627 -> 621.5).
+struct GeluPart { float xs[4], d[4]; float4 c[4]; };
+__device__ __forceinline__ void gelu_begin(GeluPart& p, const float4* lds)
 {
-    const float u = fminf(fabsf(xs), (float)GELU_K * 0x1.fffffep-1f);
-    const float d = __builtin_amdgcn_fractf(u);
-    const float4 c = lds[(int)u];
-    float h = fmaf(c.w, d, c.z);
-    h = fmaf(h, d, c.y);
-    h = fmaf(h, d, c.x);
-    return fmaxf(xs, 0.0f) - h;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const float u = fminf(fabsf(p.xs[e]), (float)GELU_K * 0x1.fffffep-1f);
+        p.d[e] = __builtin_amdgcn_fractf(u);
+        p.c[e] = lds[(int)u];
+    }
+}
+__device__ __forceinline__ int gelu_end(const GeluPart& p, const QDev& q)
+{
+    int c[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        float h = fmaf(p.c[e].w, p.d[e], p.c[e].z);
+        h = fmaf(h, p.d[e], p.c[e].y);
+        h = fmaf(h, p.d[e], p.c[e].x);
+        c[e] = quant_code(fmaxf(p.xs[e], 0.0f) - h, q);
+    }
+    return pack4(c[0], c[1], c[2], c[3]);
 }
 
 // ---- packed sub-byte codes (tensors that cross a kernel boundary) ---------------------------------
