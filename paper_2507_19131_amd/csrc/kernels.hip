@@ -842,10 +842,12 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, j = lane & 31, g = lane >> 5;
     const int hw = QS == 1 ? wave : wave >> 1, tb0 = QS == 1 ? 0 : wave & 1;   // head inside the workgroup, first token block
     const int head = hg * NH + hw;
-    // Weight fragments in flight.  STREAM (long K): the fragments of q, k and v are one stream that starts under the LayerNorm
-    // phase and runs on across the epilogues.
-    constexpr bool STREAM = KS >= 12;
-    constexpr int RING = !STREAM ? (KS < 6 ? KS : 6) : KS == 12 ? 6 : KS < 32 ? 8 : 16;
+    // Weight fragments in flight.  STREAM: the fragments of q, k and v are one stream that starts under the LayerNorm phase and runs
+    // on across the epilogues (each chain on its own starts with a wait for its first fragment: 100 x 168 x 192 87.0 -> 85.9 us,
+    // 3 x 61 x 93 x 192 75.0 -> 73.3, backbone 621.8 -> 615).  Not where the registers are taken: three heads of a wave each spill
+    // 17 to 26 of their 96, the halves of a window's heads in pairs of waves 53 to 94 of their 80.
+    constexpr bool STREAM = KS >= 12 || (HG == 1 && !(NH == 3 && QS == 1));
+    constexpr int RING = !STREAM ? (KS < 6 ? KS : 6) : KS < 6 ? KS : KS == 6 ? (QS == 1 ? 6 : 3) : KS == 12 ? 6 : KS < 32 ? 8 : 16;
     static_assert(!STREAM || KS % RING == 0, "each chain starts at ring slot 0");
     v4i ring[RING];
     auto weights_of = [&](int which) { return A.Wqkv + (size_t)(which * NHT + head) * KS * 64 + lane; };
