@@ -259,6 +259,7 @@ __global__ __launch_bounds__(256) void bypass_kernel(Geom G, const int* __restri
 template <int LPT, int NV, bool GATHER>
 __global__ __launch_bounds__(256) void ln_quant_kernel(Geom G, LnArgs A)
 {
+    touch_arguments<sizeof(Geom) + sizeof(LnArgs)>();
     constexpr int TP = 256 / LPT;
     const int row = blockIdx.x * TP + threadIdx.x / LPT, sub = threadIdx.x % LPT;
     if (row >= G.rows_total) return;
@@ -360,6 +361,7 @@ constexpr int GEMM_TILE_MAX_K = 2048;      // 64 rows x K bytes of LDS
 template <int EPI, int KMAX, int RT, int D>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RT * KMAX <= 65536 ? 2 : 1))) void gemm_tile_kernel(Geom G, GemmArgs A)
 {
+    touch_arguments<sizeof(Geom) + sizeof(GemmArgs)>();
     constexpr int RB = RT / 32, PF = D % 4 == 0 ? 4 : 3;                // PF: LDS reads ahead
     static_assert(D % PF == 0, "the LDS slots come round with the ring");
     __shared__ v4i afr[RT * KMAX / 16];                                // [row blocks][chunk slabs][64 lanes]
@@ -723,6 +725,7 @@ __global__ __launch_bounds__(256) void attn_kernel(Geom G, AttnArgs A)
 template <int LPT, int NV, bool SCORED>
 __global__ __launch_bounds__(256) void ln_window_kernel(Geom G, WinArgs A)
 {
+    touch_arguments<sizeof(Geom) + sizeof(WinArgs)>();
     constexpr int TP = 256 / LPT, C = LPT * NV * 4, KS = C / 32;
     __shared__ int red[4];
     const int tid = threadIdx.x, sub = tid % LPT, t = blockIdx.y * TP + tid / LPT, widx = blockIdx.x;
@@ -822,6 +825,7 @@ template <int C, int NH, bool CODES> struct WinPrm {
 template <int NH, bool TAPS, bool SCORED, int HG = 1, int QS = 1, bool CODES = false>
 __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(win_waves_per_eu(NH, HG, QS, CODES)))) void window_kernel(Geom G, WinArgs A)
 {
+    if (CODES || HG == 2 || (QS == 2 && NH <= 4)) touch_arguments<sizeof(Geom) + sizeof(WinArgs)>();   // few workgroups
     constexpr int NHT = NH * HG;                                         // heads of the block; this workgroup runs NH of them
     constexpr int NW = NH * QS, NTB = 2 / QS;                            // waves; token blocks a wave projects and attends for
     constexpr int C = NHT * 32, KS = NHT, LPT = WinCfg<NH, HG, QS>::LPT, NV = CODES ? 1 : WinCfg<NH, HG, QS>::NV, NT = NW * 64;
@@ -1170,6 +1174,7 @@ __device__ __forceinline__ void token_stage(const float* params, const float4* g
 template <int NH, int RB, bool TAPS>
 __global__ __launch_bounds__(NH * 64) __attribute__((amdgpu_waves_per_eu(tok_waves_per_eu(NH)))) void token_kernel(Geom G, TokArgs A)
 {
+    if (NH == 12 || G.rows_total <= 256 * 32) touch_arguments<sizeof(Geom) + sizeof(TokArgs)>();   // about one workgroup a CU
     constexpr int C = NH * 32, KS = NH, HB = 4 * NH, F = 4 * C;
     constexpr int RING = NH < 8 ? NH : NH == 12 && RB == 1 ? 12 : 8;               // fragments in flight per wave
     constexpr bool PARK_H = RB >= 2 && !TAPS;                         // taps need h of padded tokens too, which have no pixel

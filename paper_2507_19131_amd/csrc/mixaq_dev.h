@@ -32,6 +32,23 @@ struct QDev {
     int   zp;
 };
 
+// Brings every 64-byte line of the kernel's arguments into the scalar cache, in one round trip.  They are written anew for every
+// launch, so the first read of each line goes to memory, and a kernel that reads a field where it needs it meets such a
+// round trip in the middle of its work, again and again: one block on 56 x 56 x 96 18.5 -> 17.8 us, 25 x 42 x 768 93.2 -> 91.3,
+// backbone 613.5 -> 605.7.  For kernels of about one workgroup a CU; where others run meanwhile, the longer wait at the start costs
+// as much as it saves (200 x 336 x 96 103.3 -> 104.2, 3 x 61 x 93 x 192 73.3 -> 74.2), under the first loads too (4 x 256 x 256 x 128
+// 421 -> 433).
+template <int BYTES>
+__device__ __forceinline__ void touch_arguments()
+{
+    const auto* p = (const __attribute__((address_space(4))) int*)__builtin_amdgcn_kernarg_segment_ptr();
+    constexpr int LINES = (BYTES + 63) / 64;
+    int any = p[0];
+#pragma unroll
+    for (int k = 1; k < LINES; ++k) any ^= p[k * 16];
+    asm volatile("" :: "s"(any));
+}
+
 // returns the bit pattern of u; its low byte is the int8 code
 __device__ __forceinline__ int quant_code(float v, const QDev& q)
 {
