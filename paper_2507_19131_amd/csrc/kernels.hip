@@ -479,9 +479,20 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RT * KMAX <
 // The P.V sums start at nzcsum[d] = -zp * sum of the V codes of dim d over the keys, formed once per dim by the caller
 // (an integer multiply is a quarter-rate instruction; and starting the accumulators there costs no instruction, where
 // subtracting afterwards took one per output element).
+// (bias + mask) * log2e of a lane's query at its keys: quads kb * 8 + qd * 2 + g, and the last key (of the lower half only)
+struct BiasRow {
+    float4 quad[(TOK - 1) / 8];
+    float last;
+    // bq: query j of query block 0 at keys g*4 ..+3, in the [13 key quads][64 queries][4] table of the head and mask type
+    __device__ __forceinline__ void request(const float4* bq, int g, int ib)
+    {
+#pragma unroll
+        for (int k = 0; k < (TOK - 1) / 8; ++k) quad[k] = bq[k * 128 + ib * 32];
+        last = bq[(TOK / 4 - g) * 64 + ib * 32].x;
+    }
+};
 struct AttnCore {
-    const float4* bq;         // (bias + mask) * log2e of query j of query block 0 at keys g*4 ..+3, in the [13 key quads][64 queries][4]
-                              // table of this head and mask type: keys k + g*4 ..+3, query block ib are bq[k / 4 * 64 + ib * 32]
+    const float4* bq;         // see BiasRow::request
     float m2, c5;             // in vector registers, like qp's factor and addend
     QDev qp;
     const int* nzcsum;        // [HD], LDS
@@ -490,9 +501,10 @@ struct AttnCore {
     int8_t* tap_p;
 };
 
-template <bool TAPS>
+// REQUEST: the bias is requested here (A.bq), otherwise the caller has done so
+template <bool TAPS, bool REQUEST>
 __device__ __forceinline__ v16i attention_core(const v4i& qf, const v4i (&kf)[2], const v4i (&vt)[2],
-                                               const AttnCore& A, int j, int g, int ib)
+                                               const AttnCore& A, const BiasRow& bias, int j, int g, int ib)
 {
     const v16i zero16 = {0};
     v16i o;
@@ -510,9 +522,9 @@ __device__ __forceinline__ v16i attention_core(const v4i& qf, const v4i (&kf)[2]
                 const int key = kb * 32 + (r >> 2) * 8;                   // + g*4
                 float b[4] = {0.f, 0.f, 0.f, 0.f};
                 if (key + 3 + 4 < TOK) {                                  // four keys, valid for both halves
-                    const float4 b4 = A.bq[(key / 4) * 64 + ib * 32];
+                    const float4 b4 = REQUEST ? A.bq[(key / 4) * 64 + ib * 32] : bias.quad[key / 8];
                     b[0] = b4.x; b[1] = b4.y; b[2] = b4.z; b[3] = b4.w;
-                } else if (key < TOK) b[0] = A.bq[(key / 4 - g) * 64 + ib * 32].x;   // the last key, of the lower half only
+                } else if (key < TOK) b[0] = REQUEST ? A.bq[(key / 4 - g) * 64 + ib * 32].x : bias.last;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     const int kk = key + e + g * 4;
@@ -713,7 +725,7 @@ __global__ __launch_bounds__(256) void attn_kernel(Geom G, AttnArgs A)
     core.tap_p = A.tap_p ? A.tap_p + tb : nullptr;
 #pragma unroll 1
     for (int ib = 0; ib < 2; ++ib) {
-        const v16i o = attention_core<true>(ib ? qf[1] : qf[0], kf, vt, core, j, g, ib);
+        const v16i o = attention_core<true, true>(ib ? qf[1] : qf[0], kf, vt, core, BiasRow(), j, g, ib);
         attention_store<true>(o, in_vgpr(A.qo[branch]), in_vgpr(A.m_o[branch]), j, g, ib, head, G.C, A.out, row0, A.tap_o, A.tap_code, (size_t)canon_slot * TOK, PACK_FRAG);
     }
 }
@@ -812,7 +824,13 @@ struct WinCfg {
 // place on a CU when its share per SIMD, rounded up, fits twice: 360 windows at C = 192 ran in two rounds of one workgroup
 // per CU (24.6 us), now in one round (20.8 us); C = 256, 1444 windows: 83 -> 72 us.  (Three heads at five waves per SIMD spill
 // two registers, four with scores; at four waves none, but the pair of blocks on 1392 windows takes 110.5 instead of 108.0 us.)
-constexpr int win_waves_per_eu(int NH, int HG, int QS, bool CODES) { return CODES ? (NH * HG < 32 ? 4 : 2) : QS == 2 ? (NH * HG > 8 ? 4 : 6) : NH * HG > 8 ? 3 : NH == 3 ? 5 : 4; }
+constexpr bool win_pairs_share(int NH, int HG) { return (NH == 6 && HG == 1) || NH * HG == 8; }   // pairs of waves, several workgroups on a CU
+constexpr int win_waves_per_eu(int NH, int HG, int QS, bool CODES)
+{
+    if (CODES) return NH * HG < 32 ? 4 : 2;
+    if (QS == 2) return win_pairs_share(NH, HG) ? 6 : 4;
+    return NH * HG > 8 ? 3 : NH == 3 ? 5 : 4;
+}
 
 // The window kernel's parameter block of one branch (see WinArgs::params), as a workgroup of NH heads holds it in LDS:
 // LN1 gamma and beta (not with CODES), then the QKV epilogue constants of its own heads, per head [q|k|v][m|bias|-zp*colsum][32 dims]
@@ -849,8 +867,10 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
     // Weight fragments in flight.  STREAM: the fragments of q, k and v are one stream that starts under the LayerNorm phase and runs
     // on across the epilogues (each chain on its own starts with a wait for its first fragment: 100 x 168 x 192 87.0 -> 85.9 us,
     // 3 x 61 x 93 x 192 75.0 -> 73.3, backbone 621.8 -> 615).  Not where the registers are taken: three heads of a wave each spill
-    // 17 to 26 of their 96, the halves of a window's heads in pairs of waves 53 to 94 of their 80.
-    constexpr bool STREAM = KS >= 12 || (HG == 1 && !(NH == 3 && QS == 1));
+    // 17 to 26 of their 96, the pairs of C = 256 67 to 94 of their 80.  (Half a window's heads at C = 128 and 192, at most 96
+    // windows, have 128 since they are alone on their CU: six blocks on 81 windows at C = 192 147 -> 133 us, three sets in turn
+    // of two blocks on 64 windows at C = 128 36.7 -> 33.8.)
+    constexpr bool STREAM = KS >= 12 || (HG == 1 ? !(NH == 3 && QS == 1) : KS < 8);
     constexpr int RING = !STREAM ? (KS < 6 ? KS : 6) : KS < 6 ? KS : KS == 6 ? (QS == 1 ? 6 : 3) : KS == 12 ? 6 : KS < 32 ? 8 : 16;
     static_assert(!STREAM || KS % RING == 0, "each chain starts at ring slot 0");
     v4i ring[RING];
@@ -1047,6 +1067,9 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
 #pragma unroll
         for (int tb = 0; tb < NTB; ++tb) finish(tb, acc[tb]);
     }
+    // a pair of waves requests its bias ahead of the exchange, where the registers are free
+    constexpr bool BIAS_EARLY = QS == 2 && (CODES || !win_pairs_share(NH, HG));
+    BiasRow bias;
     v4i vt[2];
     {
         const int nb = 2 * NHT + head, n = nb * 32 + j;                   // this lane's output channel (dim j of the head)
@@ -1085,6 +1108,8 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
         chain(wp, nullptr, acc, false);
 #pragma unroll
         for (int tb = 0; tb < NTB; ++tb) finish(tb, acc[tb]);
+        if (BIAS_EARLY)                                                   // under the exchange
+            bias.request(A.bias2 + (size_t)(mask_type(G, w) * NHT + head) * BIAS_QUADS * 64 + g * 64 + j, g, tb0);
         cs = half_sum(cs);
         if (QS == 1) {
             if (g == 0) csum[wave][j] = -(A.qp[branch].zp * cs);
@@ -1123,7 +1148,7 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
 #pragma unroll 1
     for (int ib = tb0; ib < tb0 + NTB; ++ib) {
         asm volatile("" ::: "memory");
-        const v16i o = attention_core<TAPS>(NTB == 2 && ib ? qk[0][NTB - 1] : qk[0][0], kf, vt, core, j, g, ib);
+        const v16i o = attention_core<TAPS, !BIAS_EARLY>(NTB == 2 && ib ? qk[0][NTB - 1] : qk[0][0], kf, vt, core, bias, j, g, ib);
         attention_store<TAPS>(o, in_vgpr(A.qo[branch]), in_vgpr(A.m_o[branch]), j, g, ib, head, C, out, orow0, A.tap_o, A.tap_code, canon_row0, pack);
     }
 }
