@@ -70,6 +70,28 @@ __device__ __forceinline__ void token_ln_apply(float4 (&v)[NV], float mean, floa
     }
 }
 
+// the same with gamma and beta requested ahead (a kernel that is one chain of waits: the parameters travel with the token)
+template <int NV> struct Affine { float4 g[NV], b[NV]; };
+template <int LPT, int NV>
+__device__ __forceinline__ void request_affine(Affine<NV>& a, const float* __restrict__ gamma, const float* __restrict__ beta, int sub)
+{
+#pragma unroll
+    for (int k = 0; k < NV; ++k) { a.g[k] = *(const float4*)(gamma + (k * LPT + sub) * 4); a.b[k] = *(const float4*)(beta + (k * LPT + sub) * 4); }
+}
+template <int LPT, int NV>
+__device__ __forceinline__ void token_layernorm(float4 (&v)[NV], int C, float eps, const Affine<NV>& a)
+{
+    float mean, rstd;
+    token_ln_stats<LPT, NV>(v, C, eps, mean, rstd);
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+        v[k].x = fmaf((v[k].x - mean) * rstd, a.g[k].x, a.b[k].x);
+        v[k].y = fmaf((v[k].y - mean) * rstd, a.g[k].y, a.b[k].y);
+        v[k].z = fmaf((v[k].z - mean) * rstd, a.g[k].z, a.b[k].z);
+        v[k].w = fmaf((v[k].w - mean) * rstd, a.g[k].w, a.b[k].w);
+    }
+}
+
 template <int LPT, int NV>
 __device__ __forceinline__ void token_layernorm(float4 (&v)[NV], int C, float eps, const float* __restrict__ gamma,
                                                 const float* __restrict__ beta, int sub, int first = 0)
@@ -264,6 +286,7 @@ __global__ __launch_bounds__(256) void ln_quant_kernel(Geom G, LnArgs A)
     const int row = blockIdx.x * TP + threadIdx.x / LPT, sub = threadIdx.x % LPT;
     if (row >= G.rows_total) return;
     int branch, canon, pix;
+    float4 v[NV];
     if (GATHER) {
         RowInfo ri = row_info(G, A.perm, row);
         branch = ri.branch; canon = ri.canon; pix = ri.pix;
@@ -274,13 +297,15 @@ __global__ __launch_bounds__(256) void ln_quant_kernel(Geom G, LnArgs A)
         pix = 0;
     }
     const QDev q = in_vgpr(A.q[branch]);
-    float4 v[NV];
-    const bool real = canon >= 0 && pix >= 0;
-    if (real) {
-        const float* src = GATHER ? A.src + (size_t)pix * G.C : A.src + (size_t)row * G.C;
+    // h and the parameters with the row's mark, not behind it: every row of the region has its place in h (16 windows
+    // at C = 512, six blocks 242.6 -> 240.4 us; the kernel itself on 24 windows at C = 768 4.8 -> 3.7)
+    Affine<NV> af;
+    const float* src = A.src + (GATHER ? (size_t)max(pix, 0) : (size_t)row) * G.C;
 #pragma unroll
-        for (int k = 0; k < NV; ++k) v[k] = *(const float4*)(src + (k * LPT + sub) * 4);
-        token_layernorm<LPT, NV>(v, LPT * NV * 4, A.eps, A.gamma[branch], A.beta[branch], sub);
+    for (int k = 0; k < NV; ++k) v[k] = *(const float4*)(src + (k * LPT + sub) * 4);
+    request_affine<LPT, NV>(af, A.gamma[branch], A.beta[branch], sub);
+    if (canon >= 0 && pix >= 0) {
+        token_layernorm<LPT, NV>(v, LPT * NV * 4, A.eps, af);
     } else {
 #pragma unroll
         for (int k = 0; k < NV; ++k) v[k] = make_float4(0.f, 0.f, 0.f, 0.f);   // padding enters as LN output 0
@@ -743,9 +768,22 @@ __global__ __launch_bounds__(256) void ln_window_kernel(Geom G, WinArgs A)
     const int tid = threadIdx.x, sub = tid % LPT, t = blockIdx.y * TP + tid / LPT, widx = blockIdx.x;
     int branch = 0, row0 = 0, canon_slot = 0, slot = widx, w, bimg;
     bool pruned = false;
+    int pix = -1;
+    float4 v[NV];
+    auto gather = [&] {                                                   // needs the window only: ahead of its rank
+        if (t < TOK) {
+            const int wr = G.by_nWc(w), wc = w - wr * G.nWc, tr = t / WS, tc = t - tr * WS;
+            int pr = wr * WS + tr + G.shift; if (pr >= G.Hp) pr -= G.Hp;
+            int pc = wc * WS + tc + G.shift; if (pc >= G.Wp) pc -= G.Wp;
+            pix = (pr < G.H && pc < G.W) ? (bimg * G.H + pr) * G.W + pc : -1;
+        }
+#pragma unroll
+        for (int k = 0; k < NV; ++k) v[k] = pix >= 0 ? *(const float4*)(A.x + (size_t)pix * C + (k * LPT + sub) * 4) : make_float4(0.f, 0.f, 0.f, 0.f);
+    };
     if (SCORED) {
         bimg = G.by_nW(widx);
         w = widx - bimg * G.nW;
+        gather();
         const int rank = window_rank<256>(A.scores + (size_t)bimg * G.nW, G.nW, w, tid, red);
         if (tid == 0 && blockIdx.y == 0) A.perm_out[(size_t)bimg * G.nW + rank] = w;
         canon_slot = bimg * G.nW + rank;
@@ -766,16 +804,9 @@ __global__ __launch_bounds__(256) void ln_window_kernel(Geom G, WinArgs A)
         for (int r = G.rows_hi + tid; r < G.base_lo; r += 256) { A.row_pix[r] = -1; A.row_canon[r] = -1; }
         for (int r = G.base_lo + G.rows_lo + tid; r < G.rows_total; r += 256) { A.row_pix[r] = -1; A.row_canon[r] = -1; }
     }
-    int pix = -1;
-    if (t < TOK) {
-        const int wr = G.by_nWc(w), wc = w - wr * G.nWc, tr = t / WS, tc = t - tr * WS;
-        int pr = wr * WS + tr + G.shift; if (pr >= G.Hp) pr -= G.Hp;
-        int pc = wc * WS + tc + G.shift; if (pc >= G.Wp) pc -= G.Wp;
-        pix = (pr < G.H && pc < G.W) ? (bimg * G.H + pr) * G.W + pc : -1;
-    }
-    float4 v[NV];
-#pragma unroll
-    for (int k = 0; k < NV; ++k) v[k] = pix >= 0 ? *(const float4*)(A.x + (size_t)pix * C + (k * LPT + sub) * 4) : make_float4(0.f, 0.f, 0.f, 0.f);
+    if (!SCORED) gather();
+    Affine<NV> af;
+    request_affine<LPT, NV>(af, A.params[branch], A.params[branch] + C, sub);
     if (pruned) {                                                         // Sec. 3.4: the features are forwarded
         if (pix >= 0) {
 #pragma unroll
@@ -785,7 +816,7 @@ __global__ __launch_bounds__(256) void ln_window_kernel(Geom G, WinArgs A)
     }
     const int canon = canon_slot * TOK + t;
     if (sub == 0 && t < TOK) { A.row_pix[row0 + t] = pix; A.row_canon[row0 + t] = canon; }
-    if (pix >= 0) token_layernorm<LPT, NV>(v, C, A.eps, A.params[branch], A.params[branch] + C, sub);   // padding enters as LN output 0
+    if (pix >= 0) token_layernorm<LPT, NV>(v, C, A.eps, af);              // padding enters as LN output 0
     const QDev q = in_vgpr(A.q_in[branch]);
 #pragma unroll
     for (int k = 0; k < NV; ++k) {
