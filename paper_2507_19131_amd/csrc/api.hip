@@ -696,11 +696,12 @@ static int block_create(const mixaq_block_desc* desc, const mixaq_shared_params*
     // their floor (see exp2_pinned).  The products of a branch lie in [-P, P], P = 32 * 2^(2 bits - 2) steps of m2, so an unmasked
     // logit is at most 2 P and the span of its table row below the row's maximum: no floor while that is under 99 (1 is left for the
     // roundings).  A masked pair is worth -100 log2(e) or less, e^-100 of a probability, which neither changes a denominator (at
-    // least 1) nor makes a code: any value that keeps its exponent far below 2^-53 and above 2^-126 gives the same bits.  Where the
-    // products are narrow enough its table entry is 90 below the row's largest unmasked one, and such windows need no floor either
-    // (it costs 51 vector instructions per query block); otherwise they take it.  Anything that is no ordinary number takes it too.
+    // least 1) nor makes a code.  Nor does any value whose exponent stays at or under -59 (all 48 together are less than 2^-53, half
+    // of the last binary64 place of a sum from one on) and above -126: where the products are narrow enough its table entry is 92
+    // below the row's largest unmasked one, and such windows need no floor either (it costs 51 vector instructions per query
+    // block); otherwise they take it.  Anything that is no ordinary number takes it too.
     {
-        constexpr float MASKED_BELOW = 90.0f, MASKED_SPAN = 34.0f, STEPS_MAX = 0x1p40f;   // exponents of masked pairs: -90 +- 34
+        constexpr float MASKED_BELOW = 92.0f, MASKED_SPAN = 33.0f, STEPS_MAX = 0x1p40f;   // exponents of masked pairs: -92 +- 33
         float span[2];                                       // 2 P
         bool narrow = true;
         for (int br = 0; br < 2; ++br) {

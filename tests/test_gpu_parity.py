@@ -427,11 +427,11 @@ def test_logits_that_are_no_ordinary_numbers(C, heads, fused, kind):
     gh.assert_parity(res)
 
 
-@pytest.mark.parametrize("span,kind", [(33.0, "bias"), (35.0, "bias"), (94.0, "plain"), (101.0, "plain"), (400.0, "plain"), (30.0, "made_up")])
+@pytest.mark.parametrize("span,kind", [(32.5, "bias"), (33.5, "bias"), (35.0, "bias"), (94.0, "plain"), (101.0, "plain"), (400.0, "plain"), (30.0, "made_up")])
 @pytest.mark.parametrize("C,heads,fused,bits", [(96, 3, True, (8, 4)), (96, 3, False, (8, 4)), (384, 12, True, (4, 2))])
 def test_exponents_around_the_lines_of_their_floor(C, heads, fused, bits, span, kind):
     """Products of q and k that span `span` exponents with saturated codes, on both sides of the lines from which windows with
-    masked pairs (34) and all windows (99 with the bias) hold their exponents at the floor, and a bias that makes up for the mask
+    masked pairs (33) and all windows (99 with the bias) hold their exponents at the floor, and a bias that makes up for the mask
     of some pairs.  Every tap is the oracle's."""
     spec, inp, x, k = _case(2, 14, 21, C, heads, 3, 0.5, 83, blobs=True, bits=bits)
     rng = np.random.default_rng(84)
