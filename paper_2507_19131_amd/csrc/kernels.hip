@@ -851,10 +851,11 @@ struct WinCfg {
 };
 // Waves per SIMD the kernel is compiled for.  The loops over q / k and over the query blocks are real loops (unrolled, the
 // scheduler spreads their loads over the whole kernel and wants 160 registers): with them a wave that owns a head needs 96
-// to 128 registers instead of 160, one of a pair 80 instead of 100.  A workgroup of six or twelve waves only gets a second
-// place on a CU when its share per SIMD, rounded up, fits twice: 360 windows at C = 192 ran in two rounds of one workgroup
-// per CU (24.6 us), now in one round (20.8 us); C = 256, 1444 windows: 83 -> 72 us.  (Three heads at five waves per SIMD spill
-// two registers, four with scores; at four waves none, but the pair of blocks on 1392 windows takes 110.5 instead of 108.0 us.)
+// to 118 registers instead of 160, one of a pair 74 to 78 where several workgroups share a CU.  A workgroup of six or twelve waves
+// only gets a second place on a CU when its share per SIMD, rounded up, fits twice: 360 windows at C = 192 ran in two rounds of one
+// workgroup per CU (24.6 us), now in one round (20.8 us); C = 256, 1444 windows: 83 -> 72 us.  (Three heads at five waves per SIMD
+// spill none, six registers with scores; when they spilled two and four, and none at four waves, the pair of blocks on 1392 windows
+// took 110.5 us at four waves and 108.0 at five.)
 constexpr bool win_pairs_share(int NH, int HG) { return (NH == 6 && HG == 1) || NH * HG == 8; }   // pairs of waves, several workgroups on a CU
 constexpr int win_waves_per_eu(int NH, int HG, int QS, bool CODES)
 {
