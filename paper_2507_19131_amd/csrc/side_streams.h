@@ -1,0 +1,102 @@
+// Streams of the library's own for stages that run as two chains.  Host code.
+#pragma once
+#include <hip/hip_runtime.h>
+
+#include <mutex>
+#include <thread>
+
+namespace mixaq {
+
+constexpr int MAX_DEVICES = 64;
+
+// Side streams for stages that run as two chains (see mixaq_stage_forward).  One per stream that callers use, not one per handle:
+// the runtime spreads streams over four hardware queues, and with one per handle the second chain of every fourth handle
+// shared the first one's queue (six blocks on 192 windows at C = 384, three sets of handles in turn: 361 us as two chains, 358 as
+// one; with a side stream per caller 300).  A side stream only ever waits for its caller's stream, so callers stay independent of one
+// another.  At most MAX of them per device; a further caller takes over the one unused for longest, or runs as one
+// chain if all are in the middle of a call.  They are created when a block that may use them is, or on a caller's first call, and are
+// given back with the last such block.
+class SideStreams {
+public:
+    struct Side {
+        hipStream_t caller = nullptr, stream = nullptr;
+        std::thread::id thread;                    // of the caller, where its stream's name means another stream in every thread
+        hipEvent_t fork = nullptr, join = nullptr;
+        int calls = 0;                             // in progress
+        unsigned long long used = 0;
+        std::mutex mu;                             // an event is recorded and waited for in one piece
+    };
+    static SideStreams& of(int device)
+    {
+        static SideStreams all[MAX_DEVICES];
+        return all[device];
+    }
+    int retain(hipStream_t caller)
+    {
+        std::lock_guard<std::mutex> lock(mu_);
+        if (!find(caller) && !make(caller)) return MIXAQ_E_HIP;
+        ++blocks_;
+        return MIXAQ_OK;
+    }
+    void release()
+    {
+        std::lock_guard<std::mutex> lock(mu_);
+        if (--blocks_ > 0) return;
+        for (Side& s : side_) {
+            if (s.join) (void)hipEventDestroy(s.join);
+            if (s.fork) (void)hipEventDestroy(s.fork);
+            if (s.stream) (void)hipStreamDestroy(s.stream);
+            s.join = s.fork = nullptr;
+            s.stream = s.caller = nullptr;
+        }
+    }
+    // the caller's side stream, or NULL; ended by done()
+    Side* begin(hipStream_t caller)
+    {
+        std::lock_guard<std::mutex> lock(mu_);
+        Side* s = find(caller);
+        if (!s) s = make(caller);
+        if (s) { ++s->calls; s->used = ++clock_; }
+        return s;
+    }
+    void done(Side* s)
+    {
+        std::lock_guard<std::mutex> lock(mu_);
+        --s->calls;
+    }
+
+private:
+    static constexpr int MAX = 4;
+    static bool per_thread(hipStream_t s) { return s == hipStreamPerThread; }
+    Side* find(hipStream_t caller)
+    {
+        for (Side& s : side_)
+            if (s.stream && s.caller == caller && (!per_thread(caller) || s.thread == std::this_thread::get_id())) return &s;
+        return nullptr;
+    }
+    Side* make(hipStream_t caller)
+    {
+        Side* s = nullptr;
+        for (Side& c : side_)
+            if (!c.calls && (!s || (s->stream && (!c.stream || c.used < s->used)))) s = &c;
+        if (!s) return nullptr;
+        if (!s->stream) {
+            if ((!s->fork && hipEventCreateWithFlags(&s->fork, hipEventDisableTiming) != hipSuccess) ||
+                (!s->join && hipEventCreateWithFlags(&s->join, hipEventDisableTiming) != hipSuccess) ||
+                hipStreamCreateWithFlags(&s->stream, hipStreamNonBlocking) != hipSuccess) {
+                (void)hipGetLastError();                     // not to be mistaken for a launch error later
+                s->stream = nullptr;
+                return nullptr;
+            }
+        }
+        s->caller = caller;
+        s->thread = std::this_thread::get_id();
+        return s;
+    }
+    std::mutex mu_;
+    Side side_[MAX];
+    int blocks_ = 0;
+    unsigned long long clock_ = 0;
+};
+
+}  // namespace mixaq
