@@ -713,7 +713,7 @@ static int block_create(const mixaq_block_desc* desc, const mixaq_shared_params*
         int dev = -1;
         HIP_TRY(hipGetDevice(&dev));
         if (dev >= 0 && dev < MAX_DEVICES) {
-            if (SideStreams::of(dev).retain((hipStream_t)stream) != MIXAQ_OK) return bail(fail(MIXAQ_E_HIP, "creating the second stream of the stage failed"));
+            SideStreams::of(dev).retain((hipStream_t)stream);
             b->side_device = dev;
         }
     }

@@ -31,12 +31,13 @@ public:
         static SideStreams all[MAX_DEVICES];
         return all[device];
     }
-    int retain(hipStream_t caller)
+    // one more block that may use them; ended by release().  Its stages run as one chain where no side stream is to be had, so this
+    // cannot fail
+    void retain(hipStream_t caller)
     {
         std::lock_guard<std::mutex> lock(mu_);
-        if (!find(caller) && !make(caller)) return MIXAQ_E_HIP;
         ++blocks_;
-        return MIXAQ_OK;
+        if (!find(caller)) (void)fill(caller);
     }
     void release()
     {
@@ -55,7 +56,8 @@ public:
     {
         std::lock_guard<std::mutex> lock(mu_);
         Side* s = find(caller);
-        if (!s) s = make(caller);
+        if (!s) s = fill(caller);
+        if (!s) s = take_over(caller);
         if (s) { ++s->calls; s->used = ++clock_; }
         return s;
     }
@@ -74,24 +76,35 @@ private:
             if (s.stream && s.caller == caller && (!per_thread(caller) || s.thread == std::this_thread::get_id())) return &s;
         return nullptr;
     }
-    Side* make(hipStream_t caller)
+    // a side stream in a place that has none yet, or NULL
+    Side* fill(hipStream_t caller)
+    {
+        for (Side& s : side_) {
+            if (s.stream) continue;
+            if ((!s.fork && hipEventCreateWithFlags(&s.fork, hipEventDisableTiming) != hipSuccess) ||
+                (!s.join && hipEventCreateWithFlags(&s.join, hipEventDisableTiming) != hipSuccess) ||
+                hipStreamCreateWithFlags(&s.stream, hipStreamNonBlocking) != hipSuccess) {
+                (void)hipGetLastError();                     // not to be mistaken for a launch error later
+                s.stream = nullptr;
+                return nullptr;
+            }
+            return give(s, caller);
+        }
+        return nullptr;
+    }
+    // the one of another caller that is unused for longest, or NULL
+    Side* take_over(hipStream_t caller)
     {
         Side* s = nullptr;
         for (Side& c : side_)
-            if (!c.calls && (!s || (s->stream && (!c.stream || c.used < s->used)))) s = &c;
-        if (!s) return nullptr;
-        if (!s->stream) {
-            if ((!s->fork && hipEventCreateWithFlags(&s->fork, hipEventDisableTiming) != hipSuccess) ||
-                (!s->join && hipEventCreateWithFlags(&s->join, hipEventDisableTiming) != hipSuccess) ||
-                hipStreamCreateWithFlags(&s->stream, hipStreamNonBlocking) != hipSuccess) {
-                (void)hipGetLastError();                     // not to be mistaken for a launch error later
-                s->stream = nullptr;
-                return nullptr;
-            }
-        }
-        s->caller = caller;
-        s->thread = std::this_thread::get_id();
-        return s;
+            if (c.stream && !c.calls && (!s || c.used < s->used)) s = &c;
+        return s ? give(*s, caller) : nullptr;
+    }
+    static Side* give(Side& s, hipStream_t caller)
+    {
+        s.caller = caller;
+        s.thread = std::this_thread::get_id();
+        return &s;
     }
     std::mutex mu_;
     Side side_[MAX];

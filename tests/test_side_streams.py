@@ -1,0 +1,104 @@
+"""The side streams of the stage call (csrc/side_streams.h), compiled for the host from the lines the library uses, on a runtime
+whose streams are only told to be busy or idle.  CPU only."""
+import os
+import subprocess
+import textwrap
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2507_19131_amd", "csrc")
+
+RUNTIME = textwrap.dedent(r'''
+    #pragma once
+    #include <set>
+    struct FakeStream { bool busy = false; };
+    typedef FakeStream* hipStream_t;
+    typedef int* hipEvent_t;
+    enum hipError_t { hipSuccess = 0, hipErrorOutOfMemory = 2, hipErrorNotReady = 600 };
+    enum { hipEventDisableTiming = 2, hipStreamNonBlocking = 1 };
+    enum hipStreamCaptureMode { hipStreamCaptureModeGlobal, hipStreamCaptureModeThreadLocal, hipStreamCaptureModeRelaxed };
+    #define hipStreamPerThread ((hipStream_t)2)
+    inline bool creation_fails = false;
+    inline std::set<FakeStream*> streams;
+    inline std::set<int*> events;
+    inline hipStreamCaptureMode mode_now = hipStreamCaptureModeGlobal;
+    inline int calls_outside_relaxed = 0;
+    inline void unsafe() { calls_outside_relaxed += mode_now != hipStreamCaptureModeRelaxed; }
+    inline hipError_t hipGetLastError() { return hipSuccess; }
+    inline hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { unsafe(); events.insert(*e = new int); return hipSuccess; }
+    inline hipError_t hipEventDestroy(hipEvent_t e) { events.erase(e); delete e; return hipSuccess; }
+    inline hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned)
+    {
+        unsafe();
+        if (creation_fails) return hipErrorOutOfMemory;
+        streams.insert(*s = new FakeStream);
+        return hipSuccess;
+    }
+    inline hipError_t hipStreamDestroy(hipStream_t s) { streams.erase(s); delete s; return hipSuccess; }
+    inline hipError_t hipStreamQuery(hipStream_t s) { unsafe(); return s->busy ? hipErrorNotReady : hipSuccess; }
+    inline hipError_t hipThreadExchangeStreamCaptureMode(hipStreamCaptureMode* m) { const auto t = mode_now; mode_now = *m; *m = t; return hipSuccess; }
+''')
+
+PROGRAM = textwrap.dedent(r'''
+    #include <cstdio>
+    #include <cstring>
+    #include "side_streams.h"
+    using namespace mixaq;
+    static FakeStream users[6];
+    int main(int argc, char** argv)
+    {
+        SideStreams& pool = SideStreams::of(0);
+        auto is = [&](const char* name) { return argc > 1 && !std::strcmp(argv[1], name); };
+        bool ok = true;
+        SideStreams::Side* side[6] = {};
+        if (is("creation_while_all_are_in_use")) {
+            // a block is created on a fifth stream while four others are inside a stage call: it is, and its stage runs as one chain
+            for (int i = 0; i < 4; ++i) { pool.retain(&users[i]); side[i] = pool.begin(&users[i]); ok = ok && side[i]; }
+            pool.retain(&users[4]);
+            ok = ok && !pool.begin(&users[4]);
+            for (int i = 0; i < 4; ++i) { ok = ok && side[i]->caller == &users[i]; pool.done(side[i]); }
+            for (int i = 0; i < 5; ++i) { ok = ok && !streams.empty(); pool.release(); }
+            ok = ok && streams.empty() && events.empty();
+        }
+        if (is("creation_without_a_stream")) {
+            // the side stream is an option: a block exists without one, and gets one as soon as there are some
+            creation_fails = true;
+            pool.retain(&users[0]);
+            ok = ok && !pool.begin(&users[0]);
+            creation_fails = false;
+            side[0] = pool.begin(&users[0]);
+            ok = ok && side[0] && side[0]->stream;
+            if (side[0]) pool.done(side[0]);
+            pool.release();
+            ok = ok && streams.empty() && events.empty();
+        }
+        if (is("creation_takes_no_stream_over")) {
+            // a block created on a fifth stream leaves the callers theirs
+            for (int i = 0; i < 4; ++i) { pool.retain(&users[i]); side[i] = pool.begin(&users[i]); pool.done(side[i]); }
+            pool.retain(&users[4]);
+            for (int i = 0; i < 4; ++i) ok = ok && side[i]->caller == &users[i];
+            ok = ok && streams.size() == 4;
+            for (int i = 0; i < 5; ++i) pool.release();
+            ok = ok && streams.empty() && events.empty();
+        }
+        std::printf(ok ? "ok\n" : "bad\n");
+        return 0;
+    }
+''')
+
+
+@pytest.fixture(scope="module")
+def program(tmp_path_factory):
+    d = tmp_path_factory.mktemp("side_streams")
+    os.makedirs(d / "hip")
+    (d / "hip" / "hip_runtime.h").write_text(RUNTIME)
+    (d / "main.cpp").write_text(PROGRAM)
+    exe = str(d / "side_streams")
+    subprocess.run(["g++", "-std=c++17", "-Wall", "-Werror", "-I", str(d), "-I", CSRC, "-o", exe, str(d / "main.cpp"), "-lpthread"], check=True)
+    return exe
+
+
+@pytest.mark.parametrize("case", ["creation_while_all_are_in_use", "creation_without_a_stream", "creation_takes_no_stream_over"])
+def test_a_block_can_always_be_created(program, case):
+    assert subprocess.run([program, case], capture_output=True, text=True, check=True, timeout=20).stdout == "ok\n"
