@@ -12,10 +12,11 @@ constexpr int MAX_DEVICES = 64;
 // Side streams for stages that run as two chains (see mixaq_stage_forward).  One per stream that callers use, not one per handle:
 // the runtime spreads streams over four hardware queues, and with one per handle the second chain of every fourth handle
 // shared the first one's queue (six blocks on 192 windows at C = 384, three sets of handles in turn: 361 us as two chains, 358 as
-// one; with a side stream per caller 300).  A side stream only ever waits for its caller's stream, so callers stay independent of one
-// another.  At most MAX of them per device; a further caller takes over the one unused for longest, or runs as one
-// chain if all are in the middle of a call.  They are created when a block that may use them is, or on a caller's first call, and are
-// given back with the last such block.
+// one; with a side stream per caller 300).  What is queued on a side stream only ever waits for its caller's stream, so callers
+// stay independent of one another.  At most MAX of them per device; a further caller takes over an idle one (nothing queued and no
+// call in progress), the one unused for longest, or runs as one chain: behind work that still waits for another caller's stream its
+// second chain would wait for that stream too, for ever if that one waits for it.  They are created with a block that may use them, or on
+// a caller's first call, and are given back with the last such block.
 class SideStreams {
 public:
     struct Side {
@@ -92,12 +93,17 @@ private:
         }
         return nullptr;
     }
-    // the one of another caller that is unused for longest, or NULL
+    // of the idle ones of other callers the one unused for longest, or NULL
     Side* take_over(hipStream_t caller)
     {
         Side* s = nullptr;
+        // asked in the relaxed mode: the stream is never captured itself, and another thread's capture is not to be broken off
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) { (void)hipGetLastError(); return nullptr; }
         for (Side& c : side_)
-            if (c.stream && !c.calls && (!s || c.used < s->used)) s = &c;
+            if (c.stream && !c.calls && (!s || c.used < s->used) && hipStreamQuery(c.stream) == hipSuccess) s = &c;
+        (void)hipThreadExchangeStreamCaptureMode(&mode);
+        (void)hipGetLastError();                             // "not ready" is not to be mistaken for a launch error later
         return s ? give(*s, caller) : nullptr;
     }
     static Side* give(Side& s, hipStream_t caller)
