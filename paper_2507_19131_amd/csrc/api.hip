@@ -837,9 +837,9 @@ int mixaq_stage_forward(mixaq_block* const* blocks, int32_t n_blocks, const floa
         Workspace w;
         rounds = stage_rounds(b0);
         ws_side = carve(b0, nullptr, &w, false, most_images_of_a_round(b0));
-        std::lock_guard<std::mutex> lock(side->mu);                  // both chains start together (the second one window kernel behind the
-        hipError_t e = hipEventRecord(side->fork, st);               // first measured slower: 377 against 361 us, six blocks on 192 windows at C = 384)
-        if (e == hipSuccess) e = hipStreamWaitEvent(side->stream, side->fork, 0);
+        // both chains start together (the second one window kernel behind the first measured slower: 377 against 361 us, six blocks on
+        // 192 windows at C = 384)
+        const hipError_t e = side->fork_from(st);
         if (e != hipSuccess) {
             SideStreams::of(b0->side_device).done(side);
             return fail(MIXAQ_E_HIP, "starting the second chain failed: %s", hipGetErrorString(e));
@@ -867,12 +867,9 @@ int mixaq_stage_forward(mixaq_block* const* blocks, int32_t n_blocks, const floa
         }
     }
     if (side) {                                                      // the side chain joins, also after an error in between
-        {
-            std::lock_guard<std::mutex> lock(side->mu);
-            (void)hipEventRecord(side->join, side->stream);
-            (void)hipStreamWaitEvent(st, side->join, 0);
-        }
+        const hipError_t e = side->join_to(st);
         SideStreams::of(b0->side_device).done(side);
+        if (e != hipSuccess && !rc) rc = fail(MIXAQ_E_HIP, "joining the second chain failed: %s", hipGetErrorString(e));
     }
     return rc;
 }

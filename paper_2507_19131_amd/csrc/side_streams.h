@@ -26,6 +26,22 @@ public:
         int calls = 0;                             // in progress
         unsigned long long used = 0;
         std::mutex mu;                             // an event is recorded and waited for in one piece
+        // the side stream starts after the work already on `st`
+        hipError_t fork_from(hipStream_t st)
+        {
+            std::lock_guard<std::mutex> lock(mu);
+            const hipError_t e = hipEventRecord(fork, st);
+            return e != hipSuccess ? e : hipStreamWaitEvent(stream, fork, 0);
+        }
+        // `st` goes on behind the side stream's work; where it cannot be made to wait, the host does
+        hipError_t join_to(hipStream_t st)
+        {
+            std::lock_guard<std::mutex> lock(mu);
+            hipError_t e = hipEventRecord(join, stream);
+            if (e == hipSuccess) e = hipStreamWaitEvent(st, join, 0);
+            if (e != hipSuccess) (void)hipStreamSynchronize(stream);
+            return e;
+        }
     };
     static SideStreams& of(int device)
     {

@@ -20,6 +20,10 @@ RUNTIME = textwrap.dedent(r'''
     enum hipStreamCaptureMode { hipStreamCaptureModeGlobal, hipStreamCaptureModeThreadLocal, hipStreamCaptureModeRelaxed };
     #define hipStreamPerThread ((hipStream_t)2)
     inline bool creation_fails = false;
+    inline int recorded = 0, waited = 0, synchronized = 0, record_fails_at = 0, wait_fails_at = 0;   // the n-th one from here on
+    inline hipError_t hipEventRecord(hipEvent_t, hipStream_t) { ++recorded; return record_fails_at && !--record_fails_at ? hipErrorOutOfMemory : hipSuccess; }
+    inline hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { ++waited; return wait_fails_at && !--wait_fails_at ? hipErrorOutOfMemory : hipSuccess; }
+    inline hipError_t hipStreamSynchronize(hipStream_t) { ++synchronized; return hipSuccess; }
     inline std::set<FakeStream*> streams;
     inline std::set<int*> events;
     inline hipStreamCaptureMode mode_now = hipStreamCaptureModeGlobal;
@@ -98,6 +102,23 @@ PROGRAM = textwrap.dedent(r'''
             ok = ok && calls_outside_relaxed == 0 && mode_now == hipStreamCaptureModeGlobal;
             for (int i = 0; i < 5; ++i) pool.release();
         }
+        if (is("join_that_fails")) {
+            // the caller's stream cannot be made to wait for the second chain: the call says so, and does not return before the chain's end
+            pool.retain(&users[0]);
+            side[0] = pool.begin(&users[0]);
+            ok = ok && side[0]->fork_from(&users[0]) == hipSuccess && side[0]->join_to(&users[0]) == hipSuccess && !synchronized;
+            ok = ok && recorded == 2 && waited == 2;
+            record_fails_at = 2;
+            ok = ok && side[0]->fork_from(&users[0]) == hipSuccess && side[0]->join_to(&users[0]) != hipSuccess && synchronized == 1;
+            wait_fails_at = 2;
+            ok = ok && side[0]->fork_from(&users[0]) == hipSuccess && side[0]->join_to(&users[0]) != hipSuccess && synchronized == 2;
+            record_fails_at = 1;
+            ok = ok && side[0]->fork_from(&users[0]) != hipSuccess;
+            wait_fails_at = 1;
+            ok = ok && side[0]->fork_from(&users[0]) != hipSuccess;
+            pool.done(side[0]);
+            pool.release();
+        }
         std::printf(ok ? "ok\n" : "bad\n");
         return 0;
     }
@@ -122,3 +143,7 @@ def test_a_block_can_always_be_created(program, case):
 
 def test_a_side_stream_with_queued_work_is_not_taken_over(program):
     assert subprocess.run([program, "taken_over_when_idle"], capture_output=True, text=True, check=True, timeout=20).stdout == "ok\n"
+
+
+def test_a_join_that_fails_is_an_error_and_leaves_no_chain_behind(program):
+    assert subprocess.run([program, "join_that_fails"], capture_output=True, text=True, check=True, timeout=20).stdout == "ok\n"
