@@ -275,7 +275,9 @@ int stage_rounds(const mixaq_block* b)
     const long long windows = (long long)b->d.B * b->nW;
     return (int)std::min<long long>(b->d.B / 2, (windows + STAGE_ROUND_WINDOWS - 1) / STAGE_ROUND_WINDOWS);
 }
-int most_images_of_a_round(const mixaq_block* b) { return ((b->d.B + 1) / 2 + stage_rounds(b) - 1) / stage_rounds(b); }
+// images of the first (second) chain, and the most of them that one round takes
+int chain_images(const mixaq_block* b, int chain) { return (b->d.B + 1 - chain) / 2; }
+int round_images(const mixaq_block* b, int chain) { return (chain_images(b, chain) + stage_rounds(b) - 1) / stage_rounds(b); }
 
 void make_geom(const mixaq_block* b, int k_hi, int k_lo, Geom* G, int images = 0)
 {
@@ -709,7 +711,7 @@ static int block_create(const mixaq_block_desc* desc, const mixaq_shared_params*
     b->ws_bytes = carve(b, nullptr, &w);
     b->ws_fused_bytes = carve(b, nullptr, &w, true);
     if (stage_splits(b)) {                  // two chains: each has its own part of the workspace, enough for its longest round
-        b->ws_bytes = std::max(b->ws_bytes, 2 * carve(b, nullptr, &w, false, most_images_of_a_round(b)));
+        b->ws_bytes = std::max(b->ws_bytes, carve(b, nullptr, &w, false, round_images(b, 0)) + carve(b, nullptr, &w, false, round_images(b, 1)));
         int dev = -1;
         HIP_TRY(hipGetDevice(&dev));
         if (dev >= 0 && dev < MAX_DEVICES) {
@@ -836,7 +838,7 @@ int mixaq_stage_forward(mixaq_block* const* blocks, int32_t n_blocks, const floa
     if (side) {
         Workspace w;
         rounds = stage_rounds(b0);
-        ws_side = carve(b0, nullptr, &w, false, most_images_of_a_round(b0));
+        ws_side = carve(b0, nullptr, &w, false, round_images(b0, 0));
         // both chains start together (the second one window kernel behind the first measured slower: 377 against 361 us, six blocks on
         // 192 windows at C = 384)
         const hipError_t e = side->fork_from(st);
@@ -853,7 +855,7 @@ int mixaq_stage_forward(mixaq_block* const* blocks, int32_t n_blocks, const floa
             for (int chain = 0; chain < (side ? 2 : 1) && !rc; ++chain) {
                 Part part;                                           // one chain: all images
                 if (side) {
-                    const int first = chain ? (b0->d.B + 1) / 2 : 0, images = chain ? b0->d.B / 2 : (b0->d.B + 1) / 2;
+                    const int first = chain ? chain_images(b0, 0) : 0, images = chain_images(b0, chain);
                     const int from = (int)((long long)images * round / rounds), to = (int)((long long)images * (round + 1) / rounds);
                     part.first = first + from;
                     part.images = to - from;

@@ -460,6 +460,35 @@ def test_forked_stage_with_uneven_halves_pruning_and_streams(B, H, W, C, heads, 
     assert np.array_equal(y_gpu, cur)
 
 
+@pytest.mark.parametrize("B,H,W,C,n_blocks", [(3, 82, 137, 96, 4), (5, 75, 66, 192, 4)])
+def test_workspace_of_an_odd_batch(B, H, W, C, n_blocks):
+    """The two chains of an odd batch share a workspace of no more than its images need one by one, and write nothing behind it."""
+    spec = synth.BlockSpec(B, H, W, C, C // 32)
+    assert gh.stage_forks(spec, n_blocks)
+    with gh.GpuBlock(synth.make_block_inputs(synth.BlockSpec(1, H, W, C, C // 32), 380)) as one:
+        image = M.mixaq_block_workspace_bytes(one.blk)
+    dev = torch.device("cuda:0")
+    blocks = [gh.GpuBlock(synth.make_block_inputs(spec, 380 + i), 3 * (i % 2)) for i in range(n_blocks)]
+    try:
+        need = M.mixaq_block_workspace_bytes(blocks[0].blk)
+        assert need <= B * image, (need, image)
+        ws = torch.full((need + (1 << 20),), 0x5A, dtype=torch.uint8, device=dev)
+        k = spec.nW // 2
+        x = torch.randn((B, H, W, C), generator=torch.Generator(device=dev).manual_seed(381), device=dev)
+        y, tmp = torch.full_like(x, float("nan")), torch.full_like(x, float("nan"))
+        scores, perm = blocks[0].score_select(x, k)
+        print("workspace of an odd batch", B, H, W, "C", C, flush=True)
+        M.mixaq_stage_forward([gb.blk for gb in blocks], x, [k] * ((n_blocks + 1) // 2), None, y, tmp, scores, perm, ws[:need])
+        want = x
+        for gb in blocks:
+            want = gb.forward(want, perm, k)
+        torch.cuda.synchronize()
+        assert torch.equal(y, want) and bool((ws[need:] == 0x5A).all())
+    finally:
+        for gb in blocks:
+            gb.close()
+
+
 @pytest.mark.parametrize("B,H,W,C,heads,n_blocks", [FORKED[0], FORKED[4]])
 def test_repeated_forked_stage_calls_are_bit_stable(B, H, W, C, heads, n_blocks):
     """A stage call that runs as two chains, a hundred times over on two alternating maps: every result has the bits of its
