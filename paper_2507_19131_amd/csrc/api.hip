@@ -16,6 +16,7 @@
 #include "kernels.h"
 #include "arena.h"
 #include "side_streams.h"
+#include "stage_plan.h"
 
 using namespace mixaq;
 
@@ -239,45 +240,6 @@ int check_qparam(const mixaq_qparam& q, int bits, const char* name)
         return fail(MIXAQ_E_SHAPE, "%s: zero point outside the %d-bit range", name, bits);
     return MIXAQ_OK;
 }
-
-// Two chains pay while the kernels of the stage leave CUs idle for part of their time (one chain -> two: a pair of blocks on 2784
-// windows at C = 96 183 -> 174 us, on 1920 at 192 330 -> 314, on 1440 at 384 648 -> 602), up to this many windows in all.
-constexpr int STAGE_SPLIT_MAX_WINDOWS = 4096;
-// Each chain of a larger batch takes its half of the images in rounds of at most half this many windows, whole images: the tail of
-// a kernel still runs beside the other chain's, and what a round reads again is nearer (a pair of blocks on 8 x 1392 windows at
-// C = 96 689 -> 660 us, 4 x 1369 at 128 449 -> 442, 16 x 360 at 192 932 -> 897, 16 x 361 at 256 1392 -> 1357, 64 x 96 at 384 2597 -> 2490;
-// as two halves without rounds 711 -> 697 and equal for the first two).  Not where the halves are uneven by more than an eighth
-// (5 x 1392 at 96 416 -> 419, 3 x 2500 464 -> 467).
-constexpr int STAGE_ROUND_WINDOWS = 5600;
-// Fork and join cost 25 to 30 us, so the stage has to be long enough: the line is drawn at windows times channels over all its
-// blocks.  One chain -> two, in us (three sets of handles in turn take the same, as they share the caller's side stream):
-//   two blocks:  C = 96, 256 windows 43 -> 77; 392 54 -> 78; 840 79 -> 84; 1352 104 -> 101
-//                C = 128, 920 95 -> 94        C = 192, 450 89 -> 100; 924 175 -> 170
-//                C = 256, 480 128 -> 128; 1012 245 -> 241      C = 384, 192 114 -> 117; 300 159 -> 140; 450 236 -> 232
-//   six blocks:  C = 96, 128 windows 110 -> 142; 392 166 -> 155        C = 128, 512 190 -> 171
-//                C = 192, 98 170 -> 176; 200 204 -> 200       C = 256, 220 225 -> 219
-//                C = 384, 40 215 -> 231; 70 217 -> 232; 192 335 -> 294
-// Pruned windows count like the others: their share shortens both forms.
-constexpr long long STAGE_SPLIT_MIN_WORK = 2200LL * 100;
-bool stage_split_pays(const mixaq_block* b, int n_blocks)
-{
-    return (long long)n_blocks * b->d.B * b->nW * b->d.C >= STAGE_SPLIT_MIN_WORK;
-}
-bool stage_splits(const mixaq_block* b)
-{
-    const bool small = b->d.B * b->nW <= STAGE_SPLIT_MAX_WINDOWS, even = b->d.B % 2 == 0 || b->d.B >= 9;
-    return b->d.B >= 2 && (small || even) && b->fused_window && b->fused_token;
-}
-
-// rounds in which the two chains of such a stage go through their images
-int stage_rounds(const mixaq_block* b)
-{
-    const long long windows = (long long)b->d.B * b->nW;
-    return (int)std::min<long long>(b->d.B / 2, (windows + STAGE_ROUND_WINDOWS - 1) / STAGE_ROUND_WINDOWS);
-}
-// images of the first (second) chain, and the most of them that one round takes
-int chain_images(const mixaq_block* b, int chain) { return (b->d.B + 1 - chain) / 2; }
-int round_images(const mixaq_block* b, int chain) { return (chain_images(b, chain) + stage_rounds(b) - 1) / stage_rounds(b); }
 
 void make_geom(const mixaq_block* b, int k_hi, int k_lo, Geom* G, int images = 0)
 {
@@ -710,8 +672,9 @@ static int block_create(const mixaq_block_desc* desc, const mixaq_shared_params*
     Workspace w;
     b->ws_bytes = carve(b, nullptr, &w);
     b->ws_fused_bytes = carve(b, nullptr, &w, true);
-    if (stage_splits(b)) {                  // two chains: each has its own part of the workspace, enough for its longest round
-        b->ws_bytes = std::max(b->ws_bytes, carve(b, nullptr, &w, false, round_images(b, 0)) + carve(b, nullptr, &w, false, round_images(b, 1)));
+    if (b->fused_window && b->fused_token && stage_splits(desc->B, b->nW)) {   // two chains: each has its own part of the workspace, enough for its longest round
+        b->ws_bytes = std::max(b->ws_bytes, carve(b, nullptr, &w, false, round_images(desc->B, b->nW, 0)) +
+                                           carve(b, nullptr, &w, false, round_images(desc->B, b->nW, 1)));
         int dev = -1;
         HIP_TRY(hipGetDevice(&dev));
         if (dev >= 0 && dev < MAX_DEVICES) {
@@ -822,7 +785,7 @@ int mixaq_stage_forward(mixaq_block* const* blocks, int32_t n_blocks, const floa
     int rounds = 1;
     size_t ws_side = 0;                                              // where the side chain's part of the workspace starts
     hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
-    bool split = n_blocks > 1 && b0->side_device >= 0 && stage_split_pays(b0, n_blocks);
+    bool split = n_blocks > 1 && b0->side_device >= 0 && stage_split_pays(b0->d.B, nW, b0->d.C, n_blocks);
     for (int i = 0; split && i < n_blocks; ++i) split = blocks[i]->fused_window && blocks[i]->fused_token;
     if (split) {
         if (hipStreamIsCapturing(st, &capturing) != hipSuccess) {
@@ -837,8 +800,8 @@ int mixaq_stage_forward(mixaq_block* const* blocks, int32_t n_blocks, const floa
     }
     if (side) {
         Workspace w;
-        rounds = stage_rounds(b0);
-        ws_side = carve(b0, nullptr, &w, false, round_images(b0, 0));
+        rounds = stage_rounds(b0->d.B, nW);
+        ws_side = carve(b0, nullptr, &w, false, round_images(b0->d.B, nW, 0));
         // both chains start together (the second one window kernel behind the first measured slower: 377 against 361 us, six blocks on
         // 192 windows at C = 384)
         const hipError_t e = side->fork_from(st);
@@ -855,15 +818,14 @@ int mixaq_stage_forward(mixaq_block* const* blocks, int32_t n_blocks, const floa
             for (int chain = 0; chain < (side ? 2 : 1) && !rc; ++chain) {
                 Part part;                                           // one chain: all images
                 if (side) {
-                    const int first = chain ? chain_images(b0, 0) : 0, images = chain_images(b0, chain);
-                    const int from = (int)((long long)images * round / rounds), to = (int)((long long)images * (round + 1) / rounds);
-                    part.first = first + from;
-                    part.images = to - from;
+                    const StagePart sp = stage_part(b0->d.B, nW, chain, round);
+                    part.first = sp.first;
+                    part.images = sp.images;
                     part.ws_offset = chain ? ws_side : 0;
                 }
-                void* sp = chain ? (void*)side->stream : stream;
-                if (i == 0) rc = forward_impl(blocks[0], cur, nullptr, scores, kh, kl, dst, workspace, workspace_bytes, sp, nullptr, nullptr, perm, false, part);
-                else rc = forward_impl(blocks[i], cur, perm, nullptr, kh, kl, dst, workspace, workspace_bytes, sp, nullptr, nullptr, nullptr, false, part);
+                void* on = chain ? (void*)side->stream : stream;
+                if (i == 0) rc = forward_impl(blocks[0], cur, nullptr, scores, kh, kl, dst, workspace, workspace_bytes, on, nullptr, nullptr, perm, false, part);
+                else rc = forward_impl(blocks[i], cur, perm, nullptr, kh, kl, dst, workspace, workspace_bytes, on, nullptr, nullptr, nullptr, false, part);
             }
             cur = dst;
         }

@@ -1,7 +1,4 @@
 """Runs one block on the GPU through the C ABI and on the CPU oracle, for the parity tests."""
-import os
-import re
-
 import numpy as np
 import torch
 
@@ -12,17 +9,6 @@ from paper_2507_19131_amd import synth
 INT_TAPS = ("a_qkv_in", "acc_qkv", "qkv", "acc_s", "p", "acc_o", "a_proj_in", "acc_proj", "a_fc1_in", "acc_fc1",
             "a_fc2_in", "acc_fc2")
 FLOAT_TAPS = ("h", "y_win")
-
-
-def stage_forks(spec, n_blocks):
-    """Whether mixaq_stage_forward runs these blocks as two chains: the rule with the constants of csrc/api.hip, so that a test
-    of the two chains notices when its sizes no longer reach them."""
-    src = open(os.path.join(os.path.dirname(M.__file__), "csrc", "api.hip")).read()
-    most = int(re.search(r"STAGE_SPLIT_MAX_WINDOWS = (\d+);", src).group(1))
-    a, b = re.search(r"STAGE_SPLIT_MIN_WORK = (\d+)LL \* (\d+);", src).groups()
-    windows = spec.B * spec.nW
-    return (n_blocks > 1 and spec.B >= 2 and windows <= most and spec.C <= 384 and spec.mlp_ratio == 4 and
-            n_blocks * windows * min(spec.C, 128) >= int(a) * int(b))
 
 
 class GpuBlock:

@@ -1,0 +1,43 @@
+"""The library's own rule of which stages run as two chains and which images a chain takes when (csrc/stage_plan.h), built for the
+host."""
+import ctypes
+import os
+import subprocess
+import tempfile
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2507_19131_amd", "csrc")
+
+_SOURCE = r'''
+#include "stage_plan.h"
+extern "C" {
+int splits(int B, int nW) { return mixaq::stage_splits(B, nW); }
+int pays(int B, int nW, int C, int blocks) { return mixaq::stage_split_pays(B, nW, C, blocks); }
+int rounds(int B, int nW) { return mixaq::stage_rounds(B, nW); }
+int round_images(int B, int nW, int chain) { return mixaq::round_images(B, nW, chain); }
+int part_first(int B, int nW, int chain, int round) { return mixaq::stage_part(B, nW, chain, round).first; }
+int part_images(int B, int nW, int chain, int round) { return mixaq::stage_part(B, nW, chain, round).images; }
+}
+'''
+
+
+def _build():
+    with tempfile.TemporaryDirectory() as d:
+        src, so = os.path.join(d, "plan.cpp"), os.path.join(d, "plan.so")
+        with open(src, "w") as f:
+            f.write(_SOURCE)
+        subprocess.run(["g++", "-std=c++17", "-Wall", "-Werror", "-fPIC", "-shared", "-I", CSRC, "-o", so, src], check=True)
+        return ctypes.CDLL(so)
+
+
+lib = _build()
+
+
+def forks(spec, n_blocks):
+    """Whether mixaq_stage_forward runs these blocks as two chains (fused kernels at every block: C <= 384, mlp_ratio 4)."""
+    return bool(n_blocks > 1 and spec.C <= 384 and spec.mlp_ratio == 4 and lib.splits(spec.B, spec.nW) and
+                lib.pays(spec.B, spec.nW, spec.C, n_blocks))
+
+
+def rounds(spec):
+    """In how many rounds the two chains of such a stage go through their images."""
+    return lib.rounds(spec.B, spec.nW)

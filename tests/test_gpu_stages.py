@@ -10,6 +10,7 @@ pytestmark = pytest.mark.gpu
 
 if torch.cuda.is_available():
     import gpu_harness as gh
+    import stage_plan
     import oracle_api as O
     from paper_2507_19131_amd import binding as M
 
@@ -251,6 +252,8 @@ def test_stage_call_as_the_benchmark_launches_it(name, stage):
     spec, shifts = st["spec"], st["shifts"]
     keep = wl["keep"][len(wl["keep"]) // 2]
     seed = wl["seed"] + stage
+    if (name, stage) in (("cfg3", 0), ("cfg5", 0), ("cfg5", 1)):   # batches that run as two chains
+        assert stage_plan.forks(spec, len(shifts))
     print("stage call", name, "stage", stage + 1, "C", spec.C, "B", spec.B, "windows", spec.B * spec.nW, flush=True)
     x_np = synth.make_feature_map(spec, seed, blobs=wl["blobs"], outlier_channels=wl["outliers"])
     inputs = [synth.make_block_inputs(spec, seed + 10 * i, ranges=wl.get("ranges")) for i, _ in enumerate(shifts)]
@@ -411,7 +414,7 @@ def test_forked_stage_with_uneven_halves_pruning_and_streams(B, H, W, C, heads, 
     default stream or on one of the caller's while the default stream is kept busy (complete as soon as that stream is);
     the same bits as block after block on the whole batch on one stream, and the oracle's."""
     spec = synth.BlockSpec(B, H, W, C, heads, act_bits_low=2 if C == 128 else 4)
-    assert gh.stage_forks(spec, n_blocks)
+    assert stage_plan.forks(spec, n_blocks)
     nW, pairs = spec.nW, (n_blocks + 1) // 2
     shifts = [0, 3] * pairs
     k_high = [[nW // 2, nW // 3, 0][p % 3] for p in range(pairs)]
@@ -464,7 +467,7 @@ def test_forked_stage_with_uneven_halves_pruning_and_streams(B, H, W, C, heads, 
 def test_workspace_of_an_odd_batch(B, H, W, C, n_blocks):
     """The two chains of an odd batch share a workspace of no more than its images need one by one, and write nothing behind it."""
     spec = synth.BlockSpec(B, H, W, C, C // 32)
-    assert gh.stage_forks(spec, n_blocks)
+    assert stage_plan.forks(spec, n_blocks)
     with gh.GpuBlock(synth.make_block_inputs(synth.BlockSpec(1, H, W, C, C // 32), 380)) as one:
         image = M.mixaq_block_workspace_bytes(one.blk)
     dev = torch.device("cuda:0")
@@ -494,7 +497,7 @@ def test_repeated_forked_stage_calls_are_bit_stable(B, H, W, C, heads, n_blocks)
     """A stage call that runs as two chains, a hundred times over on two alternating maps: every result has the bits of its
     map's first, which a race between the chains or with the call before would not survive."""
     spec = synth.BlockSpec(B, H, W, C, heads)
-    assert gh.stage_forks(spec, n_blocks)
+    assert stage_plan.forks(spec, n_blocks)
     dev = torch.device("cuda:0")
     xs = [torch.from_numpy(synth.make_feature_map(spec, 330 + i, blobs=True)).to(dev) for i in range(2)]
     blocks = [gh.GpuBlock(synth.make_block_inputs(spec, 340 + i), 3 * (i % 2)) for i in range(n_blocks)]
@@ -546,6 +549,34 @@ def test_stage_of_a_large_batch_in_rounds(B, H, W, C, k_low):
             gb.close()
 
 
+@pytest.mark.parametrize("B,H,W,C,k_low", [(19, 161, 175, 96, None), (10, 224, 220, 128, 300), (17, 100, 168, 192, None), (16, 133, 130, 256, 50),
+                                           (45, 77, 91, 384, None)])
+def test_rounds_of_a_stage_at_every_width(B, H, W, C, k_low):
+    """Two chains that go through their halves in more than one round, at every width that may fork: uneven halves and rounds, pruned or
+    not; the bits are those of block after block, twice."""
+    spec = synth.BlockSpec(B, H, W, C, C // 32)
+    assert stage_plan.forks(spec, 2) and stage_plan.rounds(spec) > 1
+    k = spec.nW // 2
+    dev = torch.device("cuda:0")
+    x = torch.randn((B, H, W, C), generator=torch.Generator(device=dev).manual_seed(390), device=dev)
+    print("rounds", B, H, W, "C", C, "k_low", k_low, flush=True)
+    blocks = [gh.GpuBlock(synth.make_block_inputs(spec, 391 + i), 3 * (i % 2)) for i in range(2)]
+    try:
+        scores, perm = blocks[0].score_select(x, k)
+        want = x
+        for gb in blocks:
+            want = gb.forward(want, perm, k) if k_low is None else gh._forward_pruned(gb, want, perm, k, k_low)
+        s2, p2 = torch.empty_like(scores), torch.empty_like(perm)
+        for _ in range(2):
+            y, tmp = torch.full_like(x, float("nan")), torch.full_like(x, float("nan"))
+            M.mixaq_stage_forward([gb.blk for gb in blocks], x, [k], None if k_low is None else [k_low], y, tmp, s2, p2, blocks[0].ws)
+            torch.cuda.synchronize()
+            assert torch.equal(y, want) and torch.equal(p2, perm)
+    finally:
+        for gb in blocks:
+            gb.close()
+
+
 @pytest.mark.parametrize("threads", [1, 3])
 def test_forked_stages_on_more_streams_than_side_streams(threads):
     """Stages that run as two chains on the default stream and on six of the callers' own (more than there are side streams), in
@@ -554,7 +585,7 @@ def test_forked_stages_on_more_streams_than_side_streams(threads):
     import threading
     B, C, n_blocks = 2, 192, 6
     spec = synth.BlockSpec(B, 82, 91, C, C // 32)
-    assert gh.stage_forks(spec, n_blocks)
+    assert stage_plan.forks(spec, n_blocks)
     dev = torch.device("cuda:0")
     k, pairs = spec.nW // 2, n_blocks // 2
     inputs = [synth.make_block_inputs(spec, 360 + i) for i in range(n_blocks)]
@@ -603,12 +634,12 @@ def test_random_sweep_of_forked_stage_calls():
         C, heads = [(96, 3), (128, 4), (192, 6)][case % 3]
         B, n_blocks = int(rng.integers(2, 7)), int(rng.integers(2, 7))
         hi = int(rng.integers(4, 9))
-        windows = 1.05 * 2000 * 128 / min(C, 128) / n_blocks / B * float(rng.uniform(1.0, 1.3))
+        windows = 1.05 * 2000 * 128 / min(C, 128) / n_blocks / B * float(rng.uniform(1.0, 1.3))     # well above the rule's line
         rows = max(2, int(np.sqrt(windows * rng.uniform(0.6, 1.6))))
         cols = max(2, -(-int(windows) // rows) + 1)
         spec = synth.BlockSpec(B, 7 * rows - int(rng.integers(0, 7)), 7 * cols - int(rng.integers(0, 7)), C, heads, act_bits_high=hi,
                                act_bits_low=int(rng.integers(2, hi + 1)), weight_bits=int(rng.choice([4, 8])), score_mode=int(rng.integers(0, 2)))
-        assert gh.stage_forks(spec, n_blocks), case
+        assert stage_plan.forks(spec, n_blocks), case
         pairs = (n_blocks + 1) // 2
         k_high = [int(rng.integers(0, spec.nW + 1)) for _ in range(pairs)]
         k_low = [spec.nW - kh if rng.integers(0, 2) else int(rng.integers(0, spec.nW - kh + 1)) for kh in k_high]
