@@ -186,7 +186,7 @@ int mixaq_block_forward_scored(const mixaq_block *blk, const float *x, const dou
  * ordered on `stream`; nothing is allocated.  A batch of small maps (B >= 2, at most 4096 windows in
  * all, fused kernels) whose stage is long enough (n_blocks * B*nW * C >= 220000: fork and join cost as much as a short stage
  * would gain) runs as two chains of blocks, one per half of the images (they are independent through the whole stage), and so
- * does a larger batch whose halves are even (B even, or at least 9), in rounds of about 2800 windows a chain: the second chain
+ * does a larger batch whose halves are even (B even, or at least 9), in rounds of about 270000 windows * channels a chain (53 MB of map): the second chain
  * is enqueued on a stream of the library's own (one per calling stream, at most four per device; a caller that finds none
  * gets one chain) that starts after the work already on `stream` and that `stream` waits for before the call's work
  * counts as done, so the caller sees the same ordering as without it; under stream capture the

@@ -673,8 +673,8 @@ static int block_create(const mixaq_block_desc* desc, const mixaq_shared_params*
     b->ws_bytes = carve(b, nullptr, &w);
     b->ws_fused_bytes = carve(b, nullptr, &w, true);
     if (b->fused_window && b->fused_token && stage_splits(desc->B, b->nW)) {   // two chains: each has its own part of the workspace, enough for its longest round
-        b->ws_bytes = std::max(b->ws_bytes, carve(b, nullptr, &w, false, round_images(desc->B, b->nW, 0)) +
-                                           carve(b, nullptr, &w, false, round_images(desc->B, b->nW, 1)));
+        b->ws_bytes = std::max(b->ws_bytes, carve(b, nullptr, &w, false, round_images(desc->B, b->nW, C, 0)) +
+                                           carve(b, nullptr, &w, false, round_images(desc->B, b->nW, C, 1)));
         int dev = -1;
         HIP_TRY(hipGetDevice(&dev));
         if (dev >= 0 && dev < MAX_DEVICES) {
@@ -800,8 +800,8 @@ int mixaq_stage_forward(mixaq_block* const* blocks, int32_t n_blocks, const floa
     }
     if (side) {
         Workspace w;
-        rounds = stage_rounds(b0->d.B, nW);
-        ws_side = carve(b0, nullptr, &w, false, round_images(b0->d.B, nW, 0));
+        rounds = stage_rounds(b0->d.B, nW, b0->d.C);
+        ws_side = carve(b0, nullptr, &w, false, round_images(b0->d.B, nW, b0->d.C, 0));
         // both chains start together (the second one window kernel behind the first measured slower: 377 against 361 us, six blocks on
         // 192 windows at C = 384)
         const hipError_t e = side->fork_from(st);
@@ -818,7 +818,7 @@ int mixaq_stage_forward(mixaq_block* const* blocks, int32_t n_blocks, const floa
             for (int chain = 0; chain < (side ? 2 : 1) && !rc; ++chain) {
                 Part part;                                           // one chain: all images
                 if (side) {
-                    const StagePart sp = stage_part(b0->d.B, nW, chain, round);
+                    const StagePart sp = stage_part(b0->d.B, nW, b0->d.C, chain, round);
                     part.first = sp.first;
                     part.images = sp.images;
                     part.ws_offset = chain ? ws_side : 0;

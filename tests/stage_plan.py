@@ -12,10 +12,10 @@ _SOURCE = r'''
 extern "C" {
 int splits(int B, int nW) { return mixaq::stage_splits(B, nW); }
 int pays(int B, int nW, int C, int blocks) { return mixaq::stage_split_pays(B, nW, C, blocks); }
-int rounds(int B, int nW) { return mixaq::stage_rounds(B, nW); }
-int round_images(int B, int nW, int chain) { return mixaq::round_images(B, nW, chain); }
-int part_first(int B, int nW, int chain, int round) { return mixaq::stage_part(B, nW, chain, round).first; }
-int part_images(int B, int nW, int chain, int round) { return mixaq::stage_part(B, nW, chain, round).images; }
+int rounds(int B, int nW, int C) { return mixaq::stage_rounds(B, nW, C); }
+int round_images(int B, int nW, int C, int chain) { return mixaq::round_images(B, nW, C, chain); }
+int part_first(int B, int nW, int C, int chain, int round) { return mixaq::stage_part(B, nW, C, chain, round).first; }
+int part_images(int B, int nW, int C, int chain, int round) { return mixaq::stage_part(B, nW, C, chain, round).images; }
 }
 '''
 
@@ -40,4 +40,4 @@ def forks(spec, n_blocks):
 
 def rounds(spec):
     """In how many rounds the two chains of such a stage go through their images."""
-    return lib.rounds(spec.B, spec.nW)
+    return lib.rounds(spec.B, spec.nW, spec.C)
