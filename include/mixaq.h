@@ -183,13 +183,15 @@ int mixaq_block_forward_scored(const mixaq_block *blk, const float *x, const dou
  * overlap).  scores (device double [B,nW]) and perm (device int32 [B,nW]) are caller-owned scratch
  * that hold the stage's scores and selection list afterwards.  The workspace must satisfy
  * mixaq_block_workspace_bytes of the stage's blocks (equal shapes give equal sizes).  All work is
- * ordered on `stream`; nothing is allocated.  A batch of small maps (B >= 2, at most 4096 windows in
- * all, fused kernels) whose stage is long enough (n_blocks * B*nW * C >= 220000: fork and join cost as much as a short stage
- * would gain) runs as two chains of blocks, one per half of the images (they are independent through the whole stage), and so
- * does a larger batch whose halves are even (B even, or at least 9), in rounds of about 270000 windows * channels a chain (53 MB of map): the second chain
- * is enqueued on a stream of the library's own (one per calling stream, at most four per device; a caller that finds none
- * gets one chain) that starts after the work already on `stream` and that `stream` waits for before the call's work
- * counts as done, so the caller sees the same ordering as without it; under stream capture the
+ * ordered on `stream`; no memory is allocated and nothing waits for the GPU.  A batch of maps (B >= 2, fused kernels; at most 4096
+ * windows in all, or even halves: B even or at least 9) whose stage is long enough (n_blocks * B*nW * C >= 220000: fork and join cost
+ * as much as a short stage would gain) runs as two chains of blocks, one per half of the images (they are independent
+ * through the whole stage), a large batch in rounds of about 270000 windows * channels a chain (53 MB of map).  The second chain
+ * is enqueued on a stream of the library's own that starts after the work already on `stream` and that `stream` waits for before
+ * the call's work counts as done, so the caller sees the same ordering as without it.  There is one such stream per calling
+ * stream, at most four per device, given back with the last block that may use them: mixaq_block_create makes one for the stream it
+ * is given, and the first forking call on any other stream makes (a stream and two events) or takes over an idle one; a call that
+ * gets none runs as one chain.  Under stream capture the
  * stage stays on `stream` alone.  MIXAQ_E_SHAPE if the blocks disagree on the shape or a count is
  * out of range, MIXAQ_E_NULL for missing pointers. */
 int mixaq_stage_forward(mixaq_block *const *blocks, int32_t n_blocks, const float *x, const int32_t *k_high,
