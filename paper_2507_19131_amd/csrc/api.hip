@@ -294,8 +294,8 @@ struct Prof {
 };
 
 // a run of images of the batch handled by one call of forward_impl (images = 0: the whole batch), and where its
-// part of the workspace starts
-struct Part { int first = 0, images = 0; size_t ws_offset = 0; };
+// part of the workspace starts; chains: how many such calls run beside each other
+struct Part { int first = 0, images = 0, chains = 1; size_t ws_offset = 0; };
 
 int forward_impl(const mixaq_block* blk, const float* x, const int32_t* perm, const double* scores, int32_t k_high,
                  int32_t k_low, float* y, void* workspace, size_t workspace_bytes, void* stream, const mixaq_taps* taps,
@@ -378,7 +378,7 @@ int forward_impl(const mixaq_block* blk, const float* x, const int32_t* perm, co
         wa.tap_o = tp.acc_o; wa.tap_code = tp.a_proj_in;
         wa.taps = taps != nullptr;
         mark(9);
-        for (int r = 0; r < reps; ++r) launch_window(G, wa, st);       // also forwards pruned windows
+        for (int r = 0; r < reps; ++r) launch_window(G, wa, part.chains, st);       // also forwards pruned windows
     } else {
         launch_bypass(G, perm, x, y, st);                              // pruned windows (if any) are forwarded
         la.perm = perm; la.src = x; la.eps = d.ln_eps; la.out = ws.a1; la.row_pix = ws.row_pix; la.row_canon = ws.row_canon;
@@ -821,6 +821,7 @@ int mixaq_stage_forward(mixaq_block* const* blocks, int32_t n_blocks, const floa
                     const StagePart sp = stage_part(b0->d.B, nW, b0->d.C, chain, round);
                     part.first = sp.first;
                     part.images = sp.images;
+                    part.chains = 2;
                     part.ws_offset = chain ? ws_side : 0;
                 }
                 void* on = chain ? (void*)side->stream : stream;

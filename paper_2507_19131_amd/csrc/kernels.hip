@@ -899,9 +899,9 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
     // Weight fragments in flight.  STREAM: the fragments of q, k and v are one stream that starts under the LayerNorm phase and runs
     // on across the epilogues (each chain on its own starts with a wait for its first fragment: 100 x 168 x 192 87.0 -> 85.9 us,
     // 3 x 61 x 93 x 192 75.0 -> 73.3, backbone 621.8 -> 615).  Not where the registers are taken: three heads of a wave each spill
-    // 17 to 26 of their 96, the pairs of C = 256 67 to 94 of their 80.  (Half a window's heads at C = 128 and 192, at most 96
-    // windows, have 128 since they are alone on their CU: six blocks on 81 windows at C = 192 147 -> 133 us, three sets in turn
-    // of two blocks on 64 windows at C = 128 36.7 -> 33.8.)
+    // 17 to 26 of their 96, the pairs of C = 256 67 to 94 of their 80.  (Half a window's heads at C = 128 and 192 have 128, as few of
+    // them share a CU: six blocks on 81 windows at C = 192 147 -> 133 us, three sets in turn of two blocks on 64 windows at
+    // C = 128 36.7 -> 33.8.)
     constexpr bool STREAM = KS >= 12 || (HG == 1 ? !(NH == 3 && QS == 1) : KS < 8);
     constexpr int RING = !STREAM ? (KS < 6 ? KS : 6) : KS < 6 ? KS : KS == 6 ? (QS == 1 ? 6 : 3) : KS == 12 ? 6 : KS < 32 ? 8 : 16;
     static_assert(!STREAM || KS % RING == 0, "each chain starts at ring slot 0");
@@ -1640,20 +1640,40 @@ void launch_gemm(const Geom& G, const GemmArgs& A, int epi, hipStream_t st)
 // the window kernel (gather + LN1 + QKV + attention) and the token kernel (proj + LN2 + FFN + scatter) are chosen separately
 bool fused_token_supported(int C, int mlp_ratio) { return (C == 96 || C == 128 || C == 192 || C == 256 || C == 384) && mlp_ratio == 4; }
 
-// Up to this many windows a pair of waves shares a head.  The pair form has the shorter chain of dependent steps
-// (a workgroup alone on its CU: 9.2 instead of 10.9 us at C = 96 and 128, 11.8 instead of 12.7 at C = 192) but 15 % more
-// vector and 80 % more scalar instructions per window, so it loses once the CUs are full (1392 windows at C = 96: 29.2 instead
-// of 24.3 us; 5476 at C = 128: 111 instead of 105 us).  At C = 192 it wins on 360 windows (18.2 instead of 18.8 us) and is
-// equal on 512.
-constexpr int WINDOW_PAIR_SMALL = 256, WINDOW_PAIR_SMALL_6 = 512;
-// Up to this many windows two workgroups share a window's heads (each gathers and normalizes the whole window): a wave then has
-// fewer neighbours on its SIMD.  96 windows: 9.3 -> 8.3 us a kernel at C = 128 (130 windows: 9.4 -> 9.5), 11.8 -> 11.0 at C = 192
-// (130 windows: 11.8 -> 13.6); at C = 384, against one wave per head, 128 windows 19.5 -> 15.1 (130: 19.5 -> 25.7, two
-// workgroups on one CU).  C = 256 always: sixteen waves
-// of one workgroup, or eight of twice the registers, leave a CU half empty, three workgroups of eight fill it (6 windows:
-// 62.8 -> 51.4 us the pair, 300: 106 -> 95, 1444: 351 -> 335, 2750: 680 -> 654).
-constexpr int WINDOW_SPLIT_SMALL = 96, WINDOW_SPLIT_SMALL_12 = 128;
-void launch_window(const Geom& G, const WinArgs& A, hipStream_t st)
+// Forms of the window kernel by the number of windows.  One wave per head has the fewest instructions per window; a pair of waves per head
+// has the shorter chain of dependent steps at 15 % more vector and 80 % more scalar instructions; two workgroups per window, each
+// with half its heads in pairs (both gather and normalize the whole window), put fewer waves side by side on a SIMD.  Measured
+// as two blocks on one map, us, in the order single / pair / split (three sets of handles in turn):
+//   C = 96   66 windows 40 / 34   228 46 / 39   260 47 / 44   360 52 / 49   506 56 / 53   528 60 / 63   600 62 / 64; each of two chains (six
+//            blocks): 260 172 / 160   400 196 / 189   504 219 / 212   600 239 / 242   704 263 / 275
+//   C = 128  66 40 / 36 / 34   126 40 / 36 / 35   140 41 / 37 / 38   256 46 / 41 / 42   266 49 / 48 / 46   378 55 / 54 / 52   396 56 / 54 / 56
+//            506 62 / 60 / 63   528 68 / 71 / 69; each of two chains: 112 (twelve blocks) 276 / 253 / 246   260 184 / 177 / 169   400 218 / 215 / 219
+//            504 254 / 256 / 261   600 291 / 301 / 307
+//   C = 192  66 51 / 52 / 44   126 52 / 53 / 46   140 52 / 54 / 52   256 64 / 65 / 63   266 73 / 71 / 75   360 87 / 86 / 88   506 102 / 101 / 112
+//            576 127 / 127 / 135; each of two chains: 77 182 / 183 / 166   112 188 / 188 / 186   126 190 / 191 / 191   144 202 / 194 / 211
+//            198 240 / 231 / 236   228 257 / 253 / 258   260 274 / 282 / 287   400 377 / 406 / 418
+//   C = 384  single / split: 66 80 / 72   126 82 / 75   140 84 / 97   187 117 / 130; each of two chains: 50 251 / 227   70 260 / 240   77 263 / 259
+//            91 280 / 292   112 322 / 339
+// C = 96 and 128: pairs while a CU has no more than two of their workgroups, and at C = 128 split wherever that leaves fewer waves on
+// the fullest CU.  C = 192: split, then pairs, while a CU has no more than two of their workgroups, both chains counted, as it has
+// no room for a third.  C = 384: split while a CU has one (of two chains a few more: they are seldom in the same kernel).
+// C = 256 always split: sixteen waves of one workgroup, or eight of twice the registers, leave a CU half empty, three workgroups of
+// eight fill it (6 windows: 62.8 -> 51.4 us the pair, 300: 106 -> 95, 1444: 351 -> 335, 2750: 680 -> 654).
+constexpr int CUS = 256;
+enum WindowForm { SINGLE, PAIR, SPLIT };
+// of a launch over `windows`, beside another one like it where the stage runs as two chains
+static WindowForm window_form(int heads, int windows, int chains)
+{
+    auto per_cu = [](int workgroups) { return (workgroups + CUS - 1) / CUS; };
+    switch (heads) {
+        case 3: return windows <= 2 * CUS ? PAIR : SINGLE;
+        case 4: return windows > 2 * CUS ? SINGLE : 4 * per_cu(2 * windows) < 8 * per_cu(windows) ? SPLIT : PAIR;
+        case 6: return windows * chains <= CUS ? SPLIT : windows * chains <= 2 * CUS ? PAIR : SINGLE;
+        case 12: return windows <= (chains == 1 ? CUS / 2 : 80) ? SPLIT : SINGLE;
+        default: return SPLIT;
+    }
+}
+void launch_window(const Geom& G, const WinArgs& A, int chains, hipStream_t st)
 {
     // every window gets a workgroup: with scores it finds its own rank (and may turn out pruned), otherwise
     // the computed slots come first and the pruned windows of the list after them
@@ -1688,21 +1708,22 @@ void launch_window(const Geom& G, const WinArgs& A, hipStream_t st)
         }                                                                                                                 \
     }                                                                                                                     \
     break
+    const WindowForm form = window_form(G.C / 32, n_wg, chains);
     switch (G.C / 32) {
         case 3:
-            if (n_wg <= WINDOW_PAIR_SMALL) { WIN_CASE(3, 1, 2); }
+            if (form == PAIR) { WIN_CASE(3, 1, 2); }
             WIN_CASE(3, 1, 1);
         case 4:
-            if (n_wg <= WINDOW_SPLIT_SMALL) { WIN_CASE(2, 2, 2); }
-            if (n_wg <= WINDOW_PAIR_SMALL) { WIN_CASE(4, 1, 2); }
+            if (form == SPLIT) { WIN_CASE(2, 2, 2); }
+            if (form == PAIR) { WIN_CASE(4, 1, 2); }
             WIN_CASE(4, 1, 1);
         case 6:
-            if (n_wg <= WINDOW_SPLIT_SMALL) { WIN_CASE(3, 2, 2); }
-            if (n_wg <= WINDOW_PAIR_SMALL_6) { WIN_CASE(6, 1, 2); }
+            if (form == SPLIT) { WIN_CASE(3, 2, 2); }
+            if (form == PAIR) { WIN_CASE(6, 1, 2); }
             WIN_CASE(6, 1, 1);
         case 8: WIN_CASE(4, 2, 2);
         case 12:
-            if (n_wg <= WINDOW_SPLIT_SMALL_12) { WIN_CASE(6, 2, 2); }
+            if (form == SPLIT) { WIN_CASE(6, 2, 2); }
             WIN_CASE(12, 1, 1);
         default: break;
     }

@@ -302,6 +302,32 @@ def test_forward_from_scores_past_the_small_map_forms(B, H, W, C, heads):
     assert np.array_equal(y.cpu().numpy(), oy)
 
 
+@pytest.mark.parametrize("C,rows,cols", [(96, 16, 32), (96, 19, 27), (128, 8, 16), (128, 3, 43), (128, 16, 16), (128, 6, 43), (128, 16, 24), (128, 11, 35),
+                                         (128, 16, 32), (128, 19, 27), (192, 16, 16), (192, 6, 43), (192, 16, 32), (192, 19, 27),
+                                         (384, 8, 16), (384, 3, 43)])
+def test_forms_of_the_window_kernel_on_both_sides_of_their_lines(C, rows, cols):
+    """One block on the largest and next larger number of windows of every form, given a list, given scores and with pruned windows:
+    the oracle's bits."""
+    import oracle_api as O
+    dev = torch.device("cuda:0")
+    spec, inp, x_np, k = _case(1, 7 * rows - 3, 7 * cols - 2, C, C // 32, 3, 0.4, 700 + cols, blobs=True)
+    assert spec.nW == rows * cols
+    print("window form", C, spec.nW, flush=True)
+    sc = O.score_windows(inp, x_np)
+    x = torch.from_numpy(x_np).to(dev)
+    with gh.GpuBlock(inp) as gb:
+        for k_low in (spec.nW - k, spec.nW // 3):
+            perm_o = O.select_windows(sc, k, k_low=k_low)
+            want, _ = O.block_forward(inp, x_np, perm_o, k, 3, threads=16, k_low=k_low)
+            scores, perm = gb.score_select(x, k)
+            y = gb.forward_pruned(x, perm, k, k_low)
+            y2, p2 = torch.full_like(x, float("nan")), torch.full_like(perm, -1)
+            M.mixaq_block_forward_scored(gb.blk, x, scores, k, k_low, y2, gb.ws, perm_out=p2)
+            torch.cuda.synchronize()
+            assert np.array_equal(perm.cpu().numpy(), perm_o) and torch.equal(p2, perm)
+            assert np.array_equal(y.cpu().numpy(), want) and torch.equal(y, y2)
+
+
 def test_equal_scores_are_ordered_by_window_index():
     """Windows with exactly equal scores (here: windows that are zero everywhere, and two copies of one
     window) must be ranked by their index on both sides; the block output follows."""

@@ -463,6 +463,32 @@ def test_forked_stage_with_uneven_halves_pruning_and_streams(B, H, W, C, heads, 
     assert np.array_equal(y_gpu, cur)
 
 
+@pytest.mark.parametrize("C,rows,cols,n_blocks", [(192, 8, 16, 6), (192, 3, 43, 6), (192, 16, 16, 4), (192, 6, 43, 4), (384, 8, 10, 6), (384, 9, 9, 6)])
+def test_forms_of_the_kernels_of_two_chains_on_both_sides_of_their_lines(C, rows, cols, n_blocks):
+    """The forms of the window kernel that take the other chain into account: the bits of block after block on the whole batch,
+    which takes other forms."""
+    spec = synth.BlockSpec(2, 7 * rows - 1, 7 * cols - 5, C, C // 32)
+    assert spec.nW == rows * cols and stage_plan.forks(spec, n_blocks)
+    dev = torch.device("cuda:0")
+    x = torch.from_numpy(synth.make_feature_map(spec, 395, blobs=True)).to(dev)
+    print("forms of two chains", C, spec.nW, flush=True)
+    blocks = [gh.GpuBlock(synth.make_block_inputs(spec, 396 + i), 3 * (i % 2)) for i in range(n_blocks)]
+    try:
+        k, k_low = spec.nW // 2, spec.nW // 3
+        scores, perm = blocks[0].score_select(x, k)
+        want = x
+        for gb in blocks:
+            want = gb.forward_pruned(want, perm, k, k_low)
+        y, tmp, s2, p2 = torch.full_like(x, float("nan")), torch.full_like(x, float("nan")), torch.empty_like(scores), torch.empty_like(perm)
+        pairs = (n_blocks + 1) // 2
+        M.mixaq_stage_forward([gb.blk for gb in blocks], x, [k] * pairs, [k_low] * pairs, y, tmp, s2, p2, blocks[0].ws)
+        torch.cuda.synchronize()
+        assert torch.equal(y, want) and torch.equal(p2, perm)
+    finally:
+        for gb in blocks:
+            gb.close()
+
+
 @pytest.mark.parametrize("B,H,W,C,n_blocks", [(3, 82, 137, 96, 4), (5, 75, 66, 192, 4)])
 def test_workspace_of_an_odd_batch(B, H, W, C, n_blocks):
     """The two chains of an odd batch share a workspace of no more than its images need one by one, and write nothing behind it."""
