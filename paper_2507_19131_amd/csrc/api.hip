@@ -413,7 +413,7 @@ int forward_impl(const mixaq_block* blk, const float* x, const int32_t* perm, co
         ta.gelu_tab = blk->gelu_tab;
         ta.taps = taps != nullptr;
         mark(10);
-        for (int r = 0; r < reps; ++r) launch_token(G, ta, st);
+        for (int r = 0; r < reps; ++r) launch_token(G, ta, part.chains, st);
         mark(-1);
         HIP_TRY(hipGetLastError());
         return MIXAQ_OK;

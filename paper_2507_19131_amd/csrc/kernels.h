@@ -110,7 +110,7 @@ bool channels_supported(int C);
 bool fused_token_supported(int C, int mlp_ratio);
 // chains: how many launches like this one run beside each other (the two chains of a stage)
 void launch_window(const Geom& G, const WinArgs& A, int chains, hipStream_t st);
-void launch_token(const Geom& G, const TokArgs& A, hipStream_t st);
+void launch_token(const Geom& G, const TokArgs& A, int chains, hipStream_t st);
 bool launch_score(const Geom& G, const float* x, int mode, float eps, const float* gm, const float* bt, double* scores,
                   hipStream_t st);
 void launch_select(const double* scores, int B, int nW, int reverse, int* perm, hipStream_t st);

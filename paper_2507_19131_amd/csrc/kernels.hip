@@ -1730,8 +1730,24 @@ void launch_window(const Geom& G, const WinArgs& A, int chains, hipStream_t st)
 #undef WIN_CASE
 }
 
-constexpr int TOKEN_WIDE_SMALL = 128;        // C = 384: up to this many 64-row tiles the token kernel runs on 32-row tiles
-void launch_token(const Geom& G, const TokArgs& A, hipStream_t st)
+// Rows per workgroup of the token kernel at C = 384.  A CU holds one workgroup of twelve waves, which takes 15 units of time for 64
+// rows and 8 for 32, so the form is the one whose rounds over the CUs are shorter; two chains fill them together.  32 rows -> 64, us,
+// two blocks on one map (three sets of handles in turn):
+//   windows   66 72 -> 103   160 87 -> 114 | 170 121 -> 115   187 121 -> 117   260 157 -> 152   294 159 -> 161   330 164 -> 166 |
+//             345 197 -> 228   384 203 -> 232   442 216 -> 241   486 226 -> 244 | 504 255 -> 247   513 286 -> 277   600 293 -> 291 |
+//             704 338 -> 368   805 380 -> 403
+// and six blocks, windows of each of two chains:  70 241 -> 331   96 299 -> 359   126 373 -> 407   150 393 -> 423   176 462 -> 503   198 537
+// both   216 555 -> 598   240 592 -> 620 | 260 689 -> 667   280 700 -> 697   294 740 -> 724   322 784 -> 775 | 345 855 -> 870   360 892 -> 915
+// | 400 999 -> 988   425 1031 -> 1032   600 1445 -> 1423 | 704 1698 -> 1717.
+// While 64-row tiles of both chains are no more than the CUs the chains are seldom in this kernel together, and a long tile is
+// the latency of one chain: 32 rows.  With fewer waves (C <= 256) the registers of a second row block cost more than its weights save.
+static bool token_of_64_rows(int rows, int chains)
+{
+    const int all = rows * chains, tiles32 = all / 32, tiles64 = all / 64;
+    if (chains > 1 && tiles64 <= CUS) return false;
+    return 15 * ((tiles64 + CUS - 1) / CUS) < 8 * ((tiles32 + CUS - 1) / CUS);
+}
+void launch_token(const Geom& G, const TokArgs& A, int chains, hipStream_t st)
 {
     if (G.rows_total == 0) return;
 #define TOK_CASE(NH, RB)                                                                                                             \
@@ -1743,11 +1759,7 @@ void launch_token(const Geom& G, const TokArgs& A, hipStream_t st)
         case 6: TOK_CASE(6, 1); break;
         case 8: TOK_CASE(8, 1); break;
         default:
-            // 64-row tiles once there are enough of them to give every second CU one, else 32-row tiles, of which a CU then takes
-            // one (32-row -> 64-row: 156 windows 22.0 -> 37.3 us, 169 windows 39.3 -> 37.6, 192 39.6 -> 38.0; but 384 windows, where
-            // 64-row tiles are a few more than the CUs, 60.2 -> 74.3).  With fewer waves the registers of a second row block cost
-            // more than its weights save.
-            if (G.rows_total / 64 > TOKEN_WIDE_SMALL) { TOK_CASE(12, 2); }
+            if (token_of_64_rows(G.rows_total, chains)) { TOK_CASE(12, 2); }
             else { TOK_CASE(12, 1); }
     }
 #undef TOK_CASE

@@ -304,15 +304,15 @@ def test_forward_from_scores_past_the_small_map_forms(B, H, W, C, heads):
 
 @pytest.mark.parametrize("C,rows,cols", [(96, 16, 32), (96, 19, 27), (128, 8, 16), (128, 3, 43), (128, 16, 16), (128, 6, 43), (128, 16, 24), (128, 11, 35),
                                          (128, 16, 32), (128, 19, 27), (192, 16, 16), (192, 6, 43), (192, 16, 32), (192, 19, 27),
-                                         (384, 8, 16), (384, 3, 43)])
-def test_forms_of_the_window_kernel_on_both_sides_of_their_lines(C, rows, cols):
-    """One block on the largest and next larger number of windows of every form, given a list, given scores and with pruned windows:
-    the oracle's bits."""
+                                         (384, 8, 16), (384, 3, 43), (384, 11, 15), (384, 12, 15), (384, 15, 22), (384, 17, 21), (384, 20, 26)])
+def test_forms_of_the_fused_kernels_on_both_sides_of_their_lines(C, rows, cols):
+    """One block on the largest and next larger number of windows of every form of the window kernel, and of 32 and 64 rows of the token
+    kernel, given a list, given scores and with pruned windows: the oracle's bits."""
     import oracle_api as O
     dev = torch.device("cuda:0")
     spec, inp, x_np, k = _case(1, 7 * rows - 3, 7 * cols - 2, C, C // 32, 3, 0.4, 700 + cols, blobs=True)
     assert spec.nW == rows * cols
-    print("window form", C, spec.nW, flush=True)
+    print("forms", C, spec.nW, flush=True)
     sc = O.score_windows(inp, x_np)
     x = torch.from_numpy(x_np).to(dev)
     with gh.GpuBlock(inp) as gb:

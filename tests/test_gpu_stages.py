@@ -463,9 +463,9 @@ def test_forked_stage_with_uneven_halves_pruning_and_streams(B, H, W, C, heads, 
     assert np.array_equal(y_gpu, cur)
 
 
-@pytest.mark.parametrize("C,rows,cols,n_blocks", [(192, 8, 16, 6), (192, 3, 43, 6), (192, 16, 16, 4), (192, 6, 43, 4), (384, 8, 10, 6), (384, 9, 9, 6)])
+@pytest.mark.parametrize("C,rows,cols,n_blocks", [(192, 8, 16, 6), (192, 3, 43, 6), (192, 16, 16, 4), (192, 6, 43, 4), (384, 8, 10, 6), (384, 9, 9, 6), (384, 12, 15, 2), (384, 16, 17, 2)])
 def test_forms_of_the_kernels_of_two_chains_on_both_sides_of_their_lines(C, rows, cols, n_blocks):
-    """The forms of the window kernel that take the other chain into account: the bits of block after block on the whole batch,
+    """The forms of the two fused kernels that take the other chain into account: the bits of block after block on the whole batch,
     which takes other forms."""
     spec = synth.BlockSpec(2, 7 * rows - 1, 7 * cols - 5, C, C // 32)
     assert spec.nW == rows * cols and stage_plan.forks(spec, n_blocks)
