@@ -184,9 +184,9 @@ int mixaq_block_forward_scored(const mixaq_block *blk, const float *x, const dou
  * that hold the stage's scores and selection list afterwards.  The workspace must satisfy
  * mixaq_block_workspace_bytes of the stage's blocks (equal shapes give equal sizes).  All work is
  * ordered on `stream`; no memory is allocated and nothing waits for the GPU.  A batch of maps (B >= 2, fused kernels; at most 4096
- * windows in all, or even halves: B even or at least 9) whose stage is long enough (n_blocks * B*nW * C >= 220000: fork and join cost
- * as much as a short stage would gain) runs as two chains of blocks, one per half of the images (they are independent
- * through the whole stage), a large batch in rounds of about 270000 windows * channels a chain (53 MB of map).  The second chain
+ * windows in all, or even halves: B even or at least 9) of more than 128 windows in all (160 at C = 256) whose stage is long
+ * enough (n_blocks * B*nW * C >= 220000: fork and join cost as much as a short stage would gain) runs as two chains of blocks, one
+ * per half of the images (they are independent through the whole stage), a large batch in rounds of about 270000 windows * channels a chain (53 MB of map).  The second chain
  * is enqueued on a stream of the library's own that starts after the work already on `stream` and that `stream` waits for before
  * the call's work counts as done, so the caller sees the same ordering as without it.  There is one such stream per calling
  * stream, at most four per device, given back with the last block that may use them: mixaq_block_create makes one for the stream it

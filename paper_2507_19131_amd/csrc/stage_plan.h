@@ -24,16 +24,28 @@ constexpr int STAGE_SPLIT_MAX_WINDOWS = 4096;
 //            48 x 96 (six blocks) 5453 -> [4] 5198, [2] 5353      28 x 96 (six blocks) 3128 -> [2] 3028, [3] 3081
 constexpr long long STAGE_ROUND_WORK = 2800LL * 96;
 // Fork and join cost 25 to 30 us, so the stage has to be long enough: the line is drawn at windows times channels over all its
-// blocks.  One chain -> two, in us (three sets of handles in turn take the same, as they share the caller's side stream):
-//   two blocks:  C = 96, 256 windows 43 -> 77; 392 54 -> 78; 840 79 -> 84; 1352 104 -> 101
-//                C = 128, 920 95 -> 94        C = 192, 450 89 -> 100; 924 175 -> 170
-//                C = 256, 480 128 -> 128; 1012 245 -> 241      C = 384, 192 114 -> 117; 300 159 -> 140; 450 236 -> 232
-//   six blocks:  C = 96, 128 windows 110 -> 142; 392 166 -> 155        C = 128, 512 190 -> 171
-//                C = 192, 98 170 -> 176; 200 204 -> 200       C = 256, 220 225 -> 219
-//                C = 384, 40 215 -> 231; 70 217 -> 232; 192 335 -> 294
+// blocks.  And a chain has to leave the other one something: up to this many windows one chain's launches are at most about one
+// workgroup per CU, as long as those of half the images, and two chains lose at every number of blocks.  One chain -> two, us
+// (three sets of handles in turn, which share the caller's side stream):
+//   two blocks:    C = 96, 396 windows 49 -> 73; 850 77 -> 80; 1200 90 -> 96; 1344 99 -> 99; 1610 117 -> 115
+//                  C = 128, 588 68 -> 76; 918 89 -> 92; 1064 105 -> 100      C = 192, 456 87 -> 98; 520 119 -> 111; 588 128 -> 117
+//                  C = 256, 300 88 -> 100; 396 118 -> 113; 480 121 -> 125; 560 149 -> 144; 768 186 -> 188; 850 213 -> 205
+//                  C = 384, 120 74 -> 91; 234 119 -> 120; 300 159 -> 140; 456 211 -> 202
+//   six blocks:    C = 96, 252 119 -> 132; 300 138 -> 136; 396 153 -> 147      C = 128, 234 126 -> 133; 288 143 -> 141; 340 154 -> 148
+//                  C = 192, 154 157 -> 165; 182 185 -> 169; 234 186 -> 189; 288 209 -> 194
+//                  C = 256, 140 182 -> 196; 154 184 -> 198; 182 223 -> 203; 252 227 -> 227; 340 304 -> 277
+//                  C = 384, 72 209 -> 225; 108 212 -> 226; 140 243 -> 239; 154 248 -> 256; 192 340 -> 282
+//   twelve:        C = 96, 192 229 -> 235; 288 275 -> 250      C = 128, 154 218 -> 231; 192 244 -> 239      C = 192, 100 269 -> 296; 132 309 -> 304
+//                  C = 256, 108 324 -> 358; 140 361 -> 369      C = 384, 72 414 -> 431; 120 424 -> 443; 140 484 -> 452
+//   eighteen (24): C = 96 (132 407 -> 435; 192 459 -> 449)      C = 128 (132 424 -> 434; 192 489 -> 460)      C = 192, 100 403 -> 434; 132 463 -> 445
+//                  C = 256, 100 482 -> 522; 154 542 -> 548; 182 660 -> 563      C = 384, 72 627 -> 645; 120 657 -> 673; 132 753 -> 694
 // Pruned windows count like the others: their share shortens both forms.
 constexpr long long STAGE_SPLIT_MIN_WORK = 2200LL * 100;
-inline bool stage_split_pays(int B, int nW, int C, int n_blocks) { return (long long)n_blocks * B * nW * C >= STAGE_SPLIT_MIN_WORK; }
+constexpr int STAGE_SPLIT_MIN_WINDOWS = 128, STAGE_SPLIT_MIN_WINDOWS_256 = 160;     // at C = 256
+inline bool stage_split_pays(int B, int nW, int C, int n_blocks)
+{
+    return B * nW > (C == 256 ? STAGE_SPLIT_MIN_WINDOWS_256 : STAGE_SPLIT_MIN_WINDOWS) && (long long)n_blocks * B * nW * C >= STAGE_SPLIT_MIN_WORK;
+}
 
 // whether the map allows two chains
 inline bool stage_splits(int B, int nW)

@@ -26,3 +26,8 @@ def test_a_round_is_a_share_of_the_map_of_about_the_same_size_at_every_width(C):
         n = stage_plan.lib.rounds(B, 96, C)
         if n > 1:
             assert 0.75 * 2800 * 96 <= B * 96 * C / 2 / n <= 1.5 * 2800 * 96, (B, n)
+
+
+@pytest.mark.parametrize("C,most", [(96, 128), (128, 128), (192, 128), (256, 160), (384, 128)])
+def test_maps_of_few_windows_stay_on_one_chain_however_many_blocks(C, most):
+    assert not stage_plan.lib.pays(2, most // 2, C, 1000) and stage_plan.lib.pays(2, most // 2 + 1, C, 1000)
