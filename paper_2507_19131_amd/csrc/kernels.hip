@@ -1656,20 +1656,23 @@ bool fused_token_supported(int C, int mlp_ratio) { return (C == 96 || C == 128 |
 //            91 280 / 292   112 322 / 339
 // C = 96 and 128: pairs while a CU has no more than two of their workgroups, and at C = 128 split wherever that leaves fewer waves on
 // the fullest CU.  C = 192: split, then pairs, while a CU has no more than two of their workgroups, both chains counted, as it has
-// no room for a third.  C = 384: split while a CU has one (of two chains a few more: they are seldom in the same kernel).
+// no room for a third.  C = 384: split while a CU has one (of two chains a few more: they are seldom in the same kernel).  Pruned windows
+// count where their workgroups stand in the way of others, but not at C = 96 (461 of 576 computed: single 57, pair 56; 470 of 784 61, 59) and
+// not beside a second chain at C = 384 (58 of 96, six blocks: single 252, split 233; 77 of 96 258 both); elsewhere counting the
+// computed ones only measured slower (C = 384, 127 of 182 computed: 84 -> 90; 192, 240 of 300: 69 -> 71; 128, 461 of 576: 60 -> 62).
 // C = 256 always split: sixteen waves of one workgroup, or eight of twice the registers, leave a CU half empty, three workgroups of
 // eight fill it (6 windows: 62.8 -> 51.4 us the pair, 300: 106 -> 95, 1444: 351 -> 335, 2750: 680 -> 654).
 constexpr int CUS = 256;
 enum WindowForm { SINGLE, PAIR, SPLIT };
-// of a launch over `windows`, beside another one like it where the stage runs as two chains
-static WindowForm window_form(int heads, int windows, int chains)
+// of a launch over `windows`, `computed` of them not pruned, beside another one like it where the stage runs as two chains
+static WindowForm window_form(int heads, int windows, int computed, int chains)
 {
     auto per_cu = [](int workgroups) { return (workgroups + CUS - 1) / CUS; };
     switch (heads) {
-        case 3: return windows <= 2 * CUS ? PAIR : SINGLE;
+        case 3: return computed <= 2 * CUS ? PAIR : SINGLE;
         case 4: return windows > 2 * CUS ? SINGLE : 4 * per_cu(2 * windows) < 8 * per_cu(windows) ? SPLIT : PAIR;
         case 6: return windows * chains <= CUS ? SPLIT : windows * chains <= 2 * CUS ? PAIR : SINGLE;
-        case 12: return windows <= (chains == 1 ? CUS / 2 : 80) ? SPLIT : SINGLE;
+        case 12: return windows <= CUS / 2 && (chains == 1 || computed <= 80) ? SPLIT : SINGLE;
         default: return SPLIT;
     }
 }
@@ -1708,7 +1711,7 @@ void launch_window(const Geom& G, const WinArgs& A, int chains, hipStream_t st)
         }                                                                                                                 \
     }                                                                                                                     \
     break
-    const WindowForm form = window_form(G.C / 32, n_wg, chains);
+    const WindowForm form = window_form(G.C / 32, n_wg, G.n_slots, chains);
     switch (G.C / 32) {
         case 3:
             if (form == PAIR) { WIN_CASE(3, 1, 2); }
