@@ -177,12 +177,12 @@ def test_stage_on_a_batch_of_small_maps_runs_as_two_chains(B, C, heads):
 
 
 def test_two_chains_at_config2_shape_on_two_maps():
-    """2 x 1392 windows at C = 96: the largest kind of batch the stage call still runs as two chains."""
+    """2 x 1392 windows at C = 96 as two chains, one image each."""
     import dataclasses
     wl = synth.workload("cfg2")
     st = wl["stages"][0]
     spec = dataclasses.replace(st["spec"], B=2)
-    assert spec.B * spec.nW <= 4096
+    assert spec.B * spec.nW <= 4096 and stage_plan.forks(spec, len(st["shifts"]))
     y_blocks, y_or, perm_blocks, perm_or = run_stage(spec, st["shifts"], wl["keep"][0], wl["seed"], wl["blobs"], wl["outliers"], wl.get("ranges"))
     check(y_blocks, y_or, perm_blocks, perm_or)
     k = M.mixaq_keep_count(spec.nW, wl["keep"][0])
@@ -551,11 +551,11 @@ def test_repeated_forked_stage_calls_are_bit_stable(B, H, W, C, heads, n_blocks)
 
 
 @pytest.mark.parametrize("B,H,W,C,k_low", [(11, 161, 175, 96, None), (10, 161, 175, 96, 100), (6, 224, 220, 128, None), (3, 252, 371, 96, 200)])
-def test_stage_of_a_large_batch_in_rounds(B, H, W, C, k_low):
-    """More windows than two chains take at once: the chains go through their halves in rounds (uneven ones where the halves
-    are odd), pruned or not, or the stage stays on one chain (three images); the bits are those of block after block."""
+def test_stage_of_a_large_batch(B, H, W, C, k_low):
+    """More than 4096 windows: two chains where the halves are even, each in one round here (more of them:
+    test_rounds_of_a_stage_at_every_width), pruned or not, or one chain (three images); the bits are those of block after block."""
     spec = synth.BlockSpec(B, H, W, C, C // 32)
-    assert B * spec.nW > 5600
+    assert B * spec.nW > 5600 and stage_plan.forks(spec, 2) == (B != 3) and stage_plan.rounds(spec) == 1
     k = spec.nW // 2
     dev = torch.device("cuda:0")
     x = torch.randn((B, H, W, C), generator=torch.Generator(device=dev).manual_seed(370), device=dev)
