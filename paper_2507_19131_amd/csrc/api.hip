@@ -143,6 +143,10 @@ struct mixaq_block {
     float* win_params[2] = {nullptr, nullptr};   // parameter blocks of the fused window kernel
     int ao_pack = 0;           // packing of the low branch's attention-output codes between the two fused kernels
     const float4* gelu_tab = nullptr;            // cubic coefficients of the pinned GELU
+    const GeluStep* gelu_steps[2] = {nullptr, nullptr};   // GELU and its quantizer as a table of steps, for the token kernel
+    GeluIndex gelu_step_index[2] = {};
+    int gelu_step_pieces[2] = {0, 0};
+    bool gelu_by_steps = false;                  // both branches have one
     size_t ws_bytes = 0;
     size_t ws_fused_bytes = 0; // what the two fused kernels alone need
     int side_device = -1;      // a batch of small maps: the device whose side streams the stage call may use (see SideStreams)
@@ -411,6 +415,10 @@ int forward_impl(const mixaq_block* blk, const float* x, const int32_t* perm, co
         ta.tap_acc_proj = tp.acc_proj; ta.tap_h = tp.h; ta.tap_a2 = tp.a_fc1_in; ta.tap_acc_fc1 = tp.acc_fc1;
         ta.tap_g = tp.a_fc2_in; ta.tap_acc_fc2 = tp.acc_fc2; ta.tap_y = tp.y_win;
         ta.gelu_tab = blk->gelu_tab;
+        ta.by_steps = blk->gelu_by_steps;
+        for (int br = 0; br < 2; ++br) {
+            ta.steps[br] = blk->gelu_steps[br]; ta.step_index[br] = blk->gelu_step_index[br]; ta.step_pieces[br] = blk->gelu_step_pieces[br];
+        }
         ta.taps = taps != nullptr;
         mark(10);
         for (int r = 0; r < reps; ++r) launch_token(G, ta, part.chains, st);
@@ -628,9 +636,24 @@ static int block_create(const mixaq_block_desc* desc, const mixaq_shared_params*
         std::vector<float> tab((size_t)GELU_TAB * 4, 0.0f);
         gelu_table(tab.data());
         b->mem.add(tab, &b->gelu_tab);
+        b->fused_token = fused_token_supported(C, desc->mlp_ratio);
+        // the table of steps knows numbers only: with a constant that is none the sums take the cubic, like a quantizer that has no table
+        bool ordinary = b->fused_token;
+        for (int br = 0; br < 2; ++br)
+            for (int n = 0; n < F && ordinary; ++n) ordinary = std::isfinite(b->fc1.hm[br][n]) && std::isfinite(b->fc1.hb[br][n]);
+        GeluSteps steps[2];
+        for (int br = 0; br < 2 && ordinary; ++br) {
+            const QDev& q = b->q_fc2in[br];
+            ordinary = steps[br].build(tab.data(), GELU_K, q.inv_s, q.magic, q.lo, q.hi);
+        }
+        for (int br = 0; br < 2 && ordinary; ++br) {
+            b->mem.add(steps[br].table, &b->gelu_steps[br]);
+            b->gelu_step_index[br] = steps[br].index;
+            b->gelu_step_pieces[br] = (int)steps[br].table.size() / 128;
+        }
+        b->gelu_by_steps = ordinary;
     }
     b->fused_window = true;   // every width has a form of the window kernel
-    b->fused_token = fused_token_supported(C, desc->mlp_ratio);
     for (int br = 0; br < 2; ++br) {      // parameter blocks of the window kernel: LN1, then the QKV constants head by head
         std::vector<float> blkp = hln[br][0];
         blkp.insert(blkp.end(), hln[br][1].begin(), hln[br][1].end());

@@ -103,6 +103,10 @@ struct TokArgs {                     // fused token kernel (proj + LN2 + FFN + s
     QDev q_fc1in[2], q_fc2in[2];
     int32_t* tap_acc_proj; float* tap_h; int8_t* tap_a2; int32_t* tap_acc_fc1; int8_t* tap_g; int32_t* tap_acc_fc2; float* tap_y;
     const float4* gelu_tab;          // [GELU_K] cubic coefficients
+    const GeluStep* steps[2];        // per branch the table of steps (see gelu_steps.h) and its 1 KB pieces ...
+    GeluIndex step_index[2];
+    int step_pieces[2];
+    bool by_steps;                   // ... used where both branches have one
     bool taps;
 };
 

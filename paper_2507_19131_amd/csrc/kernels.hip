@@ -1217,18 +1217,18 @@ __device__ __forceinline__ void to_lds(const void* src, void* dst)
 {
     __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src, (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
 }
-// requests the branch's parameter block and the GELU table of a token kernel of NH waves
+// requests the branch's parameter block and the GELU table (1 KB pieces) of a token kernel of NH waves
 template <int NH>
-__device__ __forceinline__ void token_stage(const float* params, const float4* gelu_tab, float* prm, float4* gtab, int wave, int lane)
+__device__ __forceinline__ void token_stage(const float* params, const float4* gelu, int gelu_pieces, float* prm, float4* gtab, int wave, int lane)
 {
     constexpr int PIECES = TokPrm<NH * 32>::WORDS / 256;
 #pragma unroll
     for (int p0 = 0; p0 < PIECES; p0 += NH)
         if (p0 + NH <= PIECES || p0 + wave < PIECES) to_lds(params + (p0 + wave) * 256 + lane * 4, prm + (p0 + wave) * 256);
-    if (wave >= NH - 2) to_lds(gelu_tab + (wave - (NH - 2)) * 64 + lane, gtab + (wave - (NH - 2)) * 64);
+    for (int p = NH - 1 - wave; p < gelu_pieces; p += NH) to_lds(gelu + p * 64 + lane, gtab + p * 64);   // the last waves have the fewest of the others
 }
 
-template <int NH, int RB, bool TAPS>
+template <int NH, int RB, bool TAPS, bool STEPS>
 __global__ __launch_bounds__(NH * 64) __attribute__((amdgpu_waves_per_eu(tok_waves_per_eu(NH)))) void token_kernel(Geom G, TokArgs A)
 {
     if (NH == 12 || G.rows_total <= 256 * 32) touch_arguments<sizeof(Geom) + sizeof(TokArgs)>();   // about one workgroup a CU
@@ -1242,7 +1242,7 @@ __global__ __launch_bounds__(NH * 64) __attribute__((amdgpu_waves_per_eu(tok_wav
     __shared__ v4i gs[2][NH * RB * 64];                                // [buffer][hidden block of the chunk][row block][lane]
     __shared__ double part[2][NH][32 * RB];
     __shared__ __attribute__((aligned(16))) float prm[PR::WORDS];
-    __shared__ float4 gtab[GELU_TAB];
+    __shared__ float4 gtab[STEPS ? GELU_STEP_PIECES * 64 : GELU_TAB];
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, j = lane & 31, g = lane >> 5;
     const int row_base = blockIdx.x * (32 * RB);
     const int branch = row_base >= G.base_lo ? 1 : 0;                 // a tile never straddles the regions: scalar
@@ -1282,7 +1282,7 @@ __global__ __launch_bounds__(NH * 64) __attribute__((amdgpu_waves_per_eu(tok_wav
         pix[rb] = A.row_pix[row];
         canon[rb] = (TAPS && valid[rb]) ? (size_t)A.row_canon[row] : 0;
     }
-    token_stage<NH>(A.params[branch], A.gelu_tab, prm, gtab, swave, lane);
+    token_stage<NH>(A.params[branch], STEPS ? (const float4*)A.steps[branch] : A.gelu_tab, STEPS ? A.step_pieces[branch] : GELU_TAB / 64, prm, gtab, swave, lane);
     asm volatile("" ::: "memory");                                     // the weight stream is requested behind them
     v4i ring[RING];
 #pragma unroll
@@ -1434,17 +1434,19 @@ __global__ __launch_bounds__(NH * 64) __attribute__((amdgpu_waves_per_eu(tok_wav
     __syncthreads();
     v16i acc2[RB];
     start(acc2, PR::F2_NC + nb * 32);
-    const QDev qg = in_vgpr(A.q_fc2in[branch]);
+    QDev qg;
+    GeluIndex gi;
+    if constexpr (STEPS) gi = in_vgpr(A.step_index[branch]); else qg = in_vgpr(A.q_fc2in[branch]);
     // GELU + quantize of four of the FC1 sums of hidden block ch*NH + wave, and the block's codes -> LDS buffer ch & 1
     int wd[RB][4];
     auto gelu_part = [&](int ch, int rb, int qd, const v16i* acc) {
         const int n0 = (ch * NH + wave) * 32 + qd * 8 + g * 4;
         const float4 m = *(const float4*)(prm + PR::F1_M + n0), bs = *(const float4*)(prm + PR::F1_B + n0);
-        GeluPart p;
+        std::conditional_t<STEPS, GeluStepPart, GeluPart> p;
         p.xs[0] = fmaf((float)acc[rb][qd * 4 + 0], m.x, bs.x); p.xs[1] = fmaf((float)acc[rb][qd * 4 + 1], m.y, bs.y);
         p.xs[2] = fmaf((float)acc[rb][qd * 4 + 2], m.z, bs.z); p.xs[3] = fmaf((float)acc[rb][qd * 4 + 3], m.w, bs.w);
-        gelu_begin(p, gtab);
-        wd[rb][qd] = gelu_end(p, qg);
+        if constexpr (STEPS) { gelu_begin(p, (const GeluStep*)gtab, gi); wd[rb][qd] = gelu_end(p); }
+        else { gelu_begin(p, gtab); wd[rb][qd] = gelu_end(p, qg); }
         if (TAPS && valid[rb]) {
             if (A.tap_acc_fc1) *(int4*)(A.tap_acc_fc1 + canon[rb] * F + n0) = make_int4(acc[rb][qd * 4], acc[rb][qd * 4 + 1], acc[rb][qd * 4 + 2], acc[rb][qd * 4 + 3]);
             if (A.tap_g) *(int*)(A.tap_g + canon[rb] * F + n0) = wd[rb][qd];
@@ -1754,16 +1756,21 @@ void launch_token(const Geom& G, const TokArgs& A, int chains, hipStream_t st)
 {
     if (G.rows_total == 0) return;
 #define TOK_CASE(NH, RB)                                                                                                             \
-    if (A.taps) hipLaunchKernelGGL((token_kernel<NH, RB, true>), dim3(G.rows_total / (32 * RB)), dim3(NH * 64), 0, st, G, A); \
-    else hipLaunchKernelGGL((token_kernel<NH, RB, false>), dim3(G.rows_total / (32 * RB)), dim3(NH * 64), 0, st, G, A)
+    {                                                                                                                                \
+        const dim3 grid(G.rows_total / (32 * RB)), block(NH * 64);                                                                   \
+        if (A.by_steps && A.taps) hipLaunchKernelGGL((token_kernel<NH, RB, true, true>), grid, block, 0, st, G, A);                  \
+        else if (A.by_steps) hipLaunchKernelGGL((token_kernel<NH, RB, false, true>), grid, block, 0, st, G, A);                      \
+        else if (A.taps) hipLaunchKernelGGL((token_kernel<NH, RB, true, false>), grid, block, 0, st, G, A);                          \
+        else hipLaunchKernelGGL((token_kernel<NH, RB, false, false>), grid, block, 0, st, G, A);                                     \
+    }
     switch (G.C / 32) {
-        case 3: TOK_CASE(3, 1); break;
-        case 4: TOK_CASE(4, 1); break;
-        case 6: TOK_CASE(6, 1); break;
-        case 8: TOK_CASE(8, 1); break;
+        case 3: TOK_CASE(3, 1) break;
+        case 4: TOK_CASE(4, 1) break;
+        case 6: TOK_CASE(6, 1) break;
+        case 8: TOK_CASE(8, 1) break;
         default:
-            if (token_of_64_rows(G.rows_total, chains)) { TOK_CASE(12, 2); }
-            else { TOK_CASE(12, 1); }
+            if (token_of_64_rows(G.rows_total, chains)) TOK_CASE(12, 2)
+            else TOK_CASE(12, 1)
     }
 #undef TOK_CASE
 }

@@ -90,6 +90,20 @@ def test_other_mlp_ratios(C, heads, mlp_ratio):
     gh.assert_parity(res)
 
 
+@pytest.mark.parametrize("C,heads,H,W,shift,bits,hidden", [
+    (96, 3, 26, 33, 3, (8, 4), (-0.07, 0.35)),               # the high branch has no table of steps: both take the cubic
+    (128, 4, 20, 27, 0, (8, 4), (-0.07, 0.35)), (192, 6, 14, 21, 3, (8, 4), (-0.07, 0.35)), (256, 8, 20, 28, 0, (8, 4), (-0.07, 0.35)),
+    (384, 12, 20, 27, 3, (8, 4), (-0.07, 0.35)), (384, 12, 50, 84, 0, (8, 4), (-0.07, 0.35)),        # 32 and 64 rows
+    (96, 3, 26, 33, 3, (8, 8), (-0.17, 0.45)), (384, 12, 50, 84, 0, (8, 7), (-0.17, 0.45)),          # tables of 1500 entries
+    (96, 3, 26, 33, 3, (2, 2), (-0.17, 4.0)), (256, 8, 20, 28, 0, (8, 3), (-0.17, 40.0)), (192, 6, 20, 28, 0, (5, 6), (-0.6, 0.6))])
+def test_gelu_codes_by_steps_and_by_the_cubic(C, heads, H, W, shift, bits, hidden):
+    spec, inp, x, k = _case(2, H, W, C, heads, shift, 0.5, 57, blobs=True, bits=bits, ranges={"a_fc2_in": hidden})
+    print("gelu", C, H, W, bits, hidden, flush=True)
+    res = gh.compare_block(inp, x, k)
+    print(res, flush=True)
+    gh.assert_parity(res)
+
+
 def test_long_k_on_a_few_hundred_row_tiles():
     """FC2 with K = 3072 on 111 64-row tiles: the GEMM keeps the whole K of a 32-row tile in LDS (222 tiles)."""
     spec, inp, x, k = _case(2, 50, 60, 384, 12, 3, 0.5, 54, blobs=True, mlp_ratio=8)
