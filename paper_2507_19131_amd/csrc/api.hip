@@ -119,6 +119,7 @@ struct Linear {           // one shadow layer prepared for the device
     float* bias[2] = {nullptr, nullptr};
     int* negcorr[2] = {nullptr, nullptr};
     std::vector<int> colsum;   // sum_k W[n,k], kept on the host
+    long long widest = 0;      // the largest sum_k |W[n,k]|
     std::vector<float> hm[2], hb[2];   // host copies of m, bias and negcorr, while the block is being built
     std::vector<int> hnc[2];
 };
@@ -146,7 +147,8 @@ struct mixaq_block {
     const GeluStep* gelu_steps[2] = {nullptr, nullptr};   // GELU and its quantizer as a table of steps, for the token kernel
     GeluIndex gelu_step_index[2] = {};
     int gelu_step_pieces[2] = {0, 0};
-    bool gelu_by_steps = false;                  // both branches have one
+    bool short_tokens = false;                   // both branches have one, and the sums of proj and fc1 are bounded (see sum_value)
+    bool magic_windows = false;                  // the sums of q, k and v are
     size_t ws_bytes = 0;
     size_t ws_fused_bytes = 0; // what the two fused kernels alone need
     int side_device = -1;      // a batch of small maps: the device whose side streams the stage call may use (see SideStreams)
@@ -194,11 +196,14 @@ int prepare_linear(mixaq_block* blk, Linear& L, const int8_t* w_dev, const float
     std::vector<int> colsum(N, 0);
     for (int n = 0; n < N; ++n) {
         if (!(s[n] > 0.0f) || !std::isfinite(s[n])) return fail(MIXAQ_E_SHAPE, "weight scale %d is not positive", n);
+        long long width = 0;
         for (int k = 0; k < K; ++k) {
             int v = w[(size_t)n * K + k];
             if (v < wmin || v > wmax) return fail(MIXAQ_E_BITS, "weight code %d outside the %d-bit range", v, weight_bits);
             colsum[n] += v;
+            width += std::abs(v);
         }
+        L.widest = std::max(L.widest, width);
     }
     const int NB = N / 32, KS = K / 32;
     int8_t* packed = blk->mem.take<int8_t>((size_t)N * K, &L.Wp);
@@ -228,6 +233,13 @@ int prepare_linear(mixaq_block* blk, Linear& L, const int8_t* w_dev, const float
         L.hm[br] = m; L.hb[br] = b; L.hnc[br] = nc;
     }
     return MIXAQ_OK;
+}
+
+// whether the sums sum_k (code - zp) W[n,k] of a layer stay within what sum_value can hold
+bool sums_bounded(const Linear& L, const QDev& q)
+{
+    const long long qmin = (long long)(q.lo - RND_MAGIC), qmax = (long long)(q.hi - RND_MAGIC);
+    return L.widest * std::max(qmax - q.zp, q.zp - qmin) < SUM_MAGIC_BOUND;
 }
 
 // original padded coordinates of token t of window (wr,wc) in the rolled frame
@@ -381,6 +393,7 @@ int forward_impl(const mixaq_block* blk, const float* x, const int32_t* perm, co
         wa.tap_a1 = tp.a_qkv_in; wa.tap_acc = tp.acc_qkv; wa.tap_qkv = tp.qkv; wa.tap_s = tp.acc_s; wa.tap_p = tp.p;
         wa.tap_o = tp.acc_o; wa.tap_code = tp.a_proj_in;
         wa.taps = taps != nullptr;
+        wa.magic_sums = blk->magic_windows;
         mark(9);
         for (int r = 0; r < reps; ++r) launch_window(G, wa, part.chains, st);       // also forwards pruned windows
     } else {
@@ -415,7 +428,7 @@ int forward_impl(const mixaq_block* blk, const float* x, const int32_t* perm, co
         ta.tap_acc_proj = tp.acc_proj; ta.tap_h = tp.h; ta.tap_a2 = tp.a_fc1_in; ta.tap_acc_fc1 = tp.acc_fc1;
         ta.tap_g = tp.a_fc2_in; ta.tap_acc_fc2 = tp.acc_fc2; ta.tap_y = tp.y_win;
         ta.gelu_tab = blk->gelu_tab;
-        ta.by_steps = blk->gelu_by_steps;
+        ta.short_forms = blk->short_tokens;
         for (int br = 0; br < 2; ++br) {
             ta.steps[br] = blk->gelu_steps[br]; ta.step_index[br] = blk->gelu_step_index[br]; ta.step_pieces[br] = blk->gelu_step_pieces[br];
         }
@@ -651,9 +664,12 @@ static int block_create(const mixaq_block_desc* desc, const mixaq_shared_params*
             b->gelu_step_index[br] = steps[br].index;
             b->gelu_step_pieces[br] = (int)steps[br].table.size() / 128;
         }
-        b->gelu_by_steps = ordinary;
+        for (int br = 0; br < 2; ++br) ordinary = ordinary && sums_bounded(b->proj, b->q_ao[br]) && sums_bounded(b->fc1, b->q_fc1in[br]);
+        b->short_tokens = ordinary;
     }
     b->fused_window = true;   // every width has a form of the window kernel
+    b->magic_windows = sums_bounded(b->qkv, b->q_in[0]) && sums_bounded(b->qkv, b->q_in[1]);
+    const int magic = b->magic_windows ? SUM_MAGIC_BITS : 0;
     for (int br = 0; br < 2; ++br) {      // parameter blocks of the window kernel: LN1, then the QKV constants head by head
         std::vector<float> blkp = hln[br][0];
         blkp.insert(blkp.end(), hln[br][1].begin(), hln[br][1].end());
@@ -665,7 +681,7 @@ static int block_create(const mixaq_block_desc* desc, const mixaq_shared_params*
                 blkp.insert(blkp.end(), L.hb[br].begin() + n0, L.hb[br].begin() + n0 + HD);
                 const size_t at = blkp.size();
                 blkp.resize(at + HD);
-                memcpy(&blkp[at], &L.hnc[br][n0], HD * 4);
+                for (int n = 0; n < HD; ++n) { const int start = L.hnc[br][n0 + n] + magic; memcpy(&blkp[at + n], &start, 4); }
             }
         b->mem.add(blkp, &b->win_params[br]);
     }
@@ -688,6 +704,11 @@ static int block_create(const mixaq_block_desc* desc, const mixaq_shared_params*
                 const int shift_by = branch[1].a_proj_in.zero_point + pack_offset(b->ao_pack);
                 int* nc = (int*)blkp.data() + 2 * C;
                 for (int n = 0; n < C; ++n) nc[n] = -shift_by * b->proj.colsum[n];
+            }
+            if (b->short_tokens) {
+                int *np = (int*)blkp.data() + 2 * C, *n1 = (int*)blkp.data() + 8 * C + 2 * F;
+                for (int n = 0; n < C; ++n) np[n] += SUM_MAGIC_BITS;
+                for (int n = 0; n < F; ++n) n1[n] += SUM_MAGIC_BITS;
             }
             b->mem.add(blkp, &b->tok_params[br]);
         }

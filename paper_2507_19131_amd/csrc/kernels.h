@@ -83,6 +83,7 @@ struct WinArgs {                     // fused window kernel (gather + LN1 + QKV 
     int8_t* tap_a1; int32_t* tap_acc; int8_t* tap_qkv; int32_t* tap_s; int8_t* tap_p; int32_t* tap_o; int8_t* tap_code;
     int floor[2];                    // which exponents need their floor: bit 0 windows without, bit 1 windows with masked pairs
     bool taps;                       // any tap pointer set
+    bool magic_sums;                 // negcorr words are SUM_MAGIC_BITS more (see sum_value)
 };
 
 struct TokArgs {                     // fused token kernel (proj + LN2 + FFN + scatter)
@@ -106,7 +107,7 @@ struct TokArgs {                     // fused token kernel (proj + LN2 + FFN + s
     const GeluStep* steps[2];        // per branch the table of steps (see gelu_steps.h) and its 1 KB pieces ...
     GeluIndex step_index[2];
     int step_pieces[2];
-    bool by_steps;                   // ... used where both branches have one
+    bool short_forms;                // ... used where both branches have one and the negcorr words of proj and fc1 are SUM_MAGIC_BITS more
     bool taps;
 };
 

@@ -629,7 +629,7 @@ __device__ __forceinline__ v16i attention_core(const v4i& qf, const v4i (&kf)[2]
 
 // dequantization and requantization of the P.V sums; writes the codes of head `head` for the window's tokens to
 // out[row0 + token][C] (and the taps)
-template <bool TAPS>
+template <bool TAPS, bool MAGIC>
 __device__ __forceinline__ void attention_store(const v16i& o, const QDev& qo, float m_o,
                                                 int j, int g, int ib, int head, int C, int8_t* out, int row0, int32_t* tap_o,
                                                 int8_t* tap_code, size_t canon_row0, int pack = 0)
@@ -642,10 +642,10 @@ __device__ __forceinline__ void attention_store(const v16i& o, const QDev& qo, f
             for (int qd = 0; qd < 4; ++qd) {
                 const int d0 = qd * 8 + g * 4;
                 const int a0 = o[qd * 4 + 0], a1 = o[qd * 4 + 1], a2 = o[qd * 4 + 2], a3 = o[qd * 4 + 3];
-                code[qd] = pack4(quant_code((float)a0 * m_o, qo), quant_code((float)a1 * m_o, qo),
-                                 quant_code((float)a2 * m_o, qo), quant_code((float)a3 * m_o, qo));
+                code[qd] = pack4(quant_code(sum_value<MAGIC>(a0) * m_o, qo), quant_code(sum_value<MAGIC>(a1) * m_o, qo),
+                                 quant_code(sum_value<MAGIC>(a2) * m_o, qo), quant_code(sum_value<MAGIC>(a3) * m_o, qo));
                 size_t ci = (canon_row0 + qi) * C + head * HD + d0;
-                if (TAPS && tap_o) *(int4*)(tap_o + ci) = make_int4(a0, a1, a2, a3);
+                if (TAPS && tap_o) *(int4*)(tap_o + ci) = make_int4(sum_int<MAGIC>(a0), sum_int<MAGIC>(a1), sum_int<MAGIC>(a2), sum_int<MAGIC>(a3));
                 if (TAPS && tap_code) *(int*)(tap_code + ci) = code[qd];
             }
             // The halves exchange, so that a lane stores its token's sixteen (packed: eight) consecutive bytes at once: four-byte
@@ -751,7 +751,7 @@ __global__ __launch_bounds__(256) void attn_kernel(Geom G, AttnArgs A)
 #pragma unroll 1
     for (int ib = 0; ib < 2; ++ib) {
         const v16i o = attention_core<true, true>(ib ? qf[1] : qf[0], kf, vt, core, BiasRow(), j, g, ib);
-        attention_store<true>(o, in_vgpr(A.qo[branch]), in_vgpr(A.m_o[branch]), j, g, ib, head, G.C, A.out, row0, A.tap_o, A.tap_code, (size_t)canon_slot * TOK, PACK_FRAG);
+        attention_store<true, false>(o, in_vgpr(A.qo[branch]), in_vgpr(A.m_o[branch]), j, g, ib, head, G.C, A.out, row0, A.tap_o, A.tap_code, (size_t)canon_slot * TOK, PACK_FRAG);
     }
 }
 
@@ -872,7 +872,7 @@ template <int C, int NH, bool CODES> struct WinPrm {
 
 // CODES: the LN1 codes come ready from ln_window_kernel (wide blocks, whose heads are spread over many workgroups: each of
 // them would repeat the whole gather and LayerNorm); the workgroup is given a slot and there are no pruned ones.
-template <int NH, bool TAPS, bool SCORED, int HG = 1, int QS = 1, bool CODES = false>
+template <int NH, bool TAPS, bool SCORED, int HG = 1, int QS = 1, bool CODES = false, bool MAGIC = true>
 __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(win_waves_per_eu(NH, HG, QS, CODES)))) void window_kernel(Geom G, WinArgs A)
 {
     if (CODES || HG == 2 || (QS == 2 && NH <= 4)) touch_arguments<sizeof(Geom) + sizeof(WinArgs)>();   // few workgroups
@@ -905,6 +905,7 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
     constexpr bool STREAM = KS >= 12 || (HG == 1 ? !(NH == 3 && QS == 1) : KS < 8);
     constexpr int RING = !STREAM ? (KS < 6 ? KS : 6) : KS < 6 ? KS : KS == 6 ? (QS == 1 ? 6 : 3) : KS == 12 ? 6 : KS < 32 ? 8 : 16;
     static_assert(!STREAM || KS % RING == 0, "each chain starts at ring slot 0");
+    constexpr int O_START = MAGIC ? SUM_MAGIC_BITS : 0;                  // of the P.V sums: 49 * 255 * 128 at most
     v4i ring[RING];
     auto weights_of = [&](int which) { return A.Wqkv + (size_t)(which * NHT + head) * KS * 64 + lane; };
     // SCORED: the workgroup is given a window and finds its own place in the selection (its rank
@@ -1082,10 +1083,10 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
                 const int n0 = nb * 32 + qd * 8 + g * 4;
                 const float4 m = *(const float4*)(pm + qd * 8 + g * 4), bs = *(const float4*)(pm + HD + qd * 8 + g * 4);
                 const int a0 = acc[qd * 4 + 0], a1 = acc[qd * 4 + 1], a2 = acc[qd * 4 + 2], a3 = acc[qd * 4 + 3];
-                wd[qd] = pack4(quant_code(fmaf((float)a0, m.x, bs.x), qq), quant_code(fmaf((float)a1, m.y, bs.y), qq),
-                               quant_code(fmaf((float)a2, m.z, bs.z), qq), quant_code(fmaf((float)a3, m.w, bs.w), qq));
+                wd[qd] = pack4(quant_code(fmaf(sum_value<MAGIC>(a0), m.x, bs.x), qq), quant_code(fmaf(sum_value<MAGIC>(a1), m.y, bs.y), qq),
+                               quant_code(fmaf(sum_value<MAGIC>(a2), m.z, bs.z), qq), quant_code(fmaf(sum_value<MAGIC>(a3), m.w, bs.w), qq));
                 if (TAPS && tok < TOK) {
-                    if (A.tap_acc) *(int4*)(A.tap_acc + (canon_row0 + tok) * (3 * C) + n0) = make_int4(a0, a1, a2, a3);
+                    if (A.tap_acc) *(int4*)(A.tap_acc + (canon_row0 + tok) * (3 * C) + n0) = make_int4(sum_int<MAGIC>(a0), sum_int<MAGIC>(a1), sum_int<MAGIC>(a2), sum_int<MAGIC>(a3));
                     if (A.tap_qkv) *(int*)(A.tap_qkv + (canon_row0 + tok) * (3 * C) + n0) = wd[qd];
                 }
             }
@@ -1122,8 +1123,8 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
                     c[e] = 0;
                     if (QS == 2 || tb * 32 + qd * 8 + e < TOK) {      // known at compile time when the wave runs both blocks
                         if (tok < TOK) {
-                            c[e] = quant_code(fmaf((float)acc[qd * 4 + e], m, bs), qv);
-                            if (TAPS && A.tap_acc) A.tap_acc[(canon_row0 + tok) * (3 * C) + n] = acc[qd * 4 + e];
+                            c[e] = quant_code(fmaf(sum_value<MAGIC>(acc[qd * 4 + e]), m, bs), qv);
+                            if (TAPS && A.tap_acc) A.tap_acc[(canon_row0 + tok) * (3 * C) + n] = sum_int<MAGIC>(acc[qd * 4 + e]);
                             if (TAPS && A.tap_qkv) A.tap_qkv[(canon_row0 + tok) * (3 * C) + n] = (int8_t)c[e];
                         }
                     }
@@ -1144,13 +1145,13 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
             bias.request(A.bias2 + (size_t)(mask_type(G, w) * NHT + head) * BIAS_QUADS * 64 + g * 64 + j, g, tb0);
         cs = half_sum(cs);
         if (QS == 1) {
-            if (g == 0) csum[wave][j] = -(A.qp[branch].zp * cs);
+            if (g == 0) csum[wave][j] = O_START - A.qp[branch].zp * cs;
         } else {                                                          // the pair exchanges its halves of K, V and the sums
             kvx[((hw * 2 + 0) * 2 + tb0) * 64 + lane] = qk[1][0];
             kvx[((hw * 2 + 1) * 2 + tb0) * 64 + lane] = vt[0];
             if (g == 0) csp[(hw * 2 + tb0) * HD + j] = cs;
             __syncthreads();
-            if (g == 0) csum[wave][j] = -(A.qp[branch].zp * (csp[(hw * 2) * HD + j] + csp[(hw * 2 + 1) * HD + j]));
+            if (g == 0) csum[wave][j] = O_START - A.qp[branch].zp * (csp[(hw * 2) * HD + j] + csp[(hw * 2 + 1) * HD + j]);
         }
     }
     v4i kf[2];
@@ -1181,7 +1182,7 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
     for (int ib = tb0; ib < tb0 + NTB; ++ib) {
         asm volatile("" ::: "memory");
         const v16i o = attention_core<TAPS, !BIAS_EARLY>(NTB == 2 && ib ? qk[0][NTB - 1] : qk[0][0], kf, vt, core, bias, j, g, ib);
-        attention_store<TAPS>(o, in_vgpr(A.qo[branch]), in_vgpr(A.m_o[branch]), j, g, ib, head, C, out, orow0, A.tap_o, A.tap_code, canon_row0, pack);
+        attention_store<TAPS, MAGIC>(o, in_vgpr(A.qo[branch]), in_vgpr(A.m_o[branch]), j, g, ib, head, C, out, orow0, A.tap_o, A.tap_code, canon_row0, pack);
     }
 }
 
@@ -1228,7 +1229,7 @@ __device__ __forceinline__ void token_stage(const float* params, const float4* g
     for (int p = NH - 1 - wave; p < gelu_pieces; p += NH) to_lds(gelu + p * 64 + lane, gtab + p * 64);   // the last waves have the fewest of the others
 }
 
-template <int NH, int RB, bool TAPS, bool STEPS>
+template <int NH, int RB, bool TAPS, bool SHORT>
 __global__ __launch_bounds__(NH * 64) __attribute__((amdgpu_waves_per_eu(tok_waves_per_eu(NH)))) void token_kernel(Geom G, TokArgs A)
 {
     if (NH == 12 || G.rows_total <= 256 * 32) touch_arguments<sizeof(Geom) + sizeof(TokArgs)>();   // about one workgroup a CU
@@ -1242,7 +1243,7 @@ __global__ __launch_bounds__(NH * 64) __attribute__((amdgpu_waves_per_eu(tok_wav
     __shared__ v4i gs[2][NH * RB * 64];                                // [buffer][hidden block of the chunk][row block][lane]
     __shared__ double part[2][NH][32 * RB];
     __shared__ __attribute__((aligned(16))) float prm[PR::WORDS];
-    __shared__ float4 gtab[STEPS ? GELU_STEP_PIECES * 64 : GELU_TAB];
+    __shared__ float4 gtab[SHORT ? GELU_STEP_PIECES * 64 : GELU_TAB];
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, j = lane & 31, g = lane >> 5;
     const int row_base = blockIdx.x * (32 * RB);
     const int branch = row_base >= G.base_lo ? 1 : 0;                 // a tile never straddles the regions: scalar
@@ -1282,7 +1283,7 @@ __global__ __launch_bounds__(NH * 64) __attribute__((amdgpu_waves_per_eu(tok_wav
         pix[rb] = A.row_pix[row];
         canon[rb] = (TAPS && valid[rb]) ? (size_t)A.row_canon[row] : 0;
     }
-    token_stage<NH>(A.params[branch], STEPS ? (const float4*)A.steps[branch] : A.gelu_tab, STEPS ? A.step_pieces[branch] : GELU_TAB / 64, prm, gtab, swave, lane);
+    token_stage<NH>(A.params[branch], SHORT ? (const float4*)A.steps[branch] : A.gelu_tab, SHORT ? A.step_pieces[branch] : GELU_TAB / 64, prm, gtab, swave, lane);
     asm volatile("" ::: "memory");                                     // the weight stream is requested behind them
     v4i ring[RING];
 #pragma unroll
@@ -1364,14 +1365,14 @@ __global__ __launch_bounds__(NH * 64) __attribute__((amdgpu_waves_per_eu(tok_wav
             for (int qd = 0; qd < 4; ++qd) {
                 const int n0 = nb * 32 + qd * 8 + g * 4;
                 const float4 m = *(const float4*)(prm + PR::P_M + n0), bs = *(const float4*)(prm + PR::P_B + n0);
-                h[rb][qd * 4 + 0] = fmaf((float)acc[rb][qd * 4 + 0], m.x, bs.x) + sc[rb][qd].x;
-                h[rb][qd * 4 + 1] = fmaf((float)acc[rb][qd * 4 + 1], m.y, bs.y) + sc[rb][qd].y;
-                h[rb][qd * 4 + 2] = fmaf((float)acc[rb][qd * 4 + 2], m.z, bs.z) + sc[rb][qd].z;
-                h[rb][qd * 4 + 3] = fmaf((float)acc[rb][qd * 4 + 3], m.w, bs.w) + sc[rb][qd].w;
+                h[rb][qd * 4 + 0] = fmaf(sum_value<SHORT>(acc[rb][qd * 4 + 0]), m.x, bs.x) + sc[rb][qd].x;
+                h[rb][qd * 4 + 1] = fmaf(sum_value<SHORT>(acc[rb][qd * 4 + 1]), m.y, bs.y) + sc[rb][qd].y;
+                h[rb][qd * 4 + 2] = fmaf(sum_value<SHORT>(acc[rb][qd * 4 + 2]), m.z, bs.z) + sc[rb][qd].z;
+                h[rb][qd * 4 + 3] = fmaf(sum_value<SHORT>(acc[rb][qd * 4 + 3]), m.w, bs.w) + sc[rb][qd].w;
                 if (PARK_H && pix[rb] >= 0)
                     *(float4*)(A.y + (size_t)pix[rb] * C + n0) = make_float4(h[rb][qd * 4], h[rb][qd * 4 + 1], h[rb][qd * 4 + 2], h[rb][qd * 4 + 3]);
                 if (TAPS && valid[rb]) {
-                    if (A.tap_acc_proj) *(int4*)(A.tap_acc_proj + canon[rb] * C + n0) = make_int4(acc[rb][qd * 4], acc[rb][qd * 4 + 1], acc[rb][qd * 4 + 2], acc[rb][qd * 4 + 3]);
+                    if (A.tap_acc_proj) *(int4*)(A.tap_acc_proj + canon[rb] * C + n0) = make_int4(sum_int<SHORT>(acc[rb][qd * 4]), sum_int<SHORT>(acc[rb][qd * 4 + 1]), sum_int<SHORT>(acc[rb][qd * 4 + 2]), sum_int<SHORT>(acc[rb][qd * 4 + 3]));
                     if (A.tap_h) *(float4*)(A.tap_h + canon[rb] * C + n0) = make_float4(h[rb][qd * 4], h[rb][qd * 4 + 1], h[rb][qd * 4 + 2], h[rb][qd * 4 + 3]);
                 }
             }
@@ -1436,19 +1437,19 @@ __global__ __launch_bounds__(NH * 64) __attribute__((amdgpu_waves_per_eu(tok_wav
     start(acc2, PR::F2_NC + nb * 32);
     QDev qg;
     GeluIndex gi;
-    if constexpr (STEPS) gi = in_vgpr(A.step_index[branch]); else qg = in_vgpr(A.q_fc2in[branch]);
+    if constexpr (SHORT) gi = in_vgpr(A.step_index[branch]); else qg = in_vgpr(A.q_fc2in[branch]);
     // GELU + quantize of four of the FC1 sums of hidden block ch*NH + wave, and the block's codes -> LDS buffer ch & 1
     int wd[RB][4];
     auto gelu_part = [&](int ch, int rb, int qd, const v16i* acc) {
         const int n0 = (ch * NH + wave) * 32 + qd * 8 + g * 4;
         const float4 m = *(const float4*)(prm + PR::F1_M + n0), bs = *(const float4*)(prm + PR::F1_B + n0);
-        std::conditional_t<STEPS, GeluStepPart, GeluPart> p;
-        p.xs[0] = fmaf((float)acc[rb][qd * 4 + 0], m.x, bs.x); p.xs[1] = fmaf((float)acc[rb][qd * 4 + 1], m.y, bs.y);
-        p.xs[2] = fmaf((float)acc[rb][qd * 4 + 2], m.z, bs.z); p.xs[3] = fmaf((float)acc[rb][qd * 4 + 3], m.w, bs.w);
-        if constexpr (STEPS) { gelu_begin(p, (const GeluStep*)gtab, gi); wd[rb][qd] = gelu_end(p); }
+        std::conditional_t<SHORT, GeluStepPart, GeluPart> p;
+        p.xs[0] = fmaf(sum_value<SHORT>(acc[rb][qd * 4 + 0]), m.x, bs.x); p.xs[1] = fmaf(sum_value<SHORT>(acc[rb][qd * 4 + 1]), m.y, bs.y);
+        p.xs[2] = fmaf(sum_value<SHORT>(acc[rb][qd * 4 + 2]), m.z, bs.z); p.xs[3] = fmaf(sum_value<SHORT>(acc[rb][qd * 4 + 3]), m.w, bs.w);
+        if constexpr (SHORT) { gelu_begin(p, (const GeluStep*)gtab, gi); wd[rb][qd] = gelu_end(p); }
         else { gelu_begin(p, gtab); wd[rb][qd] = gelu_end(p, qg); }
         if (TAPS && valid[rb]) {
-            if (A.tap_acc_fc1) *(int4*)(A.tap_acc_fc1 + canon[rb] * F + n0) = make_int4(acc[rb][qd * 4], acc[rb][qd * 4 + 1], acc[rb][qd * 4 + 2], acc[rb][qd * 4 + 3]);
+            if (A.tap_acc_fc1) *(int4*)(A.tap_acc_fc1 + canon[rb] * F + n0) = make_int4(sum_int<SHORT>(acc[rb][qd * 4]), sum_int<SHORT>(acc[rb][qd * 4 + 1]), sum_int<SHORT>(acc[rb][qd * 4 + 2]), sum_int<SHORT>(acc[rb][qd * 4 + 3]));
             if (A.tap_g) *(int*)(A.tap_g + canon[rb] * F + n0) = wd[rb][qd];
         }
     };
@@ -1685,6 +1686,11 @@ void launch_window(const Geom& G, const WinArgs& A, int chains, hipStream_t st)
     const int n_wg = G.B * G.nW;
     if (n_wg == 0) return;
     // wide blocks: LN1 by a kernel of its own, then the heads of a window over several workgroups
+#define WIN_LAUNCH(ARGS, SCORED, NH, HG, QS, CODES)                                                                       \
+    if (ARGS.taps && ARGS.magic_sums) hipLaunchKernelGGL((window_kernel<NH, true, SCORED, HG, QS, CODES, true>), grid, block, 0, st, G, ARGS);    \
+    else if (ARGS.taps) hipLaunchKernelGGL((window_kernel<NH, true, SCORED, HG, QS, CODES, false>), grid, block, 0, st, G, ARGS);                 \
+    else if (ARGS.magic_sums) hipLaunchKernelGGL((window_kernel<NH, false, SCORED, HG, QS, CODES, true>), grid, block, 0, st, G, ARGS);           \
+    else hipLaunchKernelGGL((window_kernel<NH, false, SCORED, HG, QS, CODES, false>), grid, block, 0, st, G, ARGS);
 #define WIDE_CASE(C_, LPT, NV, NH, HG, QS)                                                                                \
     if (G.C == C_) {                                                                                                      \
         const dim3 lgrid(n_wg, 64 * LPT / 256);                                                                           \
@@ -1694,8 +1700,7 @@ void launch_window(const Geom& G, const WinArgs& A, int chains, hipStream_t st)
         WinArgs W = A;                                                                                                    \
         if (A.scores) W.perm = A.perm_out;                                                                                \
         const dim3 grid(G.n_slots * HG), block(NH * QS * 64);                                                             \
-        if (A.taps) hipLaunchKernelGGL((window_kernel<NH, true, false, HG, QS, true>), grid, block, 0, st, G, W);         \
-        else hipLaunchKernelGGL((window_kernel<NH, false, false, HG, QS, true>), grid, block, 0, st, G, W);               \
+        WIN_LAUNCH(W, false, NH, HG, QS, true)                                                                            \
         return;                                                                                                           \
     }
     WIDE_CASE(512, 32, 4, 4, 4, 2)
@@ -1706,10 +1711,10 @@ void launch_window(const Geom& G, const WinArgs& A, int chains, hipStream_t st)
     {                                                                                                                     \
         const dim3 grid(HG > 1 ? (n_wg + 7) / 8 * 8 * HG : n_wg), block(NH * QS * 64);                                     \
         if (A.scores) {   /* no entry point takes scores and taps together */                                            \
-            hipLaunchKernelGGL((window_kernel<NH, false, true, HG, QS>), grid, block, 0, st, G, A);                       \
+            if (A.magic_sums) hipLaunchKernelGGL((window_kernel<NH, false, true, HG, QS, false, true>), grid, block, 0, st, G, A);       \
+            else hipLaunchKernelGGL((window_kernel<NH, false, true, HG, QS, false, false>), grid, block, 0, st, G, A);                   \
         } else {                                                                                                          \
-            if (A.taps) hipLaunchKernelGGL((window_kernel<NH, true, false, HG, QS>), grid, block, 0, st, G, A);           \
-            else hipLaunchKernelGGL((window_kernel<NH, false, false, HG, QS>), grid, block, 0, st, G, A);                 \
+            WIN_LAUNCH(A, false, NH, HG, QS, false)                                                                       \
         }                                                                                                                 \
     }                                                                                                                     \
     break
@@ -1733,6 +1738,7 @@ void launch_window(const Geom& G, const WinArgs& A, int chains, hipStream_t st)
         default: break;
     }
 #undef WIN_CASE
+#undef WIN_LAUNCH
 }
 
 // Rows per workgroup of the token kernel at C = 384.  A CU holds one workgroup of twelve waves, which takes 15 units of time for 64
@@ -1758,8 +1764,8 @@ void launch_token(const Geom& G, const TokArgs& A, int chains, hipStream_t st)
 #define TOK_CASE(NH, RB)                                                                                                             \
     {                                                                                                                                \
         const dim3 grid(G.rows_total / (32 * RB)), block(NH * 64);                                                                   \
-        if (A.by_steps && A.taps) hipLaunchKernelGGL((token_kernel<NH, RB, true, true>), grid, block, 0, st, G, A);                  \
-        else if (A.by_steps) hipLaunchKernelGGL((token_kernel<NH, RB, false, true>), grid, block, 0, st, G, A);                      \
+        if (A.short_forms && A.taps) hipLaunchKernelGGL((token_kernel<NH, RB, true, true>), grid, block, 0, st, G, A);                  \
+        else if (A.short_forms) hipLaunchKernelGGL((token_kernel<NH, RB, false, true>), grid, block, 0, st, G, A);                      \
         else if (A.taps) hipLaunchKernelGGL((token_kernel<NH, RB, true, false>), grid, block, 0, st, G, A);                          \
         else hipLaunchKernelGGL((token_kernel<NH, RB, false, false>), grid, block, 0, st, G, A);                                     \
     }

@@ -68,6 +68,16 @@ __device__ __forceinline__ int pack4(int c0, int c1, int c2, int c3)
     return lo | hi;
 }
 
+// An integer sum as a number.  MAGIC: the sum was started at SUM_MAGIC_BITS more, so that as a binary32 it IS 1.5 * 2^23 plus the sum
+// while that stays inside +-2^22, and an exact subtraction (a fast instruction) replaces the conversion (a slow one).  Blocks whose
+// weights and quantizers do not bound their sums so convert.  (Sums of q, k, v, P.V, the projection and FC1: 100 x 168 x 192 79.9 -> 78.9 us,
+// 4 x 128 x 128 x 256 320.1 -> 316.7, 200 x 336 x 96 101.0 -> 100.2.  FC2's sums, sixteen of a tile's 112 and the widest ones, and those
+// of Q K^T, whose accumulators start at an inline zero, are converted.)
+constexpr int SUM_MAGIC_BITS = 0x4b400000;                        // of RND_MAGIC
+constexpr int SUM_MAGIC_BOUND = 1 << 22;
+template <bool MAGIC> __device__ __forceinline__ float sum_value(int a) { return MAGIC ? __int_as_float(a) - RND_MAGIC : (float)a; }
+template <bool MAGIC> __device__ __forceinline__ int sum_int(int a) { return MAGIC ? a - SUM_MAGIC_BITS : a; }
+
 // gfx950 runs binary32 multiply, add and fused multiply-add, 32-bit and / or / xor, right shifts, integer addition and moves at
 // twice the rate of its other vector instructions (2.1 to 2.8 clocks a wave instead of 4.0 to 4.3, four waves per SIMD) as long
 // as no operand is a scalar register; with one they take 4.0 to 4.3 as well, a literal constant costs nothing.  So what such an

@@ -104,6 +104,25 @@ def test_gelu_codes_by_steps_and_by_the_cubic(C, heads, H, W, shift, bits, hidde
     gh.assert_parity(res)
 
 
+@pytest.mark.parametrize("C,heads,H,W,code,layers", [
+    (128, 4, 20, 27, 127, "all"),                             # the widest sums of any block of 128 channels: 2^22 less 49 000
+    (256, 8, 20, 28, 64, "all"), (256, 8, 20, 28, 65, "all"), # 16 000 under the bound, and above it
+    (192, 6, 20, 27, 127, ("w_qkv",)), (192, 6, 20, 27, 127, ("w_proj",)), (192, 6, 20, 27, 127, ("w_fc1",)),
+    (384, 12, 50, 84, 127, "all"), (512, 16, 21, 28, 127, "all")])
+def test_sums_at_and_beyond_what_a_binary32_holds(C, heads, H, W, code, layers):
+    """Weights of one magnitude: sums that the kernels take as binary32 without a conversion reach the bound of that
+    form, and blocks beyond it convert.  A map of wide values saturates the LayerNorm codes, so that sums come near their bound."""
+    spec, inp, x, k = _case(2, H, W, C, heads, 3, 0.5, 58, blobs=True, ranges={"a_qkv_in": (-0.02, 3.0), "a_fc1_in": (-0.02, 3.0), "a_proj_in": (-0.01, 0.4)})
+    rng = np.random.default_rng(59)
+    for n in ("w_qkv", "w_proj", "w_fc1") if layers == "all" else layers:
+        w = getattr(inp.shared, n)
+        setattr(inp.shared, n, np.where(rng.random(w.shape) < (0.5 if code < 127 else 0.9), code, -code).astype(w.dtype))
+    print("sums", C, code, layers, flush=True)
+    res = gh.compare_block(inp, x, k)
+    print(res, flush=True)
+    gh.assert_parity(res)
+
+
 def test_long_k_on_a_few_hundred_row_tiles():
     """FC2 with K = 3072 on 111 64-row tiles: the GEMM keeps the whole K of a 32-row tile in LDS (222 tiles)."""
     spec, inp, x, k = _case(2, 50, 60, 384, 12, 3, 0.5, 54, blobs=True, mlp_ratio=8)
