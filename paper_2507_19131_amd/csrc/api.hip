@@ -147,7 +147,8 @@ struct mixaq_block {
     const GeluStep* gelu_steps[2] = {nullptr, nullptr};   // GELU and its quantizer as a table of steps, for the token kernel
     GeluIndex gelu_step_index[2] = {};
     int gelu_step_pieces[2] = {0, 0};
-    bool short_tokens = false;                   // both branches have one, and the sums of proj and fc1 are bounded (see sum_value)
+    bool gelu_by_steps = false;                  // both branches have one
+    bool short_tokens = false;                   // and the sums of proj and fc1 are bounded (see sum_value)
     bool magic_windows = false;                  // the sums of q, k and v are
     size_t ws_bytes = 0;
     size_t ws_fused_bytes = 0; // what the two fused kernels alone need
@@ -453,7 +454,11 @@ int forward_impl(const mixaq_block* blk, const float* x, const int32_t* perm, co
     for (int r = 0; r < reps; ++r) launch_ln_quant(G, la, false, st);
     // FFN
     fill(ga, blk->fc1, ws.a2);
-    for (int br = 0; br < 2; ++br) ga.q[br][0] = blk->q_fc2in[br];
+    for (int br = 0; br < 2; ++br) {
+        ga.q[br][0] = blk->q_fc2in[br];
+        ga.steps[br] = blk->gelu_by_steps ? blk->gelu_steps[br] : nullptr;
+        ga.step_index[br] = blk->gelu_step_index[br]; ga.step_pieces[br] = blk->gelu_step_pieces[br];
+    }
     ga.out8 = ws.g; ga.tap_acc = tp.acc_fc1; ga.tap_code = tp.a_fc2_in;
     mark(7);
     for (int r = 0; r < reps; ++r) launch_gemm(G, ga, EPI_FC1, st);
@@ -651,7 +656,7 @@ static int block_create(const mixaq_block_desc* desc, const mixaq_shared_params*
         b->mem.add(tab, &b->gelu_tab);
         b->fused_token = fused_token_supported(C, desc->mlp_ratio);
         // the table of steps knows numbers only: with a constant that is none the sums take the cubic, like a quantizer that has no table
-        bool ordinary = b->fused_token;
+        bool ordinary = true;
         for (int br = 0; br < 2; ++br)
             for (int n = 0; n < F && ordinary; ++n) ordinary = std::isfinite(b->fc1.hm[br][n]) && std::isfinite(b->fc1.hb[br][n]);
         GeluSteps steps[2];
@@ -664,8 +669,9 @@ static int block_create(const mixaq_block_desc* desc, const mixaq_shared_params*
             b->gelu_step_index[br] = steps[br].index;
             b->gelu_step_pieces[br] = (int)steps[br].table.size() / 128;
         }
+        b->gelu_by_steps = ordinary;
         for (int br = 0; br < 2; ++br) ordinary = ordinary && sums_bounded(b->proj, b->q_ao[br]) && sums_bounded(b->fc1, b->q_fc1in[br]);
-        b->short_tokens = ordinary;
+        b->short_tokens = ordinary && b->fused_token;
     }
     b->fused_window = true;   // every width has a form of the window kernel
     b->magic_windows = sums_bounded(b->qkv, b->q_in[0]) && sums_bounded(b->qkv, b->q_in[1]);

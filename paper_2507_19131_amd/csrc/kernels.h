@@ -26,7 +26,6 @@ struct GemmArgs {
     const int8_t* A;                 // activations, operand fragments (FC1, FC2: k in the order of the result registers)
     const v4i* Wp;                   // packed weights [N/32][K/32][64 lanes] x 16 bytes
     int K, N, nb_per_block;
-    int kchunk;                      // bytes of K staged in LDS at a time (a divisor of K; set by the launcher)
     const float* m[2];               // s_in * s_w[n] per branch
     const float* bias[2];
     const int* negcorr[2];           // -zp_in * sum_k W[n,k]
@@ -42,6 +41,9 @@ struct GemmArgs {
     int8_t* tap_code;
     float* tap_f;
     const float4* gelu_tab;          // [GELU_K] cubic coefficients (FC1 epilogue)
+    const GeluStep* steps[2];        // or, not NULL, the table of steps of each branch
+    GeluIndex step_index[2];
+    int step_pieces[2];
 };
 
 struct AttnArgs {

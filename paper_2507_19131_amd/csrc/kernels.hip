@@ -338,7 +338,7 @@ __device__ __forceinline__ void epilogue_residual(const GemmArgs& A, int row, in
         if (EPI == EPI_FC2) res[qd] = *(const float4*)(A.resid + (size_t)row * A.N + n0);
     }
 }
-template <int EPI>
+template <int EPI, bool STEPS = false>
 __device__ __forceinline__ void epilogue(const GemmArgs& A, const Geom& G, int branch, int row, int nb, int g, const v16i& acc,
                                          const EpiConst& ec, const float4 (&res)[4], int pix, int canon, const float4* gelu_lds)
 {
@@ -354,7 +354,11 @@ __device__ __forceinline__ void epilogue(const GemmArgs& A, const Geom& G, int b
         if (A.tap_acc && canon >= 0) *(int4*)(A.tap_acc + (size_t)canon * N + n0) = make_int4(a0, a1, a2, a3);
         if (EPI == EPI_QKV || EPI == EPI_FC1) {
             const QDev& q = A.q[branch][EPI == EPI_QKV ? n0 / G.C : 0];
-            if (EPI == EPI_FC1) {
+            if (EPI == EPI_FC1 && STEPS) {
+                GeluStepPart p = {{f0, f1, f2, f3}, {}};
+                gelu_begin(p, (const GeluStep*)gelu_lds, in_vgpr(A.step_index[branch]));
+                codes[qd] = gelu_end(p);
+            } else if (EPI == EPI_FC1) {
                 GeluPart p = {{f0, f1, f2, f3}, {}, {}};
                 gelu_begin(p, gelu_lds);
                 codes[qd] = gelu_end(p, q);
@@ -372,30 +376,25 @@ __device__ __forceinline__ void epilogue(const GemmArgs& A, const Geom& G, int b
     if (EPI == EPI_FC1) *(v4i*)(A.out8 + (((size_t)(row >> 5) * (N / 32) + nb) * 64 + g * 32 + (row & 31)) * 16) = (v4i){codes[0], codes[1], codes[2], codes[3]};
 }
 
-// One workgroup per tile of RT rows and group of output blocks (all of them once the tiles alone fill the chip; on few
-// rows, e.g. 37 row tiles at C = 768 and batch 1, groups of four, one per wave).  The activations come as MFMA operand
-// fragments ([32 rows][K slab][64 lanes][16 bytes], written so by their producers), so a tile is a contiguous run of
+// One workgroup per tile of RT rows and group of output blocks (all of them once the tiles alone fill the chip).  For the short or odd K of
+// narrow blocks off the fused path: K = C up to 384, and hidden widths up to 1344 that are no multiple of 128.  The activations come
+// as MFMA operand fragments ([32 rows][K slab][64 lanes][16 bytes], written so by their producers), so a tile is a contiguous run of
 // memory: it goes to LDS by direct loads, no register in between, all of them in flight together.  Wave w computes the
 // output blocks first + w, first + w + 4, ... of the group; its weight fragments stream through a ring of D loads that
-// starts before anything else and runs on across the output blocks.  What bounds it on few rows is the latency of that
-// stream: one CU holds four to eight such waves, so D is 16 where K allows (fc2 with K = 3072 on 19 row tiles: 9.2 us).
-// K up to 2048 stays whole in LDS for a 64-row tile, K up to 4096 for a 32-row tile; longer K passes in chunks.
-constexpr int GEMM_TILE_MAX_K = 2048;      // 64 rows x K bytes of LDS
-// KMAX: bytes of K the instantiation's LDS holds per row (a longer K goes through in chunks of A.kchunk <= KMAX, whole ring
-// turns each)
+// starts before anything else and runs on across the output blocks.
+// KMAX: bytes of K the instantiation's LDS holds per row
 template <int EPI, int KMAX, int RT, int D>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RT * KMAX <= 65536 ? 2 : 1))) void gemm_tile_kernel(Geom G, GemmArgs A)
 {
     touch_arguments<sizeof(Geom) + sizeof(GemmArgs)>();
     constexpr int RB = RT / 32, PF = D % 4 == 0 ? 4 : 3;                // PF: LDS reads ahead
     static_assert(D % PF == 0, "the LDS slots come round with the ring");
-    __shared__ v4i afr[RT * KMAX / 16];                                // [row blocks][chunk slabs][64 lanes]
+    __shared__ v4i afr[RT * KMAX / 16];                                // [row blocks][slabs][64 lanes]
     __shared__ float4 gtab[EPI == EPI_FC1 ? GELU_K : 1];
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, j = lane & 31, g = lane >> 5;
     const int row0 = blockIdx.x * RT;
     const int branch = row0 >= G.base_lo ? 1 : 0;
     const int K = A.K, ks_n = K / 32, NB = A.N / 32;
-    const int cs = A.kchunk / 32, n_ch = K / A.kchunk;                 // slabs per chunk, chunks
     const int nb_lo = blockIdx.y * A.nb_per_block, nb_hi = min(nb_lo + A.nb_per_block, NB);
     const v4i* wp = A.Wp + (size_t)min(nb_lo + wave, NB - 1) * ks_n * 64 + lane;
     int pix[RB], canon[RB];
@@ -407,15 +406,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RT * KMAX <
     v4i rw[D];
 #pragma unroll
     for (int d = 0; d < D; ++d) rw[d] = wp[min(d, ks_n - 1) * 64];     // K may hold fewer than D slabs: the last one again (unused)
-    auto stage = [&](int ch) {                                         // one fragment of the tile per wave and turn
-        for (int f = wave; f < RB * cs; f += 4) {
-            const int rb = f >= cs ? 1 : 0;
-            const int8_t* src = A.A + ((size_t)(blockIdx.x * RB + rb) * ks_n + ch * cs + f - rb * cs) * 1024 + lane * 16;
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
-                                             (__attribute__((address_space(3))) void*)(afr + f * 64), 16, 0, 0);
-        }
-    };
-    if (n_ch == 1) stage(0);                                           // the whole K stays for every output block
+    for (int f = wave; f < RB * ks_n; f += 4) {                        // one fragment of the tile per wave and turn; the whole K stays for every output block
+        const int rb = f >= ks_n ? 1 : 0;
+        const int8_t* src = A.A + ((size_t)(blockIdx.x * RB + rb) * ks_n + f - rb * ks_n) * 1024 + lane * 16;
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
+                                         (__attribute__((address_space(3))) void*)(afr + f * 64), 16, 0, 0);
+    }
     // what a block's start and epilogue read, requested ahead of its products (for the first block: with the tile)
     int4 nc[4];
     EpiConst ec;
@@ -447,48 +443,199 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RT * KMAX <
             c0[qd * 4 + 0] = nc[qd].x; c0[qd * 4 + 1] = nc[qd].y; c0[qd * 4 + 2] = nc[qd].z; c0[qd * 4 + 3] = nc[qd].w;
         }
         c1 = c0;
-#pragma unroll 1
-        for (int ch = 0; ch < n_ch; ++ch) {
-            if (n_ch > 1) {
-                if (ch > 0 || nb0 > nb_lo) __syncthreads();             // the previous chunk is no longer read
-                stage(ch);
-                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-                __syncthreads();
-            }
-            // One turn of the ring: D fragments are used, the D after them requested.  Every step is product, request into
-            // the slot just used, next LDS read, in this order: left free, the scheduler moves the requests up, the slots of
-            // the next turn need registers of their own, and the copies at the turn's end wait for every load in flight.
-            v4i b[PF][RB];
+        // One turn of the ring: D fragments are used, the D after them requested.  Every step is product, request into
+        // the slot just used, next LDS read, in this order: left free, the scheduler moves the requests up, the slots of
+        // the next turn need registers of their own, and the copies at the turn's end wait for every load in flight.
+        v4i b[PF][RB];
 #pragma unroll
-            for (int d = 0; d < PF; ++d)
+        for (int d = 0; d < PF; ++d)
 #pragma unroll
-                for (int rb = 0; rb < RB; ++rb) b[d][rb] = afr[(rb * cs + min(d, cs - 1)) * 64 + lane];
-            auto turn = [&](int k0, auto full) {
-                const bool last = ch * cs + k0 + D >= ks_n;              // the ring turns to the next output block's weights
-                const v4i* wsrc = last ? wnext : wp + (size_t)(ch * cs + k0 + D) * 64;
-                const int left = last ? ks_n - 1 : ks_n - 1 - (ch * cs + k0 + D);
+            for (int rb = 0; rb < RB; ++rb) b[d][rb] = afr[(rb * ks_n + min(d, ks_n - 1)) * 64 + lane];
+        auto turn = [&](int k0, auto full) {
+            const bool last = k0 + D >= ks_n;                            // the ring turns to the next output block's weights
+            const v4i* wsrc = last ? wnext : wp + (size_t)(k0 + D) * 64;
+            const int left = last ? ks_n - 1 : ks_n - 1 - (k0 + D);
 #pragma unroll
-                for (int d = 0; d < D; ++d) {
-                    if (decltype(full)::value || k0 + d < cs) {          // wave-uniform: the last turn may be partial
-                        c0 = mfma32(rw[d], b[d % PF][0], c0);
-                        if (RB == 2) c1 = mfma32(rw[d], b[d % PF][RB - 1], c1);
-                    }
-                    rw[d] = wsrc[min(d, left) * 64];                     // past the end: the last slab again (unused)
-#pragma unroll
-                    for (int rb = 0; rb < RB; ++rb) b[d % PF][rb] = afr[(rb * cs + min(k0 + d + PF, cs - 1)) * 64 + lane];
-                    __builtin_amdgcn_sched_barrier(0);
+            for (int d = 0; d < D; ++d) {
+                if (decltype(full)::value || k0 + d < ks_n) {            // wave-uniform: the last turn may be partial
+                    c0 = mfma32(rw[d], b[d % PF][0], c0);
+                    if (RB == 2) c1 = mfma32(rw[d], b[d % PF][RB - 1], c1);
                 }
-            };
-            int k0 = 0;
+                rw[d] = wsrc[min(d, left) * 64];                         // past the end: the last slab again (unused)
+#pragma unroll
+                for (int rb = 0; rb < RB; ++rb) b[d % PF][rb] = afr[(rb * ks_n + min(k0 + d + PF, ks_n - 1)) * 64 + lane];
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+        int k0 = 0;
 #pragma unroll 1
-            for (; k0 + D <= cs; k0 += D) turn(k0, std::true_type());
-            if (k0 < cs) turn(k0, std::false_type());
-        }
+        for (; k0 + D <= ks_n; k0 += D) turn(k0, std::true_type());
+        if (k0 < ks_n) turn(k0, std::false_type());
         wp = wnext;
         if (active) {
             epilogue<EPI>(A, G, branch, row0 + j, nb, g, c0, ec, res[0], pix[0], canon[0], gelu_lds);
             if (RB == 2) epilogue<EPI>(A, G, branch, row0 + 32 + j, nb, g, c1, ec, res[RB - 1], pix[RB - 1], canon[RB - 1], gelu_lds);
         }
+    }
+}
+
+// The same products for many rows: both operands through LDS.  A workgroup computes RT = 32 WY RB rows times NT = 32 WX NBW
+// channels, wave (wy, wx) the RB x NBW blocks of its corner, so that an operand fragment read from LDS feeds RB or NBW products
+// instead of one or two, and a byte from the caches RT or NT of them: see launch_ring for the times.  K passes in stages of KSL slabs through a ring
+// of S LDS buffers filled by direct loads; a stage is requested S - 1 stages ahead, into the buffer that all waves have left at the barrier
+// in front of it, and that barrier is the only one of a stage.  The residual is requested ahead of the last S - 2 stages, a further tile's
+// first stages ahead of the epilogue.
+// What bounds it: on many rows the epilogue's memory (the projection on 19 712 rows at C = 768 33 us, of them 26 its maps at the rate of a
+// copy; without any epilogue 14) and the GELU; on few, the ramp of launch, first loads and the chain of stages.
+// The direct loads are asm: as a builtin every LDS read behind them waits for all of them.
+template <int N>
+__device__ __forceinline__ void request_to_lds(const void* uniform_src, int lane_bytes, unsigned lds_dst)
+{
+    static_assert(N == 1 || N == 2 || N == 4, "written out for these");
+    int m0;                                                              // given back: the compiler does not let an asm statement change it
+#define MIXAQ_REQUEST(MORE_) \
+    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %3\n\t" MORE_ "s_mov_b32 m0, %0" \
+                 : "=&s"(m0) : "s"(lds_dst), "v"(lane_bytes), "s"(uniform_src) : "memory")
+    if constexpr (N == 1) MIXAQ_REQUEST("");
+    if constexpr (N == 2) MIXAQ_REQUEST("global_load_lds_dwordx4 %2, %3 offset:1024\n\t");
+    if constexpr (N == 4) MIXAQ_REQUEST("global_load_lds_dwordx4 %2, %3 offset:1024\n\tglobal_load_lds_dwordx4 %2, %3 offset:2048\n\tglobal_load_lds_dwordx4 %2, %3 offset:3072\n\t");
+#undef MIXAQ_REQUEST
+}
+__device__ __forceinline__ void group_barrier() { asm volatile("" ::: "memory"); __builtin_amdgcn_s_barrier(); asm volatile("" ::: "memory"); }
+template <int N> __device__ __forceinline__ void wait_loads() { asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"(N) : "memory"); }
+template <int EPI, int WY, int WX, int RB, int NBW, int KSL, int S, int WPE, bool STEPS>
+__global__ __launch_bounds__(WY * WX * 64) __attribute__((amdgpu_waves_per_eu(WPE))) void gemm_ring_kernel(Geom G, GemmArgs A)
+{
+    constexpr int W = WY * WX, AF = WY * RB * KSL, FR = AF + WX * NBW * KSL, LPW = FR / W, NT = WX * NBW * 32, RT = WY * RB * 32;
+    constexpr int CST = (3 * NT + 255) / 256;                            // 1 KB pieces of a tile's constants
+    static_assert(FR % W == 0 && S >= 3 && S <= 4 && LPW * (S - 2) < 64 && CST <= W, "whole fragments a wave; the counter of loads in flight");
+    __shared__ v4i buf[S][FR * 64];
+    __shared__ __attribute__((aligned(16))) float cst[2][3 * NT];        // [m | bias | negcorr] of a tile's channels, this tile's and the next one's
+    __shared__ float4 gtab[EPI != EPI_FC1 ? 1 : STEPS ? GELU_STEP_PIECES * 64 : GELU_K];
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, j = lane & 31, g = lane >> 5;
+    const int wy = wave / WX, wx = wave % WX;
+    // consecutive tiles (all channels of a run of rows) on one XCD, whose L2 then reads the rows once
+    const int tiles_n = A.N / NT, tiles = (G.rows_total / RT) * tiles_n, per_xcd = (tiles + 7) / 8, step = gridDim.x / 8;
+    const int last = min((int)(blockIdx.x & 7) * per_xcd + per_xcd, tiles);
+    int tile = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+    if (tile >= last) return;                                            // the whole workgroup
+    const int ks_n = A.K / 32, stages = ks_n / KSL;
+    const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) char*)buf, lds1 = (unsigned)(size_t)(__attribute__((address_space(3))) char*)cst;
+    constexpr int US = LPW % KSL == 0 ? KSL : KSL % 2 == 0 && LPW % 2 == 0 ? 2 : 1, UNITS = LPW / US;   // this wave requests UNITS runs of US slabs
+    const int8_t* src[UNITS];
+    int at = 0;
+    auto request = [&](int slot) {
+#pragma unroll
+        for (int i = 0; i < UNITS; ++i) request_to_lds<US>(src[i], at, lds0 + (slot * FR + wave * LPW + i * US) * 1024);
+        at += KSL * 1024;
+    };
+    // requests a tile's constants and its first S - 1 stages
+    auto begin = [&](int t, int par) {
+        const int tm = t / tiles_n, tn = t - tm * tiles_n, br = tm * RT >= G.base_lo ? 1 : 0;
+        const int w = wave * 256 + lane * 4, n = tn * NT + w % NT;
+        if (w < 3 * NT) {
+            const float* from = w < NT ? A.m[br] + n : w < 2 * NT ? A.bias[br] + n : (const float*)A.negcorr[br] + n;
+            int m0;
+            asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, off\n\ts_mov_b32 m0, %0" : "=&s"(m0) : "s"(__builtin_amdgcn_readfirstlane(lds1 + par * (12 * NT) + wave * 1024)), "v"(from) : "memory");
+        }
+#pragma unroll
+        for (int i = 0; i < UNITS; ++i) {
+            const int f = wave * LPW + i * US, r = f / KSL, s = f % KSL;
+            src[i] = r < WY * RB ? A.A + ((size_t)(tm * (WY * RB) + r) * ks_n + s) * 1024 : (const int8_t*)A.Wp + ((size_t)(tn * (WX * NBW) + r - WY * RB) * ks_n + s) * 1024;
+        }
+        at = lane * 16;
+#pragma unroll
+        for (int k = 0; k < S - 1; ++k) request(k);
+    };
+    int branch = -1, par = 0;
+    begin(tile, 0);
+    for (; tile < last; tile += step, par ^= 1) {
+        const int tm = tile / tiles_n, tn = tile - tm * tiles_n, row0 = tm * RT;
+        int pix[RB], canon[RB];
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) {
+            const int row = row0 + (wy * RB + rb) * 32 + j;
+            canon[rb] = A.row_canon[row];
+            pix[rb] = (EPI == EPI_PROJ || EPI == EPI_FC2) ? A.row_pix[row] : 0;
+        }
+        if (branch != (row0 >= G.base_lo ? 1 : 0)) {                     // once or twice: the tiles of a workgroup go up
+            branch = row0 >= G.base_lo ? 1 : 0;
+            if (EPI == EPI_FC1) {
+                group_barrier();                            // the other branch's table is no longer read
+                const float4* from = STEPS ? (const float4*)A.steps[branch] : A.gelu_tab;
+                const int entries = STEPS ? A.step_pieces[branch] * 64 : GELU_K;
+                for (int e = tid; e < entries; e += W * 64) gtab[e] = from[e];
+            }
+        }
+        v16i acc[RB][NBW];
+        auto products = [&](int slot) {
+            const v4i *a = buf[slot] + wy * RB * KSL * 64 + lane, *w = buf[slot] + (AF + wx * NBW * KSL) * 64 + lane;
+#pragma unroll
+            for (int s = 0; s < KSL; ++s) {
+                v4i av[RB], wv[NBW];
+#pragma unroll
+                for (int rb = 0; rb < RB; ++rb) av[rb] = a[(rb * KSL + s) * 64];
+#pragma unroll
+                for (int nb = 0; nb < NBW; ++nb) wv[nb] = w[(nb * KSL + s) * 64];
+#pragma unroll
+                for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+                    for (int nb = 0; nb < NBW; ++nb) acc[rb][nb] = mfma32(wv[nb], av[rb], acc[rb][nb]);
+            }
+        };
+        int slot = 0;
+        auto turn = [&](bool more) {
+            if (more) request(slot == 0 ? S - 1 : slot - 1);
+            products(slot);
+            slot = slot == S - 1 ? 0 : slot + 1;
+        };
+        auto landed = [&] {                                              // a stage has landed, for every wave
+            wait_loads<(S - 2) * LPW>();
+            group_barrier();
+        };
+        landed();
+#pragma unroll
+        for (int nb = 0; nb < NBW; ++nb) {                               // accumulators start at -zp_in * colsum(W[n,:])
+#pragma unroll
+            for (int qd = 0; qd < 4; ++qd) {
+                const int4 t4 = *(const int4*)(&cst[par][2 * NT + (wx * NBW + nb) * 32 + qd * 8 + g * 4]);
+                acc[0][nb][qd * 4 + 0] = t4.x; acc[0][nb][qd * 4 + 1] = t4.y; acc[0][nb][qd * 4 + 2] = t4.z; acc[0][nb][qd * 4 + 3] = t4.w;
+            }
+#pragma unroll
+            for (int rb = 1; rb < RB; ++rb) acc[rb][nb] = acc[0][nb];
+        }
+        turn(true);
+#pragma unroll 1
+        for (int k = 1; k < stages - (S - 2); ++k) { landed(); turn(k + S - 1 < stages); }
+        wait_loads<0>();                                                 // the last S - 2 stages together
+        group_barrier();
+        float4 res[RB][NBW][4];
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb)                                  // travels under them
+#pragma unroll
+            for (int nb = 0; nb < NBW; ++nb) epilogue_residual<EPI>(A, row0 + (wy * RB + rb) * 32 + j, tn * (WX * NBW) + wx * NBW + nb, g, pix[rb], res[rb][nb]);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int k = 0; k < S - 2; ++k) turn(false);
+        if (tile + step < last) {
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");           // this wave's reads of the ring have returned
+            group_barrier();
+            begin(tile + step, par ^ 1);                                 // travels under the epilogue
+        }
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+            for (int nb = 0; nb < NBW; ++nb) {
+                const int row = row0 + (wy * RB + rb) * 32 + j, blk = tn * (WX * NBW) + wx * NBW + nb;
+                EpiConst ec;
+#pragma unroll
+                for (int qd = 0; qd < 4; ++qd) {
+                    const int n = (wx * NBW + nb) * 32 + qd * 8 + g * 4;
+                    ec.m[qd] = *(const float4*)(&cst[par][n]);
+                    ec.bias[qd] = *(const float4*)(&cst[par][NT + n]);
+                }
+                epilogue<EPI, STEPS>(A, G, branch, row, blk, g, acc[rb][nb], ec, res[rb][nb], pix[rb], canon[rb], gtab);
+            }
     }
 }
 
@@ -1513,6 +1660,7 @@ __global__ __launch_bounds__(NH * 64) __attribute__((amdgpu_waves_per_eu(tok_wav
 }
 
 // ------------------------------------------------------------------ launchers
+constexpr int CUS = 256;
 // From C = 384 a window is taken by 1024 threads (256 threads -> 1024, launch to launch on fresh maps).  Raw score: equal where
 // the launch itself is what takes the time (24 windows at C = 768 6.5 us both), better or equal beyond (384 windows at 768 12.5 ->
 // 11.7, 3200 at 384 41.8 -> 39.1, 900 at 1024 30.8 -> 30.5).  With the scoring LayerNorm the window's arithmetic is spread wider
@@ -1587,46 +1735,60 @@ bool launch_ln_quant(const Geom& G, const LnArgs& A, bool gather, hipStream_t st
     return true;
 }
 
+// Tiles of the ring kernel.  64 x 64: the fewest bytes in front of the first product and the most workgroups; 128 x 128: half the bytes per
+// product.  Over the number of 128 x 128 tiles T, us, 64 x 64 / 128 x 128 (the kernel for narrow blocks in brackets, which these layers took
+// before):
+//   FC1         C = 768    T = 48 4.6 / 9.2 (6.9)   240 8.8 / 10.0 (10.1)   336 11.6 / 10.9 (14.1)   672 19.9 / 15.9 (19.5)   3696 90 / 64 (95)
+//               C = 512    32 4.1 / 7.7 (6.1)   320 9.4 / 9.2 (12.0)   608 15.4 / 12.7 (16.6)   1680 35.5 / 25.7 (40.3)
+//               C = 1024   64 5.1 / 10.5 (7.5)   320 14.0 / 12.9 (15.5)   1280 45 / 32 (38.5)   3552 117 / 74 (96.8)
+//   FC2         C = 768    12 7.4 / 17.0 (8.6)   60 8.4 / 17.8 (9.9)   168 18.4 / 20.6 (27.8)   330 33.3 / 29.7 (44.1)   924 79 / 64 (109)
+//               C = 512    8 5.8 / 13.0 (10.3)   152 14.1 / 15.7 (23.5)   420 28.8 / 25.5 (38.3)      C = 1024   312 37.1 / 35.6 (53.0)   888 99 / 79 (127)
+//   projection  C = 768    12 4.1 / 8.2 (5.2)   168 9.1 / 10.5 (11.1)   330 15.3 / 16.2 (18.7)   924 34.3 / 33.4 (39.4)
+//               C = 512    152 7.8 / 8.9 (10.5)   420 15.6 / 15.6 (18.5)      C = 1024   312 15.4 / 18.2 (20.7)   888 37.8 / 37.4 (40.5)
+// FC1, whose epilogue is the longest, takes one slab a stage: 48 KB, three workgroups on a CU, one's GELU beside the others' products
+// (T = 3696 67 -> 64, 3552 82 -> 74); the others two slabs, two workgroups.  64 x 128, 128 x 256 and 256 x 128 tiles lie between the
+// two or behind them everywhere but at T = 330 (14.6 and 29.4).
+template <int EPI, int WY, int WX, int RB, int NBW, int KSL, int S, int WPE>
+static void launch_ring(const Geom& G, const GemmArgs& A, hipStream_t st)
+{
+    constexpr int LDS = (WY * RB + WX * NBW) * KSL * S * 1024 + WX * NBW * 768 + (EPI == EPI_FC1 ? GELU_STEP_PIECES * 1024 : 16);
+    constexpr int PER_CU = std::min(160 * 1024 / LDS, 4 * WPE / (WY * WX));                  // more tiles than the chip holds at once: a workgroup takes several
+    const int tiles = (G.rows_total / (WY * RB * 32)) * (A.N / (WX * NBW * 32));
+    const dim3 grid(std::min((tiles + 7) / 8 * 8, CUS * PER_CU)), block(WY * WX * 64);
+    if constexpr (EPI == EPI_FC1)
+        if (A.steps[0]) {
+            hipLaunchKernelGGL((gemm_ring_kernel<EPI, WY, WX, RB, NBW, KSL, S, WPE, true>), grid, block, 0, st, G, A);
+            return;
+        }
+    hipLaunchKernelGGL((gemm_ring_kernel<EPI, WY, WX, RB, NBW, KSL, S, WPE, false>), grid, block, 0, st, G, A);
+}
 template <int EPI>
 static void launch_gemm_e(const Geom& G, const GemmArgs& A0, hipStream_t st)
 {
     GemmArgs A = A0;
     if (G.rows_total == 0) return;
+    if (A.K >= 512 && A.K % 128 == 0 && A.N % 64 == 0) {              // whole stages and tiles, at least as many stages as the ring holds
+        const int tiles128 = A.N % 128 == 0 ? G.rows_total / 128 * (A.N / 128) : 0;
+        if (tiles128 <= (EPI == EPI_FC1 || A.K > 1024 ? CUS : 3 * CUS / 2)) launch_ring<EPI, 2, 2, 1, 1, 4, 4, 2>(G, A, st);
+        else if constexpr (EPI == EPI_FC1) launch_ring<EPI, 2, 2, 2, 2, 1, 4, 3>(G, A, st);
+        else launch_ring<EPI, 2, 2, 2, 2, 2, 4, 2>(G, A, st);
+        return;
+    }
+    // the activation tile through LDS, output blocks over the waves and, while the grid is small, in groups over workgroups; a narrow layer
+    // on few rows in 32-row tiles: twice the workgroups
     const int tiles = G.rows_total / ROW_TILE, NB = A.N / 32;
-    // the activation tile through LDS, output blocks over the waves and, while the grid is small, in groups over workgroups
-    // 32-row tiles: a long K stays whole in LDS (K = 3072 on 19 row tiles: 9.2 us; 64-row tiles in chunks of 1024: 14.7 us);
-    // a narrow layer on few rows gets twice the workgroups (the projection at C = 768 on 19 row tiles: 5.6 instead of 7.5 us;
-    // with 72 or 96 output blocks the wider layers have workgroups enough and lose: 10.6 and 9.5 instead of 9.1 and 9.3 us)
-    // (only FC2 has K = mlp_ratio C; the other layers have K = C <= 1024, and QKV never as few as 32 output blocks there)
-    constexpr bool LONG_K = EPI == EPI_FC2;
-    const bool half = (A.K > GEMM_TILE_MAX_K && A.K <= 4096) || (tiles <= 32 && NB <= 32 && A.K > 384 && A.K <= 1024);
-    A.kchunk = A.K;
-    if (A.K > 4096)                                                   // chunks of whole ring turns (256 bytes of K each): the largest such size up to
-        for (A.kchunk = 1024; A.kchunk > 256 && A.K % A.kchunk; A.kchunk -= 256) {}   // 1024 that divides K (K = 768 r or 1024 r here: 256 always does)
+    const bool half = EPI == EPI_FC2 && tiles <= 32 && A.K > 384 && A.K <= 1024;
     const int nt = half ? G.rows_total / 32 : tiles;
     const int groups = std::max(1, std::min((NB + 3) / 4, (512 + nt - 1) / nt));
     A.nb_per_block = ((NB + groups - 1) / groups + 3) / 4 * 4;
     const dim3 grid(nt, (NB + A.nb_per_block - 1) / A.nb_per_block);
 #define GEMM_CASE(KMAX, RT, D) hipLaunchKernelGGL((gemm_tile_kernel<EPI, KMAX, RT, D>), grid, dim3(256), 0, st, G, A)
-    // ring length: whole turns of 16 or 12 fragments where K has them
-    const bool d16 = A.K % 512 == 0;
-    if constexpr (LONG_K)
-        if (A.K > 1024) {
-            if (half && A.K <= 3072) { if (d16) GEMM_CASE(3072, 32, 16); else GEMM_CASE(3072, 32, 12); }
-            else if (half) GEMM_CASE(4096, 32, 16);
-            else if (A.K > GEMM_TILE_MAX_K) GEMM_CASE(1024, 64, 8);   // above 4096: chunks of 1024
-            else if (d16) GEMM_CASE(GEMM_TILE_MAX_K, 64, 16);
-            else GEMM_CASE(GEMM_TILE_MAX_K, 64, 12);
-            return;
-        }
-    if constexpr (EPI != EPI_QKV)
-        if (half) {
-            if (d16) GEMM_CASE(1024, 32, 16); else GEMM_CASE(1024, 32, 12);
-            return;
-        }
-    if (A.K <= 384) GEMM_CASE(384, 64, 6);
-    else if (d16) GEMM_CASE(1024, 64, 16);
-    else GEMM_CASE(1024, 64, 12);
+    if constexpr (EPI == EPI_FC2) {                                   // only FC2 has another K than C, up to 7 * 192 here
+        if (A.K > 1024) { GEMM_CASE(1344, 64, 12); return; }
+        if (half) { GEMM_CASE(1024, 32, 12); return; }
+        if (A.K > 384) { GEMM_CASE(1024, 64, 12); return; }
+    }
+    GEMM_CASE(384, 64, 6);
 #undef GEMM_CASE
 }
 
@@ -1665,7 +1827,6 @@ bool fused_token_supported(int C, int mlp_ratio) { return (C == 96 || C == 128 |
 // computed ones only measured slower (C = 384, 127 of 182 computed: 84 -> 90; 192, 240 of 300: 69 -> 71; 128, 461 of 576: 60 -> 62).
 // C = 256 always split: sixteen waves of one workgroup, or eight of twice the registers, leave a CU half empty, three workgroups of
 // eight fill it (6 windows: 62.8 -> 51.4 us the pair, 300: 106 -> 95, 1444: 351 -> 335, 2750: 680 -> 654).
-constexpr int CUS = 256;
 enum WindowForm { SINGLE, PAIR, SPLIT };
 // of a launch over `windows`, `computed` of them not pruned, beside another one like it where the stage runs as two chains
 static WindowForm window_form(int heads, int windows, int computed, int chains)

@@ -123,6 +123,24 @@ def test_sums_at_and_beyond_what_a_binary32_holds(C, heads, H, W, code, layers):
     gh.assert_parity(res)
 
 
+@pytest.mark.parametrize("B,H,W,C,keep,kw", [
+    (1, 42, 49, 512, 0.5, {}), (1, 43, 49, 512, 0.4, {}),               # FC1 on 256 and 320 tiles of 128 x 128
+    (2, 63, 105, 512, 0.4, {}),                                         # projection, FC1 and FC2 on 420, 1680 and 420: several tiles a workgroup, both branches
+    (1, 84, 98, 512, 1.0, {}),                                          # FC2 on 264, the projection on 64 x 64; one branch
+    (2, 84, 84, 768, 0.0, dict(bits=(4, 2), wbits=4)),                  # the other branch; rows of the pad
+    (1, 43, 49, 512, 0.4, dict(ranges={"a_fc2_in": (-0.07, 0.35)})),     # the cubic on both kinds of tiles
+    (1, 14, 14, 768, 0.25, dict(ranges={"a_fc2_in": (-0.07, 0.35)})),
+    (2, 14, 21, 768, 0.5, dict(mlp_ratio=1)), (1, 28, 35, 768, 0.5, dict(mlp_ratio=3)),
+    (2, 35, 35, 192, 0.5, dict(mlp_ratio=7)), (2, 70, 84, 192, 0.5, dict(mlp_ratio=5)), (1, 35, 35, 96, 0.5, dict(mlp_ratio=7))])
+def test_products_of_the_separate_kernels_at_their_lines(B, H, W, C, keep, kw):
+    """K in whole stages of the ring kernel on both sides of the line between its tiles, and the K that it does not take."""
+    spec, inp, x, k = _case(B, H, W, C, C // 32, 3, keep, 60, blobs=True, **kw)
+    print("products", B, H, W, C, keep, kw, flush=True)
+    res = gh.compare_block(inp, x, k, taps=("acc_proj", "h", "a_fc1_in", "a_fc2_in", "acc_fc2"))
+    print(res, flush=True)
+    gh.assert_parity(res)
+
+
 def test_long_k_on_a_few_hundred_row_tiles():
     """FC2 with K = 3072 on 111 64-row tiles: the GEMM keeps the whole K of a 32-row tile in LDS (222 tiles)."""
     spec, inp, x, k = _case(2, 50, 60, 384, 12, 3, 0.5, 54, blobs=True, mlp_ratio=8)
