@@ -977,8 +977,8 @@ __global__ __launch_bounds__(256) void ln_window_kernel(Geom G, WinArgs A)
 // ------------------------------------------------------------------ fused window kernel
 // One workgroup per window slot (HG = 1) or per half of a window's heads (HG = 2: few windows, or more heads
 // than a workgroup has waves; both halves repeat the gather + LN1 phase), one wave per head (QS = 1, NH waves)
-// or a pair of waves per head (QS = 2: each wave projects one 32-token block to q, k and v, the pair exchanges
-// k and v through LDS, and each runs the attention of its own query block: half the chain of dependent steps):
+// or a pair of waves per head (QS = 2: see win_roles; otherwise each wave projects one 32-token block to q, k and v; the pair exchanges
+// through LDS what the other needs, and each runs the attention of its own query block: half the chain of dependent steps):
 //   gather (shift folded into the index map) + LN1 + quantize, shared through LDS as MFMA
 //   fragments -> per head: q, k (transposed product, lane = token) and v (plain product, lane =
 //   dim) straight into operand registers -> attention core -> codes of the attention output.
@@ -1004,10 +1004,15 @@ struct WinCfg {
 // spill none, six registers with scores; when they spilled two and four, and none at four waves, the pair of blocks on 1392 windows
 // took 110.5 us at four waves and 108.0 at five.)
 constexpr bool win_pairs_share(int NH, int HG) { return (NH == 6 && HG == 1) || NH * HG == 8; }   // pairs of waves, several workgroups on a CU
+// Pairs that have the registers share the projections by roles: one wave takes q of all tokens, the other k, and v is split by
+// tokens.  Each weight fragment of q and k then passes the L1 once and feeds two independent products, and its constants are read once.
+// Against q, k and v each split by tokens, window kernel with LN1, us: 25 windows at C = 1024 20.0 -> 18.3, 24 at 768 15.7 -> 15.0, 4 at 512
+// 12.4 -> 11.5, 96 at 384 15.2 -> 14.5, 196 at 192 14.8 -> 14.4, 64 at 128 7.8 -> 7.5, 64 at 96 8.3 -> 8.25.
+constexpr bool win_roles(int NH, int HG, int QS, bool CODES) { return QS == 2 && (CODES || !win_pairs_share(NH, HG)); }
 constexpr int win_waves_per_eu(int NH, int HG, int QS, bool CODES)
 {
-    if (CODES) return NH * HG < 32 ? 4 : 2;
-    if (QS == 2) return win_pairs_share(NH, HG) ? 6 : 4;
+    if (CODES) return QS == 1 ? 4 : 2;
+    if (QS == 2) return win_pairs_share(NH, HG) ? 6 : NH == 6 ? 3 : 4;
     return NH * HG > 8 ? 3 : NH == 3 ? 5 : 4;
 }
 
@@ -1024,7 +1029,9 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
 {
     if (CODES || HG == 2 || (QS == 2 && NH <= 4)) touch_arguments<sizeof(Geom) + sizeof(WinArgs)>();   // few workgroups
     constexpr int NHT = NH * HG;                                         // heads of the block; this workgroup runs NH of them
-    constexpr int NW = NH * QS, NTB = 2 / QS;                            // waves; token blocks a wave projects and attends for
+    constexpr int NW = NH * QS, NTB = 2 / QS;                            // waves; token blocks a wave projects to v and attends for
+    constexpr bool ROLES = win_roles(NH, HG, QS, CODES);                 // one wave of a pair projects all tokens to q, the other to k
+    constexpr int NTQ = ROLES ? 2 : NTB, PAIR_SLOTS = ROLES ? 5 : 4;
     constexpr int C = NHT * 32, KS = NHT, LPT = WinCfg<NH, HG, QS>::LPT, NV = CODES ? 1 : WinCfg<NH, HG, QS>::NV, NT = NW * 64;
     constexpr int GPW = WinCfg<NH, HG, QS>::GPW;
     using PR = WinPrm<C, NH, CODES>;
@@ -1037,7 +1044,7 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
     __shared__ v4i a1s[2 * KS * 64];                                     // LN1 codes as fragments [token block][k slab][lane]
     __shared__ __attribute__((aligned(16))) float prm[PR::WORDS];        // this branch's LN1 affine and QKV epilogue constants
     __shared__ __attribute__((aligned(16))) int csum[NW][HD];
-    __shared__ v4i kvx[QS == 2 ? NH * 4 * 64 : 1];                       // k and v operands of a wave pair [head][k|v][token block][lane]
+    __shared__ v4i kvx[QS == 2 ? NH * PAIR_SLOTS * 64 : 1];              // k and v operands of a wave pair [head][k|v][token block][lane], with ROLES q of the second block
     __shared__ int csp[QS == 2 ? NH * 2 * HD : 1];                       // V column sums of each token block [head][block][dim]
     __shared__ int red[NW];
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, j = lane & 31, g = lane >> 5;
@@ -1050,16 +1057,17 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
     // them share a CU: six blocks on 81 windows at C = 192 147 -> 133 us, three sets in turn of two blocks on 64 windows at
     // C = 128 36.7 -> 33.8.)
     constexpr bool STREAM = KS >= 12 || (HG == 1 ? !(NH == 3 && QS == 1) : KS < 8);
-    constexpr int RING = !STREAM ? (KS < 6 ? KS : 6) : KS < 6 ? KS : KS == 6 ? (QS == 1 ? 6 : 3) : KS == 12 ? 6 : KS < 32 ? 8 : 16;
+    constexpr int RING = !STREAM ? (KS < 6 ? KS : 6) : KS < 6 ? KS : KS == 6 ? (QS == 1 ? 6 : 3) : KS == 12 ? 6 : KS < 32 || QS == 1 ? 8 : 16;
     static_assert(!STREAM || KS % RING == 0, "each chain starts at ring slot 0");
     constexpr int O_START = MAGIC ? SUM_MAGIC_BITS : 0;                  // of the P.V sums: 49 * 255 * 128 at most
     v4i ring[RING];
+    const int role = ROLES ? __builtin_amdgcn_readfirstlane(tb0) : 0;
     auto weights_of = [&](int which) { return A.Wqkv + (size_t)(which * NHT + head) * KS * 64 + lane; };
     // SCORED: the workgroup is given a window and finds its own place in the selection (its rank
     // under the total order of the scores); otherwise it is given a slot and looks the window up.
     int branch = 0, row0 = 0, canon_slot = 0, w, bimg = 0;
     if (STREAM && CODES) {
-        const v4i* wp = weights_of(0);
+        const v4i* wp = weights_of(role);
 #pragma unroll
         for (int d = 0; d < RING; ++d) ring[d] = wp[d * 64];
     }
@@ -1144,7 +1152,7 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
                                                  (__attribute__((address_space(3))) void*)(a1s + f * 64), 16, 0, 0);
         }
         if (STREAM && !CODES) {
-            const v4i* wp = weights_of(0);
+            const v4i* wp = weights_of(role);
 #pragma unroll
             for (int d = 0; d < RING; ++d) ring[d] = wp[d * 64];
         }
@@ -1178,12 +1186,12 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
     // The B operand (LN1 fragments) is read from LDS inside the chain and the weight fragments come through a short ring of
     // loads: held in registers instead (24 to 64 of them) they cost the kernel its fourth and fifth wave per SIMD.
     // acc[tb] += (weights as A operand ? W * act^T : act * W^T) over the whole K; next: where the stream goes on
-    auto chain = [&](const v4i* wp, const v4i* next, v16i* acc, bool weights_first) {
-        constexpr int PF = STREAM ? 3 : 1;                                // LDS reads ahead (the scheduler's own business otherwise)
+    auto chain = [&](auto BLOCKS, const v4i* wp, const v4i* next, v16i* acc, bool weights_first) {   // both token blocks, or the wave's own
+        constexpr int PF = STREAM ? 3 : 1, NTB = decltype(BLOCKS)::value; // LDS reads ahead (the scheduler's own business otherwise)
         v4i xv[PF][NTB];
         auto operand = [&](int ks) {
 #pragma unroll
-            for (int tb = 0; tb < NTB; ++tb) xv[ks % PF][tb] = a1s[((tb0 + tb) * KS + ks) * 64 + lane];
+            for (int tb = 0; tb < NTB; ++tb) xv[ks % PF][tb] = a1s[(((ROLES && NTB == 2 ? 0 : tb0) + tb) * KS + ks) * 64 + lane];
         };
         if (STREAM) {
 #pragma unroll
@@ -1207,9 +1215,9 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
         }
     };
     const size_t canon_row0 = (size_t)canon_slot * TOK;
-    v4i qk[2][NTB] = {};                                                 // [q|k][token block]
+    v4i qk[2][NTQ] = {};                                                 // [q|k][token block]; with ROLES the wave's own in [1]
 #pragma unroll 1
-    for (int which = 0; which < 2; ++which) {
+    for (int which = role; which < (ROLES ? role + 1 : 2); ++which) {
         asm volatile("" ::: "memory");                                    // the B operand is read from LDS each time: keep the reads in the loop
         const int nb = which * NHT + head;
         const float* pm = prm + PR::HEADS + hw * PR::PER_HEAD + which * (3 * HD);
@@ -1224,7 +1232,7 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
         };
         auto finish = [&](int tb, const v16i& acc) {                      // dequantize, requantize, keep as operand
             int wd[4];
-            const int tok = (tb0 + tb) * 32 + j;
+            const int tok = ((NTQ == 2 ? 0 : tb0) + tb) * 32 + j;
 #pragma unroll
             for (int qd = 0; qd < 4; ++qd) {
                 const int n0 = nb * 32 + qd * 8 + g * 4;
@@ -1237,18 +1245,18 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
                     if (A.tap_qkv) *(int*)(A.tap_qkv + (canon_row0 + tok) * (3 * C) + n0) = wd[qd];
                 }
             }
-            qk[0][tb] = qk[1][tb];                                        // the second trip moves q to its place (a select costs twice a move)
+            if (!ROLES) qk[0][tb] = qk[1][tb];                            // the second trip moves q to its place (a select costs twice a move)
             qk[1][tb] = (v4i){wd[0], wd[1], wd[2], wd[3]};
         };
-        v16i acc[NTB];
+        v16i acc[NTQ];
         start(acc[0]);
-        if (NTB == 2) acc[NTB - 1] = acc[0];
-        chain(wp, weights_of(which + 1), acc, true);
+        if (NTQ == 2) acc[NTQ - 1] = acc[0];
+        chain(std::integral_constant<int, NTQ>(), wp, weights_of(ROLES ? 2 : which + 1), acc, true);
 #pragma unroll
-        for (int tb = 0; tb < NTB; ++tb) finish(tb, acc[tb]);
+        for (int tb = 0; tb < NTQ; ++tb) finish(tb, acc[tb]);
     }
     // a pair of waves requests its bias ahead of the exchange, where the registers are free
-    constexpr bool BIAS_EARLY = QS == 2 && (CODES || !win_pairs_share(NH, HG));
+    constexpr bool BIAS_EARLY = ROLES;
     BiasRow bias;
     v4i vt[2];
     {
@@ -1285,7 +1293,7 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[0][r] = nc;
         if (NTB == 2) acc[NTB - 1] = acc[0];
-        chain(wp, nullptr, acc, false);
+        chain(std::integral_constant<int, NTB>(), wp, nullptr, acc, false);
 #pragma unroll
         for (int tb = 0; tb < NTB; ++tb) finish(tb, acc[tb]);
         if (BIAS_EARLY)                                                   // under the exchange
@@ -1294,8 +1302,10 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
         if (QS == 1) {
             if (g == 0) csum[wave][j] = O_START - A.qp[branch].zp * cs;
         } else {                                                          // the pair exchanges its halves of K, V and the sums
-            kvx[((hw * 2 + 0) * 2 + tb0) * 64 + lane] = qk[1][0];
-            kvx[((hw * 2 + 1) * 2 + tb0) * 64 + lane] = vt[0];
+            if (!ROLES) kvx[((hw * 2 + 0) * 2 + tb0) * 64 + lane] = qk[1][0];
+            else if (role) { kvx[(hw * PAIR_SLOTS + 0) * 64 + lane] = qk[1][0]; kvx[(hw * PAIR_SLOTS + 1) * 64 + lane] = qk[1][NTQ - 1]; }
+            else kvx[(hw * PAIR_SLOTS + PAIR_SLOTS - 1) * 64 + lane] = qk[1][NTQ - 1];
+            kvx[(hw * PAIR_SLOTS + 2 + tb0) * 64 + lane] = vt[0];
             if (g == 0) csp[(hw * 2 + tb0) * HD + j] = cs;
             __syncthreads();
             if (g == 0) csum[wave][j] = O_START - A.qp[branch].zp * (csp[(hw * 2) * HD + j] + csp[(hw * 2 + 1) * HD + j]);
@@ -1304,9 +1314,10 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
     v4i kf[2];
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb) {
-        kf[kb] = QS == 1 ? qk[1][kb % NTB] : kvx[((hw * 2 + 0) * 2 + kb) * 64 + lane];
-        if (QS == 2) vt[kb] = kvx[((hw * 2 + 1) * 2 + kb) * 64 + lane];
+        kf[kb] = QS == 1 ? qk[1][kb % NTQ] : kvx[(hw * PAIR_SLOTS + kb) * 64 + lane];
+        if (QS == 2) vt[kb] = kvx[(hw * PAIR_SLOTS + 2 + kb) * 64 + lane];
     }
+    if (ROLES) qk[0][0] = role ? kvx[(hw * PAIR_SLOTS + PAIR_SLOTS - 1) * 64 + lane] : qk[1][0];
     __builtin_amdgcn_s_waitcnt(0xc07f);                                   // lgkmcnt(0): the wave's own csum entries are in LDS
     __builtin_amdgcn_wave_barrier();
     const int mtype = mask_type(G, w);
@@ -1846,14 +1857,18 @@ void launch_window(const Geom& G, const WinArgs& A, int chains, hipStream_t st)
     // the computed slots come first and the pruned windows of the list after them
     const int n_wg = G.B * G.nW;
     if (n_wg == 0) return;
-    // wide blocks: LN1 by a kernel of its own, then the heads of a window over several workgroups
+    // Wide blocks: LN1 by a kernel of its own, then the heads of a window over several workgroups: pairs of waves while each workgroup has a
+    // CU to itself, one wave per head beyond, whose weights pass the L1 once instead of one and a half times.  LN1 and window kernel, us, pairs /
+    // four heads a workgroup of one wave each / eight:   C = 512   49 windows 14.0 / 15.7 / 17.6   64 14.9 / 16.9 / 18.3 | 100 22.7 / 22.2 / 20.7
+    //   270 49 / 43 / 45   784 115 / 95 / 97      C = 768   35 16.6 / 18.4 / 26.8   42 18.0 / 19.7 / 29.0 | 48 24.9 / 23.8 / 30.3   140 48 / 45 / 50
+    //   400 112 / 102 / 98      C = 1024   25 18.4 / 29.7 / 24.4   30 19.6 / 32.0 / 25.2 | 42 29.8 / 38.1 / 27.9   100 55 / 57 / 48   288 120 / 110 / 111
 #define WIN_LAUNCH(ARGS, SCORED, NH, HG, QS, CODES)                                                                       \
     if (ARGS.taps && ARGS.magic_sums) hipLaunchKernelGGL((window_kernel<NH, true, SCORED, HG, QS, CODES, true>), grid, block, 0, st, G, ARGS);    \
     else if (ARGS.taps) hipLaunchKernelGGL((window_kernel<NH, true, SCORED, HG, QS, CODES, false>), grid, block, 0, st, G, ARGS);                 \
     else if (ARGS.magic_sums) hipLaunchKernelGGL((window_kernel<NH, false, SCORED, HG, QS, CODES, true>), grid, block, 0, st, G, ARGS);           \
     else hipLaunchKernelGGL((window_kernel<NH, false, SCORED, HG, QS, CODES, false>), grid, block, 0, st, G, ARGS);
-#define WIDE_CASE(C_, LPT, NV, NH, HG, QS)                                                                                \
-    if (G.C == C_) {                                                                                                      \
+#define WIDE_CASE(C_, LPT, NV, NH, HG, QS, WHEN)                                                                          \
+    if (G.C == C_ && (WHEN)) {                                                                                                      \
         const dim3 lgrid(n_wg, 64 * LPT / 256);                                                                           \
         if (A.scores) hipLaunchKernelGGL((ln_window_kernel<LPT, NV, true>), lgrid, dim3(256), 0, st, G, A);               \
         else hipLaunchKernelGGL((ln_window_kernel<LPT, NV, false>), lgrid, dim3(256), 0, st, G, A);                       \
@@ -1864,9 +1879,13 @@ void launch_window(const Geom& G, const WinArgs& A, int chains, hipStream_t st)
         WIN_LAUNCH(W, false, NH, HG, QS, true)                                                                            \
         return;                                                                                                           \
     }
-    WIDE_CASE(512, 32, 4, 4, 4, 2)
-    WIDE_CASE(768, 64, 3, 4, 6, 2)
-    WIDE_CASE(1024, 64, 4, 4, 8, 2)
+    const bool fits = G.n_slots * (G.heads / 4) <= CUS;
+    WIDE_CASE(512, 32, 4, 4, 4, 2, fits)
+    WIDE_CASE(768, 64, 3, 4, 6, 2, fits)
+    WIDE_CASE(1024, 64, 4, 4, 8, 2, fits)
+    WIDE_CASE(512, 32, 4, 4, 4, 1, true)
+    WIDE_CASE(768, 64, 3, 4, 6, 1, true)
+    WIDE_CASE(1024, 64, 4, 8, 4, 1, true)
 #undef WIDE_CASE
 #define WIN_CASE(NH, HG, QS)                                                                                              \
     {                                                                                                                     \

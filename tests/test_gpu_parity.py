@@ -556,6 +556,10 @@ WIDE_CASES = [
     (2, 20, 27, 1024, 0, 0.3, (4, 2), dict(wbits=4, per_branch_bias=True)),
     (2, 20, 27, 768, 3, 1.0, (6, 3), dict(mode=1)),
     (1, 20, 27, 512, 3, 0.5, (8, 4), dict(mlp_ratio=3)),
+    # both sides of 256 workgroups of four heads each
+    (1, 56, 56, 512, 3, 0.5, (8, 4), {}), (1, 35, 91, 512, 0, 0.4, (8, 4), {}),        # 64 and 65 windows
+    (1, 42, 49, 768, 3, 0.5, (8, 4), {}), (1, 7, 301, 768, 0, 0.4, (8, 4), {}),        # 42 and 43
+    (1, 28, 56, 1024, 3, 0.5, (8, 4), {}), (1, 21, 77, 1024, 3, 0.4, (8, 4), {}),      # 32 and 33
 ]
 
 
