@@ -639,6 +639,49 @@ __global__ __launch_bounds__(WY * WX * 64) __attribute__((amdgpu_waves_per_eu(WP
     }
 }
 
+// The same products for few rows: one workgroup of eight waves per 32 x 32 outputs, each wave every eighth slab of K, SPW of them, its operands
+// straight from memory to registers and all requested at once; the eight partial sums meet in LDS, and wave w < 4 finishes quad w of
+// every lane's sixteen.  No stage, no barrier but one, and four times the workgroups of the ring kernel's smaller tiles, whose 430 clocks
+// a stage of 128 bytes of K are their way through the L1 and LDS: see launch_few for the times.
+template <int EPI, int SPW>
+__global__ __launch_bounds__(512) void gemm_few_kernel(Geom G, GemmArgs A)
+{
+    touch_arguments<sizeof(Geom) + sizeof(GemmArgs)>();
+    __shared__ v4i part[8][4][64];                                       // [wave][quad][lane]
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, j = lane & 31, g = lane >> 5;
+    // the row tiles of a block of channels on one XCD, whose L2 then reads its weights once
+    const int row_tiles = G.rows_total / 32, at = blockIdx.x >> 3, nb = (blockIdx.x & 7) + 8 * (at / row_tiles), tm = at % row_tiles;
+    const int row = tm * 32 + j, branch = tm * 32 >= G.base_lo ? 1 : 0, N = A.N;
+    constexpr int KS = 8 * SPW;
+    const v4i *ap = (const v4i*)A.A + ((size_t)tm * KS + wave) * 64 + lane, *wp = A.Wp + ((size_t)nb * KS + wave) * 64 + lane;
+    v4i av[SPW], wv[SPW];
+#pragma unroll
+    for (int s = 0; s < SPW; ++s) { av[s] = ap[s * 512]; wv[s] = wp[s * 512]; }
+    const int n0 = nb * 32 + (wave & 3) * 8 + g * 4;                      // what the epilogue reads travels with them
+    const float4 m = *(const float4*)(A.m[branch] + n0), bs = *(const float4*)(A.bias[branch] + n0);
+    const int4 nc = *(const int4*)(A.negcorr[branch] + n0);
+    const int canon = A.row_canon[row], pix = A.row_pix[row];
+    float4 res = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (EPI == EPI_PROJ && pix >= 0) res = *(const float4*)(A.x + (size_t)pix * N + n0);
+    if (EPI == EPI_FC2) res = *(const float4*)(A.resid + (size_t)row * N + n0);
+    v16i acc = {};
+#pragma unroll
+    for (int s = 0; s < SPW; ++s) acc = mfma32(wv[s], av[s], acc);
+#pragma unroll
+    for (int qd = 0; qd < 4; ++qd) part[wave][qd][lane] = (v4i){acc[qd * 4], acc[qd * 4 + 1], acc[qd * 4 + 2], acc[qd * 4 + 3]};
+    __syncthreads();
+    if (wave >= 4) return;
+    v4i sum = {nc.x, nc.y, nc.z, nc.w};                                  // -zp_in * colsum(W[n,:])
+#pragma unroll
+    for (int k = 0; k < 8; ++k) sum += part[k][wave][lane];
+    if (A.tap_acc && canon >= 0) *(v4i*)(A.tap_acc + (size_t)canon * N + n0) = sum;
+    const float f0 = fmaf((float)sum[0], m.x, bs.x), f1 = fmaf((float)sum[1], m.y, bs.y), f2 = fmaf((float)sum[2], m.z, bs.z), f3 = fmaf((float)sum[3], m.w, bs.w);
+    const float4 o = make_float4(f0 + res.x, f1 + res.y, f2 + res.z, f3 + res.w);
+    if (EPI == EPI_PROJ) *(float4*)(A.outf + (size_t)row * N + n0) = o;
+    else if (pix >= 0) *(float4*)(A.y + (size_t)pix * N + n0) = o;
+    if (A.tap_f && canon >= 0) *(float4*)(A.tap_f + (size_t)canon * N + n0) = o;
+}
+
 // ------------------------------------------------------------------ attention core
 // For one (window, head) held by one wave.  S^T = K Q^T (A operand = key rows, B operand =
 // query columns) leaves a lane with one query per query block and the keys in registers,
@@ -1773,12 +1816,33 @@ static void launch_ring(const Geom& G, const GemmArgs& A, hipStream_t st)
         }
     hipLaunchKernelGGL((gemm_ring_kernel<EPI, WY, WX, RB, NBW, KSL, S, WPE, false>), grid, block, 0, st, G, A);
 }
+// The projection and FC2 at the widths of the wide blocks and mlp_ratio 4.  Over the number of 32 x 32 tiles, us, ring kernel / this one:
+//   FC2         C = 512   128 tiles 5.8 / 3.9   256 6.0 / 4.3 | 512 6.3 / 6.1 alone, and 0.7 slower within a layer   640 6.5 / 7.6
+//               C = 768   192 7.4 / 4.5   384 7.8 / 6.7 | 576 8.0 / 8.9      C = 1024   256 9.1 / 5.4   512 10.1 / 8.6 | 768 10.7 / 11.9
+//   projection  C = 512   128 3.6 / 3.6   256 3.7 / 3.7 | 512 3.9 / 4.5      C = 768   192 4.0 / 3.8 | 384 4.2 / 4.8      C = 1024   256 4.6 / 4.0 | 512 4.8 / 5.3
+// FC1 has four times FC2's tiles of a quarter of its K and gains at none of the three widths past the smallest map (C = 512, 512 tiles 4.1 / 3.9; C = 768,
+// 768 tiles 4.7 / 5.3; C = 1024, 1024 tiles 5.3 / 6.7): it stays with the ring.
+template <int EPI>
+static bool launch_few(const Geom& G, const GemmArgs& A, hipStream_t st)
+{
+    constexpr int WIDER = EPI == EPI_FC2 ? 4 : 1;
+    const int tiles = G.rows_total / 32 * (A.N / 32);
+    const dim3 grid(tiles), block(512);
+    if (A.N % 256 || tiles > (EPI == EPI_PROJ ? CUS : A.K <= 2048 ? 3 * CUS / 2 : 2 * CUS)) return false;
+    if (A.K == 512 * WIDER) hipLaunchKernelGGL((gemm_few_kernel<EPI, 2 * WIDER>), grid, block, 0, st, G, A);
+    else if (A.K == 768 * WIDER) hipLaunchKernelGGL((gemm_few_kernel<EPI, 3 * WIDER>), grid, block, 0, st, G, A);
+    else if (A.K == 1024 * WIDER) hipLaunchKernelGGL((gemm_few_kernel<EPI, 4 * WIDER>), grid, block, 0, st, G, A);
+    else return false;
+    return true;
+}
 template <int EPI>
 static void launch_gemm_e(const Geom& G, const GemmArgs& A0, hipStream_t st)
 {
     GemmArgs A = A0;
     if (G.rows_total == 0) return;
     if (A.K >= 512 && A.K % 128 == 0 && A.N % 64 == 0) {              // whole stages and tiles, at least as many stages as the ring holds
+        if constexpr (EPI == EPI_PROJ || EPI == EPI_FC2)
+            if (launch_few<EPI>(G, A, st)) return;
         const int tiles128 = A.N % 128 == 0 ? G.rows_total / 128 * (A.N / 128) : 0;
         if (tiles128 <= (EPI == EPI_FC1 || A.K > 1024 ? CUS : 3 * CUS / 2)) launch_ring<EPI, 2, 2, 1, 1, 4, 4, 2>(G, A, st);
         else if constexpr (EPI == EPI_FC1) launch_ring<EPI, 2, 2, 2, 2, 1, 4, 3>(G, A, st);

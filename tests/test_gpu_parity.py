@@ -129,7 +129,10 @@ def test_sums_at_and_beyond_what_a_binary32_holds(C, heads, H, W, code, layers):
     (1, 84, 98, 512, 1.0, {}),                                          # FC2 on 264, the projection on 64 x 64; one branch
     (2, 84, 84, 768, 0.0, dict(bits=(4, 2), wbits=4)),                  # the other branch; rows of the pad
     (1, 43, 49, 512, 0.4, dict(ranges={"a_fc2_in": (-0.07, 0.35)})),     # the cubic on both kinds of tiles
-    (1, 14, 14, 768, 0.25, dict(ranges={"a_fc2_in": (-0.07, 0.35)})),
+    (1, 14, 14, 768, 0.25, dict(ranges={"a_fc2_in": (-0.07, 0.35)})), (1, 14, 14, 512, 0.25, dict(ranges={"a_fc2_in": (-0.07, 0.35)})),
+    (1, 21, 28, 512, 0.5, {}), (1, 21, 35, 512, 1.0, {}),               # FC2 on 384 and 480 tiles of 32 x 32, the second with one branch
+    (1, 14, 35, 768, 0.4, {}), (1, 14, 42, 768, 0.0, {}),               # on 480 and 576
+    (1, 14, 14, 1024, 0.5, {}), (1, 14, 28, 1024, 0.4, dict(bits=(4, 2), wbits=4)),   # the projection on 256 tiles, and FC2 with it, and on 512
     (2, 14, 21, 768, 0.5, dict(mlp_ratio=1)), (1, 28, 35, 768, 0.5, dict(mlp_ratio=3)),
     (2, 35, 35, 192, 0.5, dict(mlp_ratio=7)), (2, 70, 84, 192, 0.5, dict(mlp_ratio=5)), (1, 35, 35, 96, 0.5, dict(mlp_ratio=7))])
 def test_products_of_the_separate_kernels_at_their_lines(B, H, W, C, keep, kw):
