@@ -43,10 +43,10 @@ def ideal_windows_per_s(C):
     return min(PEAK_HBM_GBS * 1e9 / (392 * C), PEAK_INT8_TOPS * 1e12 / (2 * macs_per_window(C)))
 
 
-# VALU instructions per element of the pinned arithmetic (one lane-operation each): dequantize = cvt + fma,
-# quantize = fma + med3 + 3/4 pack, GELU = 9, LayerNorm = 8 (+ quantize; two binary64 passes and the affine), softmax element =
-# 16 (+ quantize)
-ALU_DEQ, ALU_Q, ALU_GELU, ALU_LN, ALU_SOFTMAX = 2.0, 2.75, 9.0, 8.0, 16.0
+# VALU instructions per element of the pinned arithmetic (one lane-operation each): dequantize = conversion (or subtraction) + fma,
+# quantize = fma + med3 + 3/4 pack, GELU and its quantizer by the table of steps = 4 + 9/4, LayerNorm = 8 (+ quantize; two binary64
+# passes and the affine), softmax element = 16 (+ quantize)
+ALU_DEQ, ALU_Q, ALU_GELU_Q, ALU_LN, ALU_SOFTMAX = 2.0, 2.75, 6.25, 8.0, 16.0
 
 
 def kernel_work(name, C, F, heads, n_windows):
@@ -77,7 +77,7 @@ def kernel_work(name, C, F, heads, n_windows):
         w["hbm_bytes"] = n_windows * (4 * T * C + T * C + 4 * T * C)
         w["mfma_ops"] = n_windows * 2 * (T * C * C + 2 * T * C * F)
         w["alu_lane_ops"] = n_windows * (T * C * (ALU_DEQ + 1) + T * C * (ALU_LN + ALU_Q) +
-                                         T * F * (ALU_DEQ + ALU_GELU + ALU_Q) + T * C * (ALU_DEQ + 1))
+                                         T * F * (ALU_DEQ + ALU_GELU_Q) + T * C * (ALU_DEQ + 1))
     else:
         raise KeyError(name)
     return w

@@ -5,7 +5,8 @@
 //   token_kernel      projection + LN2 + FFN + scatter of a tile of rows
 // and, where these do not apply,
 //   ln_quant_kernel   gather (shift folded in) + LayerNorm + quantize, also LN2
-//   gemm_tile_kernel  int8 MFMA linear layers with fused epilogues   (shadow layers)
+//   gemm_ring_kernel, gemm_few_kernel, gemm_tile_kernel  int8 MFMA linear layers with fused epilogues (shadow layers): long K, long K on
+//                     few rows, short or odd K
 //   attn_kernel       per (window, head): QK^T, bias+mask, softmax, P.V
 // Arithmetic that decides an integer code follows the pinned binary32 sequences
 // of mixaq_dev.h; reductions feeding a code run in binary64.
@@ -1393,11 +1394,11 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
 //   proj + first residual (wave w owns channels 32w..32w+31) -> LN2 with statistics exchanged through LDS -> quantize -> FC1 +
 //   GELU + quantize, codes to LDS as fragments -> FC2 + second residual -> scatter to the map.
 // The weight fragments of the whole kernel form ONE stream per wave that is requested RING fragments ahead across every phase
-// boundary; the per-branch parameter block and the GELU table sit in LDS.  The FFN runs in four chunks of NH hidden blocks: FC1 +
+// boundary; the per-branch parameter block and the GELU table (of steps, or with SHORT off of cubics) sit in LDS.  The FFN runs in four chunks of NH hidden blocks: FC1 +
 // GELU + quantize of a chunk goes to one of two LDS buffers, then FC2 accumulates that chunk.  With two row blocks h is parked in
 // the output map between the first and the second residual (the same thread writes and re-reads the same address).
-// Bound: vector instructions (GELU) at C = 96 and 128 on large maps, the weights at 64 bytes per clock and CU at C = 384, the
-// chain of phases on few tiles.  Against a form with the chunks unrolled and FC1's weights a block ahead, which the three, four
+// Bound: vector instructions (51 to 62 % of the cycles) and LDS reads (43 to 54 %) that do not overlap fully at C = 96 and 128 on large
+// maps, the weights at 64 bytes per clock and CU at C = 384, the chain of phases on few tiles.  Against a form with the chunks unrolled and FC1's weights a block ahead, which the three, four
 // and eight waves had: stage of two blocks on 8 x 1392 windows at C = 96, 5476 at C = 128 and 1444 at C = 256 3 % shorter, 64
 // windows at C = 256 58.9 -> 52.7 us.
 // LN2's partial sums are read together and each by one half of the lanes, for both row blocks before either goes on, and the
