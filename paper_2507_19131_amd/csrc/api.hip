@@ -17,6 +17,7 @@
 #include "arena.h"
 #include "side_streams.h"
 #include "stage_plan.h"
+#include "weight_rows.h"
 
 using namespace mixaq;
 
@@ -119,7 +120,7 @@ struct Linear {           // one shadow layer prepared for the device
     float* bias[2] = {nullptr, nullptr};
     int* negcorr[2] = {nullptr, nullptr};
     std::vector<int> colsum;   // sum_k W[n,k], kept on the host
-    long long widest = 0;      // the largest sum_k |W[n,k]|
+    int widest = 0;            // the largest sum_k |W[n,k]|
     std::vector<float> hm[2], hb[2];   // host copies of m, bias and negcorr, while the block is being built
     std::vector<int> hnc[2];
 };
@@ -197,14 +198,14 @@ int prepare_linear(mixaq_block* blk, Linear& L, const int8_t* w_dev, const float
     std::vector<int> colsum(N, 0);
     for (int n = 0; n < N; ++n) {
         if (!(s[n] > 0.0f) || !std::isfinite(s[n])) return fail(MIXAQ_E_SHAPE, "weight scale %d is not positive", n);
-        long long width = 0;
-        for (int k = 0; k < K; ++k) {
-            int v = w[(size_t)n * K + k];
-            if (v < wmin || v > wmax) return fail(MIXAQ_E_BITS, "weight code %d outside the %d-bit range", v, weight_bits);
-            colsum[n] += v;
-            width += std::abs(v);
+        const int8_t* row = &w[(size_t)n * K];
+        const RowCodes c = row_codes(row, K);
+        if (c.lowest < wmin || c.highest > wmax) {
+            const int k = (int)(std::find_if(row, row + K, [&](int v) { return v < wmin || v > wmax; }) - row);
+            return fail(MIXAQ_E_BITS, "weight code %d outside the %d-bit range", row[k], weight_bits);
         }
-        L.widest = std::max(L.widest, width);
+        colsum[n] = c.sum;
+        L.widest = std::max(L.widest, c.width);
     }
     const int NB = N / 32, KS = K / 32;
     int8_t* packed = blk->mem.take<int8_t>((size_t)N * K, &L.Wp);
@@ -237,11 +238,7 @@ int prepare_linear(mixaq_block* blk, Linear& L, const int8_t* w_dev, const float
 }
 
 // whether the sums sum_k (code - zp) W[n,k] of a layer stay within what sum_value can hold
-bool sums_bounded(const Linear& L, const QDev& q)
-{
-    const long long qmin = (long long)(q.lo - RND_MAGIC), qmax = (long long)(q.hi - RND_MAGIC);
-    return L.widest * std::max(qmax - q.zp, q.zp - qmin) < SUM_MAGIC_BOUND;
-}
+bool sums_bounded(const Linear& L, const QDev& q) { return sums_fit(L.widest, (int)(q.lo - RND_MAGIC), (int)(q.hi - RND_MAGIC), q.zp); }
 
 // original padded coordinates of token t of window (wr,wc) in the rolled frame
 void token_src(const mixaq_block* b, int wr, int wc, int t, int* r, int* c)
@@ -614,20 +611,16 @@ static int block_create(const mixaq_block_desc* desc, const mixaq_shared_params*
         float widest = 0.0f;                                 // of the unmasked entries of a row, over all rows
         for (int type = 0; type < 4; ++type) {
             int wr = (type & 2) ? nWr - 1 : 0, wc = (type & 1) ? b->nWc - 1 : 0;
+            int src_r[TOK], src_c[TOK];
+            for (int i = 0; i < TOK; ++i) token_src(b, wr, wc, i, &src_r[i], &src_c[i]);
             for (int h = 0; h < heads; ++h)
                 for (int i = 0; i < TOK; ++i) {
                     float row[TOK], row_min = INFINITY, row_max = -INFINITY;
                     bool masked[TOK], ordinary = true;
                     for (int j = 0; j < TOK; ++j) {
                         float v = rpb[((size_t)h * TOK + i) * TOK + j];
-                        masked[j] = false;
-                        if (desc->shift > 0) {
-                            int ri, ci, rj, cj;
-                            token_src(b, wr, wc, i, &ri, &ci);
-                            token_src(b, wr, wc, j, &rj, &cj);
-                            masked[j] = !(std::abs(ri - rj) < WS && std::abs(ci - cj) < WS);
-                            if (masked[j]) v = v + MASK_VALUE;
-                        }
+                        masked[j] = desc->shift > 0 && !(std::abs(src_r[i] - src_r[j]) < WS && std::abs(src_c[i] - src_c[j]) < WS);
+                        if (masked[j]) v = v + MASK_VALUE;
                         row[j] = v = v * LOG2E_F;
                         ordinary = ordinary && std::isfinite(v);
                         if (!masked[j]) { row_min = std::min(row_min, v); row_max = std::max(row_max, v); }

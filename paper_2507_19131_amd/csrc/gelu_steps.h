@@ -54,7 +54,7 @@ public:
         return lay_out();
     }
     // the code by the pinned sequence
-    int code(float x) const { return (int)(std::min(std::max(fmaf(gelu(x), inv_s_, magic_), lo_), hi_) - GELU_STEP_MAGIC); }
+    int code(float x) const { return code_of(gelu(x)); }
     // the code by the table, with the operations of the kernel
     int looked_up(float x) const
     {
@@ -99,7 +99,11 @@ private:
         memcpy(&v, &b, 4);
         return v;
     }
-    // the steps of a monotone run from x0 to x1, codes changing by `by` at each
+    int code_of(float g) const { return (int)(std::min(std::max(fmaf(g, inv_s_, magic_), lo_), hi_) - GELU_STEP_MAGIC); }
+    double value_of(float g) const { return (double)g * (double)inv_s_ + ((double)magic_ - (double)GELU_STEP_MAGIC); }   // before rounding
+    // The steps of a monotone run from x0 to x1, codes changing by `by` at each.  A step is looked for where the two before it and two secant
+    // steps put it, a few numbers off.  (A search that starts over at each step, and a walk that evaluates each neighbour twice, took 52
+    // evaluations a step instead of 25: 8 bits on [-0.17, 0.8] 185 -> 120 us.)
     bool walk(float x0, float x1, int by)
     {
         int64_t at = order_of(x0);
@@ -108,16 +112,27 @@ private:
         int now = code(x0);
         auto passed = [&](int64_t o) { return (code(number_at(o)) - now) * by > 0; };
         if ((last - now) * by < 0) return false;
-        int64_t stride = 1 << 16;
+        double pitch = 0.0;                                          // from the last step to the one before
         while (now != last) {
-            int64_t far = std::min(at + stride, end);                // gallop, then bisect
-            while (!passed(far)) { at = far; stride *= 2; far = std::min(far + stride, end); }
-            while (far - at > 1) {
+            int64_t stride = 1 << 16, far = std::min(at + stride, end);
+            if (pitch > 0.0) {
+                double x = (double)number_at(at) + pitch;
+                for (int k = 0; k < 2; ++k) x += (now + 0.5 * by - value_of(gelu((float)x))) * by * pitch;
+                if (x > number_at(at) && x < x1) { far = std::max(order_of((float)x), at + 1); stride = 4; }
+            }
+            if (passed(far)) {                                       // gallop: `at` has not passed, nor do the numbers before it count
+                int64_t low = far - stride;
+                while (low > at && passed(low)) { far = low; stride *= 2; low = far - stride; }
+                at = std::max(at, low);
+            } else {
+                while (!passed(far)) { at = far; far = std::min(far + stride, end); stride *= 2; }
+            }
+            while (far - at > 1) {                                   // then bisect
                 const int64_t mid = at + (far - at) / 2;
                 if (passed(mid)) far = mid; else at = mid;
             }
-            stride = 1 << 16;
             if (code(number_at(far)) != now + by || !clear(at, now, -1) || !clear(far, now + by, 1)) return false;
+            pitch = steps_.empty() || steps_.back().code_after - steps_.back().code_before != by ? 0.0 : (double)number_at(far) - steps_.back().after;
             steps_.push_back({number_at(at), number_at(far), now, now + by});
             now += by;
             at = far;
@@ -130,9 +145,9 @@ private:
     bool clear(int64_t o, int expected, int dir) const
     {
         for (int n = 0; n < 1024; ++n, o += dir) {
-            const float x = number_at(o), g = gelu(x);
-            if (code(x) != expected) return false;
-            const double v = (double)g * (double)inv_s_ + ((double)magic_ - (double)GELU_STEP_MAGIC) - (double)expected;   // distance from the code's middle
+            const float g = gelu(number_at(o));
+            if (code_of(g) != expected) return false;
+            const double v = value_of(g) - (double)expected;         // distance from the code's middle
             if (n > 0 && 0.5 - fabs(v) > 0x1p-21 * fabs((double)g) * (double)inv_s_) return true;
             if (fabs(v) > 0.5 && (expected == (int)(lo_ - GELU_STEP_MAGIC) || expected == (int)(hi_ - GELU_STEP_MAGIC))) return true;                 // saturated: nothing beyond
         }

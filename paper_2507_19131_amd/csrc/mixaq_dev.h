@@ -74,7 +74,6 @@ __device__ __forceinline__ int pack4(int c0, int c1, int c2, int c3)
 // 4 x 128 x 128 x 256 320.1 -> 316.7, 200 x 336 x 96 101.0 -> 100.2.  FC2's sums, sixteen of a tile's 112 and the widest ones, and those
 // of Q K^T, whose accumulators start at an inline zero, are converted.)
 constexpr int SUM_MAGIC_BITS = 0x4b400000;                        // of RND_MAGIC
-constexpr int SUM_MAGIC_BOUND = 1 << 22;
 template <bool MAGIC> __device__ __forceinline__ float sum_value(int a) { return MAGIC ? __int_as_float(a) - RND_MAGIC : (float)a; }
 template <bool MAGIC> __device__ __forceinline__ int sum_int(int a) { return MAGIC ? a - SUM_MAGIC_BITS : a; }
 

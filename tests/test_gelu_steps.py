@@ -13,7 +13,13 @@ PROGRAM = textwrap.dedent(r'''
     #include <cstdio>
     #include <cstdlib>
     #include <random>
+    #include <cmath>
+    #include <algorithm>
+    static long fma_calls = 0;
+    static inline float counted_fma(float a, float b, float c) { ++fma_calls; return __builtin_fmaf(a, b, c); }
+    #define fmaf counted_fma
     #include "gelu_steps.h"
+    #undef fmaf
     #include "arith.h"
     using namespace mixaq;
     int main(int argc, char** argv)
@@ -27,6 +33,7 @@ PROGRAM = textwrap.dedent(r'''
         const float inv = 1.0f / s;
         GeluSteps t;
         if (!t.build(cubic, ORC_GELU_INTERVALS, inv / 16.0f, GELU_STEP_MAGIC + zp, GELU_STEP_MAGIC + qmin, GELU_STEP_MAGIC + qmax)) { printf("none\n"); return 0; }
+        const long built = fma_calls;
         long wrong = 0, seen = 0;
         auto check = [&](float x) { ++seen; wrong += t.looked_up(16.0f * x) != orc_q(orc_gelu_pinned(x), inv, zp, bits); };
         auto around = [&](float x, int n) {
@@ -52,7 +59,9 @@ PROGRAM = textwrap.dedent(r'''
         }
         const int spans = (int)(t.index.span / 8);
         for (int i = 1; i <= spans; ++i) around((((i - 0.0625f) / spans) - t.index.offset) / t.index.scale / 16.0f, 60);
-        printf("entries %d pieces %zu seen %ld wrong %ld\n", spans + 1, t.table.size() / 128, seen, wrong);
+        int steps = 0;
+        for (int i = 1; i <= spans; ++i) steps += t.table[i].addend < 0x1p99f && t.table[i].factor != t.table[i - 1].factor;
+        printf("entries %d pieces %zu seen %ld wrong %ld fma %ld steps %d\n", spans + 1, t.table.size() / 128, seen, wrong, built, steps);
         return 0;
     }
 ''')
@@ -74,6 +83,15 @@ def test_codes_by_steps_are_the_pinned_codes(program, lo, hi, bits):
     out = program(lo, hi, bits)
     assert out[0] == "entries" and 2 <= int(out[1]) <= 1664 and int(out[3]) <= 13
     assert int(out[5]) > 900000 and int(out[7]) == 0
+
+
+@pytest.mark.parametrize("lo,hi", [(-0.17, 0.8), (-0.17, 4.0), (-0.17, 50.0)])
+def test_a_step_is_found_from_the_two_before_it(program, lo, hi):
+    """The builder runs whenever a block is created.  Walking the neighbours of a step until the value is out of the roundings' reach
+    takes about eight evaluations of four fused multiply-adds on each of its two sides, finding it nine more: 100 in all."""
+    out = program(lo, hi, 8)
+    fma, steps = int(out[9]), int(out[11])
+    assert steps >= 250 and fma <= 120 * steps, out
 
 
 @pytest.mark.parametrize("lo,hi,bits", [(-0.07, 0.35, 8),                         # steps too close for the table
