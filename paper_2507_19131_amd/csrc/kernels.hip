@@ -1051,13 +1051,17 @@ constexpr bool win_pairs_share(int NH, int HG) { return (NH == 6 && HG == 1) || 
 // Pairs that have the registers share the projections by roles: one wave takes q of all tokens, the other k, and v is split by
 // tokens.  Each weight fragment of q and k then passes the L1 once and feeds two independent products, and its constants are read once.
 // Against q, k and v each split by tokens, window kernel with LN1, us: 25 windows at C = 1024 20.0 -> 18.3, 24 at 768 15.7 -> 15.0, 4 at 512
-// 12.4 -> 11.5, 96 at 384 15.2 -> 14.5, 196 at 192 14.8 -> 14.4, 64 at 128 7.8 -> 7.5, 64 at 96 8.3 -> 8.25.
-constexpr bool win_roles(int NH, int HG, int QS, bool CODES) { return QS == 2 && (CODES || !win_pairs_share(NH, HG)); }
-constexpr int win_waves_per_eu(int NH, int HG, int QS, bool CODES)
+// 12.4 -> 11.5, 96 at 384 15.2 -> 14.5, 196 at 192 14.8 -> 14.4, 64 at 128 7.8 -> 7.5; two blocks on 64 windows at C = 96 32.3 -> 31.9.
+// BESIDE (C = 96, beside a second chain; see window_beside): pairs without roles.  With their 126 registers a CU has places for two workgroups
+// of six waves, both taken by the first chain, and what is left of the second one waits behind that chain's token kernel; with 87
+// it has a third.  Four blocks on 760 windows 129 -> 126 us, 874 147 -> 135, 960 149 -> 140, 1012 163 -> 146.  And one wave per head at
+// four waves per SIMD, where it spills none with scores either.
+constexpr bool win_roles(int NH, int HG, int QS, bool CODES, bool BESIDE) { return QS == 2 && !BESIDE && (CODES || !win_pairs_share(NH, HG)); }
+constexpr int win_waves_per_eu(int NH, int HG, int QS, bool CODES, bool BESIDE)
 {
     if (CODES) return QS == 1 ? 4 : 2;
-    if (QS == 2) return win_pairs_share(NH, HG) ? 6 : NH == 6 ? 3 : 4;
-    return NH * HG > 8 ? 3 : NH == 3 ? 5 : 4;
+    if (QS == 2) return win_pairs_share(NH, HG) ? 6 : BESIDE ? 5 : NH == 6 ? 3 : 4;
+    return NH * HG > 8 ? 3 : NH == 3 && !BESIDE ? 5 : 4;
 }
 
 // The window kernel's parameter block of one branch (see WinArgs::params), as a workgroup of NH heads holds it in LDS:
@@ -1068,13 +1072,13 @@ template <int C, int NH, bool CODES> struct WinPrm {
 
 // CODES: the LN1 codes come ready from ln_window_kernel (wide blocks, whose heads are spread over many workgroups: each of
 // them would repeat the whole gather and LayerNorm); the workgroup is given a slot and there are no pruned ones.
-template <int NH, bool TAPS, bool SCORED, int HG = 1, int QS = 1, bool CODES = false, bool MAGIC = true>
-__global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(win_waves_per_eu(NH, HG, QS, CODES)))) void window_kernel(Geom G, WinArgs A)
+template <int NH, bool TAPS, bool SCORED, int HG, int QS, bool CODES, bool MAGIC, bool BESIDE>
+__global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(win_waves_per_eu(NH, HG, QS, CODES, BESIDE)))) void window_kernel(Geom G, WinArgs A)
 {
     if (CODES || HG == 2 || (QS == 2 && NH <= 4)) touch_arguments<sizeof(Geom) + sizeof(WinArgs)>();   // few workgroups
     constexpr int NHT = NH * HG;                                         // heads of the block; this workgroup runs NH of them
     constexpr int NW = NH * QS, NTB = 2 / QS;                            // waves; token blocks a wave projects to v and attends for
-    constexpr bool ROLES = win_roles(NH, HG, QS, CODES);                 // one wave of a pair projects all tokens to q, the other to k
+    constexpr bool ROLES = win_roles(NH, HG, QS, CODES, BESIDE);                 // one wave of a pair projects all tokens to q, the other to k
     constexpr int NTQ = ROLES ? 2 : NTB, PAIR_SLOTS = ROLES ? 5 : 4;
     constexpr int C = NHT * 32, KS = NHT, LPT = WinCfg<NH, HG, QS>::LPT, NV = CODES ? 1 : WinCfg<NH, HG, QS>::NV, NT = NW * 64;
     constexpr int GPW = WinCfg<NH, HG, QS>::GPW;
@@ -1300,7 +1304,7 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
         for (int tb = 0; tb < NTQ; ++tb) finish(tb, acc[tb]);
     }
     // a pair of waves requests its bias ahead of the exchange, where the registers are free
-    constexpr bool BIAS_EARLY = ROLES;
+    constexpr bool BIAS_EARLY = QS == 2 && (CODES || !win_pairs_share(NH, HG));
     BiasRow bias;
     v4i vt[2];
     {
@@ -1916,6 +1920,14 @@ static WindowForm window_form(int heads, int windows, int computed, int chains)
         default: return SPLIT;
     }
 }
+// C = 96 beside a second chain: the forms that leave it room (see win_roles): pairs, and one wave per head while the launch is more than three
+// and no more than five windows a CU.  There the two chains fall into step such that one's windows meet the tail of the other's token
+// kernel, and five workgroups of three waves on a CU, all of the launch at once, keep out of it better than six.  Five waves per SIMD ->
+// four, us, windows of both chains, two blocks / six:   1176 93.0 -> 91.9 / 227 -> 229   1260 95.7 -> 97.9 / 237 -> 243   1428 103.4 -> 105.5 /
+// 271 -> 268   1512 107.4 -> 108.5 / 279 -> 275 | 1554 114.5 -> 111.0 / 296 -> 288   1680 117.3 -> 113.1 / 309 -> 296   1848 122.4 -> 119.8 / 329 ->
+// 315   2016 131.8 -> 128.7 / 353 -> 336   2184 141.0 -> 137.2 / 388 -> 371   2352 152.7 -> 143.3 / 404 -> 386   2520 158.3 -> 153.3 / 435 -> 414 |
+// 2856 172.8 -> 170.2 / 473 -> 476   4 x 1392 315.9 -> 318.4 / 864 -> 870
+static bool window_beside(WindowForm form, int windows, int chains) { return chains > 1 && (form == PAIR || (windows > 3 * CUS && windows <= 5 * CUS)); }
 void launch_window(const Geom& G, const WinArgs& A, int chains, hipStream_t st)
 {
     // every window gets a workgroup: with scores it finds its own rank (and may turn out pruned), otherwise
@@ -1927,11 +1939,11 @@ void launch_window(const Geom& G, const WinArgs& A, int chains, hipStream_t st)
     // four heads a workgroup of one wave each / eight:   C = 512   49 windows 14.0 / 15.7 / 17.6   64 14.9 / 16.9 / 18.3 | 100 22.7 / 22.2 / 20.7
     //   270 49 / 43 / 45   784 115 / 95 / 97      C = 768   35 16.6 / 18.4 / 26.8   42 18.0 / 19.7 / 29.0 | 48 24.9 / 23.8 / 30.3   140 48 / 45 / 50
     //   400 112 / 102 / 98      C = 1024   25 18.4 / 29.7 / 24.4   30 19.6 / 32.0 / 25.2 | 42 29.8 / 38.1 / 27.9   100 55 / 57 / 48   288 120 / 110 / 111
-#define WIN_LAUNCH(ARGS, SCORED, NH, HG, QS, CODES)                                                                       \
-    if (ARGS.taps && ARGS.magic_sums) hipLaunchKernelGGL((window_kernel<NH, true, SCORED, HG, QS, CODES, true>), grid, block, 0, st, G, ARGS);    \
-    else if (ARGS.taps) hipLaunchKernelGGL((window_kernel<NH, true, SCORED, HG, QS, CODES, false>), grid, block, 0, st, G, ARGS);                 \
-    else if (ARGS.magic_sums) hipLaunchKernelGGL((window_kernel<NH, false, SCORED, HG, QS, CODES, true>), grid, block, 0, st, G, ARGS);           \
-    else hipLaunchKernelGGL((window_kernel<NH, false, SCORED, HG, QS, CODES, false>), grid, block, 0, st, G, ARGS);
+#define WIN_LAUNCH(ARGS, SCORED, NH, HG, QS, CODES, BESIDE)   /* taps: one chain */                                        \
+    if (ARGS.taps && ARGS.magic_sums) hipLaunchKernelGGL((window_kernel<NH, true, SCORED, HG, QS, CODES, true, false>), grid, block, 0, st, G, ARGS);    \
+    else if (ARGS.taps) hipLaunchKernelGGL((window_kernel<NH, true, SCORED, HG, QS, CODES, false, false>), grid, block, 0, st, G, ARGS);                 \
+    else if (ARGS.magic_sums) hipLaunchKernelGGL((window_kernel<NH, false, SCORED, HG, QS, CODES, true, BESIDE>), grid, block, 0, st, G, ARGS);          \
+    else hipLaunchKernelGGL((window_kernel<NH, false, SCORED, HG, QS, CODES, false, BESIDE>), grid, block, 0, st, G, ARGS);
 #define WIDE_CASE(C_, LPT, NV, NH, HG, QS, WHEN)                                                                          \
     if (G.C == C_ && (WHEN)) {                                                                                                      \
         const dim3 lgrid(n_wg, 64 * LPT / 256);                                                                           \
@@ -1941,7 +1953,7 @@ void launch_window(const Geom& G, const WinArgs& A, int chains, hipStream_t st)
         WinArgs W = A;                                                                                                    \
         if (A.scores) W.perm = A.perm_out;                                                                                \
         const dim3 grid(G.n_slots * HG), block(NH * QS * 64);                                                             \
-        WIN_LAUNCH(W, false, NH, HG, QS, true)                                                                            \
+        WIN_LAUNCH(W, false, NH, HG, QS, true, false)                                                                          \
         return;                                                                                                           \
     }
     const bool fits = G.n_slots * (G.heads / 4) <= CUS;
@@ -1952,34 +1964,38 @@ void launch_window(const Geom& G, const WinArgs& A, int chains, hipStream_t st)
     WIDE_CASE(768, 64, 3, 4, 6, 1, true)
     WIDE_CASE(1024, 64, 4, 8, 4, 1, true)
 #undef WIDE_CASE
-#define WIN_CASE(NH, HG, QS)                                                                                              \
+#define WIN_CASE(NH, HG, QS, BESIDE)                                                                                      \
     {                                                                                                                     \
         const dim3 grid(HG > 1 ? (n_wg + 7) / 8 * 8 * HG : n_wg), block(NH * QS * 64);                                     \
         if (A.scores) {   /* no entry point takes scores and taps together */                                            \
-            if (A.magic_sums) hipLaunchKernelGGL((window_kernel<NH, false, true, HG, QS, false, true>), grid, block, 0, st, G, A);       \
-            else hipLaunchKernelGGL((window_kernel<NH, false, true, HG, QS, false, false>), grid, block, 0, st, G, A);                   \
+            if (A.magic_sums) hipLaunchKernelGGL((window_kernel<NH, false, true, HG, QS, false, true, BESIDE>), grid, block, 0, st, G, A);       \
+            else hipLaunchKernelGGL((window_kernel<NH, false, true, HG, QS, false, false, BESIDE>), grid, block, 0, st, G, A);                   \
         } else {                                                                                                          \
-            WIN_LAUNCH(A, false, NH, HG, QS, false)                                                                       \
+            WIN_LAUNCH(A, false, NH, HG, QS, false, BESIDE)                                                               \
         }                                                                                                                 \
     }                                                                                                                     \
     break
     const WindowForm form = window_form(G.C / 32, n_wg, G.n_slots, chains);
     switch (G.C / 32) {
         case 3:
-            if (form == PAIR) { WIN_CASE(3, 1, 2); }
-            WIN_CASE(3, 1, 1);
+            if (window_beside(form, n_wg, chains)) {
+                if (form == PAIR) { WIN_CASE(3, 1, 2, true); }
+                WIN_CASE(3, 1, 1, true);
+            }
+            if (form == PAIR) { WIN_CASE(3, 1, 2, false); }
+            WIN_CASE(3, 1, 1, false);
         case 4:
-            if (form == SPLIT) { WIN_CASE(2, 2, 2); }
-            if (form == PAIR) { WIN_CASE(4, 1, 2); }
-            WIN_CASE(4, 1, 1);
+            if (form == SPLIT) { WIN_CASE(2, 2, 2, false); }
+            if (form == PAIR) { WIN_CASE(4, 1, 2, false); }
+            WIN_CASE(4, 1, 1, false);
         case 6:
-            if (form == SPLIT) { WIN_CASE(3, 2, 2); }
-            if (form == PAIR) { WIN_CASE(6, 1, 2); }
-            WIN_CASE(6, 1, 1);
-        case 8: WIN_CASE(4, 2, 2);
+            if (form == SPLIT) { WIN_CASE(3, 2, 2, false); }
+            if (form == PAIR) { WIN_CASE(6, 1, 2, false); }
+            WIN_CASE(6, 1, 1, false);
+        case 8: WIN_CASE(4, 2, 2, false);
         case 12:
-            if (form == SPLIT) { WIN_CASE(6, 2, 2); }
-            WIN_CASE(12, 1, 1);
+            if (form == SPLIT) { WIN_CASE(6, 2, 2, false); }
+            WIN_CASE(12, 1, 1, false);
         default: break;
     }
 #undef WIN_CASE

@@ -463,7 +463,7 @@ def test_forked_stage_with_uneven_halves_pruning_and_streams(B, H, W, C, heads, 
     assert np.array_equal(y_gpu, cur)
 
 
-@pytest.mark.parametrize("C,rows,cols,n_blocks", [(192, 8, 16, 6), (192, 3, 43, 6), (192, 16, 16, 4), (192, 6, 43, 4), (384, 8, 10, 6), (384, 9, 9, 6), (384, 12, 15, 2), (384, 16, 17, 2)])
+@pytest.mark.parametrize("C,rows,cols,n_blocks", [(96, 14, 44, 4), (96, 15, 41, 4), (96, 24, 32, 2), (96, 11, 70, 2), (96, 32, 40, 2), (96, 7, 183, 2), (192, 8, 16, 6), (192, 3, 43, 6), (192, 16, 16, 4), (192, 6, 43, 4), (384, 8, 10, 6), (384, 9, 9, 6), (384, 12, 15, 2), (384, 16, 17, 2)])
 def test_forms_of_the_kernels_of_two_chains_on_both_sides_of_their_lines(C, rows, cols, n_blocks):
     """The forms of the two fused kernels that take the other chain into account: the bits of block after block on the whole batch,
     which takes other forms."""
