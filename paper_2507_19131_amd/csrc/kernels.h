@@ -1,10 +1,9 @@
 // Argument blocks and launchers of the gfx950 kernels (host side sees only this).
 #pragma once
 #include "mixaq_dev.h"
+#include "product_plan.h"
 
 namespace mixaq {
-
-enum { EPI_QKV = 0, EPI_PROJ = 1, EPI_FC1 = 2, EPI_FC2 = 3 };
 
 // Host side: the GELU_K x 4 coefficient table of gelu_pinned (api.hip uploads it once per block).
 void gelu_table(float* tab);

@@ -482,7 +482,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RT * KMAX <
 
 // The same products for many rows: both operands through LDS.  A workgroup computes RT = 32 WY RB rows times NT = 32 WX NBW
 // channels, wave (wy, wx) the RB x NBW blocks of its corner, so that an operand fragment read from LDS feeds RB or NBW products
-// instead of one or two, and a byte from the caches RT or NT of them: see launch_ring for the times.  K passes in stages of KSL slabs through a ring
+// instead of one or two, and a byte from the caches RT or NT of them: see product_form for the times.  K passes in stages of KSL slabs through a ring
 // of S LDS buffers filled by direct loads; a stage is requested S - 1 stages ahead, into the buffer that all waves have left at the barrier
 // in front of it, and that barrier is the only one of a stage.  The residual is requested ahead of the last S - 2 stages, a further tile's
 // first stages ahead of the epilogue.
@@ -643,7 +643,7 @@ __global__ __launch_bounds__(WY * WX * 64) __attribute__((amdgpu_waves_per_eu(WP
 // The same products for few rows: one workgroup of eight waves per 32 x 32 outputs, each wave every eighth slab of K, SPW of them, its operands
 // straight from memory to registers, as many requested at once as 72 registers hold (all of FC2's: 768 channels, 384 tiles 6.7 -> 7.2 us); the
 // eight partial sums meet in LDS, and wave w < 4 finishes quad w of every lane's sixteen.  No stage, no barrier but one, and four times the workgroups of the ring kernel's smaller tiles, whose 430 clocks
-// a stage of 128 bytes of K are their way through the L1 and LDS: see launch_few for the times.
+// a stage of 128 bytes of K are their way through the L1 and LDS: see product_of_few_rows for the times.
 template <int EPI, int SPW>
 __global__ __launch_bounds__(512) void gemm_few_kernel(Geom G, GemmArgs A)
 {
@@ -1719,7 +1719,6 @@ __global__ __launch_bounds__(NH * 64) __attribute__((amdgpu_waves_per_eu(tok_wav
 }
 
 // ------------------------------------------------------------------ launchers
-constexpr int CUS = 256;
 // From C = 384 a window is taken by 1024 threads (256 threads -> 1024, launch to launch on fresh maps).  Raw score: equal where
 // the launch itself is what takes the time (24 windows at C = 768 6.5 us both), better or equal beyond (384 windows at 768 12.5 ->
 // 11.7, 3200 at 384 41.8 -> 39.1, 900 at 1024 30.8 -> 30.5).  With the scoring LayerNorm the window's arithmetic is spread wider
@@ -1794,19 +1793,8 @@ bool launch_ln_quant(const Geom& G, const LnArgs& A, bool gather, hipStream_t st
     return true;
 }
 
-// Tiles of the ring kernel.  64 x 64: the fewest bytes in front of the first product and the most workgroups; 128 x 128: half the bytes per
-// product.  Over the number of 128 x 128 tiles T, us, 64 x 64 / 128 x 128 (the kernel for narrow blocks in brackets, which these layers took
-// before):
-//   FC1         C = 768    T = 48 4.6 / 9.2 (6.9)   240 8.8 / 10.0 (10.1)   336 11.6 / 10.9 (14.1)   672 19.9 / 15.9 (19.5)   3696 90 / 64 (95)
-//               C = 512    32 4.1 / 7.7 (6.1)   320 9.4 / 9.2 (12.0)   608 15.4 / 12.7 (16.6)   1680 35.5 / 25.7 (40.3)
-//               C = 1024   64 5.1 / 10.5 (7.5)   320 14.0 / 12.9 (15.5)   1280 45 / 32 (38.5)   3552 117 / 74 (96.8)
-//   FC2         C = 768    12 7.4 / 17.0 (8.6)   60 8.4 / 17.8 (9.9)   168 18.4 / 20.6 (27.8)   330 33.3 / 29.7 (44.1)   924 79 / 64 (109)
-//               C = 512    8 5.8 / 13.0 (10.3)   152 14.1 / 15.7 (23.5)   420 28.8 / 25.5 (38.3)      C = 1024   312 37.1 / 35.6 (53.0)   888 99 / 79 (127)
-//   projection  C = 768    12 4.1 / 8.2 (5.2)   168 9.1 / 10.5 (11.1)   330 15.3 / 16.2 (18.7)   924 34.3 / 33.4 (39.4)
-//               C = 512    152 7.8 / 8.9 (10.5)   420 15.6 / 15.6 (18.5)      C = 1024   312 15.4 / 18.2 (20.7)   888 37.8 / 37.4 (40.5)
-// FC1, whose epilogue is the longest, takes one slab a stage: 48 KB, three workgroups on a CU, one's GELU beside the others' products
-// (T = 3696 67 -> 64, 3552 82 -> 74); the others two slabs, two workgroups.  64 x 128, 128 x 256 and 256 x 128 tiles lie between the
-// two or behind them everywhere but at T = 330 (14.6 and 29.4).
+// FC1 on 128 x 128 tiles, whose epilogue is the longest, takes one slab a stage: 48 KB, three workgroups on a CU, one's GELU beside the others'
+// products (T = 3696 67 -> 64, 3552 82 -> 74); the others two slabs, two workgroups.
 template <int EPI, int WY, int WX, int RB, int NBW, int KSL, int S, int WPE>
 static void launch_ring(const Geom& G, const GemmArgs& A, hipStream_t st)
 {
@@ -1821,38 +1809,30 @@ static void launch_ring(const Geom& G, const GemmArgs& A, hipStream_t st)
         }
     hipLaunchKernelGGL((gemm_ring_kernel<EPI, WY, WX, RB, NBW, KSL, S, WPE, false>), grid, block, 0, st, G, A);
 }
-// The projection and FC2 at the widths of the wide blocks and mlp_ratio 4.  Over the number of 32 x 32 tiles, us, ring kernel / this one:
-//   FC2         C = 512   128 tiles 5.8 / 3.9   256 6.0 / 4.3 | 512 6.3 / 6.1 alone, and 0.7 slower within a layer   640 6.5 / 7.6
-//               C = 768   192 7.4 / 4.5   384 7.8 / 6.7 | 576 8.0 / 8.9      C = 1024   256 9.1 / 5.4   512 10.1 / 8.6 | 768 10.7 / 11.9
-//   projection  C = 512   128 3.6 / 3.6   256 3.7 / 3.7 | 512 3.9 / 4.5      C = 768   192 4.0 / 3.8 | 384 4.2 / 4.8      C = 1024   256 4.6 / 4.0 | 512 4.8 / 5.3
-// FC1 has four times FC2's tiles of a quarter of its K and gains at none of the three widths past the smallest map (C = 512, 512 tiles 4.1 / 3.9; C = 768,
-// 768 tiles 4.7 / 5.3; C = 1024, 1024 tiles 5.3 / 6.7): it stays with the ring.
 template <int EPI>
-static bool launch_few(const Geom& G, const GemmArgs& A, hipStream_t st)
+static void launch_few(const Geom& G, const GemmArgs& A, hipStream_t st)
 {
     constexpr int WIDER = EPI == EPI_FC2 ? 4 : 1;
-    const int tiles = G.rows_total / 32 * (A.N / 32);
-    const dim3 grid(tiles), block(512);
-    if (A.N % 256 || tiles > (EPI == EPI_PROJ ? CUS : A.K <= 2048 ? 3 * CUS / 2 : 2 * CUS)) return false;
+    const dim3 grid(G.rows_total / 32 * (A.N / 32)), block(512);
     if (A.K == 512 * WIDER) hipLaunchKernelGGL((gemm_few_kernel<EPI, 2 * WIDER>), grid, block, 0, st, G, A);
     else if (A.K == 768 * WIDER) hipLaunchKernelGGL((gemm_few_kernel<EPI, 3 * WIDER>), grid, block, 0, st, G, A);
-    else if (A.K == 1024 * WIDER) hipLaunchKernelGGL((gemm_few_kernel<EPI, 4 * WIDER>), grid, block, 0, st, G, A);
-    else return false;
-    return true;
+    else hipLaunchKernelGGL((gemm_few_kernel<EPI, 4 * WIDER>), grid, block, 0, st, G, A);
 }
 template <int EPI>
 static void launch_gemm_e(const Geom& G, const GemmArgs& A0, hipStream_t st)
 {
     GemmArgs A = A0;
     if (G.rows_total == 0) return;
-    if (A.K >= 512 && A.K % 128 == 0 && A.N % 64 == 0) {              // whole stages and tiles, at least as many stages as the ring holds
-        if constexpr (EPI == EPI_PROJ || EPI == EPI_FC2)
-            if (launch_few<EPI>(G, A, st)) return;
-        const int tiles128 = A.N % 128 == 0 ? G.rows_total / 128 * (A.N / 128) : 0;
-        if (tiles128 <= (EPI == EPI_FC1 || A.K > 1024 ? CUS : 3 * CUS / 2)) launch_ring<EPI, 2, 2, 1, 1, 4, 4, 2>(G, A, st);
-        else if constexpr (EPI == EPI_FC1) launch_ring<EPI, 2, 2, 2, 2, 1, 4, 3>(G, A, st);
-        else launch_ring<EPI, 2, 2, 2, 2, 2, 4, 2>(G, A, st);
-        return;
+    switch (product_form(EPI, G.rows_total, A.N, A.K)) {
+        case FEW:
+            if constexpr (EPI == EPI_PROJ || EPI == EPI_FC2) launch_few<EPI>(G, A, st);
+            return;
+        case RING64: launch_ring<EPI, 2, 2, 1, 1, 4, 4, 2>(G, A, st); return;
+        case RING128:
+            if constexpr (EPI == EPI_FC1) launch_ring<EPI, 2, 2, 2, 2, 1, 4, 3>(G, A, st);
+            else launch_ring<EPI, 2, 2, 2, 2, 2, 4, 2>(G, A, st);
+            return;
+        case TILE: break;
     }
     // the activation tile through LDS, output blocks over the waves and, while the grid is small, in groups over workgroups; a narrow layer
     // on few rows in 32-row tiles: twice the workgroups
