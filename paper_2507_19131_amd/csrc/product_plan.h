@@ -9,18 +9,23 @@ constexpr int CUS = 256;
 // FEW: gemm_few_kernel.  RING64, RING128: gemm_ring_kernel on 64 x 64 or 128 x 128 tiles.  TILE: gemm_tile_kernel.
 enum ProductForm { FEW, RING64, RING128, TILE };
 
-// The projection and FC2 at the widths of the wide blocks and mlp_ratio 4.  Over the number of 32 x 32 tiles, us, ring kernel / few-rows kernel:
-//   FC2         C = 512   128 tiles 5.8 / 3.9   256 6.0 / 4.3 | 512 6.3 / 6.1 alone, and 0.7 slower within a layer   640 6.5 / 7.6
-//               C = 768   192 7.4 / 4.5   384 7.8 / 6.7 | 576 8.0 / 8.9      C = 1024   256 9.1 / 5.4   512 10.1 / 8.6 | 768 10.7 / 11.9
+// The projection and FC2 with K of the wide blocks at mlp_ratio 4.  Alone, over the number of 32 x 32 tiles, us, ring kernel / few-rows kernel:
+//   FC2         C = 512   128 tiles 5.8 / 3.9   256 6.0 / 4.3   512 6.3 / 6.1   640 6.5 / 7.6      C = 768   192 7.4 / 4.5   384 7.8 / 6.7 |
+//               576 8.0 / 8.9      C = 1024   256 9.1 / 5.4   512 10.1 / 8.6 | 768 10.7 / 11.9
 //   projection  C = 512   128 3.6 / 3.6   256 3.7 / 3.7 | 512 3.9 / 4.5      C = 768   192 4.0 / 3.8 | 384 4.2 / 4.8
 //               C = 1024   256 4.6 / 4.0 | 512 4.8 / 5.3
+// Within a layer FC2's operands come from beyond the L2 (each XCD reads all rows for N / 256 blocks of channels: the likely reason why the line
+// lies lower for small N).  A stage of two blocks, us, ring / few rows:
+//   N = 512     K = 2048, 320 tiles 67.2 / 68.8   384 67.0 / 69.6      K = 3072   384 73.3 / 74.4   512 73.6 / 77.0      K = 4096   512 79.3 / 83.0
+//   N = 256     K = 2048, 320 74.0 / 78.3   384 74.2 / 78.7
+//   N = 768     K = 3072, 288 72.5 / 71.1   384 73.1 / 72.3      N = 1024   K = 2048, 512 76.1 both   K = 3072, 512 81.9 / 80.3   K = 4096, 512 85.9 / 84.9
 // FC1 has four times FC2's tiles of a quarter of its K and gains at none of the three widths past the smallest map (C = 512, 512 tiles 4.1 / 3.9;
 // C = 768, 768 tiles 4.7 / 5.3; C = 1024, 1024 tiles 5.3 / 6.7): it stays with the ring.
 inline bool product_of_few_rows(int epi, int rows, int N, int K)
 {
     const int wider = epi == EPI_FC2 ? 4 : 1, tiles = rows / 32 * (N / 32);
     return (epi == EPI_PROJ || epi == EPI_FC2) && N % 256 == 0 && (K == 512 * wider || K == 768 * wider || K == 1024 * wider) &&
-           tiles <= (epi == EPI_PROJ ? CUS : K <= 2048 ? 3 * CUS / 2 : 2 * CUS);
+           tiles <= (epi == EPI_PROJ || N < 768 ? CUS : 2 * CUS);
 }
 
 // Tiles of the ring kernel.  64 x 64: the fewest bytes in front of the first product and the most workgroups; 128 x 128: half the bytes per

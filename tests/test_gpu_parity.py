@@ -3,6 +3,7 @@ import numpy as np
 import pytest
 import torch
 
+import product_plan
 from paper_2507_19131_amd import synth
 
 pytestmark = pytest.mark.gpu
@@ -123,21 +124,43 @@ def test_sums_at_and_beyond_what_a_binary32_holds(C, heads, H, W, code, layers):
     gh.assert_parity(res)
 
 
-@pytest.mark.parametrize("B,H,W,C,keep,kw", [
-    (1, 42, 49, 512, 0.5, {}), (1, 43, 49, 512, 0.4, {}),               # FC1 on 256 and 320 tiles of 128 x 128
-    (2, 63, 105, 512, 0.4, {}),                                         # projection, FC1 and FC2 on 420, 1680 and 420: several tiles a workgroup, both branches
-    (1, 84, 98, 512, 1.0, {}),                                          # FC2 on 264, the projection on 64 x 64; one branch
-    (2, 84, 84, 768, 0.0, dict(bits=(4, 2), wbits=4)),                  # the other branch; rows of the pad
-    (1, 43, 49, 512, 0.4, dict(ranges={"a_fc2_in": (-0.07, 0.35)})),     # the cubic on both kinds of tiles
-    (1, 14, 14, 768, 0.25, dict(ranges={"a_fc2_in": (-0.07, 0.35)})), (1, 14, 14, 512, 0.25, dict(ranges={"a_fc2_in": (-0.07, 0.35)})),
-    (1, 21, 28, 512, 0.5, {}), (1, 21, 35, 512, 1.0, {}),               # FC2 on 384 and 480 tiles of 32 x 32, the second with one branch
-    (1, 14, 35, 768, 0.4, {}), (1, 14, 42, 768, 0.0, {}),               # on 480 and 576
-    (1, 14, 14, 1024, 0.5, {}), (1, 14, 28, 1024, 0.4, dict(bits=(4, 2), wbits=4)),   # the projection on 256 tiles, and FC2 with it, and on 512
-    (2, 14, 21, 768, 0.5, dict(mlp_ratio=1)), (1, 28, 35, 768, 0.5, dict(mlp_ratio=3)),
-    (2, 35, 35, 192, 0.5, dict(mlp_ratio=7)), (2, 70, 84, 192, 0.5, dict(mlp_ratio=5)), (1, 35, 35, 96, 0.5, dict(mlp_ratio=7))])
-def test_products_of_the_separate_kernels_at_their_lines(B, H, W, C, keep, kw):
-    """K in whole stages of the ring kernel on both sides of the line between its tiles, and the K that it does not take."""
-    spec, inp, x, k = _case(B, H, W, C, C // 32, 3, keep, 60, blobs=True, **kw)
+FEW, RING64, RING128, TILE = "few", "ring64", "ring128", "tile"
+
+
+@pytest.mark.parametrize("B,H,W,C,keep,kw,forms", [                     # forms: of the projection, FC1 and FC2
+    # C = 512: the projection and FC2 on 256 and 320 tiles of 32 x 32; FC1 on 256 and 272 tiles of 128 x 128; FC2 on 256 and 260; the projection on
+    # 384 and 388
+    (1, 14, 35, 512, 1.0, {}, (FEW, RING64, FEW)), (1, 7, 91, 512, 1.0, {}, (RING64, RING64, RING64)),
+    (1, 35, 56, 512, 0.5, {}, (RING64, RING64, RING64)), (1, 28, 77, 512, 1.0, {}, (RING64, RING128, RING64)),
+    (1, 7, 1169, 512, 1.0, {}, (RING64, RING128, RING64)), (1, 84, 98, 512, 1.0, {}, (RING64, RING128, RING128)),
+    (1, 70, 175, 512, 1.0, {}, (RING64, RING128, RING128)), (1, 77, 161, 512, 1.0, {}, (RING128, RING128, RING128)),
+    (1, 42, 49, 512, 0.5, {}, (RING64, RING128, RING64)), (1, 43, 49, 512, 0.4, {}, (RING64, RING128, RING64)),
+    (1, 21, 28, 512, 0.5, {}, (RING64, RING64, RING64)), (1, 21, 35, 512, 1.0, {}, (RING64, RING64, RING64)),
+    (2, 63, 105, 512, 0.4, {}, (RING128, RING128, RING128)),            # 420, 1680 and 420 tiles: several a workgroup, both branches
+    # C = 768: the projection on 192 and 288 tiles of 32 x 32; FC2 on 480 and 576; FC1 on 240 and 264 of 128 x 128
+    (1, 7, 35, 768, 1.0, {}, (FEW, RING64, FEW)), (1, 7, 49, 768, 0.0, {}, (RING64, RING64, FEW)),
+    (1, 14, 35, 768, 0.4, {}, (RING64, RING64, FEW)), (1, 14, 42, 768, 0.0, {}, (RING64, RING64, FEW)), (1, 14, 49, 768, 1.0, {}, (RING64, RING64, RING64)),
+    (1, 14, 91, 768, 1.0, {}, (RING64, RING64, RING64)), (1, 28, 49, 768, 1.0, {}, (RING64, RING128, RING64)),
+    (2, 84, 84, 768, 0.0, dict(bits=(4, 2), wbits=4), (RING128, RING128, RING128)),   # the other branch; rows of the pad
+    # C = 1024: the projection on 256 and 384 tiles of 32 x 32; FC2 on 512 and 640; FC1 on 256 and 288 of 128 x 128
+    (1, 14, 14, 1024, 0.5, {}, (FEW, RING64, FEW)), (1, 7, 49, 1024, 1.0, {}, (RING64, RING64, FEW)),
+    (1, 14, 28, 1024, 0.4, dict(bits=(4, 2), wbits=4), (RING64, RING64, FEW)), (1, 7, 91, 1024, 1.0, {}, (RING64, RING64, RING64)),
+    (1, 28, 35, 1024, 0.5, {}, (RING64, RING64, RING64)), (1, 7, 161, 1024, 0.0, {}, (RING64, RING128, RING64)),
+    # the cubic on both kinds of tiles
+    (1, 43, 49, 512, 0.4, dict(ranges={"a_fc2_in": (-0.07, 0.35)}), (RING64, RING128, RING64)),
+    (1, 14, 14, 768, 0.25, dict(ranges={"a_fc2_in": (-0.07, 0.35)}), (RING64, RING64, FEW)),
+    (1, 14, 14, 512, 0.25, dict(ranges={"a_fc2_in": (-0.07, 0.35)}), (FEW, RING64, FEW)),
+    # other hidden widths: K that the few-rows kernel has not, N = 512 and 256 on both sides of its line, and K that the ring has not
+    (2, 14, 21, 768, 0.5, dict(mlp_ratio=1), (RING64, RING64, RING64)), (1, 28, 35, 768, 0.5, dict(mlp_ratio=3), (RING64, RING64, RING64)),
+    (1, 14, 35, 512, 1.0, dict(mlp_ratio=6), (FEW, RING64, FEW)), (1, 7, 91, 512, 1.0, dict(mlp_ratio=6), (RING64, RING64, RING64)),
+    (1, 28, 35, 256, 0.5, dict(mlp_ratio=8), (TILE, TILE, FEW)), (1, 35, 35, 256, 0.5, dict(mlp_ratio=8), (TILE, TILE, RING64)),
+    (1, 14, 14, 1024, 0.5, dict(mlp_ratio=2), (FEW, RING64, FEW)),
+    (2, 35, 35, 192, 0.5, dict(mlp_ratio=7), (TILE, TILE, TILE)), (2, 70, 84, 192, 0.5, dict(mlp_ratio=5), (TILE, TILE, TILE)),
+    (1, 35, 35, 96, 0.5, dict(mlp_ratio=7), (TILE, TILE, TILE))])
+def test_products_of_the_separate_kernels_at_their_lines(B, H, W, C, keep, kw, forms):
+    """The kernels of the linear layers on both sides of the lines between them; which one a case takes is asked of the library's own rule."""
+    spec, inp, x, k = _case(B, H, W, C, C // 32, 3 if H > 7 else 0, keep, 60, blobs=True, **kw)
+    assert product_plan.forms(spec, k) == forms
     print("products", B, H, W, C, keep, kw, flush=True)
     res = gh.compare_block(inp, x, k, taps=("acc_proj", "h", "a_fc1_in", "a_fc2_in", "acc_fc2"))
     print(res, flush=True)
