@@ -4,6 +4,7 @@ import pytest
 import torch
 
 import product_plan
+import wide_sums
 from paper_2507_19131_amd import synth
 
 pytestmark = pytest.mark.gpu
@@ -105,23 +106,28 @@ def test_gelu_codes_by_steps_and_by_the_cubic(C, heads, H, W, shift, bits, hidde
     gh.assert_parity(res)
 
 
-@pytest.mark.parametrize("C,heads,H,W,code,layers", [
-    (128, 4, 20, 27, 127, "all"),                             # the widest sums of any block of 128 channels: 2^22 less 49 000
-    (256, 8, 20, 28, 64, "all"), (256, 8, 20, 28, 65, "all"), # 16 000 under the bound, and above it
-    (192, 6, 20, 27, 127, ("w_qkv",)), (192, 6, 20, 27, 127, ("w_proj",)), (192, 6, 20, 27, 127, ("w_fc1",)),
-    (384, 12, 50, 84, 127, "all"), (512, 16, 21, 28, 127, "all")])
-def test_sums_at_and_beyond_what_a_binary32_holds(C, heads, H, W, code, layers):
-    """Weights of one magnitude: sums that the kernels take as binary32 without a conversion reach the bound of that
-    form, and blocks beyond it convert.  A map of wide values saturates the LayerNorm codes, so that sums come near their bound."""
-    spec, inp, x, k = _case(2, H, W, C, heads, 3, 0.5, 58, blobs=True, ranges={"a_qkv_in": (-0.02, 3.0), "a_fc1_in": (-0.02, 3.0), "a_proj_in": (-0.01, 0.4)})
-    rng = np.random.default_rng(59)
-    for n in ("w_qkv", "w_proj", "w_fc1") if layers == "all" else layers:
-        w = getattr(inp.shared, n)
-        setattr(inp.shared, n, np.where(rng.random(w.shape) < (0.5 if code < 127 else 0.9), code, -code).astype(w.dtype))
-    print("sums", C, code, layers, flush=True)
-    res = gh.compare_block(inp, x, k)
+AT, OVER, FAR = wide_sums.WIDEST, wide_sums.WIDEST + 1, 20480           # widths of rows: 8-bit sums of 2^22 less 64, 2^22 and 191, 1.25 * 2^22
+
+
+@pytest.mark.parametrize("C,H,W,widths,sign,bits", [                    # widths of the rows of w_qkv, w_proj and w_fc1
+    (96, 26, 33, (12288,) * 3, 1, (8, 8)), (128, 20, 27, (16384,) * 3, 1, (8, 4)),   # the widest rows of these widths: never beyond
+    (192, 20, 27, (AT,) * 3, 1, (8, 4)), (192, 20, 27, (AT,) * 3, -1, (8, 8)), (192, 20, 27, (OVER,) * 3, 1, (8, 4)), (192, 20, 27, (OVER,) * 3, -1, (8, 4)),
+    (192, 20, 27, (FAR, AT, AT), 1, (8, 4)), (192, 20, 27, (AT, FAR, AT), 1, (8, 4)), (192, 20, 27, (AT, AT, FAR), 1, (8, 4)),
+    (192, 20, 27, (FAR, AT, AT), -1, (8, 4)), (192, 20, 27, (AT, FAR, AT), -1, (8, 4)), (192, 20, 27, (AT, AT, FAR), -1, (4, 8)),
+    (256, 20, 28, (AT,) * 3, 1, (8, 4)), (256, 20, 28, (FAR,) * 3, 1, (8, 4)),
+    (384, 20, 27, (AT,) * 3, 1, (8, 4)), (384, 50, 84, (AT,) * 3, -1, (8, 4)), (384, 50, 84, (FAR,) * 3, 1, (8, 4)),     # 32 and 64 rows
+    (512, 21, 28, (AT,) * 3, 1, (8, 4)), (512, 21, 28, (FAR,) * 3, -1, (8, 4)), (512, 49, 56, (AT, FAR, FAR), 1, (8, 4)), (512, 49, 56, (FAR,) * 3, 1, (8, 4)),
+    (768, 42, 49, (AT,) * 3, 1, (8, 4)), (768, 42, 49, (FAR, AT, AT), -1, (8, 4)), (1024, 21, 56, (AT,) * 3, 1, (8, 4)), (1024, 35, 49, (FAR,) * 3, 1, (8, 4))])
+def test_sums_at_and_beyond_what_a_binary32_holds(C, H, W, widths, sign, bits):
+    """Sums of q, k, v, the projection and FC1 that the kernels take as binary32 without a conversion, up to the bound of that form, and
+    blocks beyond it, which convert (tests/test_wide_sums.py: the sums reach these sizes, and taking them for their own bits would show)."""
+    spec = synth.BlockSpec(2 if C <= 512 else 1, H, W, C, C // 32, shift=3, act_bits_high=bits[0], act_bits_low=bits[1])
+    inp, x = wide_sums.make_inputs(spec, widths, sign), synth.make_feature_map(spec, 58, blobs=True)
+    print("sums", C, H, W, widths, sign, bits, flush=True)
+    res = gh.compare_block(inp, x, spec.nW // 2)
     print(res, flush=True)
     gh.assert_parity(res)
+    assert res["y_bit_identical"] and res["h_maxabs"] == 0, res
 
 
 FEW, RING64, RING128, TILE = "few", "ring64", "ring128", "tile"
