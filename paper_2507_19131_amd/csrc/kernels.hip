@@ -1052,6 +1052,9 @@ constexpr bool win_pairs_share(int NH, int HG) { return (NH == 6 && HG == 1) || 
 // tokens.  Each weight fragment of q and k then passes the L1 once and feeds two independent products, and its constants are read once.
 // Against q, k and v each split by tokens, window kernel with LN1, us: 25 windows at C = 1024 20.0 -> 18.3, 24 at 768 15.7 -> 15.0, 4 at 512
 // 12.4 -> 11.5, 96 at 384 15.2 -> 14.5, 196 at 192 14.8 -> 14.4, 64 at 128 7.8 -> 7.5; two blocks on 64 windows at C = 96 32.3 -> 31.9.
+// Wide blocks, one wave per head (CODES, QS = 1): four waves per SIMD, at C = 768 three, which is what LDS leaves; one register of 128 is spilled
+// at C = 512, none at 768, and none at 1024 with the weights four fragments ahead.  (Eight ahead spilled 33: 33 windows 25.5 -> 22.9 us, 48
+// 29.6 -> 26.5, 100 48.6 -> 44.0, 200 85.6 -> 77.5, 288 109.5 -> 99.4.  At C = 512 and 768 four are equal up to 200 windows and 2 % behind beyond.)
 // BESIDE (C = 96, beside a second chain; see window_beside): pairs without roles.  With their 126 registers a CU has places for two workgroups
 // of six waves, both taken by the first chain, and what is left of the second one waits behind that chain's token kernel; with 87
 // it has a third.  Four blocks on 760 windows 129 -> 126 us, 874 147 -> 135, 960 149 -> 140, 1012 163 -> 146.  And one wave per head at
@@ -1059,7 +1062,7 @@ constexpr bool win_pairs_share(int NH, int HG) { return (NH == 6 && HG == 1) || 
 constexpr bool win_roles(int NH, int HG, int QS, bool CODES, bool BESIDE) { return QS == 2 && !BESIDE && (CODES || !win_pairs_share(NH, HG)); }
 constexpr int win_waves_per_eu(int NH, int HG, int QS, bool CODES, bool BESIDE)
 {
-    if (CODES) return QS == 1 ? 4 : 2;
+    if (CODES) return QS == 2 ? 2 : HG == 6 ? 3 : 4;
     if (QS == 2) return win_pairs_share(NH, HG) ? 6 : BESIDE ? 5 : NH == 6 ? 3 : 4;
     return NH * HG > 8 ? 3 : NH == 3 && !BESIDE ? 5 : 4;
 }
@@ -1105,7 +1108,7 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
     // them share a CU: six blocks on 81 windows at C = 192 147 -> 133 us, three sets in turn of two blocks on 64 windows at
     // C = 128 36.7 -> 33.8.)
     constexpr bool STREAM = KS >= 12 || (HG == 1 ? !(NH == 3 && QS == 1) : KS < 8);
-    constexpr int RING = !STREAM ? (KS < 6 ? KS : 6) : KS < 6 ? KS : KS == 6 ? (QS == 1 ? 6 : 3) : KS == 12 ? 6 : KS < 32 || QS == 1 ? 8 : 16;
+    constexpr int RING = !STREAM ? (KS < 6 ? KS : 6) : KS < 6 ? KS : KS == 6 ? (QS == 1 ? 6 : 3) : KS == 12 ? 6 : KS < 32 ? 8 : QS == 1 ? 4 : 16;
     static_assert(!STREAM || KS % RING == 0, "each chain starts at ring slot 0");
     constexpr int O_START = MAGIC ? SUM_MAGIC_BITS : 0;                  // of the P.V sums: 49 * 255 * 128 at most
     v4i ring[RING];

@@ -67,3 +67,11 @@ def test_forms_of_three_heads_beside_a_second_chain(kernels, scored, magic):
     assert workgroups_per_cu(kernels[_window(3, 0, scored, 1, 2, 0, magic, 1)]) == 3
     single = kernels[_window(3, 0, scored, 1, 1, 0, magic, 1)]
     assert workgroups_per_cu(single) == 5 and single[".vgpr_spill_count"] == 0
+
+
+@pytest.mark.parametrize("magic", [0, 1])
+@pytest.mark.parametrize("NH,HG,workgroups,spilled", [(4, 4, 4, 1), (4, 6, 3, 0), (8, 4, 2, 0)])
+def test_wide_forms_of_one_wave_per_head(kernels, NH, HG, workgroups, spilled, magic):
+    """C = 512, 768 and 1024 beyond 256 workgroups of pairs: the workgroups a CU holds, and at most the named registers in scratch memory."""
+    k = kernels[_window(NH, 0, 0, HG, 1, 1, magic, 0)]
+    assert workgroups_per_cu(k) == workgroups and k[".vgpr_spill_count"] <= spilled
