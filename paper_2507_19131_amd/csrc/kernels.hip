@@ -377,9 +377,9 @@ __device__ __forceinline__ void epilogue(const GemmArgs& A, const Geom& G, int b
     if (EPI == EPI_FC1) *(v4i*)(A.out8 + (((size_t)(row >> 5) * (N / 32) + nb) * 64 + g * 32 + (row & 31)) * 16) = (v4i){codes[0], codes[1], codes[2], codes[3]};
 }
 
-// One workgroup per tile of RT rows and group of output blocks (all of them once the tiles alone fill the chip).  For the short or odd K of
-// narrow blocks off the fused path: K = C up to 384, and hidden widths up to 1344 that are no multiple of 128.  The activations come
-// as MFMA operand fragments ([32 rows][K slab][64 lanes][16 bytes], written so by their producers), so a tile is a contiguous run of
+// One workgroup per tile of RT rows and group of output blocks (all of them once the tiles alone fill the chip).  For what the
+// other two do not take (see product_form): K below 512 or no multiple of 128, or N no multiple of 64; the longest K is 1344.  The activations
+// come as MFMA operand fragments ([32 rows][K slab][64 lanes][16 bytes], written so by their producers), so a tile is a contiguous run of
 // memory: it goes to LDS by direct loads, no register in between, all of them in flight together.  Wave w computes the
 // output blocks first + w, first + w + 4, ... of the group; its weight fragments stream through a ring of D loads that
 // starts before anything else and runs on across the output blocks.
@@ -484,8 +484,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RT * KMAX <
 // channels, wave (wy, wx) the RB x NBW blocks of its corner, so that an operand fragment read from LDS feeds RB or NBW products
 // instead of one or two, and a byte from the caches RT or NT of them: see product_form for the times.  K passes in stages of KSL slabs through a ring
 // of S LDS buffers filled by direct loads; a stage is requested S - 1 stages ahead, into the buffer that all waves have left at the barrier
-// in front of it, and that barrier is the only one of a stage.  The residual is requested ahead of the last S - 2 stages, a further tile's
-// first stages ahead of the epilogue.
+// in front of it, and that barrier is the only one of a stage.  The residual is requested ahead of the last S - 2 stages and travels under
+// their products, a further tile's first stages ahead of the epilogue: they travel under FC1's.  In the projection's and FC2's the residual's quads are
+// awaited one by one between stores that the compiler cannot count (each depends on a tap or a pixel) and behind loads it does not know of;
+// the counter goes down in order, so from the second quad on a wait includes the tile's own earlier stores, and the last one those stages too.
 // What bounds it: on many rows the epilogue's memory (the projection on 19 712 rows at C = 768 33 us, of them 26 its maps at the rate of a
 // copy; without any epilogue 14) and the GELU; on few, the ramp of launch, first loads and the chain of stages.
 // The direct loads are asm: as a builtin every LDS read behind them waits for all of them.
@@ -621,7 +623,7 @@ __global__ __launch_bounds__(WY * WX * 64) __attribute__((amdgpu_waves_per_eu(WP
         if (tile + step < last) {
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");           // this wave's reads of the ring have returned
             group_barrier();
-            begin(tile + step, par ^ 1);                                 // travels under the epilogue
+            begin(tile + step, par ^ 1);                                 // ahead of the epilogue
         }
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb)
@@ -642,8 +644,9 @@ __global__ __launch_bounds__(WY * WX * 64) __attribute__((amdgpu_waves_per_eu(WP
 
 // The same products for few rows: one workgroup of eight waves per 32 x 32 outputs, each wave every eighth slab of K, SPW of them, its operands
 // straight from memory to registers, as many requested at once as 72 registers hold (all of FC2's: 768 channels, 384 tiles 6.7 -> 7.2 us); the
-// eight partial sums meet in LDS, and wave w < 4 finishes quad w of every lane's sixteen.  No stage, no barrier but one, and four times the workgroups of the ring kernel's smaller tiles, whose 430 clocks
-// a stage of 128 bytes of K are their way through the L1 and LDS: see product_of_few_rows for the times.
+// eight partial sums meet in LDS, and wave w < 4 finishes quad w of every lane's sixteen.  No stage, no barrier but one, and four times the
+// workgroups of the ring kernel's smaller tiles, whose 430 clocks a stage of 128 bytes of K are their way through the L1 and LDS: see
+// product_of_few_rows for the times.
 template <int EPI, int SPW>
 __global__ __launch_bounds__(512) void gemm_few_kernel(Geom G, GemmArgs A)
 {
@@ -1401,13 +1404,16 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
 //   proj + first residual (wave w owns channels 32w..32w+31) -> LN2 with statistics exchanged through LDS -> quantize -> FC1 +
 //   GELU + quantize, codes to LDS as fragments -> FC2 + second residual -> scatter to the map.
 // The weight fragments of the whole kernel form ONE stream per wave that is requested RING fragments ahead across every phase
-// boundary; the per-branch parameter block and the GELU table (of steps, or with SHORT off of cubics) sit in LDS.  The FFN runs in four chunks of NH hidden blocks: FC1 +
-// GELU + quantize of a chunk goes to one of two LDS buffers, then FC2 accumulates that chunk.  With two row blocks h is parked in
-// the output map between the first and the second residual (the same thread writes and re-reads the same address).
+// boundary; the per-branch parameter block and the GELU table (of steps, or with SHORT off of cubics) sit in LDS.  The FFN runs in
+// four chunks of NH hidden blocks: FC1 + GELU + quantize of a chunk goes to one of two LDS buffers, then FC2 accumulates that chunk.
+// With two row blocks h is parked in the output map between the first and the second residual (the same thread writes and re-reads the
+// same address).
 // Bound: vector instructions (51 to 62 % of the cycles) and LDS reads (43 to 54 %) that do not overlap fully at C = 96 and 128 on large
-// maps, the weights at 64 bytes per clock and CU at C = 384, the chain of phases on few tiles.  Against a form with the chunks unrolled and FC1's weights a block ahead, which the three, four
-// and eight waves had: stage of two blocks on 8 x 1392 windows at C = 96, 5476 at C = 128 and 1444 at C = 256 3 % shorter, 64
-// windows at C = 256 58.9 -> 52.7 us.
+// maps, the weights at 64 bytes per clock and CU at C = 384, the chain of phases on few tiles.  Against a form with the chunks unrolled
+// and FC1's weights a block ahead, which the three, four and eight waves had: stage of two blocks on 8 x 1392 windows at C = 96, 5476
+// at C = 128 and 1444 at C = 256 3 % shorter, 64 windows at C = 256 58.9 -> 52.7 us.
+// SHORT: the table of steps and the sums of the projection and FC1 without a conversion, together, or neither: a block whose FC2 input has
+// no table (8 bits on a range narrower than about 0.5) in one branch, or whose sums are not bounded, runs as it did before both.
 // LN2's partial sums are read together and each by one half of the lanes, for both row blocks before either goes on, and the
 // parked h is requested ahead of the last products: 2 x 50 x 84 x 384 (six blocks) 347.4 -> 340.6 us, of 64-row tiles' 72 k clocks
 // these phases had taken 15 k and 7 k.

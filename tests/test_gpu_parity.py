@@ -83,8 +83,8 @@ def test_independent_biases_per_branch(C, heads, bits, wbits, shift, fused):
 
 @pytest.mark.parametrize("C,heads,mlp_ratio", [(96, 3, 3), (96, 3, 1), (192, 6, 3), (128, 4, 2), (96, 3, 8), (768, 24, 7)])
 def test_other_mlp_ratios(C, heads, mlp_ratio):
-    """FFN widths other than 4C run the seven-kernel path; hidden sizes that are not a whole number of
-    ring turns of the GEMM (9 or 3 slabs of 32) included, and K = 5376, which goes through LDS in seven chunks of 768."""
+    """FFN widths other than 4C run the separate kernels: hidden sizes that are not a whole number of ring turns of the tile
+    kernel (9 or 3 slabs of 32), K = 768 with an N = 96 that the ring kernel does not take, and K = 5376, 42 stages of that one."""
     spec, inp, x, k = _case(2, 20, 27, C, heads, 3, 0.5, 52, blobs=True, mlp_ratio=mlp_ratio)
     print("mlp_ratio", mlp_ratio, "C", C, flush=True)
     res = gh.compare_block(inp, x, k)
@@ -174,9 +174,9 @@ def test_products_of_the_separate_kernels_at_their_lines(B, H, W, C, keep, kw, f
 
 
 def test_long_k_on_a_few_hundred_row_tiles():
-    """FC2 with K = 3072 on 111 64-row tiles: the GEMM keeps the whole K of a 32-row tile in LDS (222 tiles)."""
+    """FC2 with K = 3072 behind a projection and an FC1 of the tile kernel: 112 x 6 tiles of 64 x 64, 24 stages of the ring kernel."""
     spec, inp, x, k = _case(2, 50, 60, 384, 12, 3, 0.5, 54, blobs=True, mlp_ratio=8)
-    assert spec.B * spec.nW * 49 > 64 * 64
+    assert product_plan.rows(spec, k) == 112 * 64 and product_plan.forms(spec, k) == (TILE, TILE, RING64)
     print("long K on many tiles", flush=True)
     res = gh.compare_block(inp, x, k)
     print(res, flush=True)
