@@ -1055,8 +1055,9 @@ constexpr bool win_pairs_share(int NH, int HG) { return (NH == 6 && HG == 1) || 
 // tokens.  Each weight fragment of q and k then passes the L1 once and feeds two independent products, and its constants are read once.
 // Against q, k and v each split by tokens, window kernel with LN1, us: 25 windows at C = 1024 20.0 -> 18.3, 24 at 768 15.7 -> 15.0, 4 at 512
 // 12.4 -> 11.5, 96 at 384 15.2 -> 14.5, 196 at 192 14.8 -> 14.4, 64 at 128 7.8 -> 7.5; two blocks on 64 windows at C = 96 32.3 -> 31.9.
-// Wide blocks, one wave per head (CODES, QS = 1): four waves per SIMD, at C = 768 three, which is what LDS leaves; one register of 128 is spilled
-// at C = 512, none at 768, and none at 1024 with the weights four fragments ahead.  (Eight ahead spilled 33: 33 windows 25.5 -> 22.9 us, 48
+// Wide blocks, one wave per head (CODES, QS = 1): four waves per SIMD, at C = 768 three: a workgroup takes 42 of a CU's 128 LDS units of 1280 bytes.
+// (With V's column sums in 512 bytes of their own it was 43, and a CU held two: two blocks on 90 windows 184.6 -> 178.6 us, 168 258 -> 254, 360
+// 507 -> 496; 64 137.5 both.)  None spills, at 1024 with the weights four fragments ahead.  (Eight ahead spilled 33: 33 windows 25.5 -> 22.9 us, 48
 // 29.6 -> 26.5, 100 48.6 -> 44.0, 200 85.6 -> 77.5, 288 109.5 -> 99.4.  At C = 512 and 768 four are equal up to 200 windows and 2 % behind beyond.)
 // BESIDE (C = 96, beside a second chain; see window_beside): pairs without roles.  With their 126 registers a CU has places for two workgroups
 // of six waves, both taken by the first chain, and what is left of the second one waits behind that chain's token kernel; with 87
@@ -1097,7 +1098,8 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
     static_assert(CODES || NW * GPW >= TOK, "one pass must cover the window");
     __shared__ v4i a1s[2 * KS * 64];                                     // LN1 codes as fragments [token block][k slab][lane]
     __shared__ __attribute__((aligned(16))) float prm[PR::WORDS];        // this branch's LN1 affine and QKV epilogue constants
-    __shared__ __attribute__((aligned(16))) int csum[NW][HD];
+    constexpr bool SUMS_IN_PRM = CODES && QS == 1;                       // the V column sums of a wave's head take the place of its q multipliers, long read
+    __shared__ __attribute__((aligned(16))) int csum[SUMS_IN_PRM ? 1 : NW][HD];
     __shared__ v4i kvx[QS == 2 ? NH * PAIR_SLOTS * 64 : 1];              // k and v operands of a wave pair [head][k|v][token block][lane], with ROLES q of the second block
     __shared__ int csp[QS == 2 ? NH * 2 * HD : 1];                       // V column sums of each token block [head][block][dim]
     __shared__ int red[NW];
@@ -1269,6 +1271,7 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
         }
     };
     const size_t canon_row0 = (size_t)canon_slot * TOK;
+    int* const column_sums = SUMS_IN_PRM ? (int*)(prm + PR::HEADS + hw * PR::PER_HEAD) : csum[wave];
     v4i qk[2][NTQ] = {};                                                 // [q|k][token block]; with ROLES the wave's own in [1]
 #pragma unroll 1
     for (int which = role; which < (ROLES ? role + 1 : 2); ++which) {
@@ -1354,7 +1357,7 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
             bias.request(A.bias2 + (size_t)(mask_type(G, w) * NHT + head) * BIAS_QUADS * 64 + g * 64 + j, g, tb0);
         cs = half_sum(cs);
         if (QS == 1) {
-            if (g == 0) csum[wave][j] = O_START - A.qp[branch].zp * cs;
+            if (g == 0) column_sums[j] = O_START - A.qp[branch].zp * cs;
         } else {                                                          // the pair exchanges its halves of K, V and the sums
             if (!ROLES) kvx[((hw * 2 + 0) * 2 + tb0) * 64 + lane] = qk[1][0];
             else if (role) { kvx[(hw * PAIR_SLOTS + 0) * 64 + lane] = qk[1][0]; kvx[(hw * PAIR_SLOTS + 1) * 64 + lane] = qk[1][NTQ - 1]; }
@@ -1362,7 +1365,7 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
             kvx[(hw * PAIR_SLOTS + 2 + tb0) * 64 + lane] = vt[0];
             if (g == 0) csp[(hw * 2 + tb0) * HD + j] = cs;
             __syncthreads();
-            if (g == 0) csum[wave][j] = O_START - A.qp[branch].zp * (csp[(hw * 2) * HD + j] + csp[(hw * 2 + 1) * HD + j]);
+            if (g == 0) column_sums[j] = O_START - A.qp[branch].zp * (csp[(hw * 2) * HD + j] + csp[(hw * 2 + 1) * HD + j]);
         }
     }
     v4i kf[2];
@@ -1372,13 +1375,13 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
         if (QS == 2) vt[kb] = kvx[(hw * PAIR_SLOTS + 2 + kb) * 64 + lane];
     }
     if (ROLES) qk[0][0] = role ? kvx[(hw * PAIR_SLOTS + PAIR_SLOTS - 1) * 64 + lane] : qk[1][0];
-    __builtin_amdgcn_s_waitcnt(0xc07f);                                   // lgkmcnt(0): the wave's own csum entries are in LDS
+    __builtin_amdgcn_s_waitcnt(0xc07f);                                   // lgkmcnt(0): the wave's own column sums are in LDS
     __builtin_amdgcn_wave_barrier();
     const int mtype = mask_type(G, w);
     AttnCore core;
     core.floor = (A.floor[branch] >> (mtype != 0)) & 1;
     core.c5 = in_vgpr(EXP2_C5);
-    core.nzcsum = csum[wave];
+    core.nzcsum = column_sums;
     core.bq = A.bias2 + (size_t)(mtype * NHT + head) * BIAS_QUADS * 64 + g * 64 + j;
     core.m2 = in_vgpr(A.m2[branch]);
     core.qp = in_vgpr(A.qp[branch]);
