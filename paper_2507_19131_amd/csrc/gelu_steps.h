@@ -22,7 +22,7 @@
 
 namespace mixaq {
 
-constexpr int GELU_STEP_PIECES = 13;                                // of 1 KB, 128 entries each: with the rest of its LDS five workgroups of the token kernel at C = 96 fit a CU
+constexpr int GELU_STEP_PIECES = 13;                                // of 1 KB, 128 entries each: five workgroups of the token kernel at C = 96 fit a CU, and more (see there)
 constexpr int GELU_STEP_MAX = GELU_STEP_PIECES * 128;
 constexpr float GELU_STEP_MAGIC = 0x1.8p23f;                          // adding it rounds to an integer, ties to even
 constexpr int GELU_STEP_MASK = 0x3ff8;                              // byte offset of an entry in the low bits of the index sum

@@ -1061,7 +1061,7 @@ constexpr bool win_pairs_share(int NH, int HG) { return (NH == 6 && HG == 1) || 
 // 29.6 -> 26.5, 100 48.6 -> 44.0, 200 85.6 -> 77.5, 288 109.5 -> 99.4.  At C = 512 and 768 four are equal up to 200 windows and 2 % behind beyond.)
 // BESIDE (C = 96, beside a second chain; see window_beside): pairs without roles.  With their 126 registers a CU has places for two workgroups
 // of six waves, both taken by the first chain, and what is left of the second one waits behind that chain's token kernel; with 87
-// it has a third.  Four blocks on 760 windows 129 -> 126 us, 874 147 -> 135, 960 149 -> 140, 1012 163 -> 146.  And one wave per head at
+// it has a third.  Four blocks on 722 windows 128 -> 124 us, 840 147 -> 134, 924 151 -> 139, 1012 164 -> 146.  And one wave per head at
 // four waves per SIMD, where it spills none with scores either.
 constexpr bool win_roles(int NH, int HG, int QS, bool CODES, bool BESIDE) { return QS == 2 && !BESIDE && (CODES || !win_pairs_share(NH, HG)); }
 constexpr int win_waves_per_eu(int NH, int HG, int QS, bool CODES, bool BESIDE)
@@ -1459,7 +1459,17 @@ __global__ __launch_bounds__(NH * 64) __attribute__((amdgpu_waves_per_eu(tok_wav
     using PR = TokPrm<C>;
     __shared__ v4i actf[RB * KS * 64];                                 // [row block][k slab][lane]
     __shared__ v4i gs[2][NH * RB * 64];                                // [buffer][hidden block of the chunk][row block][lane]
-    __shared__ double part[2][NH][32 * RB];
+    // LN2's partial sums, up to eight waves in the room of the hidden codes: the last sum is read ahead of the barrier in front of the FFN.
+    // LDS is given out in one piece of whole units, 128 of 1280 bytes, so a workgroup's size decides which ones share a CU.  At C = 96 five take
+    // 5 x 24 (with sums of their own 5 x 26, and a CU held four: 200 x 336 98.5 -> 95.4 us, 8 x 200 x 336 606 -> 594).  At C = 256 a second
+    // token workgroup has to fit behind one that lies behind a window workgroup of the other chain, 33 + 2 x 46.  (With the sums in 4 KB of
+    // their own the table of steps made it 49, and such a CU had one token workgroup until both were through: six blocks, two chains, 200
+    // windows 219.7 -> 203.3 us, 288 240 -> 229, 480 343 -> 321, 612 402 -> 401; before the table, 40 units, 211, 240, 332, 413.)  Twelve
+    // waves have a CU to themselves, and with 64 rows the shared room costs 12 spilled registers: two blocks on 840 windows 330 -> 358 us.
+    constexpr bool SUMS_IN_CODES = NH <= 8;
+    __shared__ double own_sums[SUMS_IN_CODES ? 1 : 2 * NH * 32 * RB];
+    auto& part = *reinterpret_cast<double (*)[2][NH][32 * RB]>(SUMS_IN_CODES ? (double*)gs[0] : own_sums);
+    static_assert(sizeof(part) <= sizeof(gs[0]), "in one buffer of the hidden codes");
     __shared__ __attribute__((aligned(16))) float prm[PR::WORDS];
     __shared__ float4 gtab[SHORT ? GELU_STEP_PIECES * 64 : GELU_TAB];
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, j = lane & 31, g = lane >> 5;
@@ -1915,9 +1925,9 @@ static WindowForm window_form(int heads, int windows, int computed, int chains)
 // C = 96 beside a second chain: the forms that leave it room (see win_roles): pairs, and one wave per head while the launch is more than three
 // and no more than five windows a CU.  There the two chains fall into step such that one's windows meet the tail of the other's token
 // kernel, and five workgroups of three waves on a CU, all of the launch at once, keep out of it better than six.  Five waves per SIMD ->
-// four, us, windows of both chains, two blocks / six:   1176 93.0 -> 91.9 / 227 -> 229   1260 95.7 -> 97.9 / 237 -> 243   1428 103.4 -> 105.5 /
-// 271 -> 268   1512 107.4 -> 108.5 / 279 -> 275 | 1554 114.5 -> 111.0 / 296 -> 288   1680 117.3 -> 113.1 / 309 -> 296   1848 122.4 -> 119.8 / 329 ->
-// 315   2016 131.8 -> 128.7 / 353 -> 336   2184 141.0 -> 137.2 / 388 -> 371   2352 152.7 -> 143.3 / 404 -> 386   2520 158.3 -> 153.3 / 435 -> 414 |
+// four, us, windows of both chains, two blocks / six:   1624 108.4 -> 108.0 / 276 -> 270   1740 112.8 -> 111.5 / 291 -> 282   1860 119.4 ->
+// 117.1 / 305 -> 295   2046 125.8 -> 125.7 / 327 -> 324   2244 132.9 -> 133.1 / 351 -> 343   2520 144.4 -> 144.5 / 385 -> 385.  Outside of
+// that, with the token kernel at four workgroups a CU instead of five:   1260 95.7 -> 97.9 / 237 -> 243   1428 103.4 -> 105.5 / 271 -> 268 |
 // 2856 172.8 -> 170.2 / 473 -> 476   4 x 1392 315.9 -> 318.4 / 864 -> 870
 static bool window_beside(WindowForm form, int windows, int chains) { return chains > 1 && (form == PAIR || (windows > 3 * CUS && windows <= 5 * CUS)); }
 void launch_window(const Geom& G, const WinArgs& A, int chains, hipStream_t st)

@@ -80,3 +80,24 @@ def test_wide_forms_of_one_wave_per_head(kernels, NH, HG, workgroups, magic):
     scratch memory."""
     k = kernels[_window(NH, 0, 0, HG, 1, 1, magic, 0)]
     assert workgroups_per_cu(k) == workgroups and k[".vgpr_spill_count"] == 0
+
+
+def _token(NH, RB, steps):
+    return "_ZN5mixaq12token_kernelILi%dELi%dELb0ELb%dEEEvNS_4GeomENS_7TokArgsE" % (NH, RB, steps)
+
+
+@pytest.mark.parametrize("steps", [0, 1])
+@pytest.mark.parametrize("NH,RB,workgroups", [(3, 1, 5), (4, 1, 4), (6, 1, 2), (8, 1, 2), (12, 1, 1), (12, 2, 1)])
+def test_token_workgroups_of_a_cu(kernels, NH, RB, workgroups, steps):
+    """As many with the table of steps as with the smaller one of cubics: what the registers hold."""
+    k = kernels[_token(NH, RB, steps)]
+    assert workgroups_per_cu(k) == 4 * waves_per_simd(k) // NH == workgroups
+
+
+@pytest.mark.parametrize("scored,magic", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("steps", [0, 1])
+def test_token_workgroups_beside_a_window_of_a_second_chain(kernels, steps, scored, magic):
+    """C = 256: a CU's registers hold two token workgroups, or one beside a window workgroup of the other chain.  A token workgroup that lies behind
+    a window workgroup leaves room for a second one behind itself; otherwise the CU has one until both are through."""
+    window = kernels[_window(4, 0, scored, 2, 2, 0, magic, 0)]
+    assert lds_units(window) + 2 * lds_units(kernels[_token(8, 1, steps)]) <= LDS_UNITS
