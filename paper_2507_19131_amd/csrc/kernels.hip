@@ -1271,7 +1271,7 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
         }
     };
     const size_t canon_row0 = (size_t)canon_slot * TOK;
-    int* const column_sums = SUMS_IN_PRM ? (int*)(prm + PR::HEADS + hw * PR::PER_HEAD) : csum[wave];
+    auto column_sums = [&]() -> int* { return SUMS_IN_PRM ? (int*)(prm + PR::HEADS + hw * PR::PER_HEAD) : csum[wave]; };
     v4i qk[2][NTQ] = {};                                                 // [q|k][token block]; with ROLES the wave's own in [1]
 #pragma unroll 1
     for (int which = role; which < (ROLES ? role + 1 : 2); ++which) {
@@ -1357,7 +1357,7 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
             bias.request(A.bias2 + (size_t)(mask_type(G, w) * NHT + head) * BIAS_QUADS * 64 + g * 64 + j, g, tb0);
         cs = half_sum(cs);
         if (QS == 1) {
-            if (g == 0) column_sums[j] = O_START - A.qp[branch].zp * cs;
+            if (g == 0) column_sums()[j] = O_START - A.qp[branch].zp * cs;
         } else {                                                          // the pair exchanges its halves of K, V and the sums
             if (!ROLES) kvx[((hw * 2 + 0) * 2 + tb0) * 64 + lane] = qk[1][0];
             else if (role) { kvx[(hw * PAIR_SLOTS + 0) * 64 + lane] = qk[1][0]; kvx[(hw * PAIR_SLOTS + 1) * 64 + lane] = qk[1][NTQ - 1]; }
@@ -1365,7 +1365,7 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
             kvx[(hw * PAIR_SLOTS + 2 + tb0) * 64 + lane] = vt[0];
             if (g == 0) csp[(hw * 2 + tb0) * HD + j] = cs;
             __syncthreads();
-            if (g == 0) column_sums[j] = O_START - A.qp[branch].zp * (csp[(hw * 2) * HD + j] + csp[(hw * 2 + 1) * HD + j]);
+            if (g == 0) column_sums()[j] = O_START - A.qp[branch].zp * (csp[(hw * 2) * HD + j] + csp[(hw * 2 + 1) * HD + j]);
         }
     }
     v4i kf[2];
@@ -1381,7 +1381,7 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
     AttnCore core;
     core.floor = (A.floor[branch] >> (mtype != 0)) & 1;
     core.c5 = in_vgpr(EXP2_C5);
-    core.nzcsum = column_sums;
+    core.nzcsum = column_sums();
     core.bq = A.bias2 + (size_t)(mtype * NHT + head) * BIAS_QUADS * 64 + g * 64 + j;
     core.m2 = in_vgpr(A.m2[branch]);
     core.qp = in_vgpr(A.qp[branch]);
