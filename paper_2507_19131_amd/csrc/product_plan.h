@@ -39,11 +39,20 @@ inline bool product_of_few_rows(int epi, int rows, int N, int K)
 //   projection  C = 768    12 4.1 / 8.2 (5.2)   168 9.1 / 10.5 (11.1)   330 15.3 / 16.2 (18.7)   924 34.3 / 33.4 (39.4)
 //               C = 512    152 7.8 / 8.9 (10.5)   420 15.6 / 15.6 (18.5)      C = 1024   312 15.4 / 18.2 (20.7)   888 37.8 / 37.4 (40.5)
 // 64 x 128, 128 x 256 and 256 x 128 tiles lie between the two or behind them everywhere but at T = 330 (14.6 and 29.4).
+// N = 128 (FC2 at C = 128): between one and five and a third 64 x 64 tiles a CU gemm_tile_kernel, whose four waves take a row tile's channels at
+// once, where the ring's tiles pass the rows twice.  A stage of two blocks, us, tile / ring, K = 640, 768, 896 and 1024:
+//   121 windows 66.3 / 63.5   69.1 / 66.4   73.3 / 69.5   74.0 / 70.7      156 69.4 / 68.4   72.5 / 72.1   73.3 both   73.6 / 74.2 |
+//   182 74.2 / 75.7   74.1 / 77.1   76.2 / 78.5   79.1 / 81.9      324 85.2 / 85.1   89.6 / 92.0   93.0 / 96.3   95.0 / 96.7
+//   506 113.3 / 112.2   120.3 / 125.0   127.0 / 130.6   133.3 / 137.7      650 129.5 / 131.6   134.0 / 140.1   142.5 / 146.8   148.8 / 149.5
+//   870 164.9 / 165.1   172.4 / 174.6   182.7 / 183.8   189.3 / 191.2 |    960 176.3 / 172.0   182.8 / 179.9   187.6 / 187.2   195.0 / 196.0
+//   1122 205.7 / 202.7   217.1 / 209.7   230.7 / 220.5   242.0 / 228.9
+// Other widths have no such range (N = 192 650 windows 241 / 206, N = 256 309 / 267).
 inline ProductForm product_form(int epi, int rows, int N, int K)
 {
     if (K < 512 || K % 128 || N % 64) return TILE;                   // the ring takes whole stages and tiles, at least as many stages as it holds
     if (product_of_few_rows(epi, rows, N, K)) return FEW;
     const int tiles128 = N % 128 == 0 ? rows / 128 * (N / 128) : 0;
+    if (N == 128 && 4 * tiles128 > CUS && 3 * tiles128 <= 4 * CUS && K <= 1024) return TILE;
     return tiles128 <= (epi == EPI_FC1 || K > 1024 ? CUS : 3 * CUS / 2) ? RING64 : RING128;
 }
 

@@ -161,6 +161,10 @@ FEW, RING64, RING128, TILE = "few", "ring64", "ring128", "tile"
     (1, 14, 35, 512, 1.0, dict(mlp_ratio=6), (FEW, RING64, FEW)), (1, 7, 91, 512, 1.0, dict(mlp_ratio=6), (RING64, RING64, RING64)),
     (1, 28, 35, 256, 0.5, dict(mlp_ratio=8), (TILE, TILE, FEW)), (1, 35, 35, 256, 0.5, dict(mlp_ratio=8), (TILE, TILE, RING64)),
     (1, 14, 14, 1024, 0.5, dict(mlp_ratio=2), (FEW, RING64, FEW)),
+    # N = 128: FC2 on 256 and 260, and on 1364 and 1368 tiles of 64 x 64, and on 384 and 385 of 128 x 128
+    (1, 7, 1169, 128, 1.0, dict(mlp_ratio=6), (TILE, TILE, RING64)), (1, 84, 98, 128, 1.0, dict(mlp_ratio=5), (TILE, TILE, TILE)),
+    (1, 70, 623, 128, 1.0, dict(mlp_ratio=8), (TILE, TILE, TILE)), (1, 189, 231, 128, 1.0, dict(mlp_ratio=6), (TILE, TILE, RING64)),
+    (1, 119, 413, 128, 1.0, dict(mlp_ratio=8), (TILE, TILE, RING64)), (1, 28, 1757, 128, 1.0, dict(mlp_ratio=7), (TILE, TILE, RING128)),
     (2, 35, 35, 192, 0.5, dict(mlp_ratio=7), (TILE, TILE, TILE)), (2, 70, 84, 192, 0.5, dict(mlp_ratio=5), (TILE, TILE, TILE)),
     (1, 35, 35, 96, 0.5, dict(mlp_ratio=7), (TILE, TILE, TILE))])
 def test_products_of_the_separate_kernels_at_their_lines(B, H, W, C, keep, kw, forms):

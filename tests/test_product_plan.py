@@ -29,6 +29,16 @@ def test_fc2(N, K, few):
     assert P.form(P.FC2, most, N, K) == "ring64" and P.form(P.FC2, most + R, N, K) == "ring128"
 
 
+@pytest.mark.parametrize("K", [640, 768, 896, 1024])
+def test_fc2_of_128_channels(K):
+    """64 x 64 tiles up to one a CU and from five and a third, row tiles of all channels between; 128 x 128 tiles from one and a half a CU."""
+    few, many, most = 256 * 64 * 64 // 128, 341 * 128, 384 * 128
+    assert P.form(P.FC2, R, 128, K) == P.form(P.FC2, few, 128, K) == "ring64"
+    assert P.form(P.FC2, few + R, 128, K) == P.form(P.FC2, many, 128, K) == "tile"
+    assert P.form(P.FC2, many + R, 128, K) == P.form(P.FC2, most, 128, K) == "ring64"
+    assert P.form(P.FC2, most + R, 128, K) == "ring128"
+
+
 @pytest.mark.parametrize("epi,N,K,want", [
     (P.QKV, 1536, 512, "ring64"), (P.QKV, 1152, 384, "tile"),
     (P.FC2, 96, 768, "tile"), (P.FC2, 192, 1344, "tile"), (P.FC2, 192, 1536, "ring64"), (P.FC2, 192, 960, "tile"), (P.FC2, 128, 512, "ring64"),
