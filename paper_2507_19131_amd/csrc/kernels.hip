@@ -1411,7 +1411,7 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
 // four chunks of NH hidden blocks: FC1 + GELU + quantize of a chunk goes to one of two LDS buffers, then FC2 accumulates that chunk.
 // With two row blocks h is parked in the output map between the first and the second residual (the same thread writes and re-reads the
 // same address).
-// Bound: vector instructions (51 to 62 % of the cycles) and LDS reads (43 to 54 %) that do not overlap fully at C = 96 and 128 on large
+// Bound: vector instructions (57 to 62 % of the cycles) and LDS reads (48 to 54 %) that do not overlap fully at C = 96 and 128 on large
 // maps, the weights at 64 bytes per clock and CU at C = 384, the chain of phases on few tiles.  Against a form with the chunks unrolled
 // and FC1's weights a block ahead, which the three, four and eight waves had: stage of two blocks on 8 x 1392 windows at C = 96, 5476
 // at C = 128 and 1444 at C = 256 3 % shorter, 64 windows at C = 256 58.9 -> 52.7 us.
