@@ -1,0 +1,28 @@
+// Which launches take a whole block in one kernel, a workgroup per window (block_kernel), instead of a window and a token kernel.  Host code.
+#pragma once
+
+namespace mixaq {
+
+// By the windows of the launch and those of them that are not pruned.  One kernel saves a launch, a round trip of the codes and the staging
+// of the second half, but tiles of 32 and 17 rows instead of 32 and 32 cost a third more work, so it is for launches whose workgroups run
+// all at once: one a CU, and at C = 96 and 128, whose registers hold two, a second one once most CUs have it.  Below the first line of
+// C = 128 and 192 the window kernel with half the heads a workgroup spreads a window over two CUs.  Two blocks on one map, us, two kernels /
+// one:   C = 96   128 windows 33.2 / 31.1   256 37.1 / 32.9 | 264 41.8 / 42.4   320 43.0 / 44.0 | 400 46.5 / 44.7   504 48.9 / 45.9
+//        C = 128  128 32.6 / 34.6 | 144 34.8 both   192 39.0 / 35.4   256 40.4 / 36.3 | 264 44.0 / 46.9   320 45.4 / 49.0 |
+//                 400 51.6 / 50.3   504 58.0 / 53.5
+//        C = 192  128 41.9 / 46.8 | 144 48.4 / 47.0   192 56.5 / 47.8   256 57.9 / 50.3 | 264 65.6 / 84.8   504 93.7 / 90.7
+// C = 256 needs sixteen waves a workgroup, which leave 80 registers too few: 64 50.9 / 76.2, 256 75.8 / 88.7.
+// A batch that one launch takes this way stays on one chain: six blocks, two chains of two kernels / one chain of one:   C = 96   2 x 96
+// windows 104.9 / 90.7   2 x 128 110.1 / 92.9   2 x 192 137.5 / 128.9   2 x 256 146.7 / 134.7      C = 128   2 x 96 115.9 / 100.6   2 x 128
+// 121.3 / 104.0   2 x 192 145.1 / 144.2   2 x 256 159.4 / 153.7      C = 192   2 x 72 146.7 / 135.2   2 x 128 177.5 / 143.7.
+// A pruned window's workgroup is gone as soon as its rank is known or copies its window behind the others: 2 x 140 with a fifth pruned
+// 112.4 / 98.7, 126.2 / 110.9 and 184.7 / 160.0.  Where few are left the halves are ahead again (2 x 72 at C = 192, 115 computed 129.6 / 134.7).
+inline bool whole_block(int C, int windows, int computed)
+{
+    constexpr int CUS = 256;
+    const int from = C == 96 ? 0 : C == 128 || C == 192 ? 144 : 2 * CUS + 1, second = C == 96 ? 352 : C == 128 ? 400 : 2 * CUS + 1;
+    if (computed <= CUS) return computed >= from && windows <= CUS + CUS / 4;
+    return computed >= second && windows <= 2 * CUS;
+}
+
+}  // namespace mixaq

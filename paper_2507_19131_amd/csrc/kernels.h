@@ -1,5 +1,6 @@
 // Argument blocks and launchers of the gfx950 kernels (host side sees only this).
 #pragma once
+#include "block_plan.h"
 #include "mixaq_dev.h"
 #include "product_plan.h"
 
@@ -117,6 +118,9 @@ bool fused_token_supported(int C, int mlp_ratio);
 // chains: how many launches like this one run beside each other (the two chains of a stage)
 void launch_window(const Geom& G, const WinArgs& A, int chains, hipStream_t st);
 void launch_token(const Geom& G, const TokArgs& A, int chains, hipStream_t st);
+// both halves in one launch, where block_plan.h says so and the sums and the GELU take their short forms (one chain, no taps); false:
+// nothing was launched
+bool launch_block(const Geom& G, const WinArgs& W, const TokArgs& T, int chains, hipStream_t st);
 bool launch_score(const Geom& G, const float* x, int mode, float eps, const float* gm, const float* bt, double* scores,
                   hipStream_t st);
 void launch_select(const double* scores, int B, int nW, int reverse, int* perm, hipStream_t st);

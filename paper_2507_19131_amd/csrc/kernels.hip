@@ -826,7 +826,7 @@ __device__ __forceinline__ v16i attention_core(const v4i& qf, const v4i (&kf)[2]
 template <bool TAPS, bool MAGIC>
 __device__ __forceinline__ void attention_store(const v16i& o, const QDev& qo, float m_o,
                                                 int j, int g, int ib, int head, int C, int8_t* out, int row0, int32_t* tap_o,
-                                                int8_t* tap_code, size_t canon_row0, int pack = 0)
+                                                int8_t* tap_code, size_t canon_row0, int pack = 0, int unsigned_pack = 0)
 {
     {
         const int qi = ib * 32 + j;
@@ -845,6 +845,11 @@ __device__ __forceinline__ void attention_store(const v16i& o, const QDev& qo, f
             // The halves exchange, so that a lane stores its token's sixteen (packed: eight) consecutive bytes at once: four-byte
             // stores cost a write request each.
             if (pack == 0 || pack == PACK_FRAG) {
+                if (unsigned_pack) {               // offset-binary in whole bytes, as a reader of packed codes expands them
+                    const int flip = unsigned_pack == 1 ? 0x08080808 : 0x02020202, keep = unsigned_pack == 1 ? 0x0f0f0f0f : 0x03030303;
+#pragma unroll
+                    for (int qd = 0; qd < 4; ++qd) code[qd] = (code[qd] ^ flip) & keep;
+                }
                 const auto lo = __builtin_amdgcn_permlane32_swap(code[0], code[2], false, false);   // dims 0..3, 4..7 | 16..19, 20..23
                 const auto hi = __builtin_amdgcn_permlane32_swap(code[1], code[3], false, false);   // 8..11, 12..15 | 24..27, 28..31
                 const v4i all = {(int)lo[0], (int)lo[1], (int)hi[0], (int)hi[1]};
@@ -1079,13 +1084,19 @@ template <int C, int NH, bool CODES> struct WinPrm {
 
 // CODES: the LN1 codes come ready from ln_window_kernel (wide blocks, whose heads are spread over many workgroups: each of
 // them would repeat the whole gather and LayerNorm); the workgroup is given a slot and there are no pruned ones.
-template <int NH, bool TAPS, bool SCORED, int HG, int QS, bool CODES, bool MAGIC, bool BESIDE>
-__global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(win_waves_per_eu(NH, HG, QS, CODES, BESIDE)))) void window_kernel(Geom G, WinArgs A)
+// WHOLE: the first half of block_kernel, whose workgroup goes on with the window's tokens: attention codes and pixels of the tokens stay
+// in LDS (codes as operand fragments, a row block per 32 tokens), second_half() is called as soon as the branch is known.  False: the
+// window is pruned and forwarded.
+struct WholeLds {
+    v4i *codes, *exchange;                                               // LN1's, then the attention's codes; what pairs of waves exchange
+    int* pix;
+};
+template <int NH, bool TAPS, bool SCORED, int HG, int QS, bool CODES, bool MAGIC, bool BESIDE, bool WHOLE, typename Second>
+__device__ __forceinline__ bool window_half(const Geom& G, const WinArgs& A, int& branch, const WholeLds& whole, Second second_half)
 {
-    if (CODES || HG == 2 || (QS == 2 && NH <= 4)) touch_arguments<sizeof(Geom) + sizeof(WinArgs)>();   // few workgroups
     constexpr int NHT = NH * HG;                                         // heads of the block; this workgroup runs NH of them
     constexpr int NW = NH * QS, NTB = 2 / QS;                            // waves; token blocks a wave projects to v and attends for
-    constexpr bool ROLES = win_roles(NH, HG, QS, CODES, BESIDE);                 // one wave of a pair projects all tokens to q, the other to k
+    constexpr bool ROLES = WHOLE || win_roles(NH, HG, QS, CODES, BESIDE);        // one wave of a pair projects all tokens to q, the other to k
     constexpr int NTQ = ROLES ? 2 : NTB, PAIR_SLOTS = ROLES ? 5 : 4;
     constexpr int C = NHT * 32, KS = NHT, LPT = WinCfg<NH, HG, QS>::LPT, NV = CODES ? 1 : WinCfg<NH, HG, QS>::NV, NT = NW * 64;
     constexpr int GPW = WinCfg<NH, HG, QS>::GPW;
@@ -1094,13 +1105,15 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
     // pair); with CODES, one after another
     const int widx = HG == 1 ? blockIdx.x : CODES ? blockIdx.x / HG : blockIdx.x / (8 * HG) * 8 + blockIdx.x % 8;
     const int hg = HG == 1 ? 0 : CODES ? blockIdx.x % HG : blockIdx.x / 8 % HG;
-    if (HG > 1 && !CODES && widx >= G.B * G.nW) return;
+    if (HG > 1 && !CODES && widx >= G.B * G.nW) return false;
     static_assert(CODES || NW * GPW >= TOK, "one pass must cover the window");
-    __shared__ v4i a1s[2 * KS * 64];                                     // LN1 codes as fragments [token block][k slab][lane]
+    __shared__ v4i own_a1s[WHOLE ? 1 : 2 * KS * 64];                     // LN1 codes as fragments [token block][k slab][lane]
+    auto a1s = [&]() -> v4i* { if constexpr (WHOLE) return whole.codes; else return own_a1s; };
     __shared__ __attribute__((aligned(16))) float prm[PR::WORDS];        // this branch's LN1 affine and QKV epilogue constants
     constexpr bool SUMS_IN_PRM = CODES && QS == 1;                       // the V column sums of a wave's head take the place of its q multipliers, long read
     __shared__ __attribute__((aligned(16))) int csum[SUMS_IN_PRM ? 1 : NW][HD];
-    __shared__ v4i kvx[QS == 2 ? NH * PAIR_SLOTS * 64 : 1];              // k and v operands of a wave pair [head][k|v][token block][lane], with ROLES q of the second block
+    __shared__ v4i own_kvx[QS == 2 && !WHOLE ? NH * PAIR_SLOTS * 64 : 1];   // k and v operands of a wave pair [head][k|v][token block][lane], with ROLES q of the second block
+    auto kvx = [&]() -> v4i* { if constexpr (WHOLE) return whole.exchange; else return own_kvx; };
     __shared__ int csp[QS == 2 ? NH * 2 * HD : 1];                       // V column sums of each token block [head][block][dim]
     __shared__ int red[NW];
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, j = lane & 31, g = lane >> 5;
@@ -1113,7 +1126,7 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
     // them share a CU: six blocks on 81 windows at C = 192 147 -> 133 us, three sets in turn of two blocks on 64 windows at
     // C = 128 36.7 -> 33.8.)
     constexpr bool STREAM = KS >= 12 || (HG == 1 ? !(NH == 3 && QS == 1) : KS < 8);
-    constexpr int RING = !STREAM ? (KS < 6 ? KS : 6) : KS < 6 ? KS : KS == 6 ? (QS == 1 ? 6 : 3) : KS == 12 ? 6 : KS < 32 ? 8 : QS == 1 ? 4 : 16;
+    constexpr int RING = !STREAM ? (KS < 6 ? KS : 6) : KS < 6 ? KS : KS == 6 ? (QS == 1 || WHOLE ? 6 : 3) : KS == 12 ? 6 : KS < 32 ? 8 : QS == 1 ? 4 : 16;
     static_assert(!STREAM || KS % RING == 0, "each chain starts at ring slot 0");
     constexpr int O_START = MAGIC ? SUM_MAGIC_BITS : 0;                  // of the P.V sums: 49 * 255 * 128 at most
     v4i ring[RING];
@@ -1121,7 +1134,8 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
     auto weights_of = [&](int which) { return A.Wqkv + (size_t)(which * NHT + head) * KS * 64 + lane; };
     // SCORED: the workgroup is given a window and finds its own place in the selection (its rank
     // under the total order of the scores); otherwise it is given a slot and looks the window up.
-    int branch = 0, row0 = 0, canon_slot = 0, w, bimg = 0;
+    int row0 = 0, canon_slot = 0, w, bimg = 0;
+    branch = 0;
     if (STREAM && CODES) {
         const v4i* wp = weights_of(role);
 #pragma unroll
@@ -1135,7 +1149,7 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
         w = A.perm[canon_slot];
         bimg = G.by_nW(canon_slot);
     } else {                              // workgroups past the computed slots: pruned windows (Sec. 3.4), features forwarded
-        if (hg != 0) return;
+        if (hg != 0) return false;
         const int kept = G.k_hi + G.k_lo, q = widx - G.n_slots, b = q / (G.nW - kept);
         const int wp = A.perm[b * G.nW + kept + (q - b * (G.nW - kept))];
         const int wr = G.by_nWc(wp), wc = wp - wr * G.nWc;
@@ -1148,20 +1162,20 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
                 *(float4*)(A.y + off) = *(const float4*)(A.x + off);
             }
         }
-        return;
+        return false;
     }
     // The rows that pad each region to whole tiles belong to no window: the first workgroup marks them
     // (pixel -1, slot-major row -1) for the kernels of the seven-kernel path, which read the marks of every row.
-    if (!CODES && blockIdx.x == 0) {
+    if (!CODES && !WHOLE && blockIdx.x == 0) {
         for (int r = G.rows_hi + tid; r < G.base_lo; r += NT) { A.row_pix[r] = -1; A.row_canon[r] = -1; }
         for (int r = G.base_lo + G.rows_lo + tid; r < G.rows_total; r += NT) { A.row_pix[r] = -1; A.row_canon[r] = -1; }
     }
-    int* a1w = (int*)a1s;
+    int* a1w = (int*)a1s();
     // dword index of (token slot s, channel c with c%4==0) in the fragment layout (k = channel, natural order)
     auto frag_dw = [&](int s, int c) { return ((((s >> 5) * KS + (c >> 5)) * 64 + ((c & 31) >> 4) * 32 + (s & 31)) << 2) + ((c & 15) >> 2); };
     static_assert(CODES || NT >= 32 * KS, "one pass must clear the token slots behind the window");
     if (!CODES && tid < 32 * KS && (tid & 15) < 64 - TOK)                 // the fifteen of every half slab, sixteen bytes a lane
-        a1s[(KS + (tid >> 5)) * 64 + ((tid >> 4) & 1) * 32 + TOK - 32 + (tid & 15)] = (v4i){0, 0, 0, 0};
+        a1s()[(KS + (tid >> 5)) * 64 + ((tid >> 4) & 1) * 32 + TOK - 32 + (tid & 15)] = (v4i){0, 0, 0, 0};
     const int grp = lane / LPT, sub = lane - grp * LPT, first = lane - sub;
     const int t = !CODES && grp < GPW ? wave * GPW + grp : TOK;          // lanes beyond the last whole group idle
     int pix = -1;
@@ -1186,7 +1200,7 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
 #pragma unroll
                 for (int k = 0; k < NV; ++k) *(float4*)(dst + (k * LPT + sub) * 4) = v[k];
             }
-            return;                                                       // the whole workgroup
+            return false;                                                 // the whole workgroup
         }
         canon_slot = bimg * G.nW + rank;
         if (rank < G.k_hi) { branch = 0; row0 = (bimg * G.k_hi + rank) * TOK; }
@@ -1205,7 +1219,7 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
             const int wv = __builtin_amdgcn_readfirstlane(wave);
             for (int f = wv; f < 2 * KS; f += NW)
                 __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(A.codes + ((size_t)widx * 2 * KS + f) * 1024 + lane * 16),
-                                                 (__attribute__((address_space(3))) void*)(a1s + f * 64), 16, 0, 0);
+                                                 (__attribute__((address_space(3))) void*)(a1s() + f * 64), 16, 0, 0);
         }
         if (STREAM && !CODES) {
             const v4i* wp = weights_of(role);
@@ -1214,12 +1228,14 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
         }
 #pragma unroll
         for (int k = 0; k < PVT; ++k) if (tid + k * NT < PV) ((float4*)prm)[tid + k * NT] = pv[k];
+        second_half();
     }
     if (CODES) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");           // the direct loads have landed
     __syncthreads();                                                     // parameter block visible
     if (t < TOK) {
         const int canon = canon_slot * TOK + t;
-        if (sub == 0 && hg == 0) { A.row_pix[row0 + t] = pix; A.row_canon[row0 + t] = canon; }
+        if (WHOLE) { if (sub == 0) whole.pix[t] = pix; }
+        else if (sub == 0 && hg == 0) { A.row_pix[row0 + t] = pix; A.row_canon[row0 + t] = canon; }
         if (pix >= 0) {
             token_layernorm<LPT, NV>(v, C, A.eps, prm + PR::LN_G, prm + PR::LN_B, sub, first);
         } else {
@@ -1247,7 +1263,7 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
         v4i xv[PF][NTB];
         auto operand = [&](int ks) {
 #pragma unroll
-            for (int tb = 0; tb < NTB; ++tb) xv[ks % PF][tb] = a1s[(((ROLES && NTB == 2 ? 0 : tb0) + tb) * KS + ks) * 64 + lane];
+            for (int tb = 0; tb < NTB; ++tb) xv[ks % PF][tb] = a1s()[(((ROLES && NTB == 2 ? 0 : tb0) + tb) * KS + ks) * 64 + lane];
         };
         if (STREAM) {
 #pragma unroll
@@ -1313,7 +1329,7 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
         for (int tb = 0; tb < NTQ; ++tb) finish(tb, acc[tb]);
     }
     // a pair of waves requests its bias ahead of the exchange, where the registers are free
-    constexpr bool BIAS_EARLY = QS == 2 && (CODES || !win_pairs_share(NH, HG));
+    constexpr bool BIAS_EARLY = QS == 2 && (WHOLE || CODES || !win_pairs_share(NH, HG));
     BiasRow bias;
     v4i vt[2];
     {
@@ -1359,10 +1375,10 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
         if (QS == 1) {
             if (g == 0) column_sums()[j] = O_START - A.qp[branch].zp * cs;
         } else {                                                          // the pair exchanges its halves of K, V and the sums
-            if (!ROLES) kvx[((hw * 2 + 0) * 2 + tb0) * 64 + lane] = qk[1][0];
-            else if (role) { kvx[(hw * PAIR_SLOTS + 0) * 64 + lane] = qk[1][0]; kvx[(hw * PAIR_SLOTS + 1) * 64 + lane] = qk[1][NTQ - 1]; }
-            else kvx[(hw * PAIR_SLOTS + PAIR_SLOTS - 1) * 64 + lane] = qk[1][NTQ - 1];
-            kvx[(hw * PAIR_SLOTS + 2 + tb0) * 64 + lane] = vt[0];
+            if (!ROLES) kvx()[((hw * 2 + 0) * 2 + tb0) * 64 + lane] = qk[1][0];
+            else if (role) { kvx()[(hw * PAIR_SLOTS + 0) * 64 + lane] = qk[1][0]; kvx()[(hw * PAIR_SLOTS + 1) * 64 + lane] = qk[1][NTQ - 1]; }
+            else kvx()[(hw * PAIR_SLOTS + PAIR_SLOTS - 1) * 64 + lane] = qk[1][NTQ - 1];
+            kvx()[(hw * PAIR_SLOTS + 2 + tb0) * 64 + lane] = vt[0];
             if (g == 0) csp[(hw * 2 + tb0) * HD + j] = cs;
             __syncthreads();
             if (g == 0) column_sums()[j] = O_START - A.qp[branch].zp * (csp[(hw * 2) * HD + j] + csp[(hw * 2 + 1) * HD + j]);
@@ -1371,10 +1387,10 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
     v4i kf[2];
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb) {
-        kf[kb] = QS == 1 ? qk[1][kb % NTQ] : kvx[(hw * PAIR_SLOTS + kb) * 64 + lane];
-        if (QS == 2) vt[kb] = kvx[(hw * PAIR_SLOTS + 2 + kb) * 64 + lane];
+        kf[kb] = QS == 1 ? qk[1][kb % NTQ] : kvx()[(hw * PAIR_SLOTS + kb) * 64 + lane];
+        if (QS == 2) vt[kb] = kvx()[(hw * PAIR_SLOTS + 2 + kb) * 64 + lane];
     }
-    if (ROLES) qk[0][0] = role ? kvx[(hw * PAIR_SLOTS + PAIR_SLOTS - 1) * 64 + lane] : qk[1][0];
+    if (ROLES) qk[0][0] = role ? kvx()[(hw * PAIR_SLOTS + PAIR_SLOTS - 1) * 64 + lane] : qk[1][0];
     __builtin_amdgcn_s_waitcnt(0xc07f);                                   // lgkmcnt(0): the wave's own column sums are in LDS
     __builtin_amdgcn_wave_barrier();
     const int mtype = mask_type(G, w);
@@ -1389,16 +1405,25 @@ __global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(wi
     core.tap_s = A.tap_s ? A.tap_s + tbase : nullptr;
     core.tap_p = A.tap_p ? A.tap_p + tbase : nullptr;
     // the low region's rows may be packed (dense, after the high region); operand fragments are the same for both branches
-    const int pack = A.out_pack == PACK_FRAG || branch ? A.out_pack : 0;
+    const int pack = WHOLE ? PACK_FRAG : A.out_pack == PACK_FRAG || branch ? A.out_pack : 0;
     const bool dense = pack == 1 || pack == 2;
-    int8_t* out = A.out + (dense ? (size_t)G.base_lo * C : 0);
-    const int orow0 = row0 - (dense ? G.base_lo : 0);
+    int8_t* out = WHOLE ? (int8_t*)whole.codes : A.out + (dense ? (size_t)G.base_lo * C : 0);
+    const int orow0 = WHOLE ? 0 : row0 - (dense ? G.base_lo : 0);
 #pragma unroll 1
     for (int ib = tb0; ib < tb0 + NTB; ++ib) {
         asm volatile("" ::: "memory");
         const v16i o = attention_core<TAPS, !BIAS_EARLY>(NTB == 2 && ib ? qk[0][NTB - 1] : qk[0][0], kf, vt, core, bias, j, g, ib);
-        attention_store<TAPS, MAGIC>(o, in_vgpr(A.qo[branch]), in_vgpr(A.m_o[branch]), j, g, ib, head, C, out, orow0, A.tap_o, A.tap_code, canon_row0, pack);
+        attention_store<TAPS, MAGIC>(o, in_vgpr(A.qo[branch]), in_vgpr(A.m_o[branch]), j, g, ib, head, C, out, orow0, A.tap_o, A.tap_code, canon_row0, pack, WHOLE && branch ? A.out_pack : 0);
     }
+    return true;
+}
+
+template <int NH, bool TAPS, bool SCORED, int HG, int QS, bool CODES, bool MAGIC, bool BESIDE>
+__global__ __launch_bounds__(NH * QS * 64) __attribute__((amdgpu_waves_per_eu(win_waves_per_eu(NH, HG, QS, CODES, BESIDE)))) void window_kernel(Geom G, WinArgs A)
+{
+    if (CODES || HG == 2 || (QS == 2 && NH <= 4)) touch_arguments<sizeof(Geom) + sizeof(WinArgs)>();   // few workgroups
+    int branch;
+    window_half<NH, TAPS, SCORED, HG, QS, CODES, MAGIC, BESIDE, false>(G, A, branch, WholeLds(), [] {});
 }
 
 // ------------------------------------------------------------------ fused token kernel
@@ -1437,44 +1462,55 @@ __device__ __forceinline__ void to_lds(const void* src, void* dst)
     __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src, (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
 }
 // requests the branch's parameter block and the GELU table (1 KB pieces) of a token kernel of NH waves
-template <int NH>
+template <int NH, int WORDS>
 __device__ __forceinline__ void token_stage(const float* params, const float4* gelu, int gelu_pieces, float* prm, float4* gtab, int wave, int lane)
 {
-    constexpr int PIECES = TokPrm<NH * 32>::WORDS / 256;
+    constexpr int PIECES = WORDS / 256;
 #pragma unroll
     for (int p0 = 0; p0 < PIECES; p0 += NH)
         if (p0 + NH <= PIECES || p0 + wave < PIECES) to_lds(params + (p0 + wave) * 256 + lane * 4, prm + (p0 + wave) * 256);
     for (int p = NH - 1 - wave; p < gelu_pieces; p += NH) to_lds(gelu + p * 64 + lane, gtab + p * 64);   // the last waves have the fewest of the others
 }
 
-template <int NH, int RB, bool TAPS, bool SHORT>
-__global__ __launch_bounds__(NH * 64) __attribute__((amdgpu_waves_per_eu(tok_waves_per_eu(NH)))) void token_kernel(Geom G, TokArgs A)
+// LN2's partial sums, up to eight waves in the room of the hidden codes: the last sum is read ahead of the barrier in front of the FFN.
+// LDS is given out in one piece of whole units, 128 of 1280 bytes, so a workgroup's size decides which ones share a CU.  At C = 96 five take
+// 5 x 24 (with sums of their own 5 x 26, and a CU held four: 200 x 336 98.5 -> 95.4 us, 8 x 200 x 336 606 -> 594).  At C = 256 a second
+// token workgroup has to fit behind one that lies behind a window workgroup of the other chain, 33 + 2 x 46.  (With the sums in 4 KB of
+// their own the table of steps made it 49, and such a CU had one token workgroup until both were through: six blocks, two chains, 200
+// windows 219.7 -> 203.3 us, 288 240 -> 229, 480 343 -> 321, 612 402 -> 401; before the table, 40 units, 211, 240, 332, 413.)  Twelve
+// waves have a CU to themselves, and with 64 rows the shared room costs 12 spilled registers: two blocks on 840 windows 330 -> 358 us.
+constexpr bool tok_sums_in_codes(int NH) { return NH <= 8; }
+// LDS of a workgroup whose waves take GROUPS tiles of 32 * RB rows side by side, NH waves each
+template <int NH, int RB, int GROUPS, bool SHORT>
+struct TokLds {
+    v4i actf[GROUPS][RB * NH * 64];                                    // [row block][k slab][lane]
+    v4i gs[GROUPS == 1 ? 1 : 0][2][NH * RB * 64];                      // [buffer][hidden block of the chunk][row block][lane]
+    __attribute__((aligned(16))) float prm[TokPrm<NH * 32>::WORDS];
+    float4 gtab[SHORT ? GELU_STEP_PIECES * 64 : GELU_TAB];
+};
+
+// WHOLE: the second half of block_kernel: tile `group` of the window that the workgroup has in LDS, whose parameters and table are requested.
+template <int NH, int RB, bool TAPS, bool SHORT, int GROUPS, bool WHOLE>
+__device__ __forceinline__ void token_half(const Geom& G, const TokArgs& A, TokLds<NH, RB, GROUPS, SHORT>& S, int branch, const int* whole_pix, v4i (*whole_gs)[2][NH * RB * 64])
 {
-    if (NH == 12 || G.rows_total <= 256 * 32) touch_arguments<sizeof(Geom) + sizeof(TokArgs)>();   // about one workgroup a CU
     constexpr int C = NH * 32, KS = NH, HB = 4 * NH, F = 4 * C;
     constexpr int RING = NH < 8 ? NH : NH == 12 && RB == 1 ? 12 : 8;               // fragments in flight per wave
     constexpr bool PARK_H = RB >= 2 && !TAPS;                         // taps need h of padded tokens too, which have no pixel
     static_assert((2 * KS) % RING == 0 && RING <= KS, "phases 2k start at ring slot 0, phases 2k+1 at slot KS % RING");
     constexpr int SLOT_ODD = KS % RING;
     using PR = TokPrm<C>;
-    __shared__ v4i actf[RB * KS * 64];                                 // [row block][k slab][lane]
-    __shared__ v4i gs[2][NH * RB * 64];                                // [buffer][hidden block of the chunk][row block][lane]
-    // LN2's partial sums, up to eight waves in the room of the hidden codes: the last sum is read ahead of the barrier in front of the FFN.
-    // LDS is given out in one piece of whole units, 128 of 1280 bytes, so a workgroup's size decides which ones share a CU.  At C = 96 five take
-    // 5 x 24 (with sums of their own 5 x 26, and a CU held four: 200 x 336 98.5 -> 95.4 us, 8 x 200 x 336 606 -> 594).  At C = 256 a second
-    // token workgroup has to fit behind one that lies behind a window workgroup of the other chain, 33 + 2 x 46.  (With the sums in 4 KB of
-    // their own the table of steps made it 49, and such a CU had one token workgroup until both were through: six blocks, two chains, 200
-    // windows 219.7 -> 203.3 us, 288 240 -> 229, 480 343 -> 321, 612 402 -> 401; before the table, 40 units, 211, 240, 332, 413.)  Twelve
-    // waves have a CU to themselves, and with 64 rows the shared room costs 12 spilled registers: two blocks on 840 windows 330 -> 358 us.
-    constexpr bool SUMS_IN_CODES = NH <= 8;
-    __shared__ double own_sums[SUMS_IN_CODES ? 1 : 2 * NH * 32 * RB];
-    auto& part = *reinterpret_cast<double (*)[2][NH][32 * RB]>(SUMS_IN_CODES ? (double*)gs[0] : own_sums);
-    static_assert(sizeof(part) <= sizeof(gs[0]), "in one buffer of the hidden codes");
-    __shared__ __attribute__((aligned(16))) float prm[PR::WORDS];
-    __shared__ float4 gtab[SHORT ? GELU_STEP_PIECES * 64 : GELU_TAB];
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, j = lane & 31, g = lane >> 5;
-    const int row_base = blockIdx.x * (32 * RB);
-    const int branch = row_base >= G.base_lo ? 1 : 0;                 // a tile never straddles the regions: scalar
+    const int lane = threadIdx.x & 63, all_waves = threadIdx.x >> 6, group = GROUPS == 1 ? 0 : __builtin_amdgcn_readfirstlane(all_waves / NH);
+    const int wave = GROUPS == 1 ? all_waves : all_waves - group * NH, j = lane & 31, g = lane >> 5;
+    v4i* const actf = S.actf[group];
+    auto& gs = WHOLE ? whole_gs[group] : S.gs[0];
+    __shared__ double own_sums[tok_sums_in_codes(NH) ? 1 : 2 * NH * 32 * RB];
+    auto& part = *reinterpret_cast<double (*)[2][NH][32 * RB]>(tok_sums_in_codes(NH) ? (double*)gs[0] : own_sums);
+    static_assert(GROUPS == 1 || tok_sums_in_codes(NH), "sums of a group's own");
+    static_assert(!tok_sums_in_codes(NH) || sizeof(part) <= sizeof(gs[0]), "in one buffer of the hidden codes");
+    float* const prm = S.prm;
+    float4* const gtab = S.gtab;
+    const int row_base = WHOLE ? 0 : blockIdx.x * (32 * RB);
+    if (!WHOLE) branch = row_base >= G.base_lo ? 1 : 0;               // a tile never straddles the regions: scalar
     const int nb = wave;
     const int* prmi = (const int*)prm;
     // The wave's weight stream, phase by phase (every phase has KS = NH fragments): projection block, FC1 block of
@@ -1489,9 +1525,9 @@ __global__ __launch_bounds__(NH * 64) __attribute__((amdgpu_waves_per_eu(tok_wav
     // copy goes straight to LDS and everything is requested before anything is waited for (piece by piece, load and LDS
     // write in a loop, the staging was a chain of round trips: 3.3 us of a tile's 14 at C = 192).
     const int swave = __builtin_amdgcn_readfirstlane(wave);
-    const int pack = branch ? A.ao_pack : 0;                           // packed low-branch codes: scalar per tile
+    const int pack = branch && !WHOLE ? A.ao_pack : 0;                 // packed low-branch codes: scalar per tile
     int2 pc[RB];
-    if (!pack) {
+    if (!pack && !WHOLE) {
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb)                                // fragment (rb, slab = wave), lane (half g, row j)
             to_lds(A.ao + (size_t)(row_base + rb * 32 + j) * C + swave * 32 + g * 16, actf + (rb * KS + swave) * 64);
@@ -1507,11 +1543,12 @@ __global__ __launch_bounds__(NH * 64) __attribute__((amdgpu_waves_per_eu(tok_wav
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
         const int row = row_base + rb * 32 + j;
+        if (WHOLE) { valid[rb] = group * 32 + j < TOK; continue; }     // (the pixel is in LDS behind the barrier)
         valid[rb] = branch ? (row - G.base_lo < G.rows_lo) : (row < G.rows_hi);
         pix[rb] = A.row_pix[row];
         canon[rb] = (TAPS && valid[rb]) ? (size_t)A.row_canon[row] : 0;
     }
-    token_stage<NH>(A.params[branch], SHORT ? (const float4*)A.steps[branch] : A.gelu_tab, SHORT ? A.step_pieces[branch] : GELU_TAB / 64, prm, gtab, swave, lane);
+    if (!WHOLE) token_stage<NH, PR::WORDS>(A.params[branch], SHORT ? (const float4*)A.steps[branch] : A.gelu_tab, SHORT ? A.step_pieces[branch] : GELU_TAB / 64, prm, gtab, swave, lane);
     asm volatile("" ::: "memory");                                     // the weight stream is requested behind them
     v4i ring[RING];
 #pragma unroll
@@ -1574,6 +1611,7 @@ __global__ __launch_bounds__(NH * 64) __attribute__((amdgpu_waves_per_eu(tok_wav
     float4 sc[RB][4];
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
+        if (WHOLE) pix[rb] = whole_pix[min(group * 32 + j, TOK - 1)];
         pix[rb] = valid[rb] ? pix[rb] : -1;
 #pragma unroll
         for (int qd = 0; qd < 4; ++qd) {
@@ -1738,6 +1776,40 @@ __global__ __launch_bounds__(NH * 64) __attribute__((amdgpu_waves_per_eu(tok_wav
                 if (A.tap_y) *(float4*)(A.tap_y + canon[rb] * C + n0) = o4;
             }
         }
+}
+
+template <int NH, int RB, bool TAPS, bool SHORT>
+__global__ __launch_bounds__(NH * 64) __attribute__((amdgpu_waves_per_eu(tok_waves_per_eu(NH)))) void token_kernel(Geom G, TokArgs A)
+{
+    if (NH == 12 || G.rows_total <= 256 * 32) touch_arguments<sizeof(Geom) + sizeof(TokArgs)>();   // about one workgroup a CU
+    __shared__ TokLds<NH, RB, 1, SHORT> lds;
+    token_half<NH, RB, TAPS, SHORT, 1, false>(G, A, lds, 0, nullptr, nullptr);
+}
+
+// ------------------------------------------------------------------ a whole block on small maps
+// One workgroup per window runs both halves of the block: the window kernel's form of pairs of waves, by roles, then two token kernels of
+// one row block side by side for the window's 32 and 17 rows, each wave one of a tile's channel blocks.  What the halves hand on stays in
+// LDS; the second half's parameters and table are requested with the first one's.  Bound: the chain of dependent steps of a workgroup that has
+// a CU to itself or shares it with one other.  The codes of the attention take the room of LN1's and the hidden codes that of the pairs'
+// exchange, so that at C = 96 and 128 two workgroups fit a CU, with 128 registers (one spilled at C = 128).  (The first weights of the
+// projection requested ahead of the attention: nothing.)  Window and token kernel -> this one, one block on 56 x 56 x 96 17.1 -> 16.3 us, two on
+// 256 windows 37.1 -> 32.9, at C = 192 57.9 -> 50.3; more beside whole_block(), which draws the lines.
+constexpr int whole_waves_per_eu(int NH) { return NH == 6 ? 3 : 4; }
+template <int NH, bool SCORED>
+__global__ __launch_bounds__(NH * 2 * 64) __attribute__((amdgpu_waves_per_eu(whole_waves_per_eu(NH)))) void block_kernel(Geom G, WinArgs W, TokArgs T)
+{
+    touch_arguments<sizeof(Geom) + sizeof(WinArgs) + sizeof(TokArgs)>();
+    __shared__ TokLds<NH, 1, 2, true> lds;
+    __shared__ v4i exchange[NH * 5 * 64];                              // of the pairs, then the hidden codes of both tiles
+    __shared__ int pix[64];
+    static_assert(NH * 5 >= 2 * 2 * NH, "room for two buffers of two tiles");
+    const int lane = threadIdx.x & 63, swave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    int branch;
+    const bool computed = window_half<NH, false, SCORED, 1, 2, false, true, false, true>(G, W, branch, WholeLds{lds.actf[0], exchange, pix}, [&] {
+        token_stage<2 * NH, TokPrm<NH * 32>::WORDS>(T.params[branch], (const float4*)T.steps[branch], T.step_pieces[branch], lds.prm, lds.gtab, swave, lane);
+    });
+    if (!computed) return;
+    token_half<NH, 1, false, true, 2, true>(G, T, lds, branch, pix, (v4i (*)[2][NH * 64])exchange);
 }
 
 // ------------------------------------------------------------------ launchers
@@ -2042,6 +2114,23 @@ void launch_token(const Geom& G, const TokArgs& A, int chains, hipStream_t st)
             else TOK_CASE(12, 1)
     }
 #undef TOK_CASE
+}
+
+bool launch_block(const Geom& G, const WinArgs& W, const TokArgs& T, int chains, hipStream_t st)
+{
+    const int windows = G.B * G.nW;
+    if (W.taps || !W.magic_sums || !T.short_forms || chains > 1 || windows == 0 || !whole_block(G.C, windows, G.n_slots)) return false;
+#define BLOCK_CASE(NH)                                                                                                                \
+    if (W.scores) hipLaunchKernelGGL((block_kernel<NH, true>), dim3(windows), dim3(NH * 128), 0, st, G, W, T);                        \
+    else hipLaunchKernelGGL((block_kernel<NH, false>), dim3(windows), dim3(NH * 128), 0, st, G, W, T);                                \
+    return true
+    switch (G.C / 32) {
+        case 3: BLOCK_CASE(3);
+        case 4: BLOCK_CASE(4);
+        case 6: BLOCK_CASE(6);
+        default: return false;
+    }
+#undef BLOCK_CASE
 }
 
 void launch_attn(const Geom& G, const AttnArgs& A, hipStream_t st)
