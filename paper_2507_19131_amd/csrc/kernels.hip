@@ -1921,7 +1921,11 @@ static void launch_gemm_e(const Geom& G, const GemmArgs& A0, hipStream_t st)
         case FEW:
             if constexpr (EPI == EPI_PROJ || EPI == EPI_FC2) launch_few<EPI>(G, A, st);
             return;
-        case RING64: launch_ring<EPI, 2, 2, 1, 1, 4, 4, 2>(G, A, st); return;
+        case RING64:
+            if constexpr (EPI == EPI_FC1)
+                if (fc1_ring_of_four(G.rows_total, A.N)) { launch_ring<EPI, 2, 2, 1, 1, 2, 3, 4>(G, A, st); return; }
+            launch_ring<EPI, 2, 2, 1, 1, 4, 4, 2>(G, A, st);
+            return;
         case RING128:
             if constexpr (EPI == EPI_FC1) launch_ring<EPI, 2, 2, 2, 2, 1, 4, 3>(G, A, st);
             else launch_ring<EPI, 2, 2, 2, 2, 2, 4, 2>(G, A, st);

@@ -56,4 +56,13 @@ inline ProductForm product_form(int epi, int rows, int N, int K)
     return tiles128 <= (epi == EPI_FC1 || K > 1024 ? CUS : 3 * CUS / 2) ? RING64 : RING128;
 }
 
+// FC1 on 64 x 64 tiles: a ring of three stages of two slabs, whose 39 KB let four workgroups on a CU, instead of four stages of four slabs, two
+// workgroups.  Where the latter would run in rounds the former takes all tiles at once and a stage of fewer bytes starts sooner; with at most a
+// workgroup or so a CU it waits for its operands more often.  A stage of two blocks over the number of 64 x 64 tiles, us, four slabs / two:
+//   C = 512   128 tiles 58.1 / 59.1   256 62.0 / 62.2   512 67.8 / 68.0 | 640 72.3 / 70.2   896 74.7 / 73.1
+//   C = 768   192 63.2 / 65.0   384 72.4 / 72.5 | 576 78.3 / 75.5   768 79.5 / 76.9   960 84.5 / 82.5
+//   C = 1024  256 71.1 / 72.1   512 85.2 / 84.1 | 768 92.0 / 88.0   1024 98.2 / 94.0
+// (Two slabs in four stages, three workgroups: between the two.  The projection and FC2, which have a quarter of the tiles, lose up to 8 %.)
+inline bool fc1_ring_of_four(int rows, int N) { return rows / 64 * (N / 64) > 2 * CUS; }
+
 }  // namespace mixaq
