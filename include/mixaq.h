@@ -191,7 +191,7 @@ int mixaq_block_forward_scored(const mixaq_block *blk, const float *x, const dou
  * the call's work counts as done, so the caller sees the same ordering as without it.  There is one such stream per calling
  * stream, at most four per device, given back with the last block that may use them: mixaq_block_create makes one for the stream it
  * is given, and the first forking call on any other stream makes (a stream and two events) or takes over an idle one; a call that
- * gets none runs as one chain.  Under stream capture the
+ * gets none runs as one chain.  Under stream capture, and where every block is one launch over all images (few windows), the
  * stage stays on `stream` alone.  MIXAQ_E_SHAPE if the blocks disagree on the shape or a count is
  * out of range, MIXAQ_E_NULL for missing pointers. */
 int mixaq_stage_forward(mixaq_block *const *blocks, int32_t n_blocks, const float *x, const int32_t *k_high,
@@ -305,7 +305,8 @@ int mixaq_block_set_fused(mixaq_block *blk, int32_t enable);
  * HOST array kernel_ms[MIXAQ_NUM_KERNELS] (0 for kernels that did not run, e.g.
  * score and select when perm is given).  From C = 512 on the entry of the window kernel is the sum of
  * its two kernels (LN1, then QKV + attention), launched alternately.  perm / scores as in mixaq_block_forward /
- * mixaq_block_forward_scored (at most one non-NULL).  mixaq_kernel_name(i) names entry i. */
+ * mixaq_block_forward_scored (at most one non-NULL).  A block that the other calls take in one kernel (few windows) is timed as its
+ * window and its token kernel.  mixaq_kernel_name(i) names entry i. */
 #define MIXAQ_NUM_KERNELS 11
 int mixaq_block_forward_profile(const mixaq_block *blk, const float *x, const int32_t *perm, const double *scores,
                                 int32_t k_high, float *y, void *workspace, size_t workspace_bytes, void *stream,

@@ -1792,7 +1792,7 @@ __global__ __launch_bounds__(NH * 64) __attribute__((amdgpu_waves_per_eu(tok_wav
 // LDS; the second half's parameters and table are requested with the first one's.  Bound: the chain of dependent steps of a workgroup that has
 // a CU to itself or shares it with one other.  The codes of the attention take the room of LN1's and the hidden codes that of the pairs'
 // exchange, so that at C = 96 and 128 two workgroups fit a CU, with 128 registers (one spilled at C = 128).  (The first weights of the
-// projection requested ahead of the attention: nothing.)  Window and token kernel -> this one, one block on 56 x 56 x 96 17.1 -> 16.3 us, two on
+// projection requested ahead of the attention: nothing.)  Window and token kernel -> this one, one block on 56 x 56 x 96 17.0 -> 16.1 us, two on
 // 256 windows 37.1 -> 32.9, at C = 192 57.9 -> 50.3; more beside whole_block(), which draws the lines.
 constexpr int whole_waves_per_eu(int NH) { return NH == 6 ? 3 : 4; }
 template <int NH, bool SCORED>
