@@ -9,6 +9,7 @@ import torch
 from paper_2507_19131_amd import binding as M
 from paper_2507_19131_amd import synth
 import gpu_harness as gh
+from test_kernel_resources import kernels, workgroups_per_cu      # noqa: F401 (a fixture)
 
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2507_19131_amd", "csrc")
 
@@ -28,6 +29,13 @@ def test_only_the_widths_that_have_the_kernel_and_only_what_fits_the_chip_at_onc
         for computed in {0, windows // 2, windows}:
             if whole_block(C, windows, computed):
                 assert 0 < per_cu and computed <= 256 * per_cu and windows <= 512
+
+
+@pytest.mark.parametrize("scored", [0, 1])
+@pytest.mark.parametrize("NH,per_cu", [(3, 2), (4, 2), (6, 1)])
+def test_workgroups_of_a_cu(kernels, NH, scored, per_cu):             # noqa: F811
+    """What the rule counts on, by registers and by whole units of LDS."""
+    assert workgroups_per_cu(kernels["_ZN5mixaq12block_kernelILi%dELb%dEEEvNS_4GeomENS_7WinArgsENS_7TokArgsE" % (NH, scored)]) == per_cu
 
 
 # B, rows and columns of windows, pruned share: the smallest, ragged and both ends of each range
