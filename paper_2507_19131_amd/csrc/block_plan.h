@@ -3,7 +3,7 @@
 
 namespace mixaq {
 
-// By the windows of the launch and those of them that are not pruned.  One kernel saves a launch, a round trip of the codes and the staging
+// By the windows of the launch and those of them that are not pruned; scored: the launch ranks its windows itself.  One kernel saves a launch, a round trip of the codes and the staging
 // of the second half, but tiles of 32 and 17 rows instead of 32 and 32 cost a third more work, so it is for launches whose workgroups run
 // all at once: one a CU, and at C = 96 and 128, whose registers hold two, a second one once most CUs have it.  Below the first line of
 // C = 128 and 192 the window kernel with half the heads a workgroup spreads a window over two CUs.  Two blocks on one map, us, two kernels /
@@ -15,13 +15,16 @@ namespace mixaq {
 // A batch that one launch takes this way stays on one chain: six blocks, two chains of two kernels / one chain of one:   C = 96   2 x 96
 // windows 104.9 / 90.7   2 x 128 110.1 / 92.9   2 x 192 137.5 / 128.9   2 x 256 146.7 / 134.7      C = 128   2 x 96 115.9 / 100.6   2 x 128
 // 121.3 / 104.0   2 x 192 145.1 / 144.2   2 x 256 159.4 / 153.7      C = 192   2 x 72 146.7 / 135.2   2 x 128 177.5 / 143.7.
-// A pruned window's workgroup is gone as soon as its rank is known or copies its window behind the others: 2 x 140 with a fifth pruned
-// 112.4 / 98.7, 126.2 / 110.9 and 184.7 / 160.0.  Where few are left the halves are ahead again (2 x 72 at C = 192, 115 computed 129.6 / 134.7).
-inline bool whole_block(int C, int windows, int computed)
+// Given a list, a pruned window's workgroup copies its window behind the others: 2 x 140 with a fifth pruned 112.4 / 98.7, 126.2 / 110.9 and
+// 184.7 / 160.0.  Where few are left the halves are ahead again (2 x 72 at C = 192, 115 computed 129.6 / 134.7).
+// Given scores, a pruned window takes a place like any other until its rank is known, and beyond one workgroup a CU windows that are computed
+// wait behind it: one block on 320 windows, 256 of them computed, 22.8 / 23.1, 24.7 / 26.2 and 36.3 / 46.5, 160 computed 21.6 / 23.0, 23.2 / 25.8
+// and 32.7 / 35.0 (given a list 16.4 / 14.8, 18.5 / 16.7 and 28.7 / 25.1).  Near 512 all have a place (504, 353 computed at C = 96 25.2 / 24.3).
+inline bool whole_block(int C, int windows, int computed, bool scored)
 {
     constexpr int CUS = 256;
     const int from = C == 96 ? 0 : C == 128 || C == 192 ? 144 : 2 * CUS + 1, second = C == 96 ? 352 : C == 128 ? 400 : 2 * CUS + 1;
-    if (computed <= CUS) return computed >= from && windows <= CUS + CUS / 4;
+    if (computed <= CUS) return computed >= from && windows <= (scored ? CUS : CUS + CUS / 4);
     return computed >= second && windows <= 2 * CUS;
 }
 

@@ -2123,7 +2123,7 @@ void launch_token(const Geom& G, const TokArgs& A, int chains, hipStream_t st)
 bool launch_block(const Geom& G, const WinArgs& W, const TokArgs& T, int chains, hipStream_t st)
 {
     const int windows = G.B * G.nW;
-    if (W.taps || !W.magic_sums || !T.short_forms || chains > 1 || windows == 0 || !whole_block(G.C, windows, G.n_slots)) return false;
+    if (W.taps || !W.magic_sums || !T.short_forms || chains > 1 || windows == 0 || !whole_block(G.C, windows, G.n_slots, W.scores != nullptr)) return false;
 #define BLOCK_CASE(NH)                                                                                                                \
     if (W.scores) hipLaunchKernelGGL((block_kernel<NH, true>), dim3(windows), dim3(NH * 128), 0, st, G, W, T);                        \
     else hipLaunchKernelGGL((block_kernel<NH, false>), dim3(windows), dim3(NH * 128), 0, st, G, W, T);                                \

@@ -17,7 +17,7 @@ CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
 @pytest.fixture(scope="module")
 def whole_block(tmp_path_factory):
     d = tmp_path_factory.mktemp("plan")
-    (d / "plan.cpp").write_text('#include "block_plan.h"\nextern "C" int whole(int C, int w, int n) { return mixaq::whole_block(C, w, n); }\n')
+    (d / "plan.cpp").write_text('#include "block_plan.h"\nextern "C" int whole(int C, int w, int n, int scored) { return mixaq::whole_block(C, w, n, scored); }\n')
     subprocess.run(["g++", "-std=c++17", "-Wall", "-Werror", "-fPIC", "-shared", "-I", CSRC, "-o", str(d / "plan.so"), str(d / "plan.cpp")], check=True)
     return ctypes.CDLL(str(d / "plan.so")).whole
 
@@ -26,9 +26,12 @@ def whole_block(tmp_path_factory):
 def test_only_the_widths_that_have_the_kernel_and_only_what_fits_the_chip_at_once(whole_block, C):
     per_cu = {96: 2, 128: 2, 192: 1}.get(C, 0)
     for windows in range(0, 1100):
-        for computed in {0, windows // 2, windows}:
-            if whole_block(C, windows, computed):
+        for computed in {0, windows // 2, windows * 4 // 5, windows}:
+            if whole_block(C, windows, computed, 0):
                 assert 0 < per_cu and computed <= 256 * per_cu and windows <= 512
+            if whole_block(C, windows, computed, 1):                 # which of them are pruned shows in the kernel: all take a place
+                assert windows <= 256 or computed > 256
+                assert windows <= 256 * per_cu and whole_block(C, windows, computed, 0)
 
 
 @pytest.mark.parametrize("scored", [0, 1])
@@ -54,7 +57,7 @@ def test_whole_blocks_have_the_bits_of_the_separate_kernels(whole_block, C, B, r
     k_low = n - n // 3 - int(pruned * n)
     k_high = n // 3 if n > 1 else 1
     k_low = max(0, min(k_low, n - k_high))
-    assert n == rows * cols and whole_block(C, B * n, B * (k_high + k_low))
+    assert n == rows * cols and whole_block(C, B * n, B * (k_high + k_low), 0)
     inp = synth.make_block_inputs(spec, 31 + C)
     x = torch.from_numpy(synth.make_feature_map(spec, 31 + n, blobs=True)).cuda()
     for shift in (0, 3) if min(rows, cols) > 1 else (0,):            # a shift needs two windows either way
