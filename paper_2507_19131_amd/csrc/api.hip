@@ -836,12 +836,12 @@ int mixaq_stage_forward(mixaq_block* const* blocks, int32_t n_blocks, const floa
     hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
     bool split = n_blocks > 1 && b0->side_device >= 0 && stage_split_pays(b0->d.B, nW, b0->d.C, n_blocks);
     for (int i = 0; split && i < n_blocks; ++i) split = blocks[i]->fused_window && blocks[i]->fused_token;
-    // Blocks of one kernel each stay on one chain.  (The first one, which ranks the windows itself, may be two kernels there: six blocks on 2 x 160
+    // Blocks of one kernel each may stay on one chain (whole_stage).  (The first one, which ranks the windows itself, may be two kernels there: six blocks on 2 x 160
     // windows with a fifth pruned, two chains of two kernels / one chain, 188 / 170 us at C = 192.)
     bool whole = split;
     for (int i = 0; whole && i < n_blocks; ++i) {
         const int kh = k_high[i / 2], kl = k_low ? k_low[i / 2] : nW - kh;
-        whole = blocks[i]->magic_windows && blocks[i]->short_tokens && whole_block(b0->d.C, b0->d.B * nW, b0->d.B * (kh + kl), false);
+        whole = blocks[i]->magic_windows && blocks[i]->short_tokens && whole_stage(b0->d.C, b0->d.B * nW, b0->d.B * (kh + kl), n_blocks);
     }
     if (whole) split = false;
     if (split) {

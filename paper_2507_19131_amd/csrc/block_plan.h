@@ -28,4 +28,16 @@ inline bool whole_block(int C, int windows, int computed, bool scored)
     return computed >= second && windows <= 2 * CUS;
 }
 
+// Whether a stage of blocks that are one kernel each stays on one chain where two chains would be taken.  Up to 256 computed windows always.  Near
+// 512 only while the stage is short: the fork is paid once, and per block two chains are the faster ones.  Two chains of two kernels / one
+// chain of one, us:   C = 96   2 x 176 windows, 8 blocks 172.8 / 170.0   10 210.9 / 211.9   18 363.7 / 378.4      2 x 192, 12 blocks 255.3 / 255.2
+//   2 x 224, 12 blocks 261.5 / 260.0   18 384.5 / 388.2      2 x 256, 12 blocks 275.1 / 267.4   24 529.1 / 533.9
+//   C = 128  2 x 208, 8 blocks 189.7 / 193.2   18 398.4 / 431.3      2 x 224, 8 blocks 198.8 / 194.8   10 244.5 / 243.3   18 424.4 / 435.4
+//   2 x 256, 8 blocks 205.6 / 203.0   10 252.2 / 252.6   18 439.4 / 453.6
+inline bool whole_stage(int C, int windows, int computed, int n_blocks)
+{
+    if (!whole_block(C, windows, computed, false)) return false;
+    return computed <= 256 || n_blocks <= (C == 96 ? (computed < 384 ? 8 : 12) : (computed < 448 ? 6 : 8));
+}
+
 }  // namespace mixaq

@@ -1,5 +1,5 @@
-"""The library's own rule of which stages run as two chains and which images a chain takes when (csrc/stage_plan.h), built for the
-host."""
+"""The library's own rules of which stages run as two chains and which images a chain takes when (csrc/stage_plan.h), and of which launches
+take a whole block in one kernel (csrc/block_plan.h), built for the host."""
 import ctypes
 import os
 import subprocess
@@ -8,12 +8,15 @@ import tempfile
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2507_19131_amd", "csrc")
 
 _SOURCE = r'''
+#include "block_plan.h"
 #include "stage_plan.h"
 extern "C" {
 int splits(int B, int nW) { return mixaq::stage_splits(B, nW); }
 int pays(int B, int nW, int C, int blocks) { return mixaq::stage_split_pays(B, nW, C, blocks); }
 int rounds(int B, int nW, int C) { return mixaq::stage_rounds(B, nW, C); }
 int round_images(int B, int nW, int C, int chain) { return mixaq::round_images(B, nW, C, chain); }
+int whole_block(int C, int windows, int computed, int scored) { return mixaq::whole_block(C, windows, computed, scored); }
+int whole_stage(int C, int windows, int computed, int blocks) { return mixaq::whole_stage(C, windows, computed, blocks); }
 int part_first(int B, int nW, int C, int chain, int round) { return mixaq::stage_part(B, nW, C, chain, round).first; }
 int part_images(int B, int nW, int C, int chain, int round) { return mixaq::stage_part(B, nW, C, chain, round).images; }
 }
