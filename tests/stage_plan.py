@@ -35,10 +35,17 @@ def _build():
 lib = _build()
 
 
-def forks(spec, n_blocks):
-    """Whether mixaq_stage_forward runs these blocks as two chains (fused kernels at every block: C <= 384, mlp_ratio 4)."""
-    return bool(n_blocks > 1 and spec.C <= 384 and spec.mlp_ratio == 4 and lib.splits(spec.B, spec.nW) and
-                lib.pays(spec.B, spec.nW, spec.C, n_blocks))
+def forks(spec, n_blocks, k_high=None, k_low=None):
+    """Whether mixaq_stage_forward runs these blocks as two chains (fused kernels at every block: C <= 384, mlp_ratio 4), by the counts of every
+    pair (None: no window is pruned).  Blocks with a table of steps for the GELU and bounded sums; others fork also where this says that
+    one chain of blocks in one kernel each is shorter."""
+    if not (n_blocks > 1 and spec.C <= 384 and spec.mlp_ratio == 4 and lib.splits(spec.B, spec.nW) and
+            lib.pays(spec.B, spec.nW, spec.C, n_blocks)):
+        return False
+    pairs = (n_blocks + 1) // 2
+    computed = [spec.nW] * pairs if k_low is None else [h + l for h, l in zip(k_high, k_low)]
+    assert len(computed) == pairs
+    return not all(lib.whole_stage(spec.C, spec.B * spec.nW, spec.B * n, n_blocks) for n in computed)
 
 
 def rounds(spec):

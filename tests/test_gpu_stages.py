@@ -414,11 +414,11 @@ def test_forked_stage_with_uneven_halves_pruning_and_streams(B, H, W, C, heads, 
     default stream or on one of the caller's while the default stream is kept busy (complete as soon as that stream is);
     the same bits as block after block on the whole batch on one stream, and the oracle's."""
     spec = synth.BlockSpec(B, H, W, C, heads, act_bits_low=2 if C == 128 else 4)
-    assert stage_plan.forks(spec, n_blocks)
     nW, pairs = spec.nW, (n_blocks + 1) // 2
     shifts = [0, 3] * pairs
     k_high = [[nW // 2, nW // 3, 0][p % 3] for p in range(pairs)]
     k_low = [[nW - nW // 2, nW // 3, nW // 2][p % 3] for p in range(pairs)]
+    assert stage_plan.forks(spec, n_blocks, k_high, k_low)
     dev = torch.device("cuda:0")
     x_np = synth.make_feature_map(spec, 310, blobs=True)
     inputs = [synth.make_block_inputs(spec, 311 + i) for i in range(n_blocks)]
@@ -465,22 +465,25 @@ def test_forked_stage_with_uneven_halves_pruning_and_streams(B, H, W, C, heads, 
 
 @pytest.mark.parametrize("C,rows,cols,n_blocks", [(96, 14, 44, 4), (96, 15, 41, 4), (96, 24, 32, 2), (96, 11, 70, 2), (96, 32, 40, 2), (96, 7, 183, 2), (192, 8, 16, 6), (192, 3, 43, 6), (192, 16, 16, 4), (192, 6, 43, 4), (384, 8, 10, 6), (384, 9, 9, 6), (384, 12, 15, 2), (384, 16, 17, 2)])
 def test_forms_of_the_kernels_of_two_chains_on_both_sides_of_their_lines(C, rows, cols, n_blocks):
-    """The forms of the two fused kernels that take the other chain into account: the bits of block after block on the whole batch,
-    which takes other forms."""
+    """The forms of the two fused kernels that take the other chain into account: the bits of block after block through the separate kernels on
+    the whole batch."""
     spec = synth.BlockSpec(2, 7 * rows - 1, 7 * cols - 5, C, C // 32)
-    assert spec.nW == rows * cols and stage_plan.forks(spec, n_blocks)
+    # windows enough pruned, or none, where one chain of blocks in one kernel each would take the others
+    k, k_low = {(192, 8, 16): (40, 30), (192, 3, 43): (64, 65)}.get((C, rows, cols), (spec.nW // 2, spec.nW // 3))
+    pairs = (n_blocks + 1) // 2
+    assert spec.nW == rows * cols and stage_plan.forks(spec, n_blocks, [k] * pairs, [k_low] * pairs)
     dev = torch.device("cuda:0")
     x = torch.from_numpy(synth.make_feature_map(spec, 395, blobs=True)).to(dev)
     print("forms of two chains", C, spec.nW, flush=True)
     blocks = [gh.GpuBlock(synth.make_block_inputs(spec, 396 + i), 3 * (i % 2)) for i in range(n_blocks)]
     try:
-        k, k_low = spec.nW // 2, spec.nW // 3
         scores, perm = blocks[0].score_select(x, k)
         want = x
         for gb in blocks:
+            M.mixaq_block_set_fused(gb.blk, 0)
             want = gb.forward_pruned(want, perm, k, k_low)
+            M.mixaq_block_set_fused(gb.blk, 1)
         y, tmp, s2, p2 = torch.full_like(x, float("nan")), torch.full_like(x, float("nan")), torch.empty_like(scores), torch.empty_like(perm)
-        pairs = (n_blocks + 1) // 2
         M.mixaq_stage_forward([gb.blk for gb in blocks], x, [k] * pairs, [k_low] * pairs, y, tmp, s2, p2, blocks[0].ws)
         torch.cuda.synchronize()
         assert torch.equal(y, want) and torch.equal(p2, perm)
@@ -665,10 +668,10 @@ def test_random_sweep_of_forked_stage_calls():
         cols = max(2, -(-int(windows) // rows) + 1)
         spec = synth.BlockSpec(B, 7 * rows - int(rng.integers(0, 7)), 7 * cols - int(rng.integers(0, 7)), C, heads, act_bits_high=hi,
                                act_bits_low=int(rng.integers(2, hi + 1)), weight_bits=int(rng.choice([4, 8])), score_mode=int(rng.integers(0, 2)))
-        assert stage_plan.forks(spec, n_blocks), case
         pairs = (n_blocks + 1) // 2
         k_high = [int(rng.integers(0, spec.nW + 1)) for _ in range(pairs)]
         k_low = [spec.nW - kh if rng.integers(0, 2) else int(rng.integers(0, spec.nW - kh + 1)) for kh in k_high]
+        assert stage_plan.forks(spec, n_blocks, k_high, k_low), case
         print("forked sweep case", case, "B", B, spec.H, spec.W, "C", C, "blocks", n_blocks, "k_high", k_high, "k_low", k_low, flush=True)
         x_np = synth.make_feature_map(spec, 65000 + case, blobs=True)
         inputs = [synth.make_block_inputs(spec, 66000 + 10 * case + i, per_branch_bias=bool(rng.integers(0, 2))) for i in range(n_blocks)]
