@@ -111,6 +111,21 @@ def price_kernel(name, avg_ms, C, F, heads, n_windows):
     return out
 
 
+def whole_block(C, windows):
+    """Whether the library takes a block in one kernel, no window pruned (the rule of csrc/block_plan.h)."""
+    first, second = {96: 0, 128: 144, 192: 144}.get(C, 257), {96: 352, 128: 400}.get(C, 513)
+    return first <= windows <= 256 or second <= windows <= 512
+
+
+def two_chains(B, windows, C, blocks):
+    """Whether mixaq_stage_forward runs blocks without pruned windows as two chains (the rules of csrc/stage_plan.h and csrc/block_plan.h)."""
+    if C > 384 or B < 2 or blocks < 2 or windows <= (160 if C == 256 else 128) or blocks * windows * C < 2200 * 100:
+        return False
+    if whole_block(C, windows) and (windows <= 256 or blocks <= ((8 if windows < 384 else 12) if C == 96 else (6 if windows < 448 else 8))):
+        return False
+    return windows <= 4096 or B % 2 == 0 or B >= 9
+
+
 def read_traffic(kernel, workload):
     """HBM bytes per launch of `kernel` from the committed counter summary of that workload (two rocprofv3 --pmc
     runs of this command, FETCH_SIZE and WRITE_SIZE), or None when no summary is there."""
@@ -215,14 +230,19 @@ class Stage:
                    pct_int8_mfma_peak=round(100 * tops / PEAK_INT8_TOPS, 3),
                    ideal_windows_per_s=round(ideal_windows_per_s(spec.C), 1),
                    frac_of_fused_ideal=round(wps / ideal_windows_per_s(spec.C), 5))
-        if (spec.B >= 2 and (160 if spec.C == 256 else 128) < self.n_win and (self.n_win <= 4096 or spec.B % 2 == 0 or spec.B >= 9) and
-                spec.C <= 384 and len(self.blocks) > 1 and len(self.blocks) * self.n_win * spec.C >= 2200 * 100):          # the rule of mixaq_stage_forward
+        chains = two_chains(spec.B, self.n_win, spec.C, len(self.blocks))
+        one_kernel = not chains and whole_block(spec.C, self.n_win)
+        if chains:
             out["two_chains"] = ("the stage call runs the two halves of the batch as two chains of blocks on two streams; the per-kernel "
                                  "durations below are whole-batch launches on one stream and add up to more than ms_per_pass")
+        if one_kernel:
+            out["one_kernel"] = ("the stage call runs each block as one kernel; the profile call times the window and the token kernel that it stands "
+                                 "for, which the pass does not launch: no dominant kernel is named")
         if kernels:
+            out["kernels"] = kernels
+        if kernels and not one_kernel:
             per_step = {n: kernels[n]["avg_ms"] * kernels[n]["launches_per_step"] for n in kernels}
             dom = max(per_step, key=per_step.get)
-            out["kernels"] = kernels
             out["dominant"] = dict(kernel=dom, **{k: kernels[dom][k] for k in ("bound", "achieved", "peak", "unit", "frac", "avg_ms")})
         return out
 
