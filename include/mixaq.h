@@ -191,8 +191,8 @@ int mixaq_block_forward_scored(const mixaq_block *blk, const float *x, const dou
  * the call's work counts as done, so the caller sees the same ordering as without it.  There is one such stream per calling
  * stream, at most four per device, given back with the last block that may use them: mixaq_block_create makes one for the stream it
  * is given, and the first forking call on any other stream makes (a stream and two events) or takes over an idle one; a call that
- * gets none runs as one chain.  Under stream capture, and where every block is one launch over all images (few windows), the
- * stage stays on `stream` alone.  MIXAQ_E_SHAPE if the blocks disagree on the shape or a count is
+ * gets none runs as one chain.  Under stream capture, and where every block is one launch over all images (few windows; near two
+ * windows a CU only stages of few blocks), the stage stays on `stream` alone.  MIXAQ_E_SHAPE if the blocks disagree on the shape or a count is
  * out of range, MIXAQ_E_NULL for missing pointers. */
 int mixaq_stage_forward(mixaq_block *const *blocks, int32_t n_blocks, const float *x, const int32_t *k_high,
                         const int32_t *k_low, float *y, float *tmp, double *scores, int32_t *perm, void *workspace,

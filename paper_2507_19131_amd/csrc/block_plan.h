@@ -3,15 +3,20 @@
 
 namespace mixaq {
 
-// By the windows of the launch and those of them that are not pruned; scored: the launch ranks its windows itself.  One kernel saves a launch, a round trip of the codes and the staging
-// of the second half, but tiles of 32 and 17 rows instead of 32 and 32 cost a third more work, so it is for launches whose workgroups run
-// all at once: one a CU, and at C = 96 and 128, whose registers hold two, a second one once most CUs have it.  Below the first line of
+// By the windows of the launch and those of them that are not pruned; scored: the launch ranks its windows itself.  One kernel saves a
+// launch, a round trip of the codes and the staging of the second half, but tiles of 32 and 17 rows instead of 32 and 32 cost a third more
+// work, so it is for launches whose computed windows run all at once: one a CU, and at C = 96 and 128, whose registers hold two, a second one
+// once most CUs have it (at C = 192 up to 64 workgroups of pruned windows wait behind those and only copy).  Below the first line of
 // C = 128 and 192 the window kernel with half the heads a workgroup spreads a window over two CUs.  Two blocks on one map, us, two kernels /
 // one:   C = 96   128 windows 33.2 / 31.1   256 37.1 / 32.9 | 264 41.8 / 42.4   320 43.0 / 44.0 | 400 46.5 / 44.7   504 48.9 / 45.9
 //        C = 128  128 32.6 / 34.6 | 144 34.8 both   192 39.0 / 35.4   256 40.4 / 36.3 | 264 44.0 / 46.9   320 45.4 / 49.0 |
 //                 400 51.6 / 50.3   504 58.0 / 53.5
 //        C = 192  128 41.9 / 46.8 | 144 48.4 / 47.0   192 56.5 / 47.8   256 57.9 / 50.3 | 264 65.6 / 84.8   504 93.7 / 90.7
-// C = 256 needs sixteen waves a workgroup, which leave 80 registers too few: 64 50.9 / 76.2, 256 75.8 / 88.7.
+// C = 256 needs sixteen waves a workgroup, which have 128 registers and spill 35 to 44: 64 50.9 / 76.2, 256 75.8 / 88.7.
+// Beside other streams' work the line would lie lower, as those fill the CUs that a launch leaves idle, but a call does not know of them.  Two blocks
+// on each of so many streams at once, us a pass:   C = 96, 144 windows, two streams 28.7 / 23.0, three 28.8 / 22.5   256 28.2 / 25.0, 28.9 / 22.6   400
+// 33.0 / 32.4, 29.2 / 29.3   504 37.6 / 39.1, 34.3 / 36.8      C = 128, 144 28.3 / 23.1, 29.1 / 22.6   256 29.1 / 27.2, 29.6 / 24.4   400 36.5 / 38.8,
+// 34.2 / 35.8   504 43.6 / 45.2, 41.4 / 43.7      C = 192, 144 32.3 / 30.7, 28.4 / 26.3   196 38.2 / 36.6, 34.8 / 34.7   256 46.5 / 47.0, 51.3 / 48.1
 // A batch that one launch takes this way stays on one chain: six blocks, two chains of two kernels / one chain of one:   C = 96   2 x 96
 // windows 104.9 / 90.7   2 x 128 110.1 / 92.9   2 x 192 137.5 / 128.9   2 x 256 146.7 / 134.7      C = 128   2 x 96 115.9 / 100.6   2 x 128
 // 121.3 / 104.0   2 x 192 145.1 / 144.2   2 x 256 159.4 / 153.7      C = 192   2 x 72 146.7 / 135.2   2 x 128 177.5 / 143.7.

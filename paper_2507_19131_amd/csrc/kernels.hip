@@ -3,6 +3,7 @@
 //   select_rank_kernel  top-k partition into high / low groups       (Sec. 3.2)
 //   window_kernel     gather + LN1 + QKV + attention of a window; wide blocks take LN1 from ln_window_kernel
 //   token_kernel      projection + LN2 + FFN + scatter of a tile of rows
+//   block_kernel      both of them for a window, on few windows
 // and, where these do not apply,
 //   ln_quant_kernel   gather (shift folded in) + LayerNorm + quantize, also LN2
 //   gemm_ring_kernel, gemm_few_kernel, gemm_tile_kernel  int8 MFMA linear layers with fused epilogues (shadow layers): long K, long K on
@@ -1085,8 +1086,8 @@ template <int C, int NH, bool CODES> struct WinPrm {
 // CODES: the LN1 codes come ready from ln_window_kernel (wide blocks, whose heads are spread over many workgroups: each of
 // them would repeat the whole gather and LayerNorm); the workgroup is given a slot and there are no pruned ones.
 // WHOLE: the first half of block_kernel, whose workgroup goes on with the window's tokens: attention codes and pixels of the tokens stay
-// in LDS (codes as operand fragments, a row block per 32 tokens), second_half() is called as soon as the branch is known.  False: the
-// window is pruned and forwarded.
+// in LDS (codes as operand fragments, a row block per 32 tokens), second_half() is called with the branch known, behind the write of this half's
+// parameters to LDS.  False: the window is pruned and forwarded.
 struct WholeLds {
     v4i *codes, *exchange;                                               // LN1's, then the attention's codes; what pairs of waves exchange
     int* pix;
@@ -1789,11 +1790,14 @@ __global__ __launch_bounds__(NH * 64) __attribute__((amdgpu_waves_per_eu(tok_wav
 // ------------------------------------------------------------------ a whole block on small maps
 // One workgroup per window runs both halves of the block: the window kernel's form of pairs of waves, by roles, then two token kernels of
 // one row block side by side for the window's 32 and 17 rows, each wave one of a tile's channel blocks.  What the halves hand on stays in
-// LDS; the second half's parameters and table are requested with the first one's.  Bound: the chain of dependent steps of a workgroup that has
-// a CU to itself or shares it with one other.  The codes of the attention take the room of LN1's and the hidden codes that of the pairs'
-// exchange, so that at C = 96 and 128 two workgroups fit a CU, with 128 registers (one spilled at C = 128).  (The first weights of the
-// projection requested ahead of the attention: nothing.)  Window and token kernel -> this one, one block on 56 x 56 x 96 17.0 -> 16.1 us, two on
-// 256 windows 37.1 -> 32.9, at C = 192 57.9 -> 50.3; more beside whole_block(), which draws the lines.
+// LDS.  The second half's parameters and table are requested ahead of LN1, but behind the first half's, and the barrier in front of LN1
+// waits for them, so their way is not hidden.  The compiler keeps the branch, which is handed on by reference behind a divergent copy, in
+// vector registers, and what it chooses comes by vector loads, most followed by a wait for all loads: 61 vector loads and 18 such waits in
+// the form that ranks its window at C = 96.  Bound: the chain of dependent steps, these waits among them, of a workgroup that has a CU to
+// itself or shares it with one other.  The codes of the attention take the room of LN1's and the hidden codes that of the pairs' exchange,
+// so that at C = 96 and 128 two workgroups fit a CU, with 128 registers (one spilled at C = 128).  (The first weights of the projection
+// requested ahead of the attention, with those waits in place: nothing.)  Window and token kernel -> this one, one block on 56 x 56 x 96
+// 17.0 -> 16.1 us, two on 256 windows 37.1 -> 32.9, at C = 192 57.9 -> 50.3; more beside whole_block(), which draws the lines.
 constexpr int whole_waves_per_eu(int NH) { return NH == 6 ? 3 : 4; }
 template <int NH, bool SCORED>
 __global__ __launch_bounds__(NH * 2 * 64) __attribute__((amdgpu_waves_per_eu(whole_waves_per_eu(NH)))) void block_kernel(Geom G, WinArgs W, TokArgs T)
